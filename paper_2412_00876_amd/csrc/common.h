@@ -54,8 +54,11 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return static_cast<bf16_t>(u >> 16);
 }
+// two values at once through v_cvt_pk_bf16_f32: the same rounding in one instruction instead of a dozen
+typedef __bf16 bf16_native2 __attribute__((ext_vector_type(2)));
+typedef float f32_native2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return static_cast<uint32_t>(f32_to_bf16(lo)) | (static_cast<uint32_t>(f32_to_bf16(hi)) << 16);
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32_native2{lo, hi}, bf16_native2));
 }
 
 template <typename T>
@@ -151,18 +154,17 @@ __device__ __forceinline__ float gelu_erf(float a) { return 0.5f * a * (1.0f + e
 // The same GELU with a branch-free erf: Abramowitz & Stegun 7.1.26,
 //   erf(x) = 1 - (a1 t + ... + a5 t^5) exp(-x^2),  t = 1 / (1 + p x),  x >= 0,  |error| <= 1.5e-7,
 // which is at the level of float32 rounding and keeps fused epilogues short (about a dozen instructions).
+// With h = a/2 the sign of a needs no separate step: 0.5 a (1 + erf(a/sqrt 2)) = h + |h| erf(|a|/sqrt 2).
 __device__ __forceinline__ float gelu_erf_fast(float a) {
-  const float x = fabsf(a) * 0.70710678118654752440f;
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752440f, fabsf(a), 1.0f));
   float poly = fmaf(1.061405429f, t, -1.453152027f);
   poly = fmaf(poly, t, 1.421413741f);
   poly = fmaf(poly, t, -0.284496736f);
   poly = fmaf(poly, t, 0.254829592f);
   poly *= t;
-  const float e = __builtin_amdgcn_exp2f(-1.44269504088896340736f * x * x);
-  const float erf_abs = fmaf(-poly, e, 1.0f);
-  const float erf_signed = copysignf(erf_abs, a);
-  return 0.5f * a * (1.0f + erf_signed);
+  const float e = __builtin_amdgcn_exp2f(a * (a * (-0.5f * 1.44269504088896340736f)));
+  const float h = 0.5f * a;
+  return fmaf(fabsf(h), fmaf(-poly, e, 1.0f), h);
 }
 
 }  // namespace dllava

@@ -1,41 +1,53 @@
-// 256 x (32*JB) x d tile product on the matrix cores for the large bfloat16 products of the path (predictor scoring
-// over all vision tokens, Q/K/V projection of the kept rows): one block of 4 waves per compute unit,
-//   acc[i][j] (32 x 32) += A[a_wave_row0 + A_STRIDE*i + 0..31, :] . B[32*j + 0..31, :]^T ,   i < 2, j < JB,
-// for the calling wave (64 rows of the 256-row A tile against all 32*JB rows of the B tile), with
-// v_mfma_f32_32x32x16_bf16.  Both operands are contiguous along d and are streamed in 64-element stages (one whole
+// 256 x (32*JT) x d tile product on the matrix cores for the large bfloat16 products of the path (predictor scoring
+// over all vision tokens, Q/K/V projection of the kept rows, the linear layers): one block of 4 waves per compute unit,
+//   acc[i][j] (16 x 16) += A[128*(w/2) + 16*i + 0..15, :] . B[16*JT*(w%2) + 16*j + 0..15, :]^T ,   i < 8, j < JT,
+// for wave w (2 x 2 waves: 128 rows of the 256-row A tile against half of the 32*JT rows of the B tile), with
+// v_mfma_f32_16x16x32_bf16.  Both operands are contiguous along d and are streamed in 64-element stages (one whole
 // 128-byte memory line per row).
 //
 // What shapes the loop (each point is a measurement on MI355X, not a guess):
+//  * The chip is POWER-bound here, not issue-bound: with normally distributed operands in registers and nothing else
+//    running, v_mfma_f32_32x32x16_bf16 holds 1.74 GHz (1767 TFLOP/s) and v_mfma_f32_16x16x32_bf16 2.03 GHz (2041
+//    TFLOP/s; both 2450 with zeros): the small shape moves half the accumulator bytes per product.  For the same
+//    reason the wave tile is square, 128 x 128: 16 KiB of LDS fragments per 64 products instead of the 20 KiB of
+//    64 x 256.  Measured per 256 x 256 block of the Q/K/V projection (64 stages): 102 us at 1.56 GHz with 32x32x16 on
+//    64 x 256 wave tiles, 95 us at 1.64 GHz with this form.
 //  * A compute unit pulls its operands from L2 at 40-45 bytes per clock at best, so the tile must be large: 256 x 256
 //    needs 32 bytes per clock at the full matrix rate, 128 x 128 twice that.  The accumulators of the wave tile
-//    (up to 64 x 256) fill the 256 accumulation registers; one wave per SIMD.
+//    fill the 256 accumulation registers; one wave per SIMD.
 //  * Tiles go from global memory straight into LDS (global_load_lds_dwordx4, no staging registers).  A stage is 64 KiB,
 //    LDS holds 160 KiB, and a tile requested one stage ahead does not arrive in time (latency plus transfer exceed a
 //    stage's arithmetic), so the LDS is a ring of FIVE 32 KiB half-stage slots (B, A, B, A, ...): while stage k is
 //    multiplied, A of stage k+1 and B of stages k+1 and k+2 are in flight or landed -- every tile is requested
 //    a whole stage before the barrier that needs it.
-//  * A wave issues in order: a burst of tile loads stalls it (the memory pipeline accepts about one 1 KiB load
-//    per 25 clocks per compute unit) and the matrix pipe idles meanwhile (measured: products + loads took the SUM
-//    of their times).  So the loads are dealt out one behind every other product, the fragment reads one behind each
-//    of the first products of a k-step, and scheduling barriers keep the compiler from regrouping them.
+//  * A wave issues in order and there is one wave per SIMD: whatever stands between two products idles the matrix
+//    pipe.  Fragment reads and tile loads are dealt out between the products (a burst of loads stalls the wave: the
+//    memory pipeline accepts about one 1 KiB load per 25 clocks per compute unit), scheduling barriers keep the
+//    compiler from regrouping them, and the scalar arithmetic of the next stage's addresses hides behind products too.
 //  * The stage barrier sits before the LAST k-step of a stage: by then the fragments of that k-step are in
 //    registers, so the stage's slots are free, and the first fragments of the next stage are read behind the
 //    products of the last k-step instead of after a barrier with nothing to hide them.
+//  * The products are written as instructions with their accumulators pinned to accumulation registers: with the
+//    builtin the compiler kept some of the 64 four-register accumulators in vector registers and moved them back and
+//    forth in the loop (400 moves per stage, 3.3 times slower).
 // LDS layout of a slot: row r at r*128 bytes, 16-byte chunk c of the row at position c ^ ((r/2) % 8): the 16 lanes
 // that the LDS serves together hit 16 different bank groups both when a tile load deposits 8 rows x 8 chunks and
 // when a fragment read takes one chunk of 16 rows.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "common.h"
 
 namespace dllava {
 
-typedef __bf16 ring_bf16x8 __attribute__((ext_vector_type(8)));
-typedef float ring_f32x16 __attribute__((ext_vector_type(16)));
+typedef float ring_f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t ring_u32x4 __attribute__((ext_vector_type(4)));
 
 #define DLLAVA_LDS __attribute__((address_space(3)))
 #define DLLAVA_GLB __attribute__((address_space(1)))
+#define DLLAVA_INLINE __attribute__((always_inline))
 
 constexpr int kRingThreads = 256;
 constexpr int kRingBK = 64;                       // elements of d per stage
@@ -43,7 +55,16 @@ constexpr int kRingRowBytes = 128;                // bytes per row per stage
 constexpr int kRingSlotBytes = 256 * kRingRowBytes;
 constexpr int kRingSlots = 5;
 constexpr int kRingLdsBytes = kRingSlots * kRingSlotBytes;  // 160 KiB: all of a compute unit's LDS
-constexpr int kRingALoads = 8;                    // tile loads per wave per stage for A (256 rows)
+constexpr int kRingALoads = 8;                    // tile loads per wave per stage for A (256 rows); JT for B
+
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {  // f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>)
+  static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
 
 template <int OFF>
 __device__ __forceinline__ ring_u32x4 ring_lds_read16(uint32_t addr) {
@@ -51,7 +72,10 @@ __device__ __forceinline__ ring_u32x4 ring_lds_read16(uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
   return v;
 }
-__device__ __forceinline__ ring_bf16x8 ring_frag(const ring_u32x4& v) { return __builtin_bit_cast(ring_bf16x8, v); }
+__device__ __forceinline__ void ring_mfma(ring_f32x4& c, const ring_u32x4& a, const ring_u32x4& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void ring_tie_acc(ring_f32x4& c) { asm volatile("" : "+a"(c)); }
 
 // Byte offset, from the first row of a tile, of the 16 bytes that this lane fetches with tile load j of wave w:
 // the load covers rows 8*(w + 4j) + lane/8, the lane's position lane%8 holds chunk (lane%8) ^ ((row/2)%8).
@@ -68,125 +92,153 @@ __device__ __forceinline__ void ring_tie(ring_u32x4 (&f)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i]));
 }
 
+// Tile order.  Tiles (A tile at, B tile bt) are numbered in groups of kRingGroup B tiles, inside a group A tile by A
+// tile, and XCD x (blocks x, x + 8, ...) takes the x-th eighth of that order: the 32 tiles that an XCD works on at a time
+// then cover about 6 A tiles x 5 B tiles, the square patch that pulls the fewest bytes through its L2, and the XCDs
+// are loaded alike whatever the numbers of tiles.  False: this block has no tile.
+constexpr int kRingXcds = 8;
+constexpr int kRingGroup = 5;
+__device__ __forceinline__ bool ring_tile(int n_at, int n_bt, int per_xcd, int& at, int& bt) {
+  const int xcd = blockIdx.x % kRingXcds, local = blockIdx.x / kRingXcds;
+  const int64_t idx = static_cast<int64_t>(xcd) * per_xcd + local;
+  if (local >= per_xcd || idx >= static_cast<int64_t>(n_at) * n_bt) return false;
+  const int per_group = kRingGroup * n_at;
+  const int group = static_cast<int>(idx / per_group), in_group = static_cast<int>(idx % per_group);
+  const int left = n_bt - group * kRingGroup, here = left < kRingGroup ? left : kRingGroup;
+  at = in_group / here;
+  bt = group * kRingGroup + in_group % here;
+  return true;
+}
+
+// Nanoseconds that a launch of `tiles` tiles of 256 x 32*jt over nk stages takes (linear layers of d = 512 .. 11008,
+// measured): a stage takes `busy` when every compute unit works and `alone` when few do -- the clock gives way to the
+// power --, a tile's prologue and epilogue `ends`.
+inline int64_t ring_cost(int jt, int64_t tiles, int64_t nk) {
+  static const int64_t busy[5] = {750, 870, 1030, 1120, 1310}, alone[5] = {600, 660, 760, 855, 990},
+                       ends[5] = {6300, 7300, 8400, 9300, 10200};
+  const int i = jt - 4;
+  const int64_t per_xcd = ceil_div(tiles, kRingXcds), full = per_xcd / 32, rest = per_xcd % 32;
+  int64_t t = full * (nk * busy[i] + ends[i]);
+  if (rest) t += nk * (alone[i] + (busy[i] - alone[i]) * rest / 32) + ends[i];
+  return t;
+}
+
 // Main loop.  Abase / Bbase: wave-uniform byte pointers to element 0 of the tiles' first rows; ga[j] / gb[j]: this
 // lane's byte offsets (ring_load_row / ring_load_chunk_bytes) for its tile loads; nk = d / 64 >= 1;
-// w = wave index 0..3 (wave-uniform); a_wave_row0: first A-tile row of this wave's fragments (multiple of 32).
+// w = wave index 0..3 (wave-uniform).  acc: register r of acc[i][j] in a lane is
+//   A row 128*(w/2) + 16*i + 4*(lane/16) + r  .  B row 16*JT*(w%2) + 16*j + lane%16.
 // Every row touched must be readable for all d (clamp rows past the end of a matrix to its last row).
 // On return all LDS traffic of the loop has completed; the caller must still place a block barrier before it
 // reuses the ring memory for something else.
 // BOff: uint32_t, or int64_t when the rows of B may lie more than 4 GiB apart (gathered rows).
-template <int JB, int A_STRIDE, typename BOff>
+template <int JT, typename BOff>
 __device__ __forceinline__ void gemm_ring_256(const char* Abase, const uint32_t (&ga)[kRingALoads], const char* Bbase,
-                                              const BOff (&gb)[JB], int nk, DLLAVA_LDS char* smem, int w,
-                                              int a_wave_row0, ring_f32x16 (&acc)[2][JB]) {
-  static_assert(JB >= 4 && JB <= 8, "B tile of 128 .. 256 rows");
-  static_assert(A_STRIDE % 32 == 0 && A_STRIDE * kRingRowBytes < 65536, "fragment offset must fit the instruction");
-  constexpr int kMF = 2 * JB;       // products per k-step
-  constexpr int kNR = 2 + JB;       // fragment reads per k-step
+                                              const BOff (&gb)[JT], int nk, DLLAVA_LDS char* smem, int w,
+                                              ring_f32x4 (&acc)[8][JT]) {
+  static_assert(JT >= 4 && JT <= 8, "B tile of 128 .. 256 rows");
+  constexpr int kMF = 8 * JT;  // products per k-step of 32
+  constexpr int kNR = 8 + JT;  // fragment reads per k-step
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t s0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
-  const uint32_t fo = (lane & 31) * kRingRowBytes + (((lane >> 5) ^ ((lane >> 1) & 7)) * 16);
-  const uint32_t fa_off = a_wave_row0 * kRingRowBytes + fo, fb_off = fo;
+  // fragment of k-step ks: chunk 4*ks + lane/16 of row lane%16 (+ multiples of 16): ks enters as an exclusive-or with 64*ks
+  const uint32_t fo = (lane & 15) * kRingRowBytes + (((lane >> 4) ^ ((lane & 15) >> 1)) * 16);
+  const uint32_t a_at = s0 + (w >> 1) * 128 * kRingRowBytes + fo, b_at = s0 + (w & 1) * (16 * JT) * kRingRowBytes + fo;
 
-  ring_u32x4 ua[2], ub[JB], va[2], vb[JB];
+  ring_u32x4 ua[8], ub[JT], va[8], vb[JT];  // two fragment sets: one is multiplied while the other is read
 
-#define RING_KOFF(kt) (static_cast<int64_t>((kt) < nk ? (kt) : nk - 1) * (kRingBK * 2))
-#define RING_DMA(base, off, ko, slot, j)                                                                       \
-  __builtin_amdgcn_global_load_lds((const DLLAVA_GLB void*)((base) + (ko) + (off)),                            \
-                                   (DLLAVA_LDS void*)(smem + (slot) * kRingSlotBytes + (w + 4 * (j)) * 1024), 16, 0, 0);
-  // fragment read idx of a k-step: 0, 1 = A rows + A_STRIDE*idx; 2 .. = B rows + 32*(idx-2)
-#define RING_READ1(F, ab, bb, ks, idx)                                                                         \
-  if constexpr ((idx) < 2) F##a[(idx) & 1] = ring_lds_read16<((idx) & 1) * A_STRIDE * kRingRowBytes>((ab) ^ ((ks) * 32)); \
-  else if constexpr ((idx) < kNR) F##b[((idx) - 2) & 7] = ring_lds_read16<(((idx) - 2) & 7) * 4096>((bb) ^ ((ks) * 32));
-#define RING_WAIT(F)                                \
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); \
-  ring_tie(F##a);                                    \
-  ring_tie(F##b);
-#define RING_MFMA1(F, m)                                                                                        \
-  acc[(m) / JB][(m) % JB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring_frag(F##a[(m) / JB]), ring_frag(F##b[(m) % JB]), \
-                                                                    acc[(m) / JB][(m) % JB], 0, 0, 0);
-  // Step m of a k-step: product m of set F; behind it, fragment read m of the NEXT k-step into set G, and one of the
-  // k-step's tile loads if m is among its last NL steps (load index L0 + m - (kMF - NL) of kind X into `slot`).
-#define RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, m)                                              \
-  if constexpr ((m) < kMF) {                                                                                   \
-    RING_MFMA1(F, m)                                                                                           \
-    RING_READ1(G, ab, bb, rks, m)                                                                              \
-    if constexpr ((m) >= kMF - (NL)) { RING_DMA(X##base, off[((L0) + (m) - (kMF - (NL))) & 7], ko, slot, (L0) + (m) - (kMF - (NL))) } \
-    __builtin_amdgcn_sched_barrier(0);                                                                         \
-  }
-#define RING_KSTEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL)                                                \
-  RING_WAIT(F)                                                                                                 \
-  RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 0) RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 1)   \
-  RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 2) RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 3)   \
-  RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 4) RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 5)   \
-  RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 6) RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 7)   \
-  RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 8) RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 9)   \
-  RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 10) RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 11) \
-  RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 12) RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 13) \
-  RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 14) RING_STEP(F, G, ab, bb, rks, X, off, ko, slot, L0, NL, 15)
+  // stages past the end re-read the last one (in bounds, unused)
+  auto koff = [&](int kt) DLLAVA_INLINE { return static_cast<int64_t>(kt < nk ? kt : nk - 1) * (kRingBK * 2); };
+  auto dma = [&](const char* src, uint32_t slot, int j) DLLAVA_INLINE {
+    __builtin_amdgcn_global_load_lds((const DLLAVA_GLB void*)src,
+                                     (DLLAVA_LDS void*)(smem + slot + (w + 4 * j) * 1024), 16, 0, 0);
+  };
+  auto read1 = [&](ring_u32x4 (&fa)[8], ring_u32x4 (&fb)[JT], uint32_t ab, uint32_t bb, auto I) DLLAVA_INLINE {
+    constexpr int i = decltype(I)::value;
+    if constexpr (i < 8)
+      fa[i] = ring_lds_read16<i * 16 * kRingRowBytes>(ab);
+    else
+      fb[i - 8] = ring_lds_read16<(i - 8) * 16 * kRingRowBytes>(bb);
+  };
+  auto wait = [&](ring_u32x4 (&fa)[8], ring_u32x4 (&fb)[JT]) DLLAVA_INLINE {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    ring_tie(fa);
+    ring_tie(fb);
+  };
+  // One k-step: the products of (fa, fb); behind every other one a fragment read of the NEXT k-step into (na, nb),
+  // and NL tile loads, evenly spaced, into the slot at byte offset `slot`.  hook(m): what else is to stand behind product m.
+  auto kstep = [&](ring_u32x4 (&fa)[8], ring_u32x4 (&fb)[JT], ring_u32x4 (&na)[8], ring_u32x4 (&nb)[JT], uint32_t ab, uint32_t bb,
+                   auto IS_A, const char* base, uint32_t slot, auto&& hook) DLLAVA_INLINE {
+    constexpr int NL = decltype(IS_A)::value ? kRingALoads : JT;
+    constexpr int kGap = kMF / NL;
+    static_for<kMF>([&](auto Mi) DLLAVA_INLINE {
+      constexpr int m = decltype(Mi)::value;
+      ring_mfma(acc[m / JT][m % JT], fa[m / JT], fb[m % JT]);
+      if constexpr (m % 2 == 0 && m / 2 < kNR) read1(na, nb, ab, bb, std::integral_constant<int, m / 2>{});
+      if constexpr (m % kGap == kGap - 1 && m / kGap < NL) {
+        if constexpr (decltype(IS_A)::value)
+          dma(base + ga[m / kGap], slot, m / kGap);
+        else
+          dma(base + gb[m / kGap], slot, m / kGap);
+      }
+      hook(std::integral_constant<int, kMF - 1 - m>{});
+      if constexpr (m % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  static_assert(kMF / 2 >= kNR, "a k-step has room for the reads of the next one");
 
   // Half-stages in ring order: h(2k) = B of stage k, h(2k+1) = A of stage k; h(n) lives in slot n % 5.
-  // Iteration k multiplies stage k and issues, into the slots that stage k-1 used, the second half of A(k+1)
-  // (k-step 0), B(k+2) (k-steps 1 and 2), and after its barrier, into stage k's own B slot, the first half of A(k+2)
-  // (k-step 3).  The barrier of iteration k needs B(k+1) and A(k+1): everything but the JB loads of B(k+2).
-  constexpr int kB1 = (JB + 1) / 2, kB2 = JB - kB1;  // loads of B dealt to k-steps 1 and 2
-  // prologue: B0, A0, B1, first half of A1
-#pragma unroll
-  for (int j = 0; j < JB; ++j) RING_DMA(Bbase, gb[j], RING_KOFF(0), 0, j)
-#pragma unroll
-  for (int j = 0; j < kRingALoads; ++j) RING_DMA(Abase, ga[j], RING_KOFF(0), 1, j)
-#pragma unroll
-  for (int j = 0; j < JB; ++j) RING_DMA(Bbase, gb[j], RING_KOFF(1), 2, j)
-#pragma unroll
-  for (int j = 0; j < 4; ++j) RING_DMA(Abase, ga[j], RING_KOFF(1), 3, j)
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(JB + 4) : "memory");
+  // Iteration k multiplies stage k.  Behind its first k-step it requests B(k+2) into the slot of A(k-1), behind its
+  // second -- after its barrier -- A(k+2) into stage k's own B slot.  The barrier needs A(k+1) and B(k+1): everything
+  // but the JT loads of B(k+2).
+  constexpr uint32_t kS = kRingSlotBytes;
+  static_for<JT>([&](auto J) DLLAVA_INLINE { dma(Bbase + koff(0) + gb[J.value], 0 * kS, J.value); });
+  static_for<8>([&](auto J) DLLAVA_INLINE { dma(Abase + koff(0) + ga[J.value], 1 * kS, J.value); });
+  static_for<JT>([&](auto J) DLLAVA_INLINE { dma(Bbase + koff(1) + gb[J.value], 2 * kS, J.value); });
+  static_for<8>([&](auto J) DLLAVA_INLINE { dma(Abase + koff(1) + ga[J.value], 3 * kS, J.value); });
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(JT + 8) : "memory");
   __builtin_amdgcn_s_barrier();
+  asm volatile("s_nop 15" ::: "memory");  // the accumulators' first values, written by plain instructions, before the first product
+  static_for<kNR>([&](auto I) DLLAVA_INLINE { read1(ua, ub, a_at + kS, b_at, I); });
 
-  int sb = 0, sa = 1;  // slots of B and A of the stage being multiplied
-  {
-    const uint32_t ab = s0 + sa * kRingSlotBytes + fa_off, bb = s0 + sb * kRingSlotBytes + fb_off;
-    RING_READ1(u, ab, bb, 0, 0) RING_READ1(u, ab, bb, 0, 1) RING_READ1(u, ab, bb, 0, 2) RING_READ1(u, ab, bb, 0, 3)
-    RING_READ1(u, ab, bb, 0, 4) RING_READ1(u, ab, bb, 0, 5) RING_READ1(u, ab, bb, 0, 6) RING_READ1(u, ab, bb, 0, 7)
-    RING_READ1(u, ab, bb, 0, 8) RING_READ1(u, ab, bb, 0, 9)
-  }
-  for (int kt = 0; kt < nk; ++kt) {
-    const uint32_t ab = s0 + sa * kRingSlotBytes + fa_off, bb = s0 + sb * kRingSlotBytes + fb_off;
-    const int sa1 = sb + 3 >= kRingSlots ? sb + 3 - kRingSlots : sb + 3;  // slot of A(k+1) = h(2k+3)
-    const int sb1 = sb + 2 >= kRingSlots ? sb + 2 - kRingSlots : sb + 2;  // slot of B(k+1) = h(2k+2)
-    const int sb2 = sb + 4 >= kRingSlots ? sb + 4 - kRingSlots : sb + 4;  // slot of B(k+2) = h(2k+4)
-    const int64_t ko1 = RING_KOFF(kt + 1), ko2 = RING_KOFF(kt + 2);
-    RING_KSTEP(u, v, ab, bb, 1, A, ga, ko1, sa1, 4, 4)
-    RING_KSTEP(v, u, ab, bb, 2, B, gb, ko2, sb2, 0, kB1)
-    RING_KSTEP(u, v, ab, bb, 3, B, gb, ko2, sb2, kB1, kB2)
+  const char* Ak = Abase + koff(2);  // stage kt + 2 of either matrix
+  const char* Bk = Bbase + koff(2);
+  uint32_t o0 = 0, o1 = kS, o2 = 2 * kS, o3 = 3 * kS, o4 = 4 * kS;  // byte offsets of the slots of B(k), A(k), B(k+1), A(k+1), B(k+2)
+  uint32_t ab = (a_at ^ 64u) + o1, bb = (b_at ^ 64u) + o0;
+  int left = nk;  // stages still to multiply
+  do {
+    wait(ua, ub);
+    kstep(ua, ub, va, vb, ab, bb, std::false_type{}, Bk, o4, [&](auto E) DLLAVA_INLINE {
+      if constexpr (decltype(E)::value == 4) {
+        ab = a_at + o3;
+        bb = b_at + o2;
+      }
+    });
     // the fragments of the last k-step are in registers: this wave is done with the stage's slots
-    RING_WAIT(v)
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(JB) : "memory");
+    wait(va, vb);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(JT) : "memory");
     __builtin_amdgcn_s_barrier();
-    {
-      // last k-step; behind it the first fragments of stage k+1 and the first half of A(k+2) into this stage's B slot
-      const uint32_t nab = s0 + sa1 * kRingSlotBytes + fa_off, nbb = s0 + sb1 * kRingSlotBytes + fb_off;
-      RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 0) RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 1)
-      RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 2) RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 3)
-      RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 4) RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 5)
-      RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 6) RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 7)
-      RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 8) RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 9)
-      RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 10) RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 11)
-      RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 12) RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 13)
-      RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 14) RING_STEP(v, u, nab, nbb, 0, A, ga, ko2, sb, 0, 4, 15)
-    }
-    sb = sb1;
-    sa = sa1;
-  }
-  // the reads and loads issued for stages past the end (clamped to the last stage: in bounds, unused) are drained
-  RING_WAIT(u)
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#undef RING_KOFF
-#undef RING_DMA
-#undef RING_READ1
-#undef RING_WAIT
-#undef RING_MFMA1
-#undef RING_STEP
-#undef RING_KSTEP
+    kstep(va, vb, ua, ub, ab, bb, std::true_type{}, Ak, o0, [&](auto E) DLLAVA_INLINE {
+      if constexpr (decltype(E)::value == 6) {
+        if (left > 3) {
+          Ak += kRingBK * 2;
+          Bk += kRingBK * 2;
+        }
+      }
+      if constexpr (decltype(E)::value == 4) {
+        const uint32_t t0 = o0, t1 = o1;
+        o0 = o2, o1 = o3, o2 = o4, o3 = t0, o4 = t1;
+      }
+      if constexpr (decltype(E)::value == 2) {
+        ab = (a_at ^ 64u) + o1;
+        bb = (b_at ^ 64u) + o0;
+      }
+    });
+  } while (--left > 0);
+  // the reads and loads issued for stages past the end are drained, and the last products (whose latency the
+  // compiler does not know) have been written
+  wait(ua, ub);
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+  static_for<8>([&](auto I) DLLAVA_INLINE { static_for<JT>([&](auto J) DLLAVA_INLINE { ring_tie_acc(acc[I.value][J.value]); }); });
 }
 
 }  // namespace dllava

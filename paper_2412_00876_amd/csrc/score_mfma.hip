@@ -158,23 +158,20 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(3, 4)
 // GEMM for many rows: 256 units x 32*JB tokens per block, one block per compute unit (gemm_ring.h)
 // ------------------------------------------------------------------------------------------------
 // Same decomposition and the same cross-block reduction as score_gemm_kernel (partial logit pairs per unit tile,
-// the last block of a token tile adds them in tile order), on the large-tile product: wave w holds units 64w + [0,64)
-// of the unit tile for all 32*JB tokens of the token tile.  The token-tile width is chosen on the host so that the
+// the last block of a token tile adds them in tile order), on the large-tile product: wave w holds units
+// 128*(w/2) + [0,128) of the unit tile for half of the 32*JB tokens of the token tile.  The token-tile width is chosen on the host so that the
 // launch fills the 256 compute units evenly (score_ring_pick).
 template <int JB>
 __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a, int32_t* counters, float* partial,
-                                                                     int n_unit_tiles) {
+                                                                     int n_ut, int n_mt, int per_xcd) {
   constexpr int kTok = 32 * JB;
   __shared__ __align__(1024) char smem_raw[kRingLdsBytes];
   DLLAVA_LDS char* smem = (DLLAVA_LDS char*)smem_raw;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  // XCD x takes the token tiles x, x+8, ... and, for each, all unit tiles (see score_gemm_kernel)
-  const int n_ut = n_unit_tiles;
-  const int xcd = blockIdx.x % kXcds, jb = blockIdx.x / kXcds;
-  const int ut = jb % n_ut, mt = (jb / n_ut) * kXcds + xcd;
+  int ut, mt;
+  if (!ring_tile(n_ut, n_mt, per_xcd, ut, mt)) return;
   const int64_t M = a.M, d = a.d, dh = a.dh;
-  if (static_cast<int64_t>(mt) * kTok >= M) return;  // padding of the last round of token tiles
 
   // this lane's tile loads: byte offsets from W1 / x (rows past the end repeat the last row: their units carry
   // zero W2 weights, their tokens are not written)
@@ -202,61 +199,93 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
     gb[j] = sr * a.ldx * 2 + ring_load_chunk_bytes(row, lane);
   }
   if (use_table) __syncthreads();  // the tile loads overwrite the table
-  ring_f32x16 acc[2][JB];
+  ring_f32x4 acc[8][JB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < JB; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  gemm_ring_256<JB, 32, int64_t>(static_cast<const char*>(a.W1), ga, static_cast<const char*>(a.x), gb, static_cast<int>(d / kRingBK),
-                        smem, w, 64 * w, acc);
+    for (int j = 0; j < JB; ++j) acc[i][j] = ring_f32x4{0.f, 0.f, 0.f, 0.f};
+  gemm_ring_256<JB, int64_t>(static_cast<const char*>(a.W1), ga, static_cast<const char*>(a.x), gb, static_cast<int>(d / kRingBK),
+                             smem, w, acc);
 
-  // epilogue: lane holds, for token column (lane%32) of token tile j, units 8*(r/4) + 4*(lane/32) + r%4 of unit
-  // tile i of this wave
+  // epilogue: lane holds, for token 16*JB*(w%2) + 16*j + lane%16, units 128*(w/2) + 16*i + 4*(lane/16) + 0..3
   const bf16_t* W2 = static_cast<const bf16_t*>(a.W2);
   const bool has_b1 = a.b1 != nullptr;
   const bf16_t* zero16 = reinterpret_cast<const bf16_t*>(kZeroWords);
   float p[JB][2];
 #pragma unroll
   for (int j = 0; j < JB; ++j) p[j][0] = p[j][1] = 0.f;
+  // bias and the two weights of the lane's units, all requested at once; with dh a multiple of 4 (and aligned vectors)
+  // whole quadruples of units exist or do not, one load each
+  const bool quads = dh % 4 == 0 && (reinterpret_cast<uintptr_t>(W2) % 8 == 0) && (reinterpret_cast<uintptr_t>(a.b1) % 16 == 0);
+  float4 bq[8];
+  uint2 q0[8], q1[8];
+  const int64_t u_lane = static_cast<int64_t>(ut) * 256 + 128 * (w >> 1) + 4 * (lane >> 4);
+  if (quads) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < 8; ++i) {
+      const int64_t u0 = u_lane + 16 * i;
+      const bool ok = u0 < dh;  // operands that must be zero come from kZeroWords: no load under a condition
+      bq[i] = *reinterpret_cast<const float4*>((ok & has_b1) ? a.b1 + u0 : kZeroWords);
+      q0[i] = *reinterpret_cast<const uint2*>(ok ? W2 + u0 : zero16);
+      q1[i] = *reinterpret_cast<const uint2*>(ok ? W2 + dh + u0 : zero16);
+    }
+  } else {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int64_t u = static_cast<int64_t>(ut) * 256 + 64 * w + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      const bool ok = u < dh;  // operands that must be zero come from kZeroWords: no load under a condition
-      const float bias = *((ok & has_b1) ? a.b1 + u : kZeroWords);
-      const float w20 = bf16_to_f32(*(ok ? W2 + u : zero16));
-      const float w21 = bf16_to_f32(*(ok ? W2 + dh + u : zero16));
+    for (int i = 0; i < 8; ++i) {
+      float* bv = &bq[i].x;
+      uint32_t h0[4], h1[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t u = u_lane + 16 * i + r;
+        const bool ok = u < dh;
+        bv[r] = *((ok & has_b1) ? a.b1 + u : kZeroWords);
+        h0[r] = *(ok ? W2 + u : zero16);
+        h1[r] = *(ok ? W2 + dh + u : zero16);
+      }
+      q0[i] = uint2{h0[0] | h0[1] << 16, h0[2] | h0[3] << 16};
+      q1[i] = uint2{h1[0] | h1[1] << 16, h1[2] | h1[3] << 16};
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float bias[4] = {bq[i].x, bq[i].y, bq[i].z, bq[i].w};
+    const float w20[4] = {bf16lo_to_f32(q0[i].x), bf16hi_to_f32(q0[i].x), bf16lo_to_f32(q0[i].y), bf16hi_to_f32(q0[i].y)};
+    const float w21[4] = {bf16lo_to_f32(q1[i].x), bf16hi_to_f32(q1[i].x), bf16lo_to_f32(q1[i].y), bf16hi_to_f32(q1[i].y)};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
 #pragma unroll
       for (int j = 0; j < JB; ++j) {
-        const float g = gelu_erf_fast(acc[i][j][r] + bias);
-        p[j][0] = fmaf(g, w20, p[j][0]);
-        p[j][1] = fmaf(g, w21, p[j][1]);
+        const float g = gelu_erf_fast(acc[i][j][r] + bias[r]);
+        p[j][0] = fmaf(g, w20[r], p[j][0]);
+        p[j][1] = fmaf(g, w21[r], p[j][1]);
       }
+      __builtin_amdgcn_sched_barrier(0);  // JB values at a time: the accumulators leave no registers for more
     }
   }
   // the ring memory becomes the waves' partial sums: every wave has drained its own tile loads, the barrier covers
   // the others'
   __syncthreads();
-  float* sm_p = reinterpret_cast<float*>(smem_raw);  // [4 waves][kTok][2]
-  int* sm_last = reinterpret_cast<int*>(smem_raw + 4 * kTok * 2 * sizeof(float));
+  float* sm_p = reinterpret_cast<float*>(smem_raw);  // [2 halves of the units][kTok][2]
+  int* sm_last = reinterpret_cast<int*>(smem_raw + 2 * kTok * 2 * sizeof(float));
 #pragma unroll
   for (int j = 0; j < JB; ++j) {
-    p[j][0] += __shfl_xor(p[j][0], 32, kWave);
-    p[j][1] += __shfl_xor(p[j][1], 32, kWave);
-    if (lane < 32) {
-      sm_p[(w * kTok + j * 32 + lane) * 2 + 0] = p[j][0];
-      sm_p[(w * kTok + j * 32 + lane) * 2 + 1] = p[j][1];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      p[j][c] += __shfl_xor(p[j][c], 16, kWave);
+      p[j][c] += __shfl_xor(p[j][c], 32, kWave);
+    }
+    if (lane < 16) {
+      const int t = 16 * JB * (w & 1) + 16 * j + lane;
+      sm_p[((w >> 1) * kTok + t) * 2 + 0] = p[j][0];
+      sm_p[((w >> 1) * kTok + t) * 2 + 1] = p[j][1];
     }
   }
   __syncthreads();
   for (int t = tid; t < 2 * kTok; t += kRingThreads) {
     const int tok = t >> 1, c = t & 1;
     const int64_t m = static_cast<int64_t>(mt) * kTok + tok;
-    const float v = (sm_p[(0 * kTok + tok) * 2 + c] + sm_p[(1 * kTok + tok) * 2 + c]) +
-                    (sm_p[(2 * kTok + tok) * 2 + c] + sm_p[(3 * kTok + tok) * 2 + c]);
+    const float v = sm_p[tok * 2 + c] + sm_p[(kTok + tok) * 2 + c];
     if (m < M) st_agent(partial + (static_cast<size_t>(ut) * M + m) * 2 + c, v);
   }
   block_publish();
@@ -283,31 +312,28 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
   if (tid == 0) zero_agent(&counters[mt % kMaxCounters]);
 }
 
-// Token-tile width (in 32-token units, 4..8) that fills the chip's compute units most evenly, or 0 when the launch
-// would leave most of them idle (the 128 x 128 kernel with three blocks per compute unit serves those).
-// Cost model: a block's time is proportional to its stages' products plus a fixed part per stage (measured: 2540
-// clocks per stage at 256 tokens, of which 2048 are the products); a launch takes as many rounds as its blocks
-// need on 256 compute units.
-int score_ring_pick(int64_t M, int64_t dh) {
-  const int64_t n_ut = ceil_div(dh, 256);
+// Token-tile width (in 32-token units, 4..8) that takes least by ring_cost, or 0 when the 128 x 128 kernel takes less
+// (three tiles share a compute unit: measured 1.9 us a stage when they do, 0.62 us when few blocks run, 9 us beside the stages).
+// Every token tile needs its own counter.
+int score_ring_pick(int64_t M, int64_t d, int64_t dh) {
+  const int64_t nk = d / kRingBK, tiles128 = ceil_div(M, 128) * ceil_div(dh, 128);
+  const int64_t full = tiles128 / 768, rest = tiles128 % 768;
+  int64_t best_cost = full * (nk * 1900 + 9000) + (rest ? nk * (620 + 1280 * rest / 768) + 9000 : 0);
+  if (ceil_div(M, 128) > kMaxCounters) best_cost = INT64_MAX;
   int best = 0;
-  int64_t best_cost = 0;
   for (int jb = 8; jb >= 4; --jb) {
-    const int64_t blocks = ceil_div(M, 32 * jb) * n_ut;
-    if (blocks < 128) continue;
-    const int64_t cost = ceil_div(blocks, 256) * (256 * jb + 500);
-    if (!best || cost < best_cost) best = jb, best_cost = cost;
+    const int64_t cost = ring_cost(jb, ceil_div(M, 32 * jb) * ceil_div(dh, 256), nk);
+    if (ceil_div(M, 32 * jb) <= kMaxCounters && cost < best_cost) best = jb, best_cost = cost;
   }
   return best;
 }
 
 template <int JB>
 int score_ring_launch(const ScoreArgs& a, int32_t* counters, float* partial, hipStream_t st) {
-  const int64_t n_mt = ceil_div(a.M, 32 * JB);
-  const int n_ut = static_cast<int>(ceil_div(a.dh, 256));
-  const int64_t blocks = ceil_div(n_mt, kXcds) * kXcds * n_ut;
-  hipLaunchKernelGGL(score_ring_kernel<JB>, dim3(static_cast<unsigned>(blocks)), dim3(kRingThreads), 0, st, a, counters,
-                     partial, n_ut);
+  const int64_t n_mt = ceil_div(a.M, 32 * JB), n_ut = ceil_div(a.dh, 256);
+  const int64_t per_xcd = ceil_div(n_mt * n_ut, kRingXcds);
+  hipLaunchKernelGGL(score_ring_kernel<JB>, dim3(static_cast<unsigned>(per_xcd * kRingXcds)), dim3(kRingThreads), 0, st, a, counters,
+                     partial, static_cast<int>(n_ut), static_cast<int>(n_mt), static_cast<int>(per_xcd));
   DLLAVA_CHECK_LAUNCH("score_ring_kernel");
   return DLLAVA_OK;
 }
@@ -346,7 +372,7 @@ int score_mfma_launch(const ScoreArgs& a, hipStream_t st) {
   // Many rows: the large-tile kernel, unless forced off (DLLAVA_LAUNCH_SCORE_TILE = 1) or the shape does not fit it:
   // lane offsets into W1 are 32-bit, and every token tile needs its own counter.
   {
-    int jb = score_ring_pick(a.M, a.dh);
+    int jb = score_ring_pick(a.M, a.d, a.dh);
     const int forced = launch_override(DLLAVA_LAUNCH_SCORE_TILE);
     if (forced == 1) jb = 0;
     if (forced >= 4 && forced <= 8) jb = forced;
