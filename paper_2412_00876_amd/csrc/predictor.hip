@@ -21,6 +21,7 @@
 // added in wave / part order), so the results are bit-reproducible.
 #include <cmath>
 
+#include "gemm_ring.h"
 #include "gemm_tile.h"
 #include "prefill_args.h"
 #include "score_args.h"
@@ -151,7 +152,157 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(3, 4)
   }
 }
 
+// The same layer on the large-tile product of gemm_ring.h, one block per compute unit: 256 features x 32*JT rows.
+template <int JT>
+__global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, int n_ft, int n_rt, int per_xcd) {
+  constexpr int kTok = 32 * JT;
+  __shared__ __align__(1024) char smem_raw[kRingLdsBytes];
+  DLLAVA_LDS char* smem = (DLLAVA_LDS char*)smem_raw;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  int ft, rt;
+  if (!ring_tile(n_ft, n_rt, per_xcd, ft, rt)) return;
+  const int64_t M = a.M;
+  const int N = a.N, K = a.K;
+
+  SpanTable* spans = reinterpret_cast<SpanTable*>(smem_raw);
+  const bool use_table = a.seq_off != nullptr && a.B > 0 && a.B <= kSpanLdsMax;
+  if (use_table) span_table_build<kRingThreads>(spans, a.seq_off, a.vis_start, a.vis_len, a.B);
+  uint32_t ga[kRingALoads];
+  int64_t gb[JT];  // gathered rows of X may lie far apart
+  const char* Wt = reinterpret_cast<const char*>(a.W) + static_cast<int64_t>(ft) * 256 * K * 2;
+#pragma unroll
+  for (int j = 0; j < kRingALoads; ++j) {
+    const int row = ring_load_row(w, j, lane);
+    const int u = ft * 256 + row < N ? row : N - 1 - ft * 256;  // features past N are computed and dropped
+    ga[j] = static_cast<uint32_t>(u) * static_cast<uint32_t>(K) * 2u + ring_load_chunk_bytes(row, lane);
+  }
+#pragma unroll
+  for (int j = 0; j < JT; ++j) {
+    const int row = ring_load_row(w, j, lane);
+    int64_t m = static_cast<int64_t>(rt) * kTok + row;
+    if (m >= M) m = M - 1;
+    int64_t sr = use_table ? span_table_row(spans, a.B, m) : score_src_row(a.seq_off, a.vis_start, a.vis_len, a.B, m);
+    if (sr < 0) sr = 0;
+    gb[j] = sr * a.ldx * 2 + ring_load_chunk_bytes(row, lane);
+  }
+  if (use_table) __syncthreads();  // the tile loads overwrite the table
+  ring_f32x4 acc[8][JT];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < JT; ++j) acc[i][j] = ring_f32x4{0.f, 0.f, 0.f, 0.f};
+  gemm_ring_256<JT, int64_t>(Wt, ga, reinterpret_cast<const char*>(a.X), gb, K / kRingBK, smem, w, acc);
+  __syncthreads();  // the ring memory becomes the transposed output tile
+
+  // lane: row 16*JT*(w%2) + 16*j + lane%16; register r of acc[i]: feature 128*(w/2) + 16*i + 4*(lane/16) + r
+  const int g = lane >> 4;
+  bf16_t* sO = reinterpret_cast<bf16_t*>(smem_raw);  // [kTok rows][32 chunks of 8 features], chunk c of row t at c ^ (t % 16)
+  const int f_lane = ft * 256 + 128 * (w >> 1) + 4 * g;
+  // a tile never straddles two output groups (group is N or a multiple of 256): its place is scalar arithmetic
+  const int og = ft * 256 / a.group;
+  const int64_t out0 = og * a.group_stride - static_cast<int64_t>(og) * a.group;  // + feature + row * ldy
+  // Everything the epilogue reads from memory is requested at once, into the registers the fragments have left (a load
+  // and a wait per fragment took 12 us of a 256 x 256 tile).
+  float4 bs[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    bs[i] = *reinterpret_cast<const float4*>(a.bias && f_lane + 16 * i < N ? a.bias + f_lane + 16 * i : kZeroWords);
+  uint2 rr[JT][8];
+  if (a.R) {
+#pragma unroll
+    for (int j = 0; j < JT; ++j) {
+      int64_t m = static_cast<int64_t>(rt) * kTok + 16 * JT * (w & 1) + 16 * j + (lane & 15);
+      if (m >= M) m = M - 1;
+      const bf16_t* rrow = a.R + out0 + m * a.ldy;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) rr[j][i] = *reinterpret_cast<const uint2*>(rrow + (f_lane + 16 * i < N ? f_lane + 16 * i : ft * 256));
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < JT; ++j) {
+    const int t = 16 * JT * (w & 1) + 16 * j + (lane & 15);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e];
+      v[0] += bs[i].x; v[1] += bs[i].y; v[2] += bs[i].z; v[3] += bs[i].w;
+      if (a.act == 1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = gelu_erf_fast(v[e]);
+      }
+      if (a.R) {  // block-uniform; the result is rounded once, after the addition / the product
+        const float r0 = bf16lo_to_f32(rr[j][i].x), r1 = bf16hi_to_f32(rr[j][i].x), r2 = bf16lo_to_f32(rr[j][i].y), r3 = bf16hi_to_f32(rr[j][i].y);
+        if (a.act == 2) {  // gated unit: R holds the gate, the output is this product times SiLU(gate)
+          v[0] *= silu_fast(r0); v[1] *= silu_fast(r1); v[2] *= silu_fast(r2); v[3] *= silu_fast(r3);
+        } else {
+          v[0] += r0; v[1] += r1; v[2] += r2; v[3] += r3;
+        }
+      }
+      uint2 o;
+      o.x = pack_bf16x2(v[0], v[1]);
+      o.y = pack_bf16x2(v[2], v[3]);
+      const int c = 16 * (w >> 1) + 2 * i + (g >> 1);  // chunk of 8 features; this lane's half of it: g % 2
+      *reinterpret_cast<uint2*>(sO + t * 256 + ((c ^ (t & 15)) * 8) + (g & 1) * 4) = o;
+    }
+    __builtin_amdgcn_sched_barrier(0);  // one column at a time: the accumulators leave no registers for more
+  }
+  __syncthreads();
+  // thread: chunk tid%32 of rows tid/32 + 8k
+  const int c = tid & 31, f = ft * 256 + c * 8;
+  if (f >= N) return;
+  bf16_t* out = a.Y + out0 + f;
+#pragma unroll 4
+  for (int k = 0; k < kTok / 8; ++k) {
+    const int t = (tid >> 5) + 8 * k;
+    const int64_t m = static_cast<int64_t>(rt) * kTok + t;
+    const uint4 piece = *reinterpret_cast<const uint4*>(sO + t * 256 + ((c ^ (t & 15)) * 8));
+    if (m < M) *reinterpret_cast<uint4*>(out + m * a.ldy) = piece;
+  }
+}
+
+// Row tile of the large-tile kernel, in units of 32 rows (4..8), or 0 for the 128 x 128 kernel, whichever takes less by
+// what the two take (nanoseconds, as in ring_cost; three 128 x 128 tiles share a compute unit).
+int lin_ring_pick(int64_t M, int64_t N, int64_t K) {
+  const int64_t nk = K / kRingBK, tiles128 = ceil_div(M, 128) * ceil_div(N, 128);
+  const int64_t full = tiles128 / 768, rest = tiles128 % 768;
+  int64_t best_cost = full * (nk * 1900 + 6500) + (rest ? nk * (620 + 1280 * rest / 768) + 6500 : 0);
+  int best = 0;
+  for (int jt = 8; jt >= 4; --jt) {
+    const int64_t cost = ring_cost(jt, ceil_div(M, 32 * jt) * ceil_div(N, 256), nk);
+    if (cost < best_cost) best = jt, best_cost = cost;
+  }
+  return best;
+}
+
+template <int JT>
+int launch_lin_ring(const LinArgs& a, hipStream_t st) {
+  const int64_t n_ft = ceil_div(a.N, 256), n_rt = ceil_div(a.M, 32 * JT);
+  const int64_t per_xcd = ceil_div(n_ft * n_rt, kRingXcds);
+  if (per_xcd * kRingXcds > 0x7fffffffLL) DLLAVA_FAIL(DLLAVA_ESHAPE, "linear: too many rows");
+  hipLaunchKernelGGL(lin_ring_kernel<JT>, dim3(static_cast<unsigned>(per_xcd * kRingXcds)), dim3(kRingThreads), 0, st, a,
+                     static_cast<int>(n_ft), static_cast<int>(n_rt), static_cast<int>(per_xcd));
+  DLLAVA_CHECK_LAUNCH("lin_ring_kernel");
+  return DLLAVA_OK;
+}
+
 int launch_lin(const LinArgs& a, hipStream_t st) {
+  int jt = lin_ring_pick(a.M, a.N, a.K);
+  if (const int forced = launch_override(DLLAVA_LAUNCH_LINEAR_TILE)) {
+    if (forced == 1) jt = 0;
+    if (forced >= 4 && forced <= 8) jt = forced;
+  }
+  // a lane's offsets into the 256 rows of a W tile are 32-bit
+  if (jt && static_cast<int64_t>(a.K) * 512 < (int64_t{1} << 32)) {
+    switch (jt) {
+      case 4: return launch_lin_ring<4>(a, st);
+      case 5: return launch_lin_ring<5>(a, st);
+      case 6: return launch_lin_ring<6>(a, st);
+      case 7: return launch_lin_ring<7>(a, st);
+      default: return launch_lin_ring<8>(a, st);
+    }
+  }
   const int n_ut = static_cast<int>(ceil_div(a.N, 128));
   const int64_t n_mt = ceil_div(a.M, 128);
   const int64_t blocks = ceil_div(n_mt, kXcds) * kXcds * n_ut;
