@@ -134,7 +134,7 @@ extern "C" int dllava_masked_attn(const void* Q, const void* K, const void* V, i
   a.Q = Q; a.K = K; a.V = V; a.O = O; a.off = off; a.B = B; a.H = H;
   a.scale_log2 = scale * 1.44269504088896340736f;
   a.key_words = words;
-  const int rc = prefill_mfma_launch(a, rows, Dh, st);
+  const int rc = masked_mfma_launch(a, rows, Dh, st);
   if (rc > 0) DLLAVA_FAIL(DLLAVA_ESHAPE, "masked_attn: too many rows or sequences");
   return rc;
 }

@@ -102,13 +102,12 @@ __device__ __forceinline__ u32x2 lds_read8_tr16(uint32_t addr) {
 }
 
 // One key tile for one wave.  diag: some score of the tile has to be masked: the tile reaches above the diagonal of
-// some query of the wave (keys > qi), or kmask (bit i: key j0 + i may be seen by other queries than itself) has a
-// zero bit.
+// some query of the wave (keys > qi).
 // kb / vb: LDS byte addresses of this lane's first K and V fragment pieces in the tile (see the kernel).
-template <int DH, bool MASKED>
+template <int DH>
 __device__ __forceinline__ void tile_step(uint32_t kb, uint32_t vb_in, const uint4 (&qf)[DH / 16],
                                           f32x16 (&o_acc)[DH / 32], float& m_ref, float& l_run, float scale_log2,
-                                          int j0, int qi, int g, bool diag, uint32_t kmask, int q_self) {
+                                          int j0, int qi, int g, bool diag) {
   constexpr int kDB = DH / 32;
   constexpr int kRowBytes = DH * 2;
   uint32_t vb = vb_in;
@@ -159,16 +158,14 @@ __device__ __forceinline__ void tile_step(uint32_t kb, uint32_t vb_in, const uin
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int key = j0 + 8 * (r >> 2) + 4 * g + (r & 3);
-      const bool open = !MASKED || ((kmask >> (8 * (r >> 2) + (r & 3) + 4 * g)) & 1u);
-      if (key > qi || (!open && key != q_self)) s[r] = -INFINITY;
+      if (key > qi) s[r] = -INFINITY;
     }
   }
   float tmax = -INFINITY;
 #pragma unroll
   for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
   tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
-  // scale > 0: the maximum of the scaled scores; -inf for a query that sees no key of this tile (possible with key
-  // masks only).  m_ref starts at a finite floor, so such a tile leaves the query's state as it is (alpha = 1, p = 0).
+  // scale > 0: the maximum of the scaled scores (every query sees the first key of every tile it walks)
   const float m_t = tmax * scale_log2;
   if (__any(m_t > m_ref + kSlack)) {
     const float m_new = fmaxf(m_ref, m_t);
@@ -234,9 +231,8 @@ __device__ __forceinline__ void tile_step(uint32_t kb, uint32_t vb_in, const uin
 // idle two thirds of the time); a persistent block pays them once.
 // Items are numbered by DESCENDING query-tile index over all sequences, heads adjacent: a causal item's work grows
 // with its tile index, so every block takes its longest items first and the launch ends with the shortest ones.
-// MASKED: the variant with key masks (a.key_words); the plain kernel carries none of its registers.
-template <int DH, int NWQ, bool MASKED>
-__global__ __launch_bounds__(NWQ * kWave, (NWQ >= 2 && !MASKED) ? 2 : 1) void prefill_mfma_kernel(PrefillArgs args, int items_cap) {
+template <int DH, int NWQ>
+__global__ __launch_bounds__(NWQ * kWave, NWQ >= 2 ? 2 : 1) void prefill_mfma_kernel(PrefillArgs args, int items_cap) {
   // the arguments as locals (the closures below then capture plain values, which the compiler keeps in registers)
   const int aB = args.B, aMaxPages = args.max_pages;
   const float aScale = args.scale_log2;
@@ -260,15 +256,13 @@ __global__ __launch_bounds__(NWQ * kWave, (NWQ >= 2 && !MASKED) ? 2 : 1) void pr
   const int wq = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int H = args.H;
   const int g = lane >> 5, lq = lane & 31;
-  // Offsets, page table and mask words were written by earlier launches and do not change while this kernel runs:
+  // Offsets and page table were written by earlier launches and do not change while this kernel runs:
   // read through the constant address space, block-uniform indices become scalar loads.  (As plain pointers they
   // may alias the output, which this kernel now stores inside its loop, and every page id became a vector load
   // with a full vector-memory wait behind it -- a wait for the tile loads in flight.)
   typedef const int32_t __attribute__((address_space(4)))* ConstI32;
-  typedef const uint32_t __attribute__((address_space(4)))* ConstU32;
   const ConstI32 off_c = (ConstI32)args.off;
   const ConstI32 bt_c = (ConstI32)args.block_table;
-  const ConstU32 kw_c = (ConstU32)args.key_words;
   const bool full = args.full != 0;  // no causal mask: all keys of the sequence (block-uniform)
   const bool paged = aK == nullptr;  // block-uniform
   const int step = static_cast<int>(gridDim.x);
@@ -355,12 +349,6 @@ __global__ __launch_bounds__(NWQ * kWave, (NWQ >= 2 && !MASKED) ? 2 : 1) void pr
     for (int ks = 0; ks < DH / 16; ++ks) dst[ks] = *reinterpret_cast<const uint4*>(qrow + 16 * ks);
   };
   load_queries(C, qn);
-  // key-mask word of a tile: a block-uniform scalar load, fetched one tile before it is used
-  uint32_t kmask_next = ~0u;
-  auto mask_word = [&](const Item& it, int t) __attribute__((always_inline)) {
-    return MASKED ? kw_c[(it.r0 >> 5) + it.b + t] : ~0u;
-  };
-  kmask_next = mask_word(C, 0);
 
   f32x16 o_acc[kDB];
   float m_ref = -1e30f, l_run = 0.f;  // finite floor, not -inf: see tile_step
@@ -467,7 +455,7 @@ __global__ __launch_bounds__(NWQ * kWave, (NWQ >= 2 && !MASKED) ? 2 : 1) void pr
     // This wave's own loads of the tile are waited for (those of the next tile, requested later, may stay in flight),
     // then the barrier makes every wave's part of the tile visible and says that all waves have left the tile before.
     // The count assumes that nothing but the tile loads of the NEXT tile was issued after this tile's loads; whatever
-    // else is in flight (queries of a new item, an item's output stores, mask words) only makes the wait longer.
+    // else is in flight (queries of a new item, an item's output stores) only makes the wait longer.
     // The kernel must not spill registers (scratch traffic would count too): the tests check the build's resource report.
     if (ahead > 0)
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * D::kLoads) : "memory");
@@ -493,16 +481,12 @@ __global__ __launch_bounds__(NWQ * kWave, (NWQ >= 2 && !MASKED) ? 2 : 1) void pr
       if (nextC.valid) load_queries(nextC, qn);
     }
     const int j0 = tC * kBN;
-    const uint32_t kmask = kmask_next;  // wave-uniform
-    if (MASKED && tC + 1 < nC) kmask_next = mask_word(C, tC + 1);
-    // skipped (wave-uniform): the tile lies entirely above this wave's diagonal, the wave has no query, or every key
-    // of the tile is masked and none of them is a query of this wave
-    if ((full || j0 <= iw + 31) && iw < C.n && !(kmask == 0u && j0 + kBN - 1 < iw)) {
+    // skipped (wave-uniform): the tile lies entirely above this wave's diagonal, or the wave has no query
+    if ((full || j0 <= iw + 31) && iw < C.n) {
       const uint32_t kb = kb0 + cur * (kTileElems * 2), vb = vb0 + cur * (kTileElems * 2);
-      // masking needed: some key of the tile may exceed some query of the wave (causal) or the end of the sequence
-      // (full), or is hidden by its mask bit
-      tile_step<DH, MASKED>(kb, vb, qf, o_acc, m_ref, l_run, aScale, j0, full ? C.n - 1 : qi, g,
-                            j0 + kBN - 1 > (full ? C.n - 1 : iw) || kmask != ~0u, kmask, qi);
+      // masking needed: some key of the tile may exceed some query of the wave (causal) or the end of the sequence (full)
+      tile_step<DH>(kb, vb, qf, o_acc, m_ref, l_run, aScale, j0, full ? C.n - 1 : qi, g,
+                    j0 + kBN - 1 > (full ? C.n - 1 : iw));
     }
     cur = cur == kStages - 1 ? 0 : cur + 1;
     --ahead;
@@ -517,13 +501,12 @@ __global__ __launch_bounds__(NWQ * kWave, (NWQ >= 2 && !MASKED) ? 2 : 1) void pr
     C = nextC;
     nextC = locate(item_of(jC + 1));
     nC = last_key_of(C) / kBN + 1;
-    kmask_next = mask_word(C, 0);
   }
   store_item();
 }
 
 // blocks that fit the chip at once (persistent launch): compute units x blocks per compute unit, found once per kernel
-template <int DH, int NWQ, bool MASKED>
+template <int DH, int NWQ>
 int64_t resident_blocks() {
   static int64_t cached = 0;  // the same value whichever thread gets here first
   if (cached) return cached;
@@ -531,7 +514,7 @@ int64_t resident_blocks() {
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, prefill_mfma_kernel<DH, NWQ, MASKED>, NWQ * kWave, 0) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, prefill_mfma_kernel<DH, NWQ>, NWQ * kWave, 0) != hipSuccess ||
       per_cu <= 0)
     per_cu = 2;
   cached = static_cast<int64_t>(cus) * per_cu;
@@ -547,15 +530,9 @@ int launch(const PrefillArgs& a, int64_t rows, hipStream_t st) {
   // one item per block when the sequences are too many to be numbered in a wave's lanes (see the kernel)
   const bool persistent = a.B <= kWave;
   const int forced = persistent ? launch_override(DLLAVA_LAUNCH_PREFILL_BLOCKS) : 0;  // tests: few blocks, many items each
-  if (a.key_words) {
-    const int64_t slots = forced ? forced : (persistent ? resident_blocks<DH, NWQ, true>() : items);
-    const dim3 grid(static_cast<unsigned>(items < slots ? items : slots));
-    hipLaunchKernelGGL((prefill_mfma_kernel<DH, NWQ, true>), grid, dim3(NWQ * kWave), 0, st, a, static_cast<int>(items));
-  } else {
-    const int64_t slots = forced ? forced : (persistent ? resident_blocks<DH, NWQ, false>() : items);
-    const dim3 grid(static_cast<unsigned>(items < slots ? items : slots));
-    hipLaunchKernelGGL((prefill_mfma_kernel<DH, NWQ, false>), grid, dim3(NWQ * kWave), 0, st, a, static_cast<int>(items));
-  }
+  const int64_t slots = forced ? forced : (persistent ? resident_blocks<DH, NWQ>() : items);
+  const dim3 grid(static_cast<unsigned>(items < slots ? items : slots));
+  hipLaunchKernelGGL((prefill_mfma_kernel<DH, NWQ>), grid, dim3(NWQ * kWave), 0, st, a, static_cast<int>(items));
   DLLAVA_CHECK_LAUNCH("prefill_mfma_kernel");
   return DLLAVA_OK;
 }
