@@ -1,76 +1,160 @@
 // dllava_score: predictor logits D = GELU(x W1^T + b1) W2^T + b2 (Eq. 5 line 1 / Eq. 11 line 1 of the
 // paper, with the two-layer predictor d -> dh -> 2).
 //
-// Precision-generic path: one block per scored row.  The row is staged in LDS as float32; each wave
-// takes hidden units round-robin, lanes stride over d with 16-byte loads of the W1 row, a butterfly
-// sums the wave, and lane 0 applies bias + GELU and accumulates the two logit terms.  The four wave
-// partials are added in wave order, so the result is bit-reproducible.  It serves float32 inputs and
-// shapes the matrix-core kernels do not cover.
+// Precision-generic path, for float32 inputs and shapes the matrix-core kernels do not cover.  A block takes R scored
+// rows (1 or 4: W1 is read once per block), staged in LDS as float32.  Each of its 16 waves takes eight hidden units at a
+// time (four where the registers hold no more), its lanes strided over d with 16-byte loads of those W1 rows, the next
+// loads in flight while the last are multiplied -- the first ones before the rows are staged, which they do not depend on.
+// The sums of a wave's units are reduced together: at each exchange a lane hands over half of its sums and keeps the
+// other half, so eight units cost ten lane exchanges instead of 48, and bias and GELU are applied to all of them at once.
+// All sums run in a fixed order: bit-reproducible.
+// What bounds it is the chain of these steps for few rows, the LDS and L1 reads of the multiply for many.  float32,
+// d = 512, dh = 128, with four waves and one unit per wave at a time / now: one row 22.0 / 6.4 us, 200 rows 23.5 / 7.2 us,
+// 4608 rows 104 / 51 us; d = 4096, dh = 512: one row 598 / 78 us, 4608 rows 2200 / 679 us.
 #include "score_args.h"
 
 namespace dllava {
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / kWave;
 
-template <typename T>
+// kUnits: hidden units a wave takes at a time
+template <typename T, int R, int kUnits>
 __global__ __launch_bounds__(kThreads) void score_generic_kernel(ScoreArgs a) {
-  extern __shared__ float xs[];  // [d]
-  __shared__ float sm_l[kWaves][2];
+  extern __shared__ float xs[];  // [R][d]
+  __shared__ float sm_l[kWaves][R][2];
   constexpr int E = Elem<T>::kPer16B;
-  const int64_t m = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const int64_t src = score_src_row(a.seq_off, a.vis_start, a.vis_len, a.B, m);
-  if (src < 0) return;
-  const T* xrow = static_cast<const T*>(a.x) + src * a.ldx;
-  const int chunks = static_cast<int>(a.d / E);
-  for (int c = tid; c < chunks; c += kThreads) {
-    float f[E];
-    Elem<T>::unpack(*reinterpret_cast<const uint4*>(xrow + c * E), f);
-#pragma unroll
-    for (int e = 0; e < E; ++e) xs[c * E + e] = f[e];
-  }
-  __syncthreads();
+  constexpr int kPerUnit = kWave / kUnits;
+  const int64_t m0 = (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * R;
+  if (m0 >= a.M) return;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int d = static_cast<int>(a.d), chunks = d / E, dh = static_cast<int>(a.dh);
   const T* W1 = static_cast<const T*>(a.W1);
   const T* W2 = static_cast<const T*>(a.W2);
-  float l0 = 0.f, l1 = 0.f;
-  for (int64_t j = w; j < a.dh; j += kWaves) {
-    const T* wrow = W1 + j * a.d;
-    float acc = 0.f;
-    for (int c = lane; c < chunks; c += kWave) {
-      float f[E];
-      Elem<T>::unpack(*reinterpret_cast<const uint4*>(wrow + c * E), f);
+  // piece (j0, c): chunk c of units j0 .. j0+7 (units past dh repeat the last one and get no weight; chunks past the row
+  // repeat the last one and are not used)
+  uint4 wv[kUnits];
+  auto load = [&](int j0, int c) __attribute__((always_inline)) {
+    const int cc = c < chunks ? c : chunks - 1;
 #pragma unroll
-      for (int e = 0; e < E; ++e) acc = fmaf(xs[c * E + e], f[e], acc);
+    for (int u = 0; u < kUnits; ++u) {
+      const int j = j0 + u < dh ? j0 + u : dh - 1;
+      wv[u] = *reinterpret_cast<const uint4*>(W1 + static_cast<int64_t>(j) * d + static_cast<int64_t>(cc) * E);
     }
-    acc = wave_sum(acc);
-    const float g = gelu_erf(acc + (a.b1 ? a.b1[j] : 0.f));
-    l0 = fmaf(g, Elem<T>::load(W2 + j), l0);
-    l1 = fmaf(g, Elem<T>::load(W2 + a.dh + j), l1);
-  }
-  if (lane == 0) {
-    sm_l[w][0] = l0;
-    sm_l[w][1] = l1;
+  };
+  load(w * kUnits, lane);
+  int64_t src[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) src[r] = m0 + r < a.M ? score_src_row(a.seq_off, a.vis_start, a.vis_len, a.B, m0 + r) : -1;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (src[r] < 0) continue;  // beyond the spans: not read, not written
+    const T* xrow = static_cast<const T*>(a.x) + src[r] * a.ldx;
+    for (int c = tid; c < chunks; c += kThreads) {
+      float f[E];
+      Elem<T>::unpack(*reinterpret_cast<const uint4*>(xrow + static_cast<int64_t>(c) * E), f);
+#pragma unroll
+      for (int e = 0; e < E; ++e) xs[r * d + c * E + e] = f[e];
+    }
   }
   __syncthreads();
-  if (tid == 0) {
-    float s0 = a.b2 ? a.b2[0] : 0.f, s1 = a.b2 ? a.b2[1] : 0.f;
+  float l0[R], l1[R];
 #pragma unroll
-    for (int i = 0; i < kWaves; ++i) {
-      s0 += sm_l[i][0];
-      s1 += sm_l[i][1];
+  for (int r = 0; r < R; ++r) l0[r] = l1[r] = 0.f;
+  for (int j0 = w * kUnits; j0 < dh; j0 += kWaves * kUnits) {
+    float acc[R][kUnits];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int u = 0; u < kUnits; ++u) acc[r][u] = 0.f;
+    for (int c0 = 0; c0 < chunks; c0 += kWave) {  // wave-uniform
+      const int c = c0 + lane;
+      uint4 cur[kUnits];
+#pragma unroll
+      for (int u = 0; u < kUnits; ++u) cur[u] = wv[u];
+      if (c0 + kWave < chunks)
+        load(j0, c + kWave);
+      else if (j0 + kWaves * kUnits < dh)
+        load(j0 + kWaves * kUnits, lane);
+      if (c < chunks) {
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+          float f[E];
+          Elem<T>::unpack(cur[u], f);
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[r][u] = fmaf(xs[r * d + c * E + e], f[e], acc[r][u]);
+        }
+      }
     }
-    a.logits[2 * m] = s0;
-    a.logits[2 * m + 1] = s1;
+    const int j = j0 + lane / kPerUnit;  // the unit whose whole sum this lane ends with
+    const bool ok = j < dh;
+    const float bias = ok && a.b1 ? a.b1[j] : 0.f;
+    const float w20 = ok ? Elem<T>::load(W2 + j) : 0.f, w21 = ok ? Elem<T>::load(W2 + a.dh + j) : 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float* v = acc[r];
+#pragma unroll
+      for (int half = kUnits / 2, o = 32; half >= 1; half >>= 1, o >>= 1) {
+        const bool up = (lane & o) != 0;
+#pragma unroll
+        for (int u = 0; u < half; ++u) {
+          const float give = up ? v[u] : v[u + half], keep = up ? v[u + half] : v[u];
+          v[u] = keep + __shfl_xor(give, o, kWave);
+        }
+      }
+      float sum = v[0];
+#pragma unroll
+      for (int o = kPerUnit / 2; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+      const float g = gelu_erf(sum + bias);
+      l0[r] = fmaf(g, w20, l0[r]);
+      l1[r] = fmaf(g, w21, l1[r]);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+#pragma unroll
+    for (int o = kPerUnit; o < kWave; o <<= 1) {  // over the wave's units (the lanes of a unit hold the same)
+      l0[r] += __shfl_xor(l0[r], o, kWave);
+      l1[r] += __shfl_xor(l1[r], o, kWave);
+    }
+    if (lane == 0) {
+      sm_l[w][r][0] = l0[r];
+      sm_l[w][r][1] = l1[r];
+    }
+  }
+  __syncthreads();
+  if (tid < 2 * R) {
+    const int r = tid >> 1, c = tid & 1;
+    float s = a.b2 ? a.b2[c] : 0.f;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) s += sm_l[i][r][c];
+    int64_t mine = -1;
+#pragma unroll
+    for (int q = 0; q < R; ++q) mine = q == r ? src[q] : mine;
+    if (mine >= 0) a.logits[2 * (m0 + r) + c] = s;
   }
 }
 
+// Four rows per block above 512 rows: a compute unit holds one block at a time, so up to there single rows are at most
+// two rounds of the chip (512 rows singly / in fours: float32, d = 512, dh = 128: 12.9 / 11.9 us, d = 4096, dh = 512:
+// 153 / 137 us; bfloat16, d = 520, dh = 130: 14.4 / 17.7 us) and from there at least three (768 rows, the first of these:
+// three rounds of 6.3 us singly, 12.3 us in fours).  Only while four float32 rows fit 64 KiB of LDS.
 template <typename T>
 int launch_generic(const ScoreArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((score_generic_kernel<T>), dim3(static_cast<unsigned>(a.M)), dim3(kThreads),
-                     static_cast<size_t>(a.d) * sizeof(float), st, a);
+  constexpr int U1 = sizeof(T) == 4 ? 8 : 4;  // what the registers of a 16-wave block hold
+  const size_t row = static_cast<size_t>(a.d) * sizeof(float);
+  const int R = a.M > 512 && 4 * row <= 64 * 1024 ? 4 : 1;
+  const int64_t n = ceil_div(a.M, R);
+  const int64_t gx = n < (1 << 20) ? n : (1 << 20);  // a grid dimension holds fewer than 2^32 threads
+  const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(ceil_div(n, gx)));
+  if (R == 4)
+    hipLaunchKernelGGL((score_generic_kernel<T, 4, 4>), grid, dim3(kThreads), 4 * row, st, a);
+  else
+    hipLaunchKernelGGL((score_generic_kernel<T, 1, U1>), grid, dim3(kThreads), row, st, a);
   DLLAVA_CHECK_LAUNCH("score_generic_kernel");
   return DLLAVA_OK;
 }
