@@ -152,7 +152,8 @@ def _p(t: Optional[torch.Tensor]) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        stream = torch.cuda.current_stream().cuda_stream
+        # torch's current stream of the current device, without building a Stream object for it (2.9 us per call; 0.3 us)
+        stream = torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     elif hasattr(stream, "cuda_stream"):
         stream = stream.cuda_stream
     return stream or None
