@@ -417,6 +417,7 @@ __global__ __launch_bounds__(kWave) void span_offsets_kernel(const int32_t* __re
 // 512 -> 256 -> 128 -> 2 from there on the matrix cores, the weights of both layers requested at its very start.
 constexpr int kSmallRows = 64;
 constexpr int kSmallSplit = 4;    // blocks along d
+constexpr int kSmallXcds = 8, kSmallFetch = 8;  // dies; parts of the head's weights fetched by blocks of their own
 constexpr int kZs = 520, kH1s = 264, kH2s = 136;  // LDS row strides (elements): 16-byte pieces of 16 rows fall in 16 bank groups
 
 // Register-to-LDS order inside ONE wave: the area written and read is private to the wave and the wave's LDS
@@ -521,7 +522,27 @@ __global__ __launch_bounds__(256) void small_in_kernel(const bf16_t* __restrict_
                                                        const bf16_t* __restrict__ W, float* __restrict__ partial,
                                                        int32_t B, const int32_t* __restrict__ seq_off,
                                                        const int32_t* __restrict__ vis_start,
-                                                       const int32_t* __restrict__ vis_len, int n_fg, int KQ, int N) {
+                                                       const int32_t* __restrict__ vis_len, int n_fg, int KQ, int N,
+                                                       const bf16_t* __restrict__ Wh1, const bf16_t* __restrict__ Wh2) {
+  // The blocks past the product's bring the head's weights into the second-level cache of the dies that small_head_kernel
+  // runs on next, where one compute unit pulls all 320 KiB of them: block 8p + x, on die x like block x of that launch,
+  // reads part p while the others stream W_in.  At the end of a decode step over whole layers, whose weights leave nothing
+  // cached, that took small_head_kernel from 19.8 to 12.0 us (8 rows), with this launch at 6.1 us as before.
+  if (static_cast<int>(blockIdx.x) >= n_fg * KQ) {
+    const int p = (static_cast<int>(blockIdx.x) - n_fg * KQ) / kSmallXcds;
+    if (static_cast<int>(blockIdx.x) % kSmallXcds >= NT) return;
+    constexpr int n1 = kPW * kPH1 / 8, n2 = kPH1 * kPH2 / 8, each = (n1 + n2) / (256 * kSmallFetch);  // 16-byte pieces
+    static_assert(each * 256 * kSmallFetch == n1 + n2, "whole pieces per thread");
+    uint4 v[each];
+#pragma unroll
+    for (int i = 0; i < each; ++i) {
+      const int at = (p * each + i) * 256 + static_cast<int>(threadIdx.x);
+      v[i] = *reinterpret_cast<const uint4*>(at < n1 ? Wh1 + 8 * at : Wh2 + 8 * (at - n1));
+    }
+#pragma unroll
+    for (int i = 0; i < each; ++i) want_now(v[i]);
+    return;
+  }
   // per wave: 32 weight rows and 32*NT input rows x 64 elements; after its last line a wave's area carries its sums
   __shared__ __align__(16) bf16_t stage[4][(1 + NT) * 32 * 64];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
@@ -1171,11 +1192,13 @@ extern "C" int dllava_predict(const void* x, int64_t ldx, int64_t M, int32_t B, 
     const int Mi = static_cast<int>(M), Ki = static_cast<int>(p->d);
     const bf16_t* Wi = static_cast<const bf16_t*>(p->W_in);
     if (nt == 1)
-      hipLaunchKernelGGL(small_in_kernel<1>, dim3(16 * kSmallSplit), dim3(256), 0, st, X, ldx, Mi, Ki, Wi, r.small, B,
-                         seq_off, vis_start, vis_len, 16, kSmallSplit, kPW);
+      hipLaunchKernelGGL(small_in_kernel<1>, dim3(16 * kSmallSplit + kSmallXcds * kSmallFetch), dim3(256), 0, st, X, ldx, Mi, Ki, Wi,
+                         r.small, B, seq_off, vis_start, vis_len, 16, kSmallSplit, kPW, static_cast<const bf16_t*>(p->W_h1),
+                         static_cast<const bf16_t*>(p->W_h2));
     else
-      hipLaunchKernelGGL(small_in_kernel<2>, dim3(16 * kSmallSplit), dim3(256), 0, st, X, ldx, Mi, Ki, Wi, r.small, B,
-                         seq_off, vis_start, vis_len, 16, kSmallSplit, kPW);
+      hipLaunchKernelGGL(small_in_kernel<2>, dim3(16 * kSmallSplit + kSmallXcds * kSmallFetch), dim3(256), 0, st, X, ldx, Mi, Ki, Wi,
+                         r.small, B, seq_off, vis_start, vis_len, 16, kSmallSplit, kPW, static_cast<const bf16_t*>(p->W_h1),
+                         static_cast<const bf16_t*>(p->W_h2));
     DLLAVA_CHECK_LAUNCH("small_in_kernel");
     hipLaunchKernelGGL(small_head_kernel, dim3(nt), dim3(256), 0, st, r.small, 32 * nt, Mi, p->b_in,
                        static_cast<const bf16_t*>(p->W_h1), p->b_h1, static_cast<const bf16_t*>(p->W_h2), p->b_h2,
