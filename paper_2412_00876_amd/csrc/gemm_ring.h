@@ -241,4 +241,89 @@ __device__ __forceinline__ void gemm_ring_256(const char* Abase, const uint32_t 
   static_for<8>([&](auto I) DLLAVA_INLINE { static_for<JT>([&](auto J) DLLAVA_INLINE { ring_tie_acc(acc[I.value][J.value]); }); });
 }
 
+// 32*FI x 32*TJ x d tile product for launches whose tiles of 256 rows would leave most of the chip idle: the same wave
+// layout (2 x 2 waves, wave w: A rows 16*FI*(w/2), B rows 16*TJ*(w%2)), fragments and LDS row layout as above.
+// Such a tile is bound by the bytes its compute unit pulls (32 KiB per stage at 128 x 128 against 0.25 us of products)
+// and by their latency, so all of the LDS is a ring of D whole stages: a stage's slot is requested again, D stages ahead,
+// once its last fragments are in registers.  A wave issues in order and stalls on loads issued together, so the loads are
+// dealt out, unconditionally, behind the products of a whole stage (128 x 128: 0.44 us a stage with all of them at its
+// end, 0.37 us dealt out; 0.62 us in the two-slot form with staging registers that this replaced; under a condition each,
+// the compiler moved the accumulators out of their registers and back).  One barrier per stage, before its last k-step.
+// Register r of acc[i][j]: A row 16*FI*(w/2) + 16*i + 4*(lane/16) + r  .  B row 16*TJ*(w%2) + 16*j + lane%16.
+// As above: clamped rows, all LDS traffic complete on return, a block barrier before the memory is used for something else.
+template <int FI, int TJ, int D>
+__device__ __forceinline__ void gemm_ring_small(const char* Abase, const int64_t (&ga)[FI], const char* Bbase, const int64_t (&gb)[TJ],
+                                                int nk, DLLAVA_LDS char* smem, int w, ring_f32x4 (&acc)[FI][TJ]) {
+  constexpr int kMF = FI * TJ, kNR = FI + TJ, kL = FI + TJ;  // products and fragment reads per k-step, tile loads per stage
+  constexpr int kL1 = kL / 2;  // loads behind the stage's last k-step; the others follow behind the next stage's first
+  constexpr uint32_t kA = 32 * FI * kRingRowBytes, kS = kA + 32 * TJ * kRingRowBytes;  // bytes of a stage's A part, of a stage
+  static_assert(D >= 3 && (D - 1) * kL < 64, "the wait counter holds the loads in flight");
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t s0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
+  const uint32_t fo = (lane & 15) * kRingRowBytes + (((lane >> 4) ^ ((lane & 15) >> 1)) * 16);
+  const uint32_t a_at = s0 + (w >> 1) * (16 * FI) * kRingRowBytes + fo, b_at = s0 + kA + (w & 1) * (16 * TJ) * kRingRowBytes + fo;
+  ring_u32x4 ua[FI], ub[TJ], va[FI], vb[TJ];
+
+  auto dma1 = [&](int64_t k, uint32_t slot, auto I) DLLAVA_INLINE {
+    constexpr int i = decltype(I)::value;
+    const char* src = i < FI ? Abase + k + ga[i < FI ? i : 0] : Bbase + k + gb[i < FI ? 0 : i - FI];
+    const uint32_t at = slot + (i < FI ? 0 : kA) + (w + 4 * (i < FI ? i : i - FI)) * 1024;
+    __builtin_amdgcn_global_load_lds((const DLLAVA_GLB void*)src, (DLLAVA_LDS void*)(smem + at), 16, 0, 0);
+  };
+  auto read1 = [&](ring_u32x4 (&fa)[FI], ring_u32x4 (&fb)[TJ], uint32_t ab, uint32_t bb, auto I) DLLAVA_INLINE {
+    constexpr int i = decltype(I)::value;
+    if constexpr (i < FI)
+      fa[i] = ring_lds_read16<i * 16 * kRingRowBytes>(ab);
+    else
+      fb[i - FI] = ring_lds_read16<(i - FI) * 16 * kRingRowBytes>(bb);
+  };
+  auto wait = [&](ring_u32x4 (&fa)[FI], ring_u32x4 (&fb)[TJ]) DLLAVA_INLINE {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    ring_tie(fa);
+    ring_tie(fb);
+  };
+  // the products of (fa, fb); behind them the reads of the next k-step and loads L0 .. L0+NL-1 of a stage
+  auto kstep = [&](ring_u32x4 (&fa)[FI], ring_u32x4 (&fb)[TJ], ring_u32x4 (&na)[FI], ring_u32x4 (&nb)[TJ], uint32_t ab, uint32_t bb,
+                   auto L0, auto NL, int64_t k, uint32_t slot) DLLAVA_INLINE {
+    static_for<kMF>([&](auto Mi) DLLAVA_INLINE {
+      constexpr int m = decltype(Mi)::value, n = decltype(NL)::value;
+      ring_mfma(acc[m / TJ][m % TJ], fa[m / TJ], fb[m % TJ]);
+      if constexpr (m < kNR) read1(na, nb, ab, bb, Mi);
+      constexpr int i = m * n / kMF;  // load i stands behind the last product with that quotient
+      if constexpr (i != (m + 1) * n / kMF)
+        dma1(k, slot, std::integral_constant<int, decltype(L0)::value + i>{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  static_assert(kMF >= kNR && kMF >= kL - kL1, "a k-step has room for the reads of the next one");
+  // byte offset along d of stage k; stages past the end re-read the last one (in bounds, unused)
+  auto koff = [&](int k) DLLAVA_INLINE { return static_cast<int64_t>(k < nk ? k : nk - 1) * (kRingBK * 2); };
+  // Loads are counted: stage k + D's follow stage k's barrier, the first kL1 behind its last k-step, the others behind the
+  // next stage's first.
+  static_for<D - 1>([&](auto P) DLLAVA_INLINE { static_for<kL>([&](auto I) DLLAVA_INLINE { dma1(koff(P.value), P.value * kS, I); }); });
+  static_for<kL1>([&](auto I) DLLAVA_INLINE { dma1(koff(D - 1), (D - 1) * kS, I); });
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * kL + kL1) : "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("s_nop 15" ::: "memory");  // the accumulators' first values, written by plain instructions, before the first product
+  static_for<kNR>([&](auto I) DLLAVA_INLINE { read1(ua, ub, a_at, b_at, I); });
+  uint32_t here = 0, before = (D - 1) * kS;  // byte offsets of the slots of this stage and of the one before it
+  int64_t ahead = koff(D - 1);               // of the stage that goes into slot `before`
+  for (int k = 0; k < nk; ++k) {
+    wait(ua, ub);
+    kstep(ua, ub, va, vb, (a_at ^ 64u) + here, (b_at ^ 64u) + here, std::integral_constant<int, kL1>{},
+          std::integral_constant<int, kL - kL1>{}, ahead, before);
+    // the fragments of the last k-step are in registers: this wave is done with the stage's slot
+    wait(va, vb);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * kL) : "memory");  // stage k + 1 has landed
+    __builtin_amdgcn_s_barrier();
+    before = here;
+    here = here + kS < D * kS ? here + kS : 0;
+    ahead = koff(k + D);
+    kstep(va, vb, ua, ub, a_at + here, b_at + here, std::integral_constant<int, 0>{}, std::integral_constant<int, kL1>{}, ahead, before);
+  }
+  wait(ua, ub);  // reads and loads issued for stages past the end are drained
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");  // the last products, whose latency the compiler does not know, are written
+  static_for<FI>([&](auto I) DLLAVA_INLINE { static_for<TJ>([&](auto J) DLLAVA_INLINE { ring_tie_acc(acc[I.value][J.value]); }); });
+}
+
 }  // namespace dllava

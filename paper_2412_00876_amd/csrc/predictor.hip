@@ -2,10 +2,10 @@
 // 512, for the image predictor two pre-norm transformer blocks over the image tokens of each sequence, and the MLP
 // head 512 -> 256 -> 128 -> 2.  bfloat16 storage, float32 sums.
 //
-//  * lin_gemm_kernel   Y = act(X W^T + b) (+ R): the 128 x 128 matrix-core tile product of gemm_tile.h (transposed
-//                      product W . X^T, so a lane holds many output features of ONE token), bias / GELU / residual in
+//  * lin_ring_kernel   Y = act(X W^T + b) (+ R): the matrix-core tile products of gemm_ring.h (transposed product
+//                      W . X^T, so a lane holds many output features of ONE token), bias / GELU / residual in
 //                      registers, then a transposition through LDS so that every token leaves as whole 16-byte
-//                      pieces of a 256-byte run.  The first layer gathers its rows from the vision spans.
+//                      pieces.  The first layer gathers its rows from the vision spans.
 //  * ln_kernel         LayerNorm of 512-wide rows, one wave per row, the row held in registers.
 //  * attention         prefill_mfma_kernel without the causal mask, 8 heads of 64, one "sequence" per span.
 //  * head_out_kernel   the last layer 128 -> 2, one wave per row.
@@ -35,7 +35,6 @@ constexpr int kPHeads = 8;     // heads of 64
 constexpr int kPMlp = 2048;    // hidden width of a block's MLP
 constexpr int kPH1 = 256, kPH2 = 128;  // head: 512 -> 256 -> 128 -> 2
 constexpr float kLnEps = 1e-6f;
-constexpr int kXcds = 8;
 
 // SiLU g / (1 + e^-g) with the hardware exponential and reciprocal (relative error ~1e-6)
 __device__ __forceinline__ float silu_fast(float g) {
@@ -61,101 +60,11 @@ struct LinArgs {
   const int32_t* vis_len;
 };
 
-__global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(3, 4))) void lin_gemm_kernel(LinArgs a,
-                                                                                                         int n_ut) {
-  __shared__ __align__(16) bf16_t sAB[2 * kTileElems];  // W tile | X tile during the product, output tile afterwards
-  bf16_t* sA = sAB;
-  bf16_t* sB = sAB + kTileElems;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  // XCD x takes the token tiles x, x+8, ... and, for each, all feature tiles (see score_gemm_kernel)
-  const int xcd = blockIdx.x % kXcds, jb = blockIdx.x / kXcds;
-  const int ut = jb % n_ut, mt = (jb / n_ut) * kXcds + xcd;
-  const int64_t M = a.M;
-  const int N = a.N, K = a.K;
-  if (static_cast<int64_t>(mt) * 128 >= M) return;
-
-  const int lc = tid & 7, lr = tid >> 3;
-  static_assert(sizeof(SpanTable) <= sizeof(sAB), "the span table borrows the tiles' memory");
-  SpanTable* spans = reinterpret_cast<SpanTable*>(sAB);
-  const bool use_table = a.seq_off != nullptr && a.B > 0 && a.B <= kSpanLdsMax;
-  if (use_table) span_table_build<kGThreads>(spans, a.seq_off, a.vis_start, a.vis_len, a.B);
-  const bf16_t *ga[4], *gb[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    int u = ut * 128 + lr + 32 * j;
-    if (u >= N) u = N - 1;  // such features are computed and dropped
-    ga[j] = a.W + static_cast<int64_t>(u) * K + lc * 8;
-    int64_t m = static_cast<int64_t>(mt) * 128 + lr + 32 * j;
-    if (m >= M) m = M - 1;
-    int64_t sr = use_table ? span_table_row(spans, a.B, m) : score_src_row(a.seq_off, a.vis_start, a.vis_len, a.B, m);
-    if (sr < 0) sr = 0;
-    gb[j] = a.X + sr * a.ldx + lc * 8;
-  }
-  if (use_table) __syncthreads();  // the tile loads overwrite the table
-  const int wu = (w >> 1) * 64, wm = (w & 1) * 64;  // this wave's 64 features x 64 tokens
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  gemm_tile_128x128<32>(ga[0], ga[1], ga[2], ga[3], gb[0], gb[1], gb[2], gb[3], K / kBK, sA, sB, wu, wm, acc);
-
-  // lane: token column wm + 32*j + lane%32; register r of fragment i: feature wu + 32*i + 8*(r/4) + 4*(lane/32) + r%4
-  const int g = lane >> 5;
-  bf16_t* sO = sAB;  // [128 tokens][16 chunks of 8 features], chunk c of token t at chunk position c ^ (t % 16)
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int fl = wu + 32 * i + 8 * q4 + 4 * g;  // this lane's four features of the tile
-      const int f0 = ut * 128 + fl;
-      const bool ok = f0 < N;
-      const float4 bs = *reinterpret_cast<const float4*>((ok && a.bias) ? a.bias + f0 : kZeroWords);
-      const int fs = ok ? f0 : 0;  // features past N: any valid address, the result is dropped
-      const int64_t col = static_cast<int64_t>(fs / a.group) * a.group_stride + fs % a.group;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int t = wm + 32 * j + (lane & 31);
-        int64_t m = static_cast<int64_t>(mt) * 128 + t;
-        if (m >= M) m = M - 1;
-        float v0 = acc[i][j][4 * q4] + bs.x, v1 = acc[i][j][4 * q4 + 1] + bs.y;
-        float v2 = acc[i][j][4 * q4 + 2] + bs.z, v3 = acc[i][j][4 * q4 + 3] + bs.w;
-        if (a.act == 1) {
-          v0 = gelu_erf_fast(v0); v1 = gelu_erf_fast(v1); v2 = gelu_erf_fast(v2); v3 = gelu_erf_fast(v3);
-        }
-        if (a.R) {  // block-uniform; the result is rounded once, after the addition / the product
-          const uint2 rr = *reinterpret_cast<const uint2*>(a.R + col + m * a.ldy);
-          const float r0 = bf16lo_to_f32(rr.x), r1 = bf16hi_to_f32(rr.x), r2 = bf16lo_to_f32(rr.y), r3 = bf16hi_to_f32(rr.y);
-          if (a.act == 2) {  // gated unit: R holds the gate, the output is this product times SiLU(gate)
-            v0 *= silu_fast(r0); v1 *= silu_fast(r1); v2 *= silu_fast(r2); v3 *= silu_fast(r3);
-          } else {
-            v0 += r0; v1 += r1; v2 += r2; v3 += r3;
-          }
-        }
-        uint2 v;
-        v.x = pack_bf16x2(v0, v1);
-        v.y = pack_bf16x2(v2, v3);
-        *reinterpret_cast<uint2*>(sO + t * 128 + (((fl >> 3) ^ (t & 15)) * 8) + g * 4) = v;
-      }
-    }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int idx = tid + kGThreads * k, t = idx >> 4, c = idx & 15;
-    const int64_t m = static_cast<int64_t>(mt) * 128 + t;
-    const int f = ut * 128 + c * 8;
-    if (m < M && f < N)
-      *reinterpret_cast<uint4*>(a.Y + static_cast<int64_t>(f / a.group) * a.group_stride + m * a.ldy + f % a.group) =
-          *reinterpret_cast<const uint4*>(sO + t * 128 + ((c ^ (t & 15)) * 8));
-  }
-}
-
-// The same layer on the large-tile product of gemm_ring.h, one block per compute unit: 256 features x 32*JT rows.
-template <int JT>
+// A linear layer on the products of gemm_ring.h, one block per compute unit: 32*FI features x 32*JT rows.
+template <int FI, int JT>
 __global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, int n_ft, int n_rt, int per_xcd) {
-  constexpr int kTok = 32 * JT;
+  constexpr int kTok = 32 * JT, kFeat = 32 * FI, kChunks = kFeat / 8;
+  constexpr int kDepth = kRingLdsBytes / ((FI + JT) * 32 * kRingRowBytes);  // FI < 8: stages that LDS holds
   __shared__ __align__(1024) char smem_raw[kRingLdsBytes];
   DLLAVA_LDS char* smem = (DLLAVA_LDS char*)smem_raw;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -168,14 +77,14 @@ __global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, in
   SpanTable* spans = reinterpret_cast<SpanTable*>(smem_raw);
   const bool use_table = a.seq_off != nullptr && a.B > 0 && a.B <= kSpanLdsMax;
   if (use_table) span_table_build<kRingThreads>(spans, a.seq_off, a.vis_start, a.vis_len, a.B);
-  uint32_t ga[kRingALoads];
+  std::conditional_t<FI == 8, uint32_t, int64_t> ga[FI];
   int64_t gb[JT];  // gathered rows of X may lie far apart
-  const char* Wt = reinterpret_cast<const char*>(a.W) + static_cast<int64_t>(ft) * 256 * K * 2;
+  const char* Wt = reinterpret_cast<const char*>(a.W) + static_cast<int64_t>(ft) * kFeat * K * 2;
 #pragma unroll
-  for (int j = 0; j < kRingALoads; ++j) {
+  for (int j = 0; j < FI; ++j) {
     const int row = ring_load_row(w, j, lane);
-    const int u = ft * 256 + row < N ? row : N - 1 - ft * 256;  // features past N are computed and dropped
-    ga[j] = static_cast<uint32_t>(u) * static_cast<uint32_t>(K) * 2u + ring_load_chunk_bytes(row, lane);
+    const int u = ft * kFeat + row < N ? row : N - 1 - ft * kFeat;  // features past N are computed and dropped
+    ga[j] = static_cast<decltype(+ga[0])>(u) * K * 2 + ring_load_chunk_bytes(row, lane);
   }
 #pragma unroll
   for (int j = 0; j < JT; ++j) {
@@ -187,28 +96,32 @@ __global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, in
     gb[j] = sr * a.ldx * 2 + ring_load_chunk_bytes(row, lane);
   }
   if (use_table) __syncthreads();  // the tile loads overwrite the table
-  ring_f32x4 acc[8][JT];
+  ring_f32x4 acc[FI][JT];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < FI; ++i)
 #pragma unroll
     for (int j = 0; j < JT; ++j) acc[i][j] = ring_f32x4{0.f, 0.f, 0.f, 0.f};
-  gemm_ring_256<JT, int64_t>(Wt, ga, reinterpret_cast<const char*>(a.X), gb, K / kRingBK, smem, w, acc);
+  if constexpr (FI == 8)
+    gemm_ring_256<JT, int64_t>(Wt, ga, reinterpret_cast<const char*>(a.X), gb, K / kRingBK, smem, w, acc);
+  else
+    gemm_ring_small<FI, JT, kDepth>(Wt, ga, reinterpret_cast<const char*>(a.X), gb, K / kRingBK, smem, w, acc);
   __syncthreads();  // the ring memory becomes the transposed output tile
 
-  // lane: row 16*JT*(w%2) + 16*j + lane%16; register r of acc[i]: feature 128*(w/2) + 16*i + 4*(lane/16) + r
+  // lane: row 16*JT*(w%2) + 16*j + lane%16; register r of acc[i]: feature 16*FI*(w/2) + 16*i + 4*(lane/16) + r
+  constexpr int kMask = kChunks < 16 ? kChunks - 1 : 15;
   const int g = lane >> 4;
-  bf16_t* sO = reinterpret_cast<bf16_t*>(smem_raw);  // [kTok rows][32 chunks of 8 features], chunk c of row t at c ^ (t % 16)
-  const int f_lane = ft * 256 + 128 * (w >> 1) + 4 * g;
+  bf16_t* sO = reinterpret_cast<bf16_t*>(smem_raw);  // [kTok rows][chunks of 8 features], chunk c of row t at c ^ (t & kMask)
+  const int f_lane = ft * kFeat + 16 * FI * (w >> 1) + 4 * g;
   // a tile never straddles two output groups (group is N or a multiple of 256): its place is scalar arithmetic
-  const int og = ft * 256 / a.group;
+  const int og = ft * kFeat / a.group;
   const int64_t out0 = og * a.group_stride - static_cast<int64_t>(og) * a.group;  // + feature + row * ldy
   // Everything the epilogue reads from memory is requested at once, into the registers the fragments have left (a load
   // and a wait per fragment took 12 us of a 256 x 256 tile).
-  float4 bs[8];
+  float4 bs[FI];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < FI; ++i)
     bs[i] = *reinterpret_cast<const float4*>(a.bias && f_lane + 16 * i < N ? a.bias + f_lane + 16 * i : kZeroWords);
-  uint2 rr[JT][8];
+  uint2 rr[JT][FI];
   if (a.R) {
 #pragma unroll
     for (int j = 0; j < JT; ++j) {
@@ -216,14 +129,14 @@ __global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, in
       if (m >= M) m = M - 1;
       const bf16_t* rrow = a.R + out0 + m * a.ldy;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) rr[j][i] = *reinterpret_cast<const uint2*>(rrow + (f_lane + 16 * i < N ? f_lane + 16 * i : ft * 256));
+      for (int i = 0; i < FI; ++i) rr[j][i] = *reinterpret_cast<const uint2*>(rrow + (f_lane + 16 * i < N ? f_lane + 16 * i : ft * kFeat));
     }
   }
 #pragma unroll
   for (int j = 0; j < JT; ++j) {
     const int t = 16 * JT * (w & 1) + 16 * j + (lane & 15);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < FI; ++i) {
       float v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e];
@@ -243,73 +156,85 @@ __global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, in
       uint2 o;
       o.x = pack_bf16x2(v[0], v[1]);
       o.y = pack_bf16x2(v[2], v[3]);
-      const int c = 16 * (w >> 1) + 2 * i + (g >> 1);  // chunk of 8 features; this lane's half of it: g % 2
-      *reinterpret_cast<uint2*>(sO + t * 256 + ((c ^ (t & 15)) * 8) + (g & 1) * 4) = o;
+      const int c = 2 * FI * (w >> 1) + 2 * i + (g >> 1);  // chunk of 8 features; this lane's half of it: g % 2
+      *reinterpret_cast<uint2*>(sO + t * kFeat + ((c ^ (t & kMask)) * 8) + (g & 1) * 4) = o;
     }
     __builtin_amdgcn_sched_barrier(0);  // one column at a time: the accumulators leave no registers for more
   }
   __syncthreads();
-  // thread: chunk tid%32 of rows tid/32 + 8k
-  const int c = tid & 31, f = ft * 256 + c * 8;
+  // thread: one chunk of every kStep-th row
+  constexpr int kStep = kRingThreads / kChunks;
+  const int c = tid % kChunks, f = ft * kFeat + c * 8;
   if (f >= N) return;
   bf16_t* out = a.Y + out0 + f;
 #pragma unroll 4
-  for (int k = 0; k < kTok / 8; ++k) {
-    const int t = (tid >> 5) + 8 * k;
+  for (int k = 0; k < kTok / kStep; ++k) {
+    const int t = tid / kChunks + kStep * k;
     const int64_t m = static_cast<int64_t>(rt) * kTok + t;
-    const uint4 piece = *reinterpret_cast<const uint4*>(sO + t * 256 + ((c ^ (t & 15)) * 8));
+    const uint4 piece = *reinterpret_cast<const uint4*>(sO + t * kFeat + ((c ^ (t & kMask)) * 8));
     if (m < M) *reinterpret_cast<uint4*>(out + m * a.ldy) = piece;
   }
 }
 
-// Row tile of the large-tile kernel, in units of 32 rows (4..8), or 0 for the 128 x 128 kernel, whichever takes less by
-// what the two take (nanoseconds, as in ring_cost; three 128 x 128 tiles share a compute unit).
-int lin_ring_pick(int64_t M, int64_t N, int64_t K) {
-  const int64_t nk = K / kRingBK, tiles128 = ceil_div(M, 128) * ceil_div(N, 128);
-  const int64_t full = tiles128 / 768, rest = tiles128 % 768;
-  int64_t best_cost = full * (nk * 1900 + 6500) + (rest ? nk * (620 + 1280 * rest / 768) + 6500 : 0);
-  int best = 0;
-  for (int jt = 8; jt >= 4; --jt) {
-    const int64_t cost = ring_cost(jt, ceil_div(M, 32 * jt) * ceil_div(N, 256), nk);
-    if (cost < best_cost) best = jt, best_cost = cost;
+// Tiles of lin_ring_kernel, by number (which is also what the launch override takes): 4 .. 8 are 256 features x 32*number
+// rows.  Nanoseconds per stage when every compute unit works and when few do, and beside the stages (measured, as in
+// ring_cost); `load` is what the stage's tile loads alone take.
+struct LinTile {
+  int id, fi, jt;
+  int64_t busy, alone, ends, load;
+};
+constexpr LinTile kLinTiles[] = {{8, 8, 8, 1310, 990, 10200, 800}, {7, 8, 7, 1120, 855, 9300, 750}, {6, 8, 6, 1030, 760, 8400, 700},
+                                 {5, 8, 5, 870, 660, 7300, 650},   {4, 8, 4, 750, 600, 6300, 600},  {9, 4, 6, 540, 430, 7500, 430},
+                                 {3, 4, 4, 460, 370, 6200, 370},   {2, 2, 4, 300, 260, 4500, 260},  {1, 2, 2, 210, 200, 4200, 200}};
+
+// The tile that takes least.  A stage touches one 128-byte line of every row of its tile: once those rows span more than
+// about 2.5 MiB (11008 columns: 16 KiB and more apart) its loads slow down, by about 65 ns for every further MiB --
+// 4096 features, 500 rows: 0.98 us a stage of 256 x 128 at 11008 columns against 0.60 at 4096, 0.25 against 0.20 for 64 x 64.
+// Small launches, new / 256-row or 128 x 128 tiles only: 214 x 4096 x 4096 18 / 52 us, 214 x 4096 x 11008 44 / 173 us,
+// 1000 x 4096 x 11008 106 / 171 us.
+const LinTile* lin_pick(int64_t M, int64_t N, int64_t K) {
+  const int64_t nk = K / kRingBK;
+  const LinTile* best = nullptr;
+  int64_t best_cost = 0;
+  for (const LinTile& t : kLinTiles) {
+    if (t.fi == 8 && K * 512 >= (int64_t{1} << 32)) continue;  // a lane's offsets into the 256 rows of a W tile are 32-bit
+    const int64_t span = 32 * (t.fi + t.jt) * K * 2 - (5 << 19), slow = t.load + (span > 0 ? span / (1 << 10) * 65 / (1 << 10) : 0);
+    const int64_t busy = t.busy > slow ? t.busy : slow, alone = t.alone > slow ? t.alone : slow;
+    const int64_t per_xcd = ceil_div(ceil_div(M, 32 * t.jt) * ceil_div(N, 32 * t.fi), kRingXcds), full = per_xcd / 32, rest = per_xcd % 32;
+    int64_t cost = full * (nk * busy + t.ends);
+    if (rest) cost += nk * (alone + (busy - alone) * rest / 32) + t.ends;
+    if (!best || cost < best_cost) best = &t, best_cost = cost;
   }
   return best;
 }
 
-template <int JT>
+template <int FI, int JT>
 int launch_lin_ring(const LinArgs& a, hipStream_t st) {
-  const int64_t n_ft = ceil_div(a.N, 256), n_rt = ceil_div(a.M, 32 * JT);
+  const int64_t n_ft = ceil_div(a.N, 32 * FI), n_rt = ceil_div(a.M, 32 * JT);
   const int64_t per_xcd = ceil_div(n_ft * n_rt, kRingXcds);
   if (per_xcd * kRingXcds > 0x7fffffffLL) DLLAVA_FAIL(DLLAVA_ESHAPE, "linear: too many rows");
-  hipLaunchKernelGGL(lin_ring_kernel<JT>, dim3(static_cast<unsigned>(per_xcd * kRingXcds)), dim3(kRingThreads), 0, st, a,
+  hipLaunchKernelGGL((lin_ring_kernel<FI, JT>), dim3(static_cast<unsigned>(per_xcd * kRingXcds)), dim3(kRingThreads), 0, st, a,
                      static_cast<int>(n_ft), static_cast<int>(n_rt), static_cast<int>(per_xcd));
   DLLAVA_CHECK_LAUNCH("lin_ring_kernel");
   return DLLAVA_OK;
 }
 
 int launch_lin(const LinArgs& a, hipStream_t st) {
-  int jt = lin_ring_pick(a.M, a.N, a.K);
-  if (const int forced = launch_override(DLLAVA_LAUNCH_LINEAR_TILE)) {
-    if (forced == 1) jt = 0;
-    if (forced >= 4 && forced <= 8) jt = forced;
+  const LinTile* t = lin_pick(a.M, a.N, a.K);
+  const int forced = launch_override(DLLAVA_LAUNCH_LINEAR_TILE);
+  for (const LinTile& f : kLinTiles)
+    if (f.id == forced && (f.fi < 8 || static_cast<int64_t>(a.K) * 512 < (int64_t{1} << 32))) t = &f;
+  switch (t->id) {
+    case 1: return launch_lin_ring<2, 2>(a, st);
+    case 2: return launch_lin_ring<2, 4>(a, st);
+    case 3: return launch_lin_ring<4, 4>(a, st);
+    case 9: return launch_lin_ring<4, 6>(a, st);
+    case 4: return launch_lin_ring<8, 4>(a, st);
+    case 5: return launch_lin_ring<8, 5>(a, st);
+    case 6: return launch_lin_ring<8, 6>(a, st);
+    case 7: return launch_lin_ring<8, 7>(a, st);
+    default: return launch_lin_ring<8, 8>(a, st);
   }
-  // a lane's offsets into the 256 rows of a W tile are 32-bit
-  if (jt && static_cast<int64_t>(a.K) * 512 < (int64_t{1} << 32)) {
-    switch (jt) {
-      case 4: return launch_lin_ring<4>(a, st);
-      case 5: return launch_lin_ring<5>(a, st);
-      case 6: return launch_lin_ring<6>(a, st);
-      case 7: return launch_lin_ring<7>(a, st);
-      default: return launch_lin_ring<8>(a, st);
-    }
-  }
-  const int n_ut = static_cast<int>(ceil_div(a.N, 128));
-  const int64_t n_mt = ceil_div(a.M, 128);
-  const int64_t blocks = ceil_div(n_mt, kXcds) * kXcds * n_ut;
-  if (blocks > 0x7fffffffLL) DLLAVA_FAIL(DLLAVA_ESHAPE, "predict: too many rows");
-  hipLaunchKernelGGL(lin_gemm_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kGThreads), 0, st, a, n_ut);
-  DLLAVA_CHECK_LAUNCH("lin_gemm_kernel");
-  return DLLAVA_OK;
 }
 
 // LayerNorm over rows of 512: lane holds 8 consecutive elements; mean and biased variance in two passes over the
@@ -431,7 +356,7 @@ __device__ __forceinline__ void want_now(const uint4& v) { asm volatile("" ::"v"
 
 // Operands are loaded 8 lanes per 128-byte line (a load instruction then touches 8 whole lines; a fragment-shaped
 // load, one row per lane, touches 32 lines for the same bytes and was measured 4x slower here) and turned into
-// matrix-core fragments through a wave-private LDS area in the swizzled row-major form of gemm_tile.h: chunk c of
+// matrix-core fragments through a wave-private LDS area in a swizzled row-major form: chunk c of
 // row rr at chunk position c ^ ((rr / 2) % 8).
 //
 // few_accumulate: one wave's share of a product on few rows.  wrow[j] / xrow[tt][j]: this lane's 16-byte column

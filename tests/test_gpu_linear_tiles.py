@@ -1,4 +1,4 @@
-"""dllava_linear through every tile of its two kernels (dllava_set_launch_override forces each): row and feature counts
+"""dllava_linear through every tile of its kernel (dllava_set_launch_override forces each): row and feature counts
 that end inside a tile, stage counts around the depth of the operand ring, all epilogues."""
 import numpy as np
 import pytest
@@ -19,9 +19,9 @@ def _dev(a):
     return torch.from_numpy(a.view(np.int16).copy()).to(DEV).view(torch.bfloat16)
 
 
-@pytest.mark.parametrize("tile", [1, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("tile", [1, 2, 3, 9, 4, 5, 6, 7, 8])
 @pytest.mark.parametrize("M,N,K,act,res", [(1, 8, 64, 0, False), (129, 264, 128, 1, False), (161, 256, 192, 0, True), (257, 520, 256, 2, True),
-                                           (193, 248, 320, 1, True), (449, 512, 704, 0, False)])
+                                           (193, 248, 320, 1, True), (449, 512, 704, 0, False), (70, 72, 1088, 1, True)])
 def test_every_tile(tile, M, N, K, act, res):
     x = W.store(rng.normal(3, "x", (M, K)), "bf16")
     w = W.store(rng.normal(3, "w", (N, K)) / np.sqrt(K), "bf16")
