@@ -102,8 +102,8 @@ const char* dllava_last_error(void);
  *   DLLAVA_LAUNCH_PREFILL_WAVES  waves (of 32 queries each) per block of the matrix-core attention kernel: 1, 2 or 4
  *   DLLAVA_LAUNCH_PREFILL_BLOCKS blocks of the matrix-core attention kernel's launch (its blocks are persistent and
  *                                share the work items; by default as many as the chip holds at once): 1 .. 65535
- *   DLLAVA_LAUNCH_SCORE_TILE     tile of the many-rows scoring kernel: 1 = 128 units x 128 tokens, three blocks per
- *                                compute unit; 4 .. 8 = 256 units x 32*value tokens, one block per compute unit
+ *   DLLAVA_LAUNCH_SCORE_TILE     tile of the many-rows scoring kernel: 1 = 128 units x 128 tokens, 9 = 128 x 192,
+ *                                10 = 128 x 64, 4 .. 8 = 256 units x 32*value tokens
  *   DLLAVA_LAUNCH_QKV_TILE       the same for the projection kernel of dllava_qkv_project
  *   DLLAVA_LAUNCH_LINEAR_TILE    tile of the many-rows linear layers (dllava_linear, dllava_predict): 1 = 64 features x
  *                                64 rows, 2 = 64 x 128, 3 = 128 x 128, 9 = 128 x 192, 4 .. 8 = 256 x 32*value

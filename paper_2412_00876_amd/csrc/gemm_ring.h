@@ -110,17 +110,40 @@ __device__ __forceinline__ bool ring_tile(int n_at, int n_bt, int per_xcd, int& 
   return true;
 }
 
-// Nanoseconds that a launch of `tiles` tiles of 256 x 32*jt over nk stages takes (linear layers of d = 512 .. 11008,
-// measured): a stage takes `busy` when every compute unit works and `alone` when few do -- the clock gives way to the
-// power --, a tile's prologue and epilogue `ends`.
-inline int64_t ring_cost(int jt, int64_t tiles, int64_t nk) {
-  static const int64_t busy[5] = {750, 870, 1030, 1120, 1310}, alone[5] = {600, 660, 760, 855, 990},
-                       ends[5] = {6300, 7300, 8400, 9300, 10200};
-  const int i = jt - 4;
-  const int64_t per_xcd = ceil_div(tiles, kRingXcds), full = per_xcd / 32, rest = per_xcd % 32;
-  int64_t t = full * (nk * busy[i] + ends[i]);
-  if (rest) t += nk * (alone[i] + (busy[i] - alone[i]) * rest / 32) + ends[i];
-  return t;
+// The tiles of the products below: 32*fi rows of A x 32*jt rows of B, one block per compute unit.  Nanoseconds per stage when
+// every compute unit works and when few do -- the clock gives way to the power --, beside the stages (prologue and
+// epilogue), and what the tile loads of a stage alone take (measured on linear layers of d = 512 .. 11008).
+struct RingTile {
+  int id;  // what the launch overrides take
+  int fi, jt;
+  int64_t busy, alone, ends, load;
+};
+constexpr RingTile kRingTiles[] = {{8, 8, 8, 1310, 990, 10200, 800}, {7, 8, 7, 1120, 855, 9300, 750}, {6, 8, 6, 1030, 760, 8400, 700},
+                                   {5, 8, 5, 870, 660, 7300, 650},   {4, 8, 4, 750, 600, 6300, 600},  {9, 4, 6, 540, 430, 7500, 430},
+                                   {3, 4, 4, 460, 370, 6200, 370},   {10, 4, 2, 300, 270, 4700, 270}, {2, 2, 4, 300, 260, 4500, 260},
+                                   {1, 2, 2, 210, 200, 4200, 200}};
+
+// The tile that takes least; tiles_of(t): how many of it the launch has, 0 if it cannot use it.  Null if none can be used.
+// A stage touches one 128-byte line of every row of its tile: once those rows span more than about 2.5 MiB (11008
+// columns: 22 KiB apart) its loads slow down, by about 65 ns for every further MiB -- 4096 x 500 results: 0.98 us a stage
+// of 256 x 128 at 11008 columns against 0.60 at 4096, 0.25 against 0.20 of 64 x 64.
+template <typename F>
+inline const RingTile* ring_pick(int64_t d, int forced, F&& tiles_of) {
+  const int64_t nk = d / kRingBK;
+  const RingTile* best = nullptr;
+  int64_t best_cost = 0;
+  for (const RingTile& t : kRingTiles) {
+    const int64_t tiles = tiles_of(t);
+    if (tiles <= 0) continue;
+    if (t.id == forced) return &t;
+    const int64_t span = 32 * (t.fi + t.jt) * d * 2 - (5 << 19), slow = t.load + (span > 0 ? span / (1 << 10) * 65 / (1 << 10) : 0);
+    const int64_t busy = t.busy > slow ? t.busy : slow, alone = t.alone > slow ? t.alone : slow;
+    const int64_t per_xcd = ceil_div(tiles, kRingXcds), full = per_xcd / 32, rest = per_xcd % 32;
+    int64_t cost = full * (nk * busy + t.ends);
+    if (rest) cost += nk * (alone + (busy - alone) * rest / 32) + t.ends;
+    if (!best || cost < best_cost) best = &t, best_cost = cost;
+  }
+  return best;
 }
 
 // Main loop.  Abase / Bbase: wave-uniform byte pointers to element 0 of the tiles' first rows; ga[j] / gb[j]: this

@@ -22,13 +22,21 @@
 #include <cmath>
 
 #include "gemm_ring.h"
-#include "gemm_tile.h"
 #include "prefill_args.h"
 #include "score_args.h"
 
 namespace dllava {
 
 namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ bf16x8 as_frag(const uint4& v) {
+  union { uint4 u; bf16x8 f; } c;
+  c.u = v;
+  return c.f;
+}
 
 constexpr int kPW = 512;       // predictor width (Appendix A.4.1)
 constexpr int kPHeads = 8;     // heads of 64
@@ -176,38 +184,6 @@ __global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, in
   }
 }
 
-// Tiles of lin_ring_kernel, by number (which is also what the launch override takes): 4 .. 8 are 256 features x 32*number
-// rows.  Nanoseconds per stage when every compute unit works and when few do, and beside the stages (measured, as in
-// ring_cost); `load` is what the stage's tile loads alone take.
-struct LinTile {
-  int id, fi, jt;
-  int64_t busy, alone, ends, load;
-};
-constexpr LinTile kLinTiles[] = {{8, 8, 8, 1310, 990, 10200, 800}, {7, 8, 7, 1120, 855, 9300, 750}, {6, 8, 6, 1030, 760, 8400, 700},
-                                 {5, 8, 5, 870, 660, 7300, 650},   {4, 8, 4, 750, 600, 6300, 600},  {9, 4, 6, 540, 430, 7500, 430},
-                                 {3, 4, 4, 460, 370, 6200, 370},   {2, 2, 4, 300, 260, 4500, 260},  {1, 2, 2, 210, 200, 4200, 200}};
-
-// The tile that takes least.  A stage touches one 128-byte line of every row of its tile: once those rows span more than
-// about 2.5 MiB (11008 columns: 16 KiB and more apart) its loads slow down, by about 65 ns for every further MiB --
-// 4096 features, 500 rows: 0.98 us a stage of 256 x 128 at 11008 columns against 0.60 at 4096, 0.25 against 0.20 for 64 x 64.
-// Small launches, new / 256-row or 128 x 128 tiles only: 214 x 4096 x 4096 18 / 52 us, 214 x 4096 x 11008 44 / 173 us,
-// 1000 x 4096 x 11008 106 / 171 us.
-const LinTile* lin_pick(int64_t M, int64_t N, int64_t K) {
-  const int64_t nk = K / kRingBK;
-  const LinTile* best = nullptr;
-  int64_t best_cost = 0;
-  for (const LinTile& t : kLinTiles) {
-    if (t.fi == 8 && K * 512 >= (int64_t{1} << 32)) continue;  // a lane's offsets into the 256 rows of a W tile are 32-bit
-    const int64_t span = 32 * (t.fi + t.jt) * K * 2 - (5 << 19), slow = t.load + (span > 0 ? span / (1 << 10) * 65 / (1 << 10) : 0);
-    const int64_t busy = t.busy > slow ? t.busy : slow, alone = t.alone > slow ? t.alone : slow;
-    const int64_t per_xcd = ceil_div(ceil_div(M, 32 * t.jt) * ceil_div(N, 32 * t.fi), kRingXcds), full = per_xcd / 32, rest = per_xcd % 32;
-    int64_t cost = full * (nk * busy + t.ends);
-    if (rest) cost += nk * (alone + (busy - alone) * rest / 32) + t.ends;
-    if (!best || cost < best_cost) best = &t, best_cost = cost;
-  }
-  return best;
-}
-
 template <int FI, int JT>
 int launch_lin_ring(const LinArgs& a, hipStream_t st) {
   const int64_t n_ft = ceil_div(a.N, 32 * FI), n_rt = ceil_div(a.M, 32 * JT);
@@ -219,11 +195,14 @@ int launch_lin_ring(const LinArgs& a, hipStream_t st) {
   return DLLAVA_OK;
 }
 
+// Small launches, these tiles / 256-row or 128 x 128 tiles of two LDS slots only: 214 x 4096 x 4096 18 / 52 us,
+// 214 x 4096 x 11008 46 / 173 us, 1000 x 4096 x 11008 111 / 171 us, 2000 x 512 x 4096 18 / 45 us (rows x features x width).
 int launch_lin(const LinArgs& a, hipStream_t st) {
-  const LinTile* t = lin_pick(a.M, a.N, a.K);
-  const int forced = launch_override(DLLAVA_LAUNCH_LINEAR_TILE);
-  for (const LinTile& f : kLinTiles)
-    if (f.id == forced && (f.fi < 8 || static_cast<int64_t>(a.K) * 512 < (int64_t{1} << 32))) t = &f;
+  const RingTile* t = ring_pick(a.K, launch_override(DLLAVA_LAUNCH_LINEAR_TILE), [&](const RingTile& c) -> int64_t {
+    if (c.id == 10) return 0;  // 64 x 128 does the same with its roles exchanged, and reads fewer of the weights per block
+    if (c.fi == 8 && static_cast<int64_t>(a.K) * 512 >= (int64_t{1} << 32)) return 0;  // 32-bit lane offsets into the rows of a W tile
+    return ceil_div(a.M, 32 * c.jt) * ceil_div(a.N, 32 * c.fi);
+  });
   switch (t->id) {
     case 1: return launch_lin_ring<2, 2>(a, st);
     case 2: return launch_lin_ring<2, 4>(a, st);

@@ -5,19 +5,13 @@
 // mention positions), queries go to a compacted [rows, H, Dh] tensor, keys and values straight into the paged
 // cache, so that compaction has to move hidden states only.
 //
-//  * qkv_gemm_kernel (bfloat16, Dh = 128): the transposed product W . x^T of gemm_tile.h, one block per
-//    (128 features = one head of Q, K or V) x (128 compacted rows).  A wave holds features 32w' + [0,32) and
-//    64 + 32w' + [0,32) of the head, i.e. both members of every rotary pair (i, i + 64), for 64 tokens: the
-//    rotation happens in registers.  The tile is then transposed through LDS (chunk-swizzled) so that every
-//    (token, head) row leaves as 256 contiguous bytes.  XCD-aware block order: an XCD owns a group of feature
-//    tiles and walks the token tiles eight at a time, so that its share of W and the x tiles stay in its L2.
-//  * qkv_ring_kernel (bfloat16, Dh = 128, many rows): the same on the large-tile product of gemm_ring.h, one block per
-//    compute unit: 256 features = two heads of Q, K or V against 128 .. 256 compacted rows; wave w holds head w/2 for
-//    half of the rows of the tile.
+//  * qkv_ring_kernel (bfloat16, Dh = 128): the transposed product W . x^T of gemm_ring.h, one block per compute unit: one or
+//    two heads of Q, K or V against 64 .. 256 compacted rows.  A wave holds both members of every rotary pair (i, i + 64)
+//    it works on, so the rotation happens in registers; the tile is then transposed through LDS (chunk-swizzled) so that
+//    every (token, head) row leaves as 256 contiguous bytes.
 //  * qkv_generic_kernel: any dtype / head size, one thread per rotary pair of one row.
 #include "dllava.h"
 #include "gemm_ring.h"
-#include "gemm_tile.h"
 
 namespace dllava {
 
@@ -78,117 +72,14 @@ __device__ __forceinline__ void set_lengths(const QkvArgs& a, int tid, int nthre
   }
 }
 
-constexpr int kXcds = 8;
-constexpr int kTokGroup = 8;  // token tiles an XCD keeps in flight per feature tile group
-
-__global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(3, 4))) void qkv_gemm_kernel(
-    QkvArgs a, RopeTable rt, int n_ft, int ft_per_xcd) {
-  __shared__ __align__(16) bf16_t sAB[2 * kTileElems];  // W tile | x tile, then the transposed output tile
-  __shared__ int64_t sm_dst[128];
-  bf16_t* sA = sAB;
-  bf16_t* sB = sAB + kTileElems;
-
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const int xcd = blockIdx.x % kXcds, jb = blockIdx.x / kXcds;
-  const int per_group = ft_per_xcd * kTokGroup;
-  const int local = jb % per_group;
-  const int ft = xcd * ft_per_xcd + local % ft_per_xcd;          // feature tile (128 features)
-  const int tt = (jb / per_group) * kTokGroup + local / ft_per_xcd;  // token tile (128 compacted rows)
-  const int total = a.off[a.B];
-  const int H = a.H;
-  if (ft == H && tt == 0) set_lengths(a, tid, kGThreads);
-  if (ft >= n_ft || tt * 128 >= total) return;
-  const int which = ft / H, head = ft % H;  // Dh = 128: a feature tile is one head of Q (0), K (1) or V (2)
-  const int64_t d = a.d;
-
-  const int lc = tid & 7, lr = tid >> 3;
-  const bf16_t* Wm = static_cast<const bf16_t*>(a.W[which]) + static_cast<int64_t>(head) * 128 * d;
-  const bf16_t* X = static_cast<const bf16_t*>(a.x);
-  const bf16_t *ga[4], *gb[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    ga[j] = Wm + static_cast<int64_t>(lr + 32 * j) * d + lc * 8;
-    int r = tt * 128 + lr + 32 * j;
-    if (r >= total) r = total - 1;  // such rows are computed and dropped
-    gb[j] = X + static_cast<int64_t>(r) * a.ldx + lc * 8;
-  }
-  const int wf = (w >> 1) * 32, wm = (w & 1) * 64;  // features wf + [0,32) and wf + 64 + [0,32); tokens wm + [0,64)
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  gemm_tile_128x128<64>(ga[0], ga[1], ga[2], ga[3], gb[0], gb[1], gb[2], gb[3], static_cast<int>(d / kBK), sA, sB,
-                        wf, wm, acc);
-
-  // where the rows of this tile go (one thread per token)
-  if (tid < 128) {
-    const int r = tt * 128 + tid;
-    int64_t dst = -1;
-    if (r < total) {
-      if (which == 0) {
-        dst = (static_cast<int64_t>(r) * H + head) * 128;
-      } else {
-        const int b = seq_of_row(a.off, a.B, r);
-        dst = page_slot(a, b, r - a.off[b], head);
-        if (dst >= 0 && which == 2) dst += static_cast<int64_t>(H) * kPage * 128;
-      }
-    }
-    sm_dst[tid] = dst;
-  }
-
-  // lane: token column wm + 32*j + lane%32; register r of fragment i: feature wf + 64*i + 8*(r/4) + 4*(lane/32) + r%4
-  const int g = lane >> 5;
-  bf16_t* sO = sAB;  // [128 tokens][16 chunks of 8 features], chunk c of token t at chunk position c ^ (t % 16)
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int t = wm + 32 * j + (lane & 31);
-    if (which < 2 && a.pos) {
-      int r = tt * 128 + t;
-      if (r >= total) r = total - 1;
-      const float p = static_cast<float>(a.pos[r]);
-#pragma unroll
-      for (int r16 = 0; r16 < 16; ++r16) {
-        const int i = wf + 8 * (r16 >> 2) + 4 * g + (r16 & 3);  // rotary pair (i, i + 64)
-        // angle in revolutions, reduced to its fraction without losing the low bits of the product
-        const float hi = rt.hi[i];
-        const float ph = p * hi;
-        const float fr = __builtin_amdgcn_fractf(ph) + (__builtin_fmaf(p, hi, -ph) + p * rt.lo[i]);
-        const float sn = __builtin_amdgcn_sinf(fr), cs = __builtin_amdgcn_cosf(fr);
-        const float x0 = acc[0][j][r16], x1 = acc[1][j][r16];
-        acc[0][j][r16] = x0 * cs - x1 * sn;
-        acc[1][j][r16] = x1 * cs + x0 * sn;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int c = (wf + 64 * i) / 8 + q4;  // chunk of features wf + 64*i + 8*q4 + [0,8); this lane's half: g
-        uint2 v;
-        v.x = pack_bf16x2(acc[i][j][4 * q4], acc[i][j][4 * q4 + 1]);
-        v.y = pack_bf16x2(acc[i][j][4 * q4 + 2], acc[i][j][4 * q4 + 3]);
-        *reinterpret_cast<uint2*>(sO + t * 128 + ((c ^ (t & 15)) * 8) + g * 4) = v;
-      }
-  }
-  __syncthreads();
-  bf16_t* out = static_cast<bf16_t*>(which == 0 ? a.Q_out : a.pages);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int idx = tid + kGThreads * k, t = idx >> 4, c = idx & 15;
-    const int64_t dst = sm_dst[t];
-    if (dst >= 0)
-      *reinterpret_cast<uint4*>(out + dst + c * 8) = *reinterpret_cast<const uint4*>(sO + t * 128 + ((c ^ (t & 15)) * 8));
-  }
-}
-
-// Large-tile form.  Feature tile f of matrix `which` = heads 2f and 2f+1 (the second may not exist when H is odd:
-// its weight rows are clamped and nothing of it is stored).
-template <int JB>
+// FI = 8: feature tile f of matrix `which` = heads 2f and 2f+1 (the second may not exist when H is odd: its weight rows are
+// clamped and nothing of it is stored), wave w holds head w/2 of the tile.  FI = 4: one head, wave w holds features
+// 32*(w/2) + [0, 32) and 64 + 32*(w/2) + [0, 32): the tile's rows are loaded in that order.
+template <int FI, int JB>
 __global__ __launch_bounds__(kRingThreads, 1) void qkv_ring_kernel(QkvArgs a, RopeTable rt, int n_ft, int n_tt, int per_xcd) {
-  constexpr int kTok = 32 * JB;
+  constexpr int kTok = 32 * JB, kHeads = FI / 4;
+  constexpr int kDepth = kRingLdsBytes / ((FI + JB) * 32 * kRingRowBytes);  // FI < 8: stages that LDS holds
+  using Off = std::conditional_t<FI == 8, uint32_t, int64_t>;
   __shared__ __align__(1024) char smem_raw[kRingLdsBytes];
   DLLAVA_LDS char* smem = (DLLAVA_LDS char*)smem_raw;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -196,41 +87,43 @@ __global__ __launch_bounds__(kRingThreads, 1) void qkv_ring_kernel(QkvArgs a, Ro
   const int total = a.off[a.B];
   const int H = a.H;
   if (blockIdx.x == 0) set_lengths(a, tid, kRingThreads);
-  int ft, tt;  // feature tile (256 features), token tile (kTok compacted rows)
+  int ft, tt;  // feature tile (kHeads heads), token tile (kTok compacted rows)
   if (!ring_tile(n_ft, n_tt, per_xcd, ft, tt) || tt * kTok >= total) return;
-  const int tiles_per_matrix = (H + 1) / 2;
-  const int which = ft / tiles_per_matrix, head0 = 2 * (ft % tiles_per_matrix);
+  const int tiles_per_matrix = (H + kHeads - 1) / kHeads;
+  const int which = ft / tiles_per_matrix, head0 = kHeads * (ft % tiles_per_matrix);
   const int64_t d = a.d;
 
-  uint32_t ga[kRingALoads], gb[JB];
+  Off ga[FI], gb[JB];
 #pragma unroll
-  for (int j = 0; j < kRingALoads; ++j) {
+  for (int j = 0; j < FI; ++j) {
     const int row = ring_load_row(w, j, lane);
-    int64_t f = static_cast<int64_t>(head0) * 128 + row;
+    int64_t f = static_cast<int64_t>(head0) * 128 + (FI == 8 ? row : 32 * (row >> 6) + (row & 31) + 64 * ((row >> 5) & 1));
     if (f >= static_cast<int64_t>(H) * 128) f = static_cast<int64_t>(H) * 128 - 1;
-    ga[j] = static_cast<uint32_t>(f * d * 2) + ring_load_chunk_bytes(row, lane);
+    ga[j] = static_cast<Off>(f * d * 2) + ring_load_chunk_bytes(row, lane);
   }
 #pragma unroll
   for (int j = 0; j < JB; ++j) {
     const int row = ring_load_row(w, j, lane);
     int r = tt * kTok + row;
     if (r >= total) r = total - 1;  // such rows are computed and dropped
-    gb[j] = static_cast<uint32_t>(static_cast<int64_t>(r) * a.ldx * 2) + ring_load_chunk_bytes(row, lane);
+    gb[j] = static_cast<Off>(static_cast<int64_t>(r) * a.ldx * 2) + ring_load_chunk_bytes(row, lane);
   }
-  const int hh = w >> 1;  // head of the tile; the wave's 16*JB tokens start at 16*JB*(w%2)
-  ring_f32x4 acc[8][JB];
+  ring_f32x4 acc[FI][JB];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < FI; ++i)
 #pragma unroll
     for (int j = 0; j < JB; ++j) acc[i][j] = ring_f32x4{0.f, 0.f, 0.f, 0.f};
-  gemm_ring_256<JB, uint32_t>(static_cast<const char*>(a.W[which]), ga, static_cast<const char*>(a.x), gb,
-                              static_cast<int>(d / kRingBK), smem, w, acc);
+  const char *Ab = static_cast<const char*>(a.W[which]), *Bb = static_cast<const char*>(a.x);
+  if constexpr (FI == 8)
+    gemm_ring_256<JB, uint32_t>(Ab, ga, Bb, gb, static_cast<int>(d / kRingBK), smem, w, acc);
+  else
+    gemm_ring_small<FI, JB, kDepth>(Ab, ga, Bb, gb, static_cast<int>(d / kRingBK), smem, w, acc);
   __syncthreads();  // the ring memory becomes the transposed output tile
 
   // where the rows of this tile go: one entry per (head of the tile, token)
-  bf16_t* sO = reinterpret_cast<bf16_t*>(smem_raw);  // [kTok tokens][32 chunks of 8 features], chunk c of token t at c ^ (t % 16)
-  int64_t* sm_dst = reinterpret_cast<int64_t*>(smem_raw + kTok * 512);  // [2][kTok]
-  for (int e = tid; e < 2 * kTok; e += kRingThreads) {
+  bf16_t* sO = reinterpret_cast<bf16_t*>(smem_raw);  // [kTok tokens][16*kHeads chunks of 8 features], chunk c of token t at c ^ (t % 16)
+  int64_t* sm_dst = reinterpret_cast<int64_t*>(smem_raw + kTok * 256 * kHeads);  // [kHeads][kTok]
+  for (int e = tid; e < kHeads * kTok; e += kRingThreads) {
     const int h2 = e / kTok, t = e % kTok;
     const int r = tt * kTok + t, head = head0 + h2;
     int64_t dst = -1;
@@ -246,12 +139,14 @@ __global__ __launch_bounds__(kRingThreads, 1) void qkv_ring_kernel(QkvArgs a, Ro
     sm_dst[e] = dst;
   }
 
-  // lane: token 16*JB*(w%2) + 16*j + lane%16; register r of acc[i]: feature 16*i + 4*(lane/16) + r of head hh, so that
-  // acc[i] and acc[i + 4] hold the two members of a rotary pair
+  // lane: token 16*JB*(w%2) + 16*j + lane%16; register r of acc[i], i < FI/2: feature f_wave + 16*i + 4*(lane/16) + r of the
+  // wave's head; acc[i + FI/2] holds the other members of the rotary pairs, 64 features on
+  constexpr int kHalf = FI / 2;
+  const int f_wave = FI == 8 ? 0 : 32 * (w >> 1);
   const int g = lane >> 4;
   const bool rotate = which < 2 && a.pos;  // block-uniform
-  // all of the epilogue's loads at once: the positions of the lane's rows and the revolutions per position of its 16 pairs
-  float pos[JB], fh[16], fl[16];
+  // all of the epilogue's loads at once: the positions of the lane's rows and the revolutions per position of its pairs
+  float pos[JB], fh[4 * kHalf], fl[4 * kHalf];
 #pragma unroll
   for (int j = 0; j < JB; ++j) {
     int r = tt * kTok + 16 * JB * (w & 1) + 16 * j + (lane & 15);
@@ -259,42 +154,43 @@ __global__ __launch_bounds__(kRingThreads, 1) void qkv_ring_kernel(QkvArgs a, Ro
     pos[j] = rotate ? static_cast<float>(a.pos[r]) : 0.f;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < kHalf; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      fh[4 * i + r] = rt.hi[16 * i + 4 * g + r];
-      fl[4 * i + r] = rt.lo[16 * i + 4 * g + r];
+      fh[4 * i + r] = rt.hi[f_wave + 16 * i + 4 * g + r];
+      fl[4 * i + r] = rt.lo[f_wave + 16 * i + 4 * g + r];
     }
   auto column = [&](auto ROTATE, auto J) DLLAVA_INLINE {
     constexpr int j = decltype(J)::value;
     const int t = 16 * JB * (w & 1) + 16 * j + (lane & 15);
-    float v[8][4];
+    float v[FI][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < FI; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[i][e] = acc[i][j][e];
     if constexpr (decltype(ROTATE)::value) {
       const float p = pos[j];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < kHalf; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float hi = fh[4 * i + e];
           const float ph = p * hi;
           const float fr = __builtin_amdgcn_fractf(ph) + (__builtin_fmaf(p, hi, -ph) + p * fl[4 * i + e]);
           const float sn = __builtin_amdgcn_sinf(fr), cs = __builtin_amdgcn_cosf(fr);
-          const float x0 = v[i][e], x1 = v[i + 4][e];
+          const float x0 = v[i][e], x1 = v[i + kHalf][e];
           v[i][e] = x0 * cs - x1 * sn;
-          v[i + 4][e] = x1 * cs + x0 * sn;
+          v[i + kHalf][e] = x1 * cs + x0 * sn;
         }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int c = 16 * hh + 2 * i + (g >> 1);  // chunk of 8 features; this lane's half of it: g % 2
+    for (int i = 0; i < FI; ++i) {
+      // chunk of 8 features; this lane's half of it: g % 2
+      const int c = (FI == 8 ? 16 * (w >> 1) + 2 * i : f_wave / 8 + 2 * (i % kHalf) + 8 * (i / kHalf)) + (g >> 1);
       uint2 o;
       o.x = pack_bf16x2(v[i][0], v[i][1]);
       o.y = pack_bf16x2(v[i][2], v[i][3]);
-      *reinterpret_cast<uint2*>(sO + t * 256 + ((c ^ (t & 15)) * 8) + (g & 1) * 4) = o;
+      *reinterpret_cast<uint2*>(sO + t * (128 * kHeads) + ((c ^ (t & 15)) * 8) + (g & 1) * 4) = o;
     }
     __builtin_amdgcn_sched_barrier(0);  // one column at a time: the accumulators leave no registers for more
   };
@@ -305,13 +201,14 @@ __global__ __launch_bounds__(kRingThreads, 1) void qkv_ring_kernel(QkvArgs a, Ro
     static_for<JB>([&](auto J) DLLAVA_INLINE { column(std::false_type{}, J); });
   __syncthreads();
   bf16_t* out = static_cast<bf16_t*>(which == 0 ? a.Q_out : a.pages);
-  // thread: chunk tid%32 of rows tid/32 + 8k; four rows' LDS reads in flight together
-  const int c = tid & 31, t0 = tid >> 5;
+  // thread: one chunk of every kStep-th row; four rows' LDS reads in flight together
+  constexpr int kStep = kRingThreads / (16 * kHeads);
+  const int c = tid % (16 * kHeads), t0 = tid / (16 * kHeads);
   const int64_t* dst_of = sm_dst + (c >> 4) * kTok;
 #pragma unroll 4
-  for (int k = 0; k < kTok / 8; ++k) {
-    const int t = t0 + 8 * k;
-    const uint4 piece = *reinterpret_cast<const uint4*>(sO + t * 256 + ((c ^ (t & 15)) * 8));
+  for (int k = 0; k < kTok / kStep; ++k) {
+    const int t = t0 + kStep * k;
+    const uint4 piece = *reinterpret_cast<const uint4*>(sO + t * (128 * kHeads) + ((c ^ (t & 15)) * 8));
     const int64_t dst = dst_of[t];
     if (dst >= 0) *reinterpret_cast<uint4*>(out + dst + (c & 15) * 8) = piece;
   }
@@ -379,49 +276,31 @@ int launch_mfma(const QkvArgs& a, int64_t rows, double base, hipStream_t st) {
     rt.hi[i] = static_cast<float>(rev);
     rt.lo[i] = static_cast<float>(rev - static_cast<double>(rt.hi[i]));
   }
-  // The large-tile kernel (one block per compute unit) with the token tile that takes least by ring_cost, unless the
-  // 128 x 128 kernel takes less (three tiles share a compute unit; measured 2.5 us a stage and 9 us when they do, 0.65 us
-  // a stage when few blocks run).  DLLAVA_LAUNCH_QKV_TILE forces a width (4..8) or the 128 x 128 kernel (1).
-  {
-    const int n_ft2 = 3 * ((a.H + 1) / 2);
-    const int64_t nk = a.d / kRingBK, tiles128 = ceil_div(rows, 128) * 3 * a.H;
-    const int64_t full = tiles128 / 768, rest = tiles128 % 768;
-    int64_t best_cost = full * (nk * 1900 + 9000) + (rest ? nk * (620 + 1280 * rest / 768) + 9000 : 0);
-    int best = 0;
-    for (int jb = 8; jb >= 4; --jb) {
-      const int64_t cost = ring_cost(jb, ceil_div(rows, 32 * jb) * n_ft2, nk);
-      if (cost < best_cost) best = jb, best_cost = cost;
-    }
-    const int forced = launch_override(DLLAVA_LAUNCH_QKV_TILE);
-    if (forced == 1) best = 0;
-    if (forced >= 4 && forced <= 8) best = forced;
+  // The tile that takes least.  In place of 128 x 128 tiles of two LDS slots, three to a compute unit, or 256-row tiles: 107
+  // rows of 32 heads at d = 4096 32 / 50 us, 214 rows 39 / 53 us, 350 rows 48 / 76 us.  Lane offsets into the whole of a matrix and of x are 32-bit in the 256-row tiles.
+  const int forced = launch_override(DLLAVA_LAUNCH_QKV_TILE);
+  auto heads_tiles = [&](const RingTile& c) -> int64_t { return 3 * ceil_div(a.H, c.fi / 4); };
+  const RingTile* t = ring_pick(a.d, forced == 1 ? 3 : forced, [&](const RingTile& c) -> int64_t {
+    if (c.fi < 4) return 0;
     const bool fits = static_cast<int64_t>(a.H) * 128 * a.d * 2 < (int64_t{1} << 32) && rows * a.ldx * 2 < (int64_t{1} << 32);
-    if (best && fits) {
-      const int64_t n_tt2 = ceil_div(rows, 32 * best);
-      const int64_t per_xcd = ceil_div(n_tt2 * n_ft2, kRingXcds);
-      if (per_xcd * kRingXcds <= 0x7fffffffLL) {
-        const dim3 grid(static_cast<unsigned>(per_xcd * kRingXcds)), block(kRingThreads);
-        const int tts = static_cast<int>(n_tt2), px = static_cast<int>(per_xcd);
-        switch (best) {
-          case 4: hipLaunchKernelGGL(qkv_ring_kernel<4>, grid, block, 0, st, a, rt, n_ft2, tts, px); break;
-          case 5: hipLaunchKernelGGL(qkv_ring_kernel<5>, grid, block, 0, st, a, rt, n_ft2, tts, px); break;
-          case 6: hipLaunchKernelGGL(qkv_ring_kernel<6>, grid, block, 0, st, a, rt, n_ft2, tts, px); break;
-          case 7: hipLaunchKernelGGL(qkv_ring_kernel<7>, grid, block, 0, st, a, rt, n_ft2, tts, px); break;
-          default: hipLaunchKernelGGL(qkv_ring_kernel<8>, grid, block, 0, st, a, rt, n_ft2, tts, px); break;
-        }
-        DLLAVA_CHECK_LAUNCH("qkv_ring_kernel");
-        return DLLAVA_OK;
-      }
-    }
+    const int64_t n = ceil_div(rows, 32 * c.jt) * heads_tiles(c);
+    return (c.fi == 8 && !fits) || n > 0x7fffffffLL - 8 ? 0 : n;
+  });
+  if (!t) return 1;
+  const int n_ft = static_cast<int>(heads_tiles(*t)), n_tt = static_cast<int>(ceil_div(rows, 32 * t->jt));
+  const int per_xcd = static_cast<int>(ceil_div(static_cast<int64_t>(n_tt) * n_ft, kRingXcds));
+  const dim3 grid(static_cast<unsigned>(per_xcd) * kRingXcds), block(kRingThreads);
+  switch (t->id) {
+    case 10: hipLaunchKernelGGL((qkv_ring_kernel<4, 2>), grid, block, 0, st, a, rt, n_ft, n_tt, per_xcd); break;
+    case 3: hipLaunchKernelGGL((qkv_ring_kernel<4, 4>), grid, block, 0, st, a, rt, n_ft, n_tt, per_xcd); break;
+    case 9: hipLaunchKernelGGL((qkv_ring_kernel<4, 6>), grid, block, 0, st, a, rt, n_ft, n_tt, per_xcd); break;
+    case 4: hipLaunchKernelGGL((qkv_ring_kernel<8, 4>), grid, block, 0, st, a, rt, n_ft, n_tt, per_xcd); break;
+    case 5: hipLaunchKernelGGL((qkv_ring_kernel<8, 5>), grid, block, 0, st, a, rt, n_ft, n_tt, per_xcd); break;
+    case 6: hipLaunchKernelGGL((qkv_ring_kernel<8, 6>), grid, block, 0, st, a, rt, n_ft, n_tt, per_xcd); break;
+    case 7: hipLaunchKernelGGL((qkv_ring_kernel<8, 7>), grid, block, 0, st, a, rt, n_ft, n_tt, per_xcd); break;
+    default: hipLaunchKernelGGL((qkv_ring_kernel<8, 8>), grid, block, 0, st, a, rt, n_ft, n_tt, per_xcd); break;
   }
-  const int n_ft = 3 * a.H;
-  const int ft_per_xcd = static_cast<int>(ceil_div(n_ft, kXcds));
-  const int64_t n_tt = ceil_div(rows, 128);
-  const int64_t blocks = ceil_div(n_tt, kTokGroup) * kTokGroup * ft_per_xcd * kXcds;
-  if (blocks > 0x7fffffffLL) return 1;
-  hipLaunchKernelGGL(qkv_gemm_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kGThreads), 0, st, a, rt, n_ft,
-                     ft_per_xcd);
-  DLLAVA_CHECK_LAUNCH("qkv_gemm_kernel");
+  DLLAVA_CHECK_LAUNCH("qkv_ring_kernel");
   return DLLAVA_OK;
 }
 
