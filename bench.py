@@ -76,6 +76,14 @@ def to_dev(a: np.ndarray, dtype: str):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
 
 
+def _between_middle_margins(D):
+    """A threshold that keeps the upper half of the margins: between the lower median and the margin above it, so that no
+    margin equals it and the two forms of a decode step, whose sums differ in their order, decide alike."""
+    m = (D[:, 1] - D[:, 0]).double().sort().values
+    i = (m.numel() - 1) // 2
+    return float(((m[i] + m[min(i + 1, m.numel() - 1)]) / 2).item())
+
+
 class Path:
     """The whole hot path for one workload, resident on the GPU."""
 
@@ -138,7 +146,7 @@ class Path:
         self.P.dllava_score(x, w.d, M, 0, None, None, None, w.d, w.dh, p["W1"], p["b1"], p["W2"], p["b2"],
                             self.code, D, ws)
         torch.cuda.synchronize()
-        w.theta = float(torch.median(D[:, 1] - D[:, 0]).item())
+        w.theta = _between_middle_margins(D)
 
     # ---- the stages, exactly as a caller would issue them -------------------------------------
     def score_vision(self):
@@ -295,7 +303,7 @@ class PaperPredictors:
         ws = torch.zeros(p.P.dllava_predict_workspace(M, 0, 0), dtype=torch.uint8, device=x.device)
         p.P.dllava_predict(x, w.d, M, 0, None, None, None, self.text, p.code, D, ws)
         torch.cuda.synchronize()
-        self.theta = float(torch.median(D[:, 1] - D[:, 0]).item())
+        self.theta = _between_middle_margins(D)
         self.logits_steps = torch.zeros((w.T, w.B, 2), dtype=torch.float32, device=x.device)
         self.ws_attn = torch.zeros(p.P.dllava_decode_workspace(w.B, w.H, w.Dh, p.cache.max_pages_per_seq), dtype=torch.uint8,
                                    device=x.device)
