@@ -33,7 +33,7 @@ __global__ __launch_bounds__(kThreads) void score_generic_kernel(ScoreArgs a) {
   const int d = static_cast<int>(a.d), chunks = d / E, dh = static_cast<int>(a.dh);
   const T* W1 = static_cast<const T*>(a.W1);
   const T* W2 = static_cast<const T*>(a.W2);
-  // piece (j0, c): chunk c of units j0 .. j0+7 (units past dh repeat the last one and get no weight; chunks past the row
+  // piece (j0, c): chunk c of units j0 .. j0+7 (units past dh repeat the last one and count as zero; chunks past the row
   // repeat the last one and are not used)
   uint4 wv[kUnits];
   auto load = [&](int j0, int c) __attribute__((always_inline)) {
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kThreads) void score_generic_kernel(ScoreArgs a) {
       float sum = v[0];
 #pragma unroll
       for (int o = kPerUnit / 2; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, kWave);
-      const float g = gelu_erf(sum + bias);
+      const float g = ok ? gelu_erf(sum + bias) : 0.f;  // a weight of zero alone would make NaN of an infinite repeat
       l0[r] = fmaf(g, w20, l0[r]);
       l1[r] = fmaf(g, w21, l1[r]);
     }

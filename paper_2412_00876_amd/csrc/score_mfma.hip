@@ -45,8 +45,8 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
   if (!ring_tile(n_ut, n_mt, per_xcd, ut, mt)) return;
   const int64_t M = a.M, d = a.d, dh = a.dh;
 
-  // this lane's tile loads: byte offsets from W1 / x (rows past the end repeat the last row: their units carry
-  // zero W2 weights, their tokens are not written)
+  // this lane's tile loads: byte offsets from W1 / x (rows past the end repeat the last row: their units count as
+  // zero, their tokens are not written)
   std::conditional_t<FI == 8, uint32_t, int64_t> ga[FI];
   int64_t gb[JB];  // gathered rows of x may lie far apart
 #pragma unroll
@@ -94,12 +94,12 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
   const bool quads = dh % 4 == 0 && (reinterpret_cast<uintptr_t>(W2) % 8 == 0) && (reinterpret_cast<uintptr_t>(a.b1) % 16 == 0);
   float4 bq[FI];
   uint2 q0[FI], q1[FI];
-  const int64_t u_lane = static_cast<int64_t>(ut) * kUnits + 16 * FI * (w >> 1) + 4 * (lane >> 4);
+  const int units = static_cast<int>(dh), u_lane = ut * kUnits + 16 * FI * (w >> 1) + 4 * (lane >> 4);  // dh <= 2^20
   if (quads) {
 #pragma unroll
     for (int i = 0; i < FI; ++i) {
-      const int64_t u0 = u_lane + 16 * i;
-      const bool ok = u0 < dh;  // operands that must be zero come from kZeroWords: no load under a condition
+      const int u0 = u_lane + 16 * i;
+      const bool ok = u0 < units;  // operands that must be zero come from kZeroWords: no load under a condition
       bq[i] = *reinterpret_cast<const float4*>((ok & has_b1) ? a.b1 + u0 : kZeroWords);
       q0[i] = *reinterpret_cast<const uint2*>(ok ? W2 + u0 : zero16);
       q1[i] = *reinterpret_cast<const uint2*>(ok ? W2 + dh + u0 : zero16);
@@ -111,8 +111,8 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
       uint32_t h0[4], h1[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t u = u_lane + 16 * i + r;
-        const bool ok = u < dh;
+        const int u = u_lane + 16 * i + r;
+        const bool ok = u < units;
         bv[r] = *((ok & has_b1) ? a.b1 + u : kZeroWords);
         h0[r] = *(ok ? W2 + u : zero16);
         h1[r] = *(ok ? W2 + dh + u : zero16);
@@ -124,17 +124,24 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
   }
 #pragma unroll
   for (int i = 0; i < FI; ++i) {
+#pragma unroll
+    for (int j = 0; j < JB; ++j) ring_tie_acc(acc[i][j]);  // in accumulation registers until here: the others do not hold them all
     const float bias[4] = {bq[i].x, bq[i].y, bq[i].z, bq[i].w};
     const float w20[4] = {bf16lo_to_f32(q0[i].x), bf16hi_to_f32(q0[i].x), bf16lo_to_f32(q0[i].y), bf16hi_to_f32(q0[i].y)};
     const float w21[4] = {bf16lo_to_f32(q1[i].x), bf16hi_to_f32(q1[i].x), bf16lo_to_f32(q1[i].y), bf16hi_to_f32(q1[i].y)};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
+      // past dh the last unit repeats: its weight of zero alone would make NaN of an infinite value
+      const uint64_t real = __ballot(u_lane + 16 * i + r < units);
 #pragma unroll
       for (int j = 0; j < JB; ++j) {
-        const float g = gelu_erf_fast(acc[i][j][r] + bias[r]);
+        float g = gelu_erf_fast(acc[i][j][r] + bias[r]);
+        asm("v_cndmask_b32_e64 %0, 0, %0, %1" : "+v"(g) : "s"(real));  // written out: of `real ? g : 0` the compiler makes a branch
         p[j][0] = fmaf(g, w20[r], p[j][0]);
         p[j][1] = fmaf(g, w21[r], p[j][1]);
       }
+#pragma unroll
+      for (int j = 0; j < JB; ++j) asm volatile("" : "+v"(p[j][0]), "+v"(p[j][1]));  // summed here: the compiler kept all values to sum them at the end
       __builtin_amdgcn_sched_barrier(0);  // JB values at a time: the accumulators leave no registers for more
     }
   }

@@ -41,3 +41,24 @@ def test_matches_float64(M, d, dh, dtype):
     assert n < M or M == 1
     assert ((got[:n] - ref).abs() <= tol).all(), f"worst {((got[:n] - ref).abs() / tol).max():.2f} of the bound"
     assert (got[n:] == 7.0).all()   # rows beyond the spans are not written
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("M,dh", [(3, 1), (3, 5), (7, 13), (600, 130)])
+def test_infinite_last_unit(M, dh, dtype):
+    """The last hidden unit overflows and is repeated in the places past dh: the logits are infinite, not NaN.  They are
+    NaN in the one row that holds one."""
+    d, code = 72, P.F32 if dtype == torch.float32 else P.BF16
+    _infinite_last_unit(M, d, dh, dtype, code)
+
+
+def _infinite_last_unit(M, d, dh, dtype, code):
+    x, W1, W2 = torch.zeros(M, d, dtype=dtype), torch.zeros(dh, d, dtype=dtype), torch.ones(2, dh, dtype=dtype)
+    x[:, 0], W1[-1, 0], W2[1, -1] = 1e30, 1e30, -2.0
+    x[1, 1] = float("nan")
+    out = torch.zeros((M, 2), device=DEV)
+    ws = torch.zeros(P.dllava_score_workspace(M, d, dh, code), dtype=torch.uint8, device=DEV)
+    P.dllava_score(x.to(DEV), d, M, 0, None, None, None, d, dh, W1.to(DEV), None, W2.to(DEV), None, code, out, ws)
+    assert out[1].isnan().all()
+    other = torch.arange(M, device=DEV) != 1
+    assert (out[other, 0] == float("inf")).all() and (out[other, 1] == -float("inf")).all()
