@@ -52,11 +52,12 @@ struct SplitPlan {
   int ppb;  // 64-element pairs per slice
 };
 
-// Host and device agree on the plan through the launch arguments; about 256 blocks, one per compute unit.
+// Host and device agree on the plan through the launch arguments; about 256 blocks, one per compute unit.  The workspace
+// queries ask for a plan of any width, also of those that only the generic kernel takes (d < 64: no pair of k-steps).
 inline SplitPlan split_plan(int64_t d, int64_t dh) {
   SplitPlan p;
-  p.G = static_cast<int>((dh + kSpUnits - 1) / kSpUnits);
-  const int npairs = static_cast<int>(d / 64);
+  p.G = dh > 0 ? static_cast<int>((dh + kSpUnits - 1) / kSpUnits) : 1;
+  const int npairs = d >= 64 ? static_cast<int>(d / 64) : 1;
   int ks = 256 / p.G;
   if (ks > kSpMaxSplit) ks = kSpMaxSplit;
   if (ks > npairs) ks = npairs;

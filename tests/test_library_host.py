@@ -173,6 +173,17 @@ def test_score_workspace_is_monotonic_in_rows(lib):
         assert sizes == sorted(sizes), (d, dh, sizes)
 
 
+def test_score_workspace_of_narrow_rows(lib):
+    """d % 8 == 0 is all that dllava_score asks for: widths below one k-step of the matrix-core forms have a workspace too,
+    alone and inside a decode step, and a query without units answers."""
+    for d in (8, 40, 56):
+        for dh in (1, 10, 1024):
+            sizes = [lib.dllava_score_workspace(m, d, dh, lib.BF16) for m in (1, 64, 65, 100, 100000)]
+            assert sizes[0] >= 256 and sizes == sorted(sizes), (d, dh, sizes)
+            assert lib.dllava_decode_step_workspace(3, 4, 64, 8, d, dh, lib.BF16) > sizes[0]
+    assert lib.dllava_score_workspace(100, 64, 0, lib.BF16) > 0
+
+
 def test_predictor_entry_points_validate_on_the_host(lib):
     L = lib.lib()
     EINVAL, ENULL, ESHAPE, EDTYPE, EWORKSPACE = -1, -2, -3, -4, -6
