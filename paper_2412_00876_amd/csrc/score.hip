@@ -2,27 +2,26 @@
 // paper, with the two-layer predictor d -> dh -> 2).
 //
 // Precision-generic path, for float32 inputs and shapes the matrix-core kernels do not cover.  A block takes R scored
-// rows (1 or 4: W1 is read once per block), staged in LDS as float32.  Each of its 16 waves takes eight hidden units at a
-// time (four where the registers hold no more), its lanes strided over d with 16-byte loads of those W1 rows, the next
-// loads in flight while the last are multiplied -- the first ones before the rows are staged, which they do not depend on.
+// rows (1 or 4: W1 is read once per block), staged in LDS as float32.  Each of its waves takes 1 to 8 hidden units at a
+// time, its lanes strided over d with 16-byte loads of those W1 rows, the next loads in flight while the last are
+// multiplied -- the first ones before the rows are staged, which they do not depend on.
 // The sums of a wave's units are reduced together: at each exchange a lane hands over half of its sums and keeps the
 // other half, so eight units cost ten lane exchanges instead of 48, and bias and GELU are applied to all of them at once.
 // All sums run in a fixed order: bit-reproducible.
 // What bounds it is the chain of these steps for few rows, the LDS and L1 reads of the multiply for many.  float32,
-// d = 512, dh = 128, with four waves and one unit per wave at a time / now: one row 22.0 / 6.4 us, 200 rows 23.5 / 7.2 us,
-// 4608 rows 104 / 51 us; d = 4096, dh = 512: one row 598 / 78 us, 4608 rows 2200 / 679 us.
+// d = 512, dh = 128, with four waves and one unit per wave at a time / now: one row 19.8 / 4.7 us, 200 rows 20.9 / 5.4 us,
+// 4608 rows 104 / 32 us; d = 4096, dh = 512: one row 591 / 77 us, 4608 rows 2195 / 581 us.  The form follows dh and M, see
+// launch_generic.
 #include "score_args.h"
 
 namespace dllava {
 
 namespace {
 
-constexpr int kThreads = 1024;
-constexpr int kWaves = kThreads / kWave;
-
-// kUnits: hidden units a wave takes at a time
-template <typename T, int R, int kUnits>
-__global__ __launch_bounds__(kThreads) void score_generic_kernel(ScoreArgs a) {
+// kUnits: hidden units a wave takes at a time; kWaves: waves of a block
+template <typename T, int R, int kUnits, int kWaves>
+__global__ __launch_bounds__(kWaves* kWave) void score_generic_kernel(ScoreArgs a) {
+  constexpr int kThreads = kWaves * kWave;
   extern __shared__ float xs[];  // [R][d]
   __shared__ float sm_l[kWaves][R][2];
   constexpr int E = Elem<T>::kPer16B;
@@ -44,7 +43,8 @@ __global__ __launch_bounds__(kThreads) void score_generic_kernel(ScoreArgs a) {
       wv[u] = *reinterpret_cast<const uint4*>(W1 + static_cast<int64_t>(j) * d + static_cast<int64_t>(cc) * E);
     }
   };
-  load(w * kUnits, lane);
+  constexpr bool kAhead = kUnits > 2;  // with one or two units the loop is left to the compiler, which has several pieces in flight
+  if constexpr (kAhead) load(w * kUnits, lane);
   int64_t src[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) src[r] = m0 + r < a.M ? score_src_row(a.seq_off, a.vis_start, a.vis_len, a.B, m0 + r) : -1;
@@ -64,36 +64,44 @@ __global__ __launch_bounds__(kThreads) void score_generic_kernel(ScoreArgs a) {
 #pragma unroll
   for (int r = 0; r < R; ++r) l0[r] = l1[r] = 0.f;
   for (int j0 = w * kUnits; j0 < dh; j0 += kWaves * kUnits) {
+    const int j = j0 + lane / kPerUnit;  // the unit whose whole sum this lane ends with
+    const bool ok = j < dh;
+    const float bias = ok && a.b1 ? a.b1[j] : 0.f;
+    const float w20 = ok ? Elem<T>::load(W2 + j) : 0.f, w21 = ok ? Elem<T>::load(W2 + a.dh + j) : 0.f;
     float acc[R][kUnits];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int u = 0; u < kUnits; ++u) acc[r][u] = 0.f;
-    for (int c0 = 0; c0 < chunks; c0 += kWave) {  // wave-uniform
-      const int c = c0 + lane;
-      uint4 cur[kUnits];
+    auto multiply = [&](const uint4 (&piece)[kUnits], int c) __attribute__((always_inline)) {
 #pragma unroll
-      for (int u = 0; u < kUnits; ++u) cur[u] = wv[u];
-      if (c0 + kWave < chunks)
-        load(j0, c + kWave);
-      else if (j0 + kWaves * kUnits < dh)
-        load(j0 + kWaves * kUnits, lane);
-      if (c < chunks) {
+      for (int u = 0; u < kUnits; ++u) {
+        float f[E];
+        Elem<T>::unpack(piece[u], f);
 #pragma unroll
-        for (int u = 0; u < kUnits; ++u) {
-          float f[E];
-          Elem<T>::unpack(cur[u], f);
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-          for (int r = 0; r < R; ++r)
+          for (int e = 0; e < E; ++e) acc[r][u] = fmaf(xs[r * d + c * E + e], f[e], acc[r][u]);
+      }
+    };
+    if constexpr (!kAhead) {
+      for (int c = lane; c < chunks; c += kWave) {
+        load(j0, c);
+        multiply(wv, c);
+      }
+    } else {
+      for (int c0 = 0; c0 < chunks; c0 += kWave) {  // wave-uniform
+        const int c = c0 + lane;
+        uint4 cur[kUnits];
 #pragma unroll
-            for (int e = 0; e < E; ++e) acc[r][u] = fmaf(xs[r * d + c * E + e], f[e], acc[r][u]);
-        }
+        for (int u = 0; u < kUnits; ++u) cur[u] = wv[u];
+        if (c0 + kWave < chunks)
+          load(j0, c + kWave);
+        else if (j0 + kWaves * kUnits < dh)
+          load(j0 + kWaves * kUnits, lane);
+        if (c < chunks) multiply(cur, c);
       }
     }
-    const int j = j0 + lane / kPerUnit;  // the unit whose whole sum this lane ends with
-    const bool ok = j < dh;
-    const float bias = ok && a.b1 ? a.b1[j] : 0.f;
-    const float w20 = ok ? Elem<T>::load(W2 + j) : 0.f, w21 = ok ? Elem<T>::load(W2 + a.dh + j) : 0.f;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       float* v = acc[r];
@@ -139,22 +147,39 @@ __global__ __launch_bounds__(kThreads) void score_generic_kernel(ScoreArgs a) {
   }
 }
 
-// Four rows per block above 512 rows: a compute unit holds one block at a time, so up to there single rows are at most
-// two rounds of the chip (512 rows singly / in fours: float32, d = 512, dh = 128: 12.9 / 11.9 us, d = 4096, dh = 512:
-// 153 / 137 us; bfloat16, d = 520, dh = 130: 14.4 / 17.7 us) and from there at least three (768 rows, the first of these:
-// three rounds of 6.3 us singly, 12.3 us in fours).  Only while four float32 rows fit 64 KiB of LDS.
-template <typename T>
-int launch_generic(const ScoreArgs& a, hipStream_t st) {
-  constexpr int U1 = sizeof(T) == 4 ? 8 : 4;  // what the registers of a 16-wave block hold
-  const size_t row = static_cast<size_t>(a.d) * sizeof(float);
-  const int R = a.M > 512 && 4 * row <= 64 * 1024 ? 4 : 1;
+template <typename T, int R, int kUnits, int kWaves>
+void launch_form(const ScoreArgs& a, hipStream_t st) {
   const int64_t n = ceil_div(a.M, R);
   const int64_t gx = n < (1 << 20) ? n : (1 << 20);  // a grid dimension holds fewer than 2^32 threads
   const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(ceil_div(n, gx)));
-  if (R == 4)
-    hipLaunchKernelGGL((score_generic_kernel<T, 4, 4>), grid, dim3(kThreads), 4 * row, st, a);
+  hipLaunchKernelGGL((score_generic_kernel<T, R, kUnits, kWaves>), grid, dim3(kWaves * kWave), R * static_cast<size_t>(a.d) * sizeof(float), st, a);
+}
+
+// Which form.  As many waves and units per wave as there are units for, up to 16 and 8; a row whose units are few is cheap
+// and wants many small blocks in flight instead (one row, float32, d = 512, waves x units: dh = 4 2.5 us at 4x1 against 4.3
+// at 16x8, dh = 16 3.0 at 4x4 against 4.5, dh = 32 3.1 at 8x4 against 4.6, dh = 48 4.0 at 8x4 against 4.6; 20000 rows,
+// dh = 2: 19 us at 4x1, 92 at 16x4).  A compute unit holds one block of 16 waves at a time, so more than 256 rows singly go
+// two to a compute unit with 8 waves (float32 / bfloat16, dh = 128, 500 rows: 9.1 / 11.1 us against 11.6 / 12.9), and above
+// 512 rows, a third round, a block takes four of them (500 rows that way: 10.8 / 16.1; 600 rows 11.0 / 16.4 against 11.2 /
+// 16.8 with 8 waves), with four waves of eight units from the second round of those blocks on (1000 rows 14.7 us against
+// 11.0 with 16 waves, 2000 rows 16.2 against 20.9).  Four float32 rows have to fit 64 KiB of LDS.
+template <typename T>
+int launch_generic(const ScoreArgs& a, hipStream_t st) {
+  const bool four = a.M > 512 && 4 * a.d * static_cast<int64_t>(sizeof(float)) <= 64 * 1024;
+  if (a.dh <= 4)
+    launch_form<T, 1, 1, 4>(a, st);
+  else if (a.dh <= 8)
+    launch_form<T, 1, 2, 4>(a, st);
+  else if (a.dh <= 16)
+    launch_form<T, 1, 4, 4>(a, st);
+  else if (four && a.M > 1024)
+    launch_form<T, 4, 8, 4>(a, st);
+  else if (four)
+    launch_form<T, 4, 4, 16>(a, st);
+  else if (a.M > 256 || a.dh <= 32)
+    launch_form<T, 1, 4, 8>(a, st);
   else
-    hipLaunchKernelGGL((score_generic_kernel<T, 1, U1>), grid, dim3(kThreads), row, st, a);
+    launch_form<T, 1, sizeof(T) == 4 ? 8 : 4, 16>(a, st);  // the units that the registers of 16 waves hold
   DLLAVA_CHECK_LAUNCH("score_generic_kernel");
   return DLLAVA_OK;
 }

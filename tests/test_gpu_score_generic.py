@@ -1,6 +1,6 @@
-"""dllava_score on the precision-generic kernel: one and four rows per block, hidden units that end inside a wave's group or
-a block's round, rows shorter and longer than one pass of a wave, spans with gaps and logits rows beyond the spans.
-(bfloat16 comes here when d is no multiple of 64, as in all of these.)"""
+"""dllava_score on the precision-generic kernel: all of its forms (4, 8 or 16 waves, one or four rows per block, one to eight
+hidden units per wave), hidden units that end inside a wave's group or a block's round, rows shorter and longer than one pass of a wave, spans with gaps and logits rows beyond the spans.
+(bfloat16 comes here when d is no multiple of 64.)"""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,8 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("M,d,dh", [(1, 8, 1), (3, 248, 7), (7, 520, 129), (512, 72, 9), (513, 264, 130), (1030, 40, 137), (515, 4104, 5), (9, 16376, 3)])
+@pytest.mark.parametrize("M,d,dh", [(1, 8, 1), (3, 248, 7), (7, 520, 129), (512, 72, 9), (513, 264, 130), (1030, 40, 137), (515, 4104, 5), (9, 16376, 3),
+                                    (5, 512, 20), (300, 264, 47), (2049, 136, 33), (600, 8200, 40), (1025, 4096, 9)])
 def test_matches_float64(M, d, dh, dtype):
     f32 = dtype == torch.float32
     t = lambda name, shape, s=1.0: torch.from_numpy(rng.normal(11, name, shape) * s).to(dtype)
@@ -41,6 +42,26 @@ def test_matches_float64(M, d, dh, dtype):
     assert n < M or M == 1
     assert ((got[:n] - ref).abs() <= tol).all(), f"worst {((got[:n] - ref).abs() / tol).max():.2f} of the bound"
     assert (got[n:] == 7.0).all()   # rows beyond the spans are not written
+
+
+def test_few_hidden_units_are_cheap():
+    """A row with two hidden units is a fraction of the work of a row with 128.  On blocks of 16 waves it took nearly half the
+    time of one."""
+    M, d, ms = 20000, 512, {}
+    x = torch.randn(M, d, device=DEV)
+    for dh in (2, 128):
+        W1, W2, out = torch.randn(dh, d, device=DEV), torch.randn(2, dh, device=DEV), torch.zeros(M, 2, device=DEV)
+        ws = torch.zeros(P.dllava_score_workspace(M, d, dh, P.F32), dtype=torch.uint8, device=DEV)
+        ev, t = [torch.cuda.Event(enable_timing=True) for _ in range(2)], []
+        for _ in range(10):
+            ev[0].record()
+            for _ in range(10):
+                P.dllava_score(x, d, M, 0, None, None, None, d, dh, W1, None, W2, None, P.F32, out, ws)
+            ev[1].record()
+            torch.cuda.synchronize()
+            t.append(ev[0].elapsed_time(ev[1]))
+        ms[dh] = min(t)
+    assert ms[2] < 0.3 * ms[128], ms
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
