@@ -37,6 +37,25 @@ def test_tile_edges(lens, blocks, Dh):
     assert torch.equal(O.view(torch.int16), again.view(torch.int16))   # same bits every time
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens", [[1], [31, 32, 33, 0, 64, 65], [0, 0, 7, 0], [1000, 5, 96], [(37 * b) % 70 for b in range(130)]])
+def test_mask_words(lens):
+    """The packed masks that the kernel reads, as they stand in the workspace: word t of sequence b at off[b] / 32 + b + t."""
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows, B = int(off[-1]), len(lens)
+    keep = (np.arange(rows) * 2654435761 >> 7 & 3 != 0).astype(np.uint8) * 5     # any non-zero byte is "kept"
+    d = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    x = torch.zeros((rows, 1, 64), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((P.dllava_masked_attn_workspace(rows, B),), 0xa5, dtype=torch.uint8, device="cuda")
+    P.dllava_masked_attn(x, x, x, B, d(off), rows, 1, 64, 0.125, d(keep), torch.zeros_like(x), P.BF16, ws)
+    words = ws.cpu().numpy().view(np.uint32)
+    for b, n in enumerate(lens):
+        bits = np.zeros((n + 31) // 32 * 32, np.uint8)
+        bits[:n] = keep[off[b]:off[b + 1]] != 0
+        want = np.packbits(bits, bitorder="little").view(np.uint32)
+        assert (words[off[b] // 32 + b:][:len(want)] == want).all(), b
+
+
 def test_masked_kernel_does_not_spill():
     """The kernel counts its outstanding vector-memory operations; scratch traffic would add to them."""
     import re
