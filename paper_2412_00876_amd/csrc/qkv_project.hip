@@ -168,9 +168,11 @@ __global__ __launch_bounds__(kRingThreads, 1) void qkv_ring_kernel(QkvArgs a, Ro
     const int t = 16 * JB * (w & 1) + 16 * j + (lane & 15);
     float v[FI][4];
 #pragma unroll
-    for (int i = 0; i < FI; ++i)
+    for (int i = 0; i < FI; ++i) {
+      ring_tie_acc(acc[i][j]);  // in accumulation registers until its column: the others do not hold them all
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[i][e] = acc[i][j][e];
+    }
     if constexpr (decltype(ROTATE)::value) {
       const float p = pos[j];
 #pragma unroll

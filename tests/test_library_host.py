@@ -166,6 +166,26 @@ def test_prefill_kernel_does_not_spill():
             assert re.search(r"ScratchSize \[bytes/lane\]: 0\b", b), b[:400]
 
 
+def test_ring_kernels_do_not_spill():
+    """The loops of the tile products count their loads in the same way; here scratch traffic would also stand between their
+    matrix instructions."""
+    import subprocess
+    from concurrent.futures import ThreadPoolExecutor
+    from paper_2412_00876_amd import build
+
+    def report(source):
+        r = subprocess.run([build.HIPCC, *build.COMMON, *build.HIP_FLAGS, "-Rpass-analysis=kernel-resource-usage", "--cuda-device-only", "-c",
+                            os.path.join(build.CSRC, source), "-o", os.devnull], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return [b for b in r.stderr.split("Function Name: ")[1:] if "_ring_kernel" in b.split()[0]]
+
+    with ThreadPoolExecutor(3) as ex:
+        kernels = list(ex.map(report, ("score_mfma.hip", "qkv_project.hip", "predictor.hip")))
+    assert [len(k) for k in kernels] == [8, 8, 9]      # every tile
+    for b in sum(kernels, []):
+        assert re.search(r"ScratchSize \[bytes/lane\]: 0\b", b), b[:400]
+
+
 def test_score_workspace_is_monotonic_in_rows(lib):
     """A workspace sized for the largest row count must serve every smaller one."""
     for d, dh in ((4096, 1024), (256, 64), (64, 1)):
