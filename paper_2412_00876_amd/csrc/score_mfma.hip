@@ -104,22 +104,25 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
       q0[i] = *reinterpret_cast<const uint2*>(ok ? W2 + u0 : zero16);
       q1[i] = *reinterpret_cast<const uint2*>(ok ? W2 + dh + u0 : zero16);
     }
-  } else {
+  } else {  // through the ring memory, one thread per unit
+    __syncthreads();
+    float* sb = reinterpret_cast<float*>(smem_raw);
+    bf16_t* s0 = reinterpret_cast<bf16_t*>(sb + kUnits);
+    bf16_t* s1 = s0 + kUnits;
+    if (tid < kUnits) {
+      const int u = ut * kUnits + tid;
+      const bool ok = u < units;
+      sb[tid] = ok && has_b1 ? a.b1[u] : 0.f;
+      s0[tid] = ok ? W2[u] : bf16_t{0};
+      s1[tid] = ok ? W2[dh + u] : bf16_t{0};
+    }
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < FI; ++i) {
-      float* bv = &bq[i].x;
-      uint32_t h0[4], h1[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int u = u_lane + 16 * i + r;
-        const bool ok = u < units;
-        bv[r] = *((ok & has_b1) ? a.b1 + u : kZeroWords);
-        h0[r] = *(ok ? W2 + u : zero16);
-        h1[r] = *(ok ? W2 + dh + u : zero16);
-      }
-      q0[i] = uint2{h0[0] | h0[1] << 16, h0[2] | h0[3] << 16};
-      q1[i] = uint2{h1[0] | h1[1] << 16, h1[2] | h1[3] << 16};
-      __builtin_amdgcn_sched_barrier(0);
+      const int at = u_lane - ut * kUnits + 16 * i;
+      bq[i] = *reinterpret_cast<const float4*>(sb + at);
+      q0[i] = *reinterpret_cast<const uint2*>(s0 + at);
+      q1[i] = *reinterpret_cast<const uint2*>(s1 + at);
     }
   }
 #pragma unroll
@@ -132,11 +135,11 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       // past dh the last unit repeats: its weight of zero alone would make NaN of an infinite value
-      const uint64_t real = __ballot(u_lane + 16 * i + r < units);
+      uint32_t real = u_lane + 16 * i + r < units ? ~0u : 0u;
+      asm("" : "+v"(real));  // of a choice it knows the compiler makes a branch around every GELU
 #pragma unroll
       for (int j = 0; j < JB; ++j) {
-        float g = gelu_erf_fast(acc[i][j][r] + bias[r]);
-        asm("v_cndmask_b32_e64 %0, 0, %0, %1" : "+v"(g) : "s"(real));  // written out: of `real ? g : 0` the compiler makes a branch
+        const float g = __uint_as_float(__float_as_uint(gelu_erf_fast(acc[i][j][r] + bias[r])) & real);
         p[j][0] = fmaf(g, w20[r], p[j][0]);
         p[j][1] = fmaf(g, w21[r], p[j][1]);
       }

@@ -68,3 +68,26 @@ def test_projection_work_follows_the_rows_there_are():
     assert torch.equal(Q1.view(torch.int16), Q4.view(torch.int16)) and torch.equal(p1.view(torch.int16), p4.view(torch.int16))
     assert not Q4[total:].any()
     assert t4 < 1.7 * t1, (t1, t4)
+
+
+@pytest.mark.parametrize("tile", [1, 4, 5, 6, 7, 8, 9, 10])
+@pytest.mark.parametrize("dh", [128, 300])
+def test_score_vectors_at_any_address(tile, dh):
+    """Bias and output weights one element off their alignment (read through LDS) give the bits of aligned ones (read by fours)."""
+    M, d = 130, 128
+    g = torch.Generator(device="cuda").manual_seed(9)
+    rnd = lambda *s, dtype=torch.bfloat16: torch.randn(s, generator=g, device="cuda", dtype=dtype)  # noqa: E731
+    x, W1, b1, W2 = rnd(M, d), rnd(dh, d), rnd(dh + 1, dtype=torch.float32), rnd(2 * dh + 1)
+    ws = torch.zeros(P.dllava_score_workspace(M, d, dh, P.BF16), dtype=torch.uint8, device="cuda")
+    out = []
+    P.dllava_set_launch_override(P.LAUNCH_SCORE_TILE, tile)
+    try:
+        for off in (0, 1):
+            bias, weights = torch.zeros(dh + 1, device="cuda"), torch.zeros(2 * dh + 1, dtype=torch.bfloat16, device="cuda")
+            bias[off:off + dh], weights[off:off + 2 * dh] = b1[:dh], W2[:2 * dh]
+            D = torch.zeros((M, 2), device="cuda")
+            P.dllava_score(x, d, M, 0, None, None, None, d, dh, W1, bias[off:], weights[off:], None, P.BF16, D, ws)
+            out.append(D)
+    finally:
+        P.dllava_set_launch_override(P.LAUNCH_SCORE_TILE, 0)
+    assert out[0].abs().max() > 0 and torch.equal(*out)
