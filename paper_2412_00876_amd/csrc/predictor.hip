@@ -195,8 +195,9 @@ int launch_lin_ring(const LinArgs& a, hipStream_t st) {
   return DLLAVA_OK;
 }
 
-// Small launches, these tiles / 256-row or 128 x 128 tiles of two LDS slots only: 214 x 4096 x 4096 18 / 52 us,
-// 214 x 4096 x 11008 46 / 173 us, 1000 x 4096 x 11008 111 / 171 us, 2000 x 512 x 4096 18 / 45 us (rows x features x width).
+// The tile that takes least: few rows or features want the small tiles, which leave less of the chip idle (this pick / the
+// best tile of 256 features: 214 rows x 4096 features x 4096 wide 17 / 44 us, 214 x 4096 x 11008 38 / 113, 1000 x 4096 x
+// 11008 80 / 118, 2000 x 512 x 4096 17 / 45; 3982 x 4096 x 4096 takes the latter, 96).
 int launch_lin(const LinArgs& a, hipStream_t st) {
   const RingTile* t = ring_pick(a.K, launch_override(DLLAVA_LAUNCH_LINEAR_TILE), [&](const RingTile& c) -> int64_t {
     if (c.id == 10) return 0;  // 64 x 128 does the same with its roles exchanged, and reads fewer of the weights per block

@@ -281,8 +281,9 @@ int launch_mfma(const QkvArgs& a, int64_t rows, double base, hipStream_t st) {
     rt.hi[i] = static_cast<float>(rev);
     rt.lo[i] = static_cast<float>(rev - static_cast<double>(rt.hi[i]));
   }
-  // The tile that takes least.  In place of 128 x 128 tiles of two LDS slots, three to a compute unit, or 256-row tiles: 107
-  // rows of 32 heads at d = 4096 32 / 50 us, 214 rows 39 / 53 us, 350 rows 48 / 76 us.  Lane offsets into the whole of a matrix and of x are 32-bit in the 256-row tiles.
+  // The tile that takes least: few rows want the tiles of one head, which leave less of the chip idle (32 heads, d = 4096,
+  // this pick / the best tile of two heads: 107 rows 22 / 46 us, 214 rows 31 / 47, 350 rows 41 / 48, 1000 rows the latter,
+  // 83 us).  Lane offsets into the whole of a matrix and of x are 32-bit in the tiles of two heads.
   const int forced = launch_override(DLLAVA_LAUNCH_QKV_TILE);
   auto heads_tiles = [&](const RingTile& c) -> int64_t { return 3 * ceil_div(a.H, c.fi / 4); };
   const RingTile* t = ring_pick(a.d, forced == 1 ? 3 : forced, [&](const RingTile& c) -> int64_t {

@@ -22,8 +22,6 @@ namespace dllava {
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kMaxCounters = static_cast<int>(kGemmCntBytes / sizeof(int32_t));  // one per token tile
 
 // ------------------------------------------------------------------------------------------------
@@ -238,9 +236,10 @@ int score_mfma_launch(const ScoreArgs& a, hipStream_t st) {
     DLLAVA_CHECK_LAUNCH("score_splitk_kernel");
     return DLLAVA_OK;
   }
-  // Many rows.  In place of 128 x 128 tiles of two LDS slots, three to a compute unit, which small launches used: 576 rows,
-  // d = 4096, dh = 1024 22 / 48 us, 2880 rows 34 / 51 us, 5760 rows 48 / 59 us.  Every token tile needs its own counter, the workspace holds partials of unit tiles of 128 or more, and lane
-  // offsets into the 256 rows of a large W1 tile are 32-bit.
+  // Many rows.  The tile that takes least: few rows want the tiles of 128 units, which leave less of the chip idle (d = 4096,
+  // dh = 1024, this pick / the best tile of 256 units: 576 rows 22 / 48 us, 2880 rows 34 / 50, 5760 rows 48 / 52, 11520 rows
+  // the latter, 77 us).  Every token tile needs its own counter, the workspace holds partials of unit tiles of 128 or more,
+  // and lane offsets into the 256 rows of a large W1 tile are 32-bit.
   const int forced = launch_override(DLLAVA_LAUNCH_SCORE_TILE);
   const RingTile* t = ring_pick(a.d, forced == 1 ? 3 : forced, [&](const RingTile& c) -> int64_t {
     const int64_t n_mt = ceil_div(a.M, 32 * c.jt), n = n_mt * ceil_div(a.dh, 32 * c.fi);
