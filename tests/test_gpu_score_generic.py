@@ -14,7 +14,8 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("M,d,dh", [(1, 8, 1), (3, 248, 7), (7, 520, 129), (512, 72, 9), (513, 264, 130), (1030, 40, 137), (515, 4104, 5), (9, 16376, 3),
-                                    (5, 512, 20), (300, 264, 47), (2049, 136, 33), (600, 8200, 40), (1025, 4096, 9)])
+                                    (5, 512, 20), (300, 264, 47), (2049, 136, 33), (600, 8200, 40), (1025, 4096, 9),
+                                    (2, 16384, 130), (300, 16384, 33), (600, 16384, 3)])
 def test_matches_float64(M, d, dh, dtype):
     f32 = dtype == torch.float32
     t = lambda name, shape, s=1.0: torch.from_numpy(rng.normal(11, name, shape) * s).to(dtype)
