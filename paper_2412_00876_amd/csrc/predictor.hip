@@ -94,15 +94,22 @@ __global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, in
     const int u = ft * kFeat + row < N ? row : N - 1 - ft * kFeat;  // features past N are computed and dropped
     ga[j] = static_cast<decltype(+ga[0])>(u) * K * 2 + ring_load_chunk_bytes(row, lane);
   }
+  const int64_t m_first = static_cast<int64_t>(rt) * kTok, m_last = m_first + kTok <= M ? m_first + kTok - 1 : M - 1;
+  int64_t m_of[JT], src[JT];
 #pragma unroll
   for (int j = 0; j < JT; ++j) {
-    const int row = ring_load_row(w, j, lane);
-    int64_t m = static_cast<int64_t>(rt) * kTok + row;
-    if (m >= M) m = M - 1;
-    int64_t sr = use_table ? span_table_row(spans, a.B, m) : score_src_row(a.seq_off, a.vis_start, a.vis_len, a.B, m);
-    if (sr < 0) sr = 0;
-    gb[j] = sr * a.ldx * 2 + ring_load_chunk_bytes(row, lane);
+    m_of[j] = m_first + ring_load_row(w, j, lane);
+    if (m_of[j] >= M) m_of[j] = M - 1;
   }
+  if (use_table) {
+#pragma unroll
+    for (int j = 0; j < JT; ++j) src[j] = span_table_row(spans, a.B, m_of[j]);
+  } else {
+    score_src_rows<JT>(a.seq_off, a.vis_start, a.vis_len, a.B, m_first, m_last, m_of, src);
+  }
+#pragma unroll
+  for (int j = 0; j < JT; ++j)
+    gb[j] = (src[j] < 0 ? 0 : src[j]) * a.ldx * 2 + ring_load_chunk_bytes(ring_load_row(w, j, lane), lane);
   if (use_table) __syncthreads();  // the tile loads overwrite the table
   ring_f32x4 acc[FI][JT];
 #pragma unroll

@@ -45,9 +45,13 @@ __global__ __launch_bounds__(kWaves* kWave) void score_generic_kernel(ScoreArgs 
   };
   constexpr bool kAhead = kUnits > 2;  // with one or two units the loop is left to the compiler, which has several pieces in flight
   if constexpr (kAhead) load(w * kUnits, lane);
-  int64_t src[R];
+  int64_t src[R], m_of[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) src[r] = m0 + r < a.M ? score_src_row(a.seq_off, a.vis_start, a.vis_len, a.B, m0 + r) : -1;
+  for (int r = 0; r < R; ++r) m_of[r] = m0 + r < a.M ? m0 + r : a.M - 1;
+  score_src_rows<R>(a.seq_off, a.vis_start, a.vis_len, a.B, m0, m_of[R - 1], m_of, src);
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (m0 + r >= a.M) src[r] = -1;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     if (src[r] < 0) continue;  // beyond the spans: not read, not written

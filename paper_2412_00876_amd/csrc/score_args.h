@@ -39,6 +39,30 @@ __device__ __forceinline__ int64_t score_src_row(const int32_t* seq_off, const i
   return -1;
 }
 
+// The same for N rows at once, all between first and last (uniform over the wave), in one pass over the sequences whose loads
+// do not depend on one another: looking the rows up one by one is a chain of loads, B long, for each of them (1100 spans, eight
+// rows per lane, 3300 rows of 5120 against 1280 units: 997 us one by one, 126 so).  Returns the rows in all spans.
+template <int N>
+__device__ __forceinline__ int64_t score_src_rows(const int32_t* seq_off, const int32_t* vis_start, const int32_t* vis_len, int B,
+                                                  int64_t first, int64_t last, const int64_t (&m)[N], int64_t (&src)[N]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) src[j] = seq_off ? -1 : m[j];
+  if (!seq_off) return last + 1;
+  int64_t acc = 0;
+#pragma unroll 8
+  for (int b = 0; b < B; ++b) {
+    const int len = vis_len[b], n = len > 0 ? len : 0;
+    const int64_t base = static_cast<int64_t>(seq_off[b]) + vis_start[b];
+    if (acc <= last && acc + n > first) {
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (m[j] >= acc && m[j] < acc + n) src[j] = base + (m[j] - acc);
+    }
+    acc += n;
+  }
+  return acc;
+}
+
 // The same mapping for a whole block: the spans of up to kSpanLdsMax sequences as a table in LDS (exclusive prefix
 // sums of the clamped span lengths and each span's first row), built with one round of loads, then searched per row
 // with LDS reads only.  The per-row loop above is a chain of dependent loads, B long, for every row a lane maps: at

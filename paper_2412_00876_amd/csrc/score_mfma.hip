@@ -58,16 +58,24 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
   SpanTable* spans = reinterpret_cast<SpanTable*>(smem_raw);
   const bool use_table = a.seq_off != nullptr && a.B > 0 && a.B <= kSpanLdsMax;
   if (use_table) span_table_build<kRingThreads>(spans, a.seq_off, a.vis_start, a.vis_len, a.B);
-  const int64_t rows_in_spans = use_table ? spans->prefix[a.B] : -1;
+  const int64_t m_first = static_cast<int64_t>(mt) * kTok, m_last = m_first + kTok <= M ? m_first + kTok - 1 : M - 1;
+  int64_t m_of[JB], src[JB];
 #pragma unroll
   for (int j = 0; j < JB; ++j) {
-    const int row = ring_load_row(w, j, lane);
-    int64_t m = static_cast<int64_t>(mt) * kTok + row;
-    if (m >= M) m = M - 1;
-    int64_t sr = use_table ? span_table_row(spans, a.B, m) : score_src_row(a.seq_off, a.vis_start, a.vis_len, a.B, m);
-    if (sr < 0) sr = 0;
-    gb[j] = sr * a.ldx * 2 + ring_load_chunk_bytes(row, lane);
+    m_of[j] = m_first + ring_load_row(w, j, lane);
+    if (m_of[j] >= M) m_of[j] = M - 1;
   }
+  int64_t rows_in_spans;
+  if (use_table) {
+    rows_in_spans = spans->prefix[a.B];
+#pragma unroll
+    for (int j = 0; j < JB; ++j) src[j] = span_table_row(spans, a.B, m_of[j]);
+  } else {
+    rows_in_spans = score_src_rows<JB>(a.seq_off, a.vis_start, a.vis_len, a.B, m_first, m_last, m_of, src);
+  }
+#pragma unroll
+  for (int j = 0; j < JB; ++j)
+    gb[j] = (src[j] < 0 ? 0 : src[j]) * a.ldx * 2 + ring_load_chunk_bytes(ring_load_row(w, j, lane), lane);
   if (use_table) __syncthreads();  // the tile loads overwrite the table
   ring_f32x4 acc[FI][JB];
 #pragma unroll
@@ -178,8 +186,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
   for (int t = tid; t < 2 * kTok; t += kRingThreads) {
     const int tok = t >> 1, c = t & 1;
     const int64_t m = static_cast<int64_t>(mt) * kTok + tok;
-    const bool in_spans = use_table ? m < rows_in_spans : score_src_row(a.seq_off, a.vis_start, a.vis_len, a.B, m) >= 0;
-    if (m < M && in_spans) {
+    if (m < M && m < rows_in_spans) {
       float s = a.b2 ? a.b2[c] : 0.f;
       for (int t0 = 0; t0 < n_ut; t0 += 8) {  // independent loads in flight, then a fixed-order sum
         float v[8];
