@@ -56,6 +56,53 @@ def test_mask_words(lens):
         assert (words[off[b] // 32 + b:][:len(want)] == want).all(), b
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("B", [65, 128, 193])
+@pytest.mark.parametrize("Dh", [64, 128])
+def test_many_sequences(B, Dh):
+    """Above 64 sequences a block finds its item by scans of 64: the same bits as calls of at most 64 sequences, which number
+    their items another way."""
+    rs = np.random.RandomState(B)
+    lens = np.where(rs.rand(B) < 0.2, 0, rs.randint(1, 300, size=B))
+    lens[[0, 63, 64, B - 1]] = [129, 0, 257, 1]
+    H, off = 2, np.concatenate([[0], np.cumsum(lens)])
+    g = torch.Generator(device="cuda").manual_seed(B)
+    q, k, v = (torch.randn((int(off[-1]), H, Dh), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    keep = (torch.rand(int(off[-1]), generator=g, device="cuda") < 0.4).to(torch.uint8)
+
+    def run(first, last):
+        a, z = int(off[first]), int(off[last])
+        O = torch.zeros((z - a, H, Dh), dtype=torch.bfloat16, device="cuda")
+        ws = torch.zeros(P.dllava_masked_attn_workspace(z - a, last - first), dtype=torch.uint8, device="cuda")
+        P.dllava_masked_attn(q[a:z].contiguous(), k[a:z].contiguous(), v[a:z].contiguous(), last - first,
+                             torch.tensor(off[first:last + 1] - a, dtype=torch.int32, device="cuda"), z - a, H, Dh, Dh ** -0.5, keep[a:z].contiguous(),
+                             O, P.BF16, ws)
+        return O
+
+    parts = torch.cat([run(b, min(b + 64, B)) for b in range(0, B, 64)])
+    assert torch.equal(run(0, B).view(torch.int16), parts.view(torch.int16)) and parts.any()
+
+
+@pytest.mark.gpu
+def test_time_of_many_short_sequences():
+    """500 sequences of one row take 4 times as long as 64.  When every block walked the sequences it was 18 times."""
+    t = []
+    for B in (64, 500):
+        x = torch.randn((B, 8, 64), device="cuda").to(torch.bfloat16)
+        off, keep = torch.arange(B + 1, dtype=torch.int32, device="cuda"), torch.ones(B, dtype=torch.uint8, device="cuda")
+        O, ws = torch.zeros_like(x), torch.zeros(P.dllava_masked_attn_workspace(B, B), dtype=torch.uint8, device="cuda")
+        ev, ms = [torch.cuda.Event(enable_timing=True) for _ in range(2)], []
+        for _ in range(8):
+            ev[0].record()
+            for _ in range(10):
+                P.dllava_masked_attn(x, x, x, B, off, B, 8, 64, 0.125, keep, O, P.BF16, ws)
+            ev[1].record()
+            torch.cuda.synchronize()
+            ms.append(ev[0].elapsed_time(ev[1]))
+        t.append(min(ms))
+    assert t[1] < 12 * t[0], t
+
+
 def test_masked_kernel_does_not_spill():
     """The kernel counts its outstanding vector-memory operations; scratch traffic would add to them."""
     import re
