@@ -99,8 +99,9 @@ const char* dllava_last_error(void);
  * choice, values a knob does not support are ignored.  Host, no GPU work; not meant for production callers.
  *   DLLAVA_LAUNCH_DECODE_WAVES   waves per block of the decode-attention kernels: 4 or 8
  *   DLLAVA_LAUNCH_DECODE_SPLITS  blocks per (sequence, head) of the decode-attention kernels: 1 .. 16
- *   DLLAVA_LAUNCH_PREFILL_WAVES  waves (of 32 queries each) per block of the matrix-core attention kernel: 1, 2 or 4
- *                                (dllava_masked_attn has a kernel of its own, always with 4)
+ *   DLLAVA_LAUNCH_PREFILL_WAVES  waves (of 32 queries each) per block of the matrix-core attention kernels: 1, 2 or 4
+ *                                (dllava_masked_attn always has 4); plus 16: the kernel for long sequences whatever
+ *                                their length, plus 32: the one for short ones (16 or 32 alone: automatic waves)
  *   DLLAVA_LAUNCH_PREFILL_BLOCKS blocks of the matrix-core attention kernel's launch (its blocks are persistent and
  *                                share the work items; by default as many as the chip holds at once): 1 .. 65535
  *   DLLAVA_LAUNCH_SCORE_TILE     tile of the many-rows scoring kernel: 1 = 128 units x 128 tokens, 9 = 128 x 192,

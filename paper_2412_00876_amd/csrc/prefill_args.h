@@ -26,6 +26,8 @@ struct PrefillArgs {
 
 // matrix-core path (prefill_mfma.hip); returns 1 if it does not handle the shape
 int prefill_mfma_launch(const PrefillArgs& a, int64_t rows, int Dh, hipStream_t st);
+// its software-pipelined kernel (prefill_tiles.hip), blocks of nwq waves; Dh 64 or 128; 1 if the launch would be too large
+int prefill_tiles_launch(const PrefillArgs& a, int64_t rows, int Dh, int nwq, hipStream_t st);
 // the causal form over rows with key masks (masked_mfma.hip); returns 1 if it does not handle the shape
 int masked_mfma_launch(const PrefillArgs& a, int64_t rows, int Dh, hipStream_t st);
 

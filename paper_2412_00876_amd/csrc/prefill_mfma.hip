@@ -537,6 +537,20 @@ int launch(const PrefillArgs& a, int64_t rows, hipStream_t st) {
   return DLLAVA_OK;
 }
 
+// Which calls take the software-pipelined kernel of prefill_tiles.hip: its tile step is 10-35 % shorter, but the first and last tile of
+// an item cost it about 1.5 us more (more straight-line code, fetched once), so the line follows the tiles per item and, where
+// blocks walk several items, the amount of work.  Both kernels measured over means of 32..768 rows and 1x8..64x40 sequences x
+// heads, here / there in us: causal, head size 128, 16x32: 128 rows 23.5 / 23.6, 160 rows 29.2 / 27.0, 768 rows 206 / 182; 1x32:
+// 224 rows 12.9 / 12.6 (paged), 11.7 / 11.9 (rows), 768 rows 29.9 / 25.0; 64x40: 64 rows 42.7 / 43.9, 96 rows 59.7 / 53.7.  Head size 64,
+// 16x32: 256 rows 25.9 / 26.3, 320 rows 33.3 / 32.0; 1x32: 320 rows 10.6 / 10.9, 384 rows 13.9 / 13.6; 64x40: 128 rows 43.7 / 41.2.
+// Unmasked, head size 64: 4x32: 96 rows 7.4 / 7.3, 320 rows 18.3 / 16.1; 1x32: 128 rows 6.6 / 6.8, 160 rows 8.2 / 7.9.
+bool pipelined(const PrefillArgs& a, int64_t rows, int Dh) {
+  const int64_t mean = rows / a.B, work = rows * a.H;
+  if (a.full) return mean >= 160 || (mean >= 96 && work >= 16384);
+  if (Dh == 128) return mean >= 288 || (mean >= 144 && work >= 65536) || (mean >= 80 && work >= 200000);
+  return mean >= 352 || (mean >= 288 && work >= 32768) || (mean >= 112 && work >= 262144);
+}
+
 }  // namespace
 
 // returns 1 if the shape is not handled here
@@ -546,9 +560,10 @@ int prefill_mfma_launch(const PrefillArgs& a, int64_t rows, int Dh, hipStream_t 
   // measured: 2 waves win for the 7B batch-1 prefill (214 rows x 32 heads), 4 waves from batch 2 upwards
   const int64_t work = rows * a.H;  // query rows x heads
   int nwq = work >= 8 * 1024 ? 4 : (work >= 1024 ? 2 : 1);
-  if (const int v = launch_override(DLLAVA_LAUNCH_PREFILL_WAVES)) {  // forced through dllava_set_launch_override
-    if (v == 1 || v == 2 || v == 4) nwq = v;
-  }
+  const int forced = launch_override(DLLAVA_LAUNCH_PREFILL_WAVES);  // through dllava_set_launch_override
+  if (const int v = forced & 7; v == 1 || v == 2 || v == 4) nwq = v;
+  const bool tiles = forced & 16 ? true : forced & 32 ? false : pipelined(a, rows, Dh);
+  if ((Dh == 128 || Dh == 64) && tiles) return prefill_tiles_launch(a, rows, Dh, nwq, st);
   if (Dh == 128) {
     if (nwq == 4) return launch<128, 4>(a, rows, st);
     if (nwq == 2) return launch<128, 2>(a, rows, st);

@@ -1,0 +1,156 @@
+"""The software-pipelined attention kernel of prefill_tiles.hip, forced through dllava_set_launch_override (the library takes it
+for long sequences only): even and odd numbers of key tiles per wave, sequence lengths around the 32-key tiles and the items, few
+blocks with many items each, keys in pages and in rows, the unmasked form, a maximum that keeps growing along the keys."""
+import math
+import os
+import re
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2412_00876_amd as P
+from oracle import dllava_ref as R
+from oracle import predictor_ref as PR
+from synth import rng
+from synth import workloads as W
+from tests.test_gpu_parity import _assert_out_close
+
+TILES = 16      # added to the waves of LAUNCH_PREFILL_WAVES: this kernel whatever the size
+
+
+def _run(q, k, v, lens, H, Dh, form, waves, blocks, scale):
+    """q, k, v: bfloat16 bit patterns as the oracle takes them.  Page slots past a sequence's end hold NaN."""
+    from tests import harness as h
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows, B = int(off[-1]), len(lens)
+    d = lambda a: h.to_dev(a, "bf16")  # noqa: E731
+    qd, kd, vd, od = d(q), d(k), d(v), torch.from_numpy(off).to(h.DEV)
+    cache = None
+    if form == "paged":
+        mp = max(1, (max(lens) + 15) // 16)
+        pages = torch.full((B * mp, 2, H, 16, Dh), float("nan"), dtype=torch.bfloat16, device=h.DEV)
+        table = torch.from_numpy(np.random.RandomState(1).permutation(B * mp).astype(np.int32).reshape(B, mp)).to(h.DEV)
+        for b, n in enumerate(lens):
+            for j in range(0, n, 16):
+                m, pg = min(16, n - j), int(table[b, j // 16])
+                pages[pg, 0, :, :m] = kd[off[b] + j:off[b] + j + m].transpose(0, 1)
+                pages[pg, 1, :, :m] = vd[off[b] + j:off[b] + j + m].transpose(0, 1)
+        cache, kd, vd = P.KVCache(pages, table, torch.tensor(lens, dtype=torch.int32, device=h.DEV)), None, None
+    out = []
+    P.dllava_set_launch_override(P.LAUNCH_PREFILL_WAVES, TILES + waves)
+    P.dllava_set_launch_override(P.LAUNCH_PREFILL_BLOCKS, blocks)
+    try:
+        for _ in range(2):
+            O = torch.full((rows, H, Dh), float("nan"), dtype=torch.bfloat16, device=h.DEV)
+            if form == "full":
+                P.dllava_span_attn(qd, kd, vd, B, od, rows, H, Dh, scale, O, P.BF16)
+            else:
+                P.dllava_prefill_attn(qd, kd, vd, cache, B, od, rows, H, Dh, scale, O, P.BF16)
+            out.append(O)
+        torch.cuda.synchronize()
+    finally:
+        P.dllava_set_launch_override(P.LAUNCH_PREFILL_WAVES, 0)
+        P.dllava_set_launch_override(P.LAUNCH_PREFILL_BLOCKS, 0)
+    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))   # same bits every time
+    return h.as_f64(out[0]), off
+
+
+def _reference(q, k, v, off, H, Dh, form, scale):
+    if form != "full":
+        return R.prefill_attn(q, k, v, off, scale, "bf16")
+    ref = np.zeros((len(q), H * Dh))
+    f = lambda a: R.widen(a, "bf16").reshape(len(a), H * Dh)  # noqa: E731
+    for a, b in zip(off[:-1], off[1:]):
+        if b > a:
+            ref[a:b] = PR.attention(f(q[a:b]), f(k[a:b]), f(v[a:b]), heads=H)
+    return ref.reshape(len(q), H, Dh)
+
+
+def _qkv(seed, rows, H, Dh):
+    return tuple(W.store(rng.normal(seed, t, (rows, H, Dh)), "bf16") for t in "qkv")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", ["paged", "rows", "full"])
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("waves,blocks", [(4, 0), (4, 1), (4, 3), (2, 0), (2, 3), (1, 0), (1, 7)])
+@pytest.mark.parametrize("lens", [[1, 15, 16, 17, 31, 32, 33, 48], [127, 128, 129, 0, 95, 64], [160, 257, 385]])
+def test_tile_edges(lens, waves, blocks, Dh, form):
+    H, rows = 3, int(sum(lens))
+    q, k, v = _qkv(80 + Dh, rows, H, Dh)
+    O, off = _run(q, k, v, lens, H, Dh, form, waves, blocks, 1.0 / math.sqrt(Dh))
+    _assert_out_close(O, _reference(q, k, v, off, H, Dh, form, 1.0 / math.sqrt(Dh)), "bf16", f"{form} {lens}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", ["paged", "rows", "full"])
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("falling", [False, True])
+def test_growing_maximum(Dh, form, falling):
+    """Keys whose scores grow (or fall) by several powers of two per tile: the reference of the exponentials moves in every tile, while
+    the products of the tile before are pending, or never again."""
+    H, lens = 2, [200, 33, 96]
+    rows = sum(lens)
+    q, k, v = _qkv(90 + Dh, rows, H, Dh)
+    kf = R.widen(k, "bf16")
+    q1 = np.abs(R.widen(q, "bf16"))
+    at = 0
+    for n in lens:
+        ramp = np.arange(n)[::-1] if falling else np.arange(n)
+        kf[at:at + n] = 0.05 * kf[at:at + n] + (ramp / 32.0 * 0.12)[:, None, None]   # about 12 / sqrt(Dh) * Dh/12 powers of two a tile
+        at += n
+    q, k = W.store(q1, "bf16"), W.store(kf, "bf16")
+    scale = 8.0 / Dh
+    O, off = _run(q, k, v, lens, H, Dh, form, 4, 0, scale)
+    if form == "full":      # the oracle's unmasked form scales by 1 / sqrt(Dh): through the queries
+        assert abs(scale * math.sqrt(Dh) - 8.0 / math.sqrt(Dh)) < 1e-12
+        f = [R.widen(a, "bf16") for a in (q, k, v)]
+        ref = np.zeros((rows, H, Dh))
+        for a, b in zip(off[:-1], off[1:]):
+            for hh in range(H):
+                s = f[0][a:b, hh] @ f[1][a:b, hh].T * scale
+                w = np.exp(s - s.max(1, keepdims=True))
+                ref[a:b, hh] = w / w.sum(1, keepdims=True) @ f[2][a:b, hh]
+    else:
+        ref = R.prefill_attn(q, k, v, off, scale, "bf16")
+    _assert_out_close(O, ref, "bf16", f"growing maximum {form} {Dh}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Dh", [64, 128])
+def test_many_sequences(Dh):
+    """Above 64 sequences: one item per block, found by scans."""
+    H, lens = 2, [(37 * b) % 150 for b in range(80)]
+    q, k, v = _qkv(100 + Dh, int(sum(lens)), H, Dh)
+    O, off = _run(q, k, v, lens, H, Dh, "paged", 4, 0, 1.0 / math.sqrt(Dh))
+    _assert_out_close(O, _reference(q, k, v, off, H, Dh, "paged", 1.0 / math.sqrt(Dh)), "bf16", "80 sequences")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Dh", [64, 128])
+def test_special_values_pass_through(Dh):
+    """An infinity in a query, a NaN in a value and a key of zeros: not-a-number results where the definition gives them, the other
+    rows as without them."""
+    from tests import harness as h
+    H, lens = 1, [130]
+    q, k, v = (R.widen(a, "bf16") for a in _qkv(110 + Dh, 130, H, Dh))
+    clean, _ = _run(*(W.store(a, "bf16") for a in (q, k, v)), lens, H, Dh, "rows", 4, 0, 0.1)
+    q[70, 0, 3] = np.inf
+    v[100, 0, 5] = np.nan
+    O, _ = _run(*(W.store(a, "bf16") for a in (q, k, v)), lens, H, Dh, "rows", 4, 0, 0.1)
+    bad = np.isnan(O)
+    assert bad[70].all() and bad[101:, 0, 5].all() and not bad[:70].any() and not bad[71:100, 0, :5].any()
+    keep = [i for i in range(96) if i != 70]      # rows of key tiles without the NaN
+    assert np.array_equal(O[keep], clean[keep])
+
+
+def test_tiles_kernels_do_not_spill():
+    """The kernels count their outstanding vector-memory operations; scratch traffic would add to them."""
+    from paper_2412_00876_amd import build
+    r = subprocess.run([build.HIPCC, *build.COMMON, *build.HIP_FLAGS, "-Rpass-analysis=kernel-resource-usage", "--cuda-device-only", "-c",
+                        os.path.join(build.CSRC, "prefill_tiles.hip"), "-o", os.devnull], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    scratch = re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)
+    assert len(scratch) == 18 and set(scratch) == {"0"}
