@@ -1,4 +1,7 @@
-"""Thin ctypes binding of libdllava.so: argument marshalling only.
+"""Thin binding of libdllava.so: argument marshalling only.
+
+The functions below say through ctypes what each call takes; at the end of the module they are bound to their native forms
+(native/calls.cpp), which convert the same arguments without ctypes and leave whatever they do not know to them.
 
 Every function has the name and argument order of its C entry point (include/dllava.h); tensors are
 torch tensors used purely as device buffers (data_ptr), and the stream defaults to torch's current
@@ -8,6 +11,7 @@ if the shared library is missing the import fails.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Optional
 
@@ -367,3 +371,22 @@ def dllava_decode_attn_append_static(q, k_new, v_new, B, logits, threshold, keep
     _check(_lib.dllava_decode_attn_append_static(_p(q), _p(k_new), _p(v_new), B, _p(logits), threshold,
                                                  _p(keep_override), cache.ref, scale, _p(o), _p(keep_out),
                                                  _p(err_flag), _stream(stream)))
+
+
+def _bind_native() -> None:
+    calls_path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_calls.so")
+    if not os.path.exists(calls_path):
+        raise ImportError(f"{calls_path} is missing: build it with `python -m paper_2412_00876_amd.build`")
+    from . import _calls
+    _calls.init(KVCache, Predictor, _check, torch.cuda.current_device, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    for name in EXPORTS:
+        python = globals().get(name)
+        if python is None:
+            continue
+        code = python.__code__
+        names = code.co_varnames[:code.co_argcount]
+        if names and names[-1] == "stream":
+            globals()[name] = functools.update_wrapper(_calls.bind(name, python, names), python)
+
+
+_bind_native()

@@ -1,4 +1,5 @@
-"""Builds libdllava.so (gfx950) in-tree with hipcc: one object per source, compiled in parallel, then linked."""
+"""Builds libdllava.so (gfx950) in-tree with hipcc: one object per source, compiled in parallel, then linked; and _calls.so, the
+native half of the Python binding, with the host compiler."""
 from __future__ import annotations
 
 import os
@@ -12,6 +13,8 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB_DIR = os.path.join(PKG, "lib")
 LIB = os.path.join(LIB_DIR, "libdllava.so")
+CALLS_SRC = os.path.join(PKG, "native", "calls.cpp")
+CALLS = os.path.join(PKG, "_calls.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"]
@@ -40,16 +43,44 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_calls() -> str:
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    obj = os.path.join(OBJ, "calls.o")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
+    for p in include_paths():
+        cmd += ["-isystem", p]
+    r = subprocess.run([*cmd, "-c", CALLS_SRC, "-o", obj], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed on {CALLS_SRC}:\n{r.stdout}\n{r.stderr}")
+    return obj
+
+
+def _link_calls(obj: str) -> None:
+    import torch
+    # torch's libraries are in the process when the binding loads this one; the library beside it is found by its place
+    r = subprocess.run([os.environ.get("CXX", "g++"), "-shared", obj, "-o", CALLS, "-L", LIB_DIR, "-ldllava", "-Wl,-rpath,$ORIGIN/lib",
+                        "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+
+
 def build(verbose: bool = True, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     os.makedirs(LIB_DIR, exist_ok=True)
     srcs = sources()
-    with ThreadPoolExecutor(max_workers=min(jobs, len(srcs))) as ex:
+    with ThreadPoolExecutor(max_workers=min(jobs, len(srcs) + 1)) as ex:
+        calls = ex.submit(_compile_calls)
         objs = list(ex.map(_compile, srcs))
-    cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", LIB]
+        calls = calls.result()
+    cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-Wl,-soname,libdllava.so", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    _link_calls(calls)
     if verbose:
         print(f"built {LIB} from {len(srcs)} sources")
     return LIB

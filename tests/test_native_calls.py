@@ -1,0 +1,113 @@
+"""The native forms of the binding's calls against the Python functions they stand for, without a GPU: the same refusals and the same
+library errors for the same arguments, whatever way they are given.  Every call below fails on the host, before a launch."""
+import ctypes
+import inspect
+import pickle
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2412_00876_amd.binding as b
+from paper_2412_00876_amd import _calls
+
+pytestmark = pytest.mark.skipif(torch.cuda.is_available(), reason="calls with host pointers: only where nothing can be launched")
+NAMES = [n for n in b.EXPORTS if hasattr(b, n) and "stream" in inspect.signature(getattr(b, n)).parameters]
+
+
+@pytest.fixture(autouse=True)
+def no_device(monkeypatch):
+    """Both forms believe that stream 0 is current."""
+    monkeypatch.setattr(b, "_stream", lambda stream: None if stream is None else getattr(stream, "cuda_stream", stream) or None)
+    _calls.init(b.KVCache, b.Predictor, b._check, lambda: 0, lambda: 0, lambda device: 0)
+    yield
+    _calls.init(b.KVCache, b.Predictor, b._check, torch.cuda.current_device, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+
+
+def _outcome(f, *args, **kw):
+    try:
+        return "returned", f(*args, **kw)
+    except Exception as e:  # noqa: BLE001
+        return type(e), getattr(e, "status", None), str(e)
+
+
+def _both(name, *args, **kw):
+    f = getattr(b, name)
+    native, python = _outcome(f, *args, **kw), _outcome(f.__wrapped__, *args, **kw)
+    assert native == python, (name, native, python)
+    return native
+
+
+def _cache(Dh=64, H=2, dtype=torch.bfloat16):
+    return b.KVCache(torch.zeros(4, 2, H, 16, Dh, dtype=dtype), torch.zeros(2, 2, dtype=torch.int32), torch.zeros(2, dtype=torch.int32))
+
+
+def _valid(name):
+    """Arguments of every kind in their places, and a dtype or head size that the library refuses."""
+    t = torch.zeros(64)
+    special = dict(cache=_cache(), p=b.Predictor(64, {}, []), workspace=torch.zeros(512, dtype=torch.uint8), dtype=9, scale=0.1, threshold=0.0,
+                   keep_ratio=0.5, rope_base=1e4, eps=1e-5, mode=0, act=0, B=1, M=1, H=2, Dh=64, d=64, dh=16, K=64, N=64, F=64, rows=1, sumN=1,
+                   ldx=64, ldy=64)
+    out = []
+    for q in inspect.signature(getattr(b, name)).parameters:
+        if q == "stream":
+            continue
+        out.append(t if name.endswith(("_attn", "_compact")) and q in ("K", "V") else special.get(q, t))
+    if name.startswith("dllava_decode"):
+        out[[q for q in inspect.signature(getattr(b, name)).parameters].index("threshold")] = float("nan")
+    return out
+
+
+def test_every_call_with_a_stream_is_native():
+    assert len(NAMES) == 19
+    for n in NAMES:
+        f = getattr(b, n)
+        assert type(f).__name__ == "Call" and f.__name__ == n and inspect.isfunction(f.__wrapped__)
+        assert inspect.signature(f) == inspect.signature(f.__wrapped__)
+        assert list(inspect.signature(f).parameters)[-1] == "stream"
+        assert pickle.loads(pickle.dumps(f)) is f
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_the_library_sees_the_same_arguments(name):
+    """The library's own refusal, with the offending value in its message: positional, by keyword, mixed, with an explicit stream."""
+    args = _valid(name)
+    names = list(inspect.signature(getattr(b, name)).parameters)
+    first = _both(name, *args)
+    assert first[0] is b.DllavaError, first
+    for i in range(len(args)):                    # a library check that names the value, wherever one does
+        if isinstance(args[i], int):
+            for v in (-3, 7, 1 << 33, True, np.int64(5)):
+                _both(name, *args[:i], v, *args[i + 1:])
+        if isinstance(args[i], float):
+            for v in (-1.0, 2, float("inf"), np.float64(0.25), np.float32(-2.0), 10 ** 400):
+                _both(name, *args[:i], v, *args[i + 1:])
+        if isinstance(args[i], (torch.Tensor, b.KVCache)):
+            for v in (None, args[i][1:] if isinstance(args[i], torch.Tensor) and len(args[i]) > 1 else None):
+                _both(name, *args[:i], v, *args[i + 1:])
+    assert _both(name, **dict(zip(names, args))) == first
+    assert _both(name, *args[:2], **dict(zip(names[2:], args[2:]))) == first
+    for stream in (None, 0, type("S", (), {"cuda_stream": 0})()):
+        assert _both(name, *args, stream) == first and _both(name, *args, stream=stream) == first
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_what_is_refused_is_refused_alike(name):
+    args = _valid(name)
+    names = list(inspect.signature(getattr(b, name)).parameters)
+    assert _both(name)[0] is TypeError and _both(name, *args[:-1])[0] is TypeError
+    assert _both(name, *args, None, None)[0] is TypeError and _both(name, *args, nothing=1)[0] is TypeError
+    assert _both(name, *args, **{names[0]: args[0]})[0] is TypeError
+    for i, a in enumerate(args):
+        for v in ("text", 1.5, object(), torch.zeros(4, device="meta"), torch.nn.Parameter(torch.zeros(64)), type("T", (torch.Tensor,), {})(64), [1]):
+            if isinstance(a, float) and isinstance(v, float):
+                continue
+            _both(name, *args[:i], v, *args[i + 1:])
+        if isinstance(a, int):
+            assert _both(name, *args[:i], 1.0, *args[i + 1:])[0] is ctypes.ArgumentError
+
+
+def test_without_a_device_the_python_function_says_so():
+    _calls.init(b.KVCache, b.Predictor, b._check, torch.cuda.current_device, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
+    with pytest.raises((RuntimeError, AssertionError)):
+        b.dllava_rope(torch.zeros(64), torch.zeros(1, dtype=torch.int32), 1, 1, 64, 1e4, b.BF16)
