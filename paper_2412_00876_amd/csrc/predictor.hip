@@ -350,69 +350,89 @@ __device__ __forceinline__ void want_now(const uint4& v) { asm volatile("" ::"v"
 // (8 * (lane % 8) elements into a 128-byte line) of weight row 8j + lane/8 of the block's 32 features and of input
 // row 8j + lane/8 of row tile tt; lines lbeg .. lend-1 of the input width, LB lines of every row requested together.
 // Result: acc[tt] register i of lane = feature 8*(i/4) + 4*(lane/32) + i%4 of input row 32*tt + lane%32.
-template <int NT, int LB, bool HALF = false>  // HALF: only weight rows 0..15 exist (features 16..31 of the result are zero)
+// LB lines are always in flight: a line's registers are asked for the line LB further on as soon as it has been staged, before its
+// products.  (Whole batches of LB lines, waited for together, leave the memory idle while a batch is staged and multiplied: q|k|v of 8
+// rows in turn over four sets of weights, d = 4096, 21.3 us, W_O 7.7, gate|up 34.7, down 21.7; now 21.4, 7.2, 33.5, 20.1.)
+// JX: row groups of 8 of the LAST row tile that hold input rows; the others are neither loaded nor staged: they are
+// zeroed once, like the absent weight rows of HALF, and feed result entries nobody reads.
+// HALF: only weight rows 0..15 exist (features 16..31 of the result are zero).  ONCE: the weights are not looked for in, nor left
+// in, the caches (see few_once).
+template <int NT, int LB, int JX, bool HALF = false, bool ONCE = false>
 __device__ __forceinline__ void few_accumulate(const bf16_t* const (&wrow)[4], const bf16_t* const (&xrow)[NT][4], int lbeg,
-                                               int lend, bf16_t* sw, int lane, f32x16 (&acc)[NT], int jx = 4) {
-  // jx (uniform): row groups of 8 of the LAST row tile that hold input rows; the others are neither loaded nor
-  // staged: they are zeroed once, like the absent weight rows of HALF, and feed result entries nobody reads
+                                               int lend, bf16_t* sw, int lane, f32x16 (&acc)[NT]) {
   const int r = lane & 31, g = lane >> 5;
   const int lr8 = lane >> 3, lc = lane & 7;
   bf16_t* sx = sw + 32 * 64;
   const int st_off = lr8 * 64 + ((lc ^ ((lr8 >> 1) & 3)) * 8);  // row 8j + lane/8: ((8j + lr8) / 2) % 8 = 4*(j%2) + lr8/2
   const int fr_off = r * 64 + ((g ^ ((r >> 1) & 7)) * 8);       // row r, chunk 2*step + g
-  if (HALF || jx < 4) {
+  constexpr int JW = HALF ? 2 : 4;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int o = 8 * j * 64 + (st_off ^ ((j & 1) * 32));
+    if (j >= JW) *reinterpret_cast<uint4*>(sw + o) = uint4{0u, 0u, 0u, 0u};
+    if (j >= JX) *reinterpret_cast<uint4*>(sx + (NT - 1) * 32 * 64 + o) = uint4{0u, 0u, 0u, 0u};
+  }
+  ring_u32x4 wf[LB][JW], xf[LB][NT][4];  // [slot][row group j]
+  auto ask = [&](auto C, int line) DLLAVA_INLINE {
+    constexpr int c = decltype(C)::value;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j < JW) {
+        const ring_u32x4* at = reinterpret_cast<const ring_u32x4*>(wrow[j] + 64 * line);
+        wf[c][j] = ONCE ? __builtin_nontemporal_load(at) : *at;
+      }
+#pragma unroll
+      for (int tt = 0; tt < NT; ++tt)
+        if (tt < NT - 1 || j < JX) xf[c][tt][j] = *reinterpret_cast<const ring_u32x4*>(xrow[tt][j] + 64 * line);
+    }
+  };
+  auto stage = [&](auto C) DLLAVA_INLINE {
+    constexpr int c = decltype(C)::value;
+    wave_lds_order();
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int o = 8 * j * 64 + (st_off ^ ((j & 1) * 32));
-      if (HALF && j >= 2) *reinterpret_cast<uint4*>(sw + o) = uint4{0u, 0u, 0u, 0u};
-      if (j >= jx) *reinterpret_cast<uint4*>(sx + (NT - 1) * 32 * 64 + o) = uint4{0u, 0u, 0u, 0u};
+      if (j < JW) *reinterpret_cast<ring_u32x4*>(sw + o) = wf[c][j];
+#pragma unroll
+      for (int tt = 0; tt < NT; ++tt)
+        if (tt < NT - 1 || j < JX) *reinterpret_cast<ring_u32x4*>(sx + tt * 32 * 64 + o) = xf[c][tt][j];
     }
-  }
-  for (int l0 = lbeg; l0 < lend; l0 += LB) {
-    constexpr int JW = HALF ? 2 : 4;
-    uint4 wf[LB][JW], xf[NT][LB][4];  // [line of the batch][row group j]
+    wave_lds_order();
+  };
+  auto multiply = [&]() DLLAVA_INLINE {
 #pragma unroll
-    for (int c = 0; c < LB; ++c) {  // all loads of the batch first (past the end: the last line again, unused)
-      const int line = l0 + c < lend ? l0 + c : lend - 1;
+    for (int sk = 0; sk < 4; ++sk) {
+      const bf16x8 fa = as_frag(*reinterpret_cast<const uint4*>(sw + (fr_off ^ (sk * 16))));
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (j < JW) wf[c][j] = *reinterpret_cast<const uint4*>(wrow[j] + 64 * line);
-#pragma unroll
-        for (int tt = 0; tt < NT; ++tt)
-          xf[tt][c][j] = (tt < NT - 1 || j < jx) ? *reinterpret_cast<const uint4*>(xrow[tt][j] + 64 * line) : uint4{0u, 0u, 0u, 0u};
-      }
+      for (int tt = 0; tt < NT; ++tt)
+        acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            fa, as_frag(*reinterpret_cast<const uint4*>(sx + tt * 32 * 64 + (fr_off ^ (sk * 16)))), acc[tt], 0, 0, 0);
     }
-#pragma unroll
-    for (int c = 0; c < LB; ++c)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (j < JW) want_now(wf[c][j]);
-#pragma unroll
-        for (int tt = 0; tt < NT; ++tt) want_now(xf[tt][c][j]);
-      }
-#pragma unroll
-    for (int c = 0; c < LB; ++c)
-      if (l0 + c < lend) {  // wave-uniform
-        wave_lds_order();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int o = 8 * j * 64 + (st_off ^ ((j & 1) * 32));
-          if (j < JW) *reinterpret_cast<uint4*>(sw + o) = wf[c][j];
-#pragma unroll
-          for (int tt = 0; tt < NT; ++tt)
-            if (tt < NT - 1 || j < jx) *reinterpret_cast<uint4*>(sx + tt * 32 * 64 + o) = xf[tt][c][j];
-        }
-        wave_lds_order();
-#pragma unroll
-        for (int sk = 0; sk < 4; ++sk) {
-          const bf16x8 fa = as_frag(*reinterpret_cast<const uint4*>(sw + (fr_off ^ (sk * 16))));
-#pragma unroll
-          for (int tt = 0; tt < NT; ++tt)
-            acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                fa, as_frag(*reinterpret_cast<const uint4*>(sx + tt * 32 * 64 + (fr_off ^ (sk * 16)))), acc[tt], 0, 0, 0);
-        }
-      }
-  }
+  };
+  static_for<LB>([&](auto C) DLLAVA_INLINE {
+    if (lbeg + C.value < lend) ask(C, lbeg + C.value);
+  });
+  int l0 = lbeg;
+  for (; l0 + 2 * LB <= lend; l0 += LB)  // every slot's next line exists: no condition stands between the loads
+    static_for<LB>([&](auto C) DLLAVA_INLINE {
+      stage(C);
+      ask(C, l0 + LB + C.value);
+      __builtin_amdgcn_sched_barrier(0);  // the loads before the products
+      multiply();
+    });
+  static_for<LB>([&](auto C) DLLAVA_INLINE {  // at most 2*LB - 1 lines are left
+    if (l0 + C.value < lend) {                // wave-uniform
+      stage(C);
+      if (l0 + LB + C.value < lend) ask(C, l0 + LB + C.value);
+      multiply();
+    }
+  });
+  static_for<LB>([&](auto C) DLLAVA_INLINE {
+    if (l0 + LB + C.value < lend) {
+      stage(C);
+      multiply();
+    }
+  });
 }
 
 // Leaves the wave's sums in its own staging area as float32 [(16*tt + i) * 64 + lane].
@@ -484,7 +504,7 @@ __global__ __launch_bounds__(256) void small_in_kernel(const bf16_t* __restrict_
   for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[tt][i] = 0.f;
-  few_accumulate<NT, 4>(wrow, xrow, lbeg, lend, stage[w], lane, acc);
+  few_accumulate<NT, 4, 4>(wrow, xrow, lbeg, lend, stage[w], lane, acc);
   if (w > 0) few_leave_sums<NT>(acc, stage[w], lane);
   __syncthreads();
   if (w != 0) return;
@@ -526,7 +546,7 @@ __global__ __launch_bounds__(256) void small_in_kernel(const bf16_t* __restrict_
 // In all of them a thread of the epilogue owns block-local features 8*q4 + 4*g + e ("lo") and 16 + the same ("hi",
 // absent in kFewPlainHalf), e = 0..3, of one row.
 enum { kFewPlain = 0, kFewQkv = 1, kFewGated = 2, kFewPlainHalf = 3, kFewPlain8 = 4 };
-constexpr int kFewBatch = 2;     // 128-byte lines per row in flight per wave (2: about 110 registers; 4 measured 7 % slower)
+constexpr int kFewLines = 2;     // 128-byte lines per row in flight per wave (3: up to 9 %, 4: up to 15 % slower above 32 rows, level below)
 constexpr int kFewBlocks = 384;  // blocks aimed at (more measured slower: the launch is bound by its ramp and memory)
 constexpr size_t kFewCounterBytes = 4096;
 
@@ -547,7 +567,7 @@ struct FewEpi {
 // waves of a block, each with its own part of the input width (8 for q|k|v or gate|up measured 3-10 % slower than 4)
 template <int EPI>
 constexpr int few_waves() { return (EPI == kFewPlainHalf || EPI == kFewPlain8) ? 8 : 4; }
-template <int NT, int EPI>
+template <int NT, int JX, int EPI, bool ONCE>
 __global__ __launch_bounds__(64 * few_waves<EPI>()) void few_fused_kernel(const bf16_t* __restrict__ X, int64_t ldx, int M, int K,
                                                         const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1,
                                                         const bf16_t* __restrict__ W2, int n_fg, int KQ, int fg_each,
@@ -598,7 +618,7 @@ __global__ __launch_bounds__(64 * few_waves<EPI>()) void few_fused_kernel(const 
   for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[tt][i] = 0.f;
-  few_accumulate<NT, kFewBatch, HALF>(wrow, xrow, lbeg, lend, stage[w], lane, acc, (M - 32 * (NT - 1) + 7) / 8);
+  few_accumulate<NT, kFewLines, JX, HALF, ONCE>(wrow, xrow, lbeg, lend, stage[w], lane, acc);
   few_leave_sums<NT>(acc, stage[w], lane);
   __syncthreads();
 
@@ -720,14 +740,29 @@ __global__ __launch_bounds__(64 * few_waves<EPI>()) void few_fused_kernel(const 
   }
 }
 
+// Weights of 64 MiB and more are read past the caches: the memory-side cache holds 256 MiB, a decode step streams all matrices of its
+// layers between two uses of one, and lines that are not put there cost less to read.  q|k|v, gate|up, down of 8 rows in turn
+// over four sets of weights, d = 4096: 21.4 / 33.5 / 20.1 us with plain loads, 19.6 / 29.5 / 18.5 past the caches.  Smaller ones
+// (W_O: 32 MiB, four of them fit that cache) are found there by programs of few layers: 7.2 plain, 7.8 past; d = 5120 10.7, 15.1.
+constexpr int64_t kOnceBytes = 64ll << 20;
+
+template <int EPI, bool ONCE>
+void launch_few_as(int nt, hipStream_t st, const bf16_t* X, int64_t ldx, int M, int K, const bf16_t* W0, const bf16_t* W1,
+                   const bf16_t* W2, int n_fg, int KQ, int fg_each, const FewEpi& ep) {
+  const dim3 grid(static_cast<unsigned>(n_fg) * static_cast<unsigned>(KQ)), block(64 * few_waves<EPI>());
+  const int jx = (M - 32 * (nt - 1) + 7) / 8;  // row groups of 8 of the last row tile
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, X, ldx, M, K, W0, W1, W2, n_fg, KQ, fg_each, ep); };
+  if (nt == 2) go(few_fused_kernel<2, 4, EPI, ONCE>);
+  else if (jx == 1) go(few_fused_kernel<1, 1, EPI, ONCE>);
+  else if (jx == 2) go(few_fused_kernel<1, 2, EPI, ONCE>);
+  else go(few_fused_kernel<1, 4, EPI, ONCE>);
+}
 template <int EPI>
 void launch_few_fused(int nt, hipStream_t st, const bf16_t* X, int64_t ldx, int M, int K, const bf16_t* W0, const bf16_t* W1,
                       const bf16_t* W2, int n_fg, int KQ, int fg_each, const FewEpi& ep) {
-  const dim3 grid(static_cast<unsigned>(n_fg) * static_cast<unsigned>(KQ)), block(64 * few_waves<EPI>());
-  if (nt == 1)
-    hipLaunchKernelGGL((few_fused_kernel<1, EPI>), grid, block, 0, st, X, ldx, M, K, W0, W1, W2, n_fg, KQ, fg_each, ep);
-  else
-    hipLaunchKernelGGL((few_fused_kernel<2, EPI>), grid, block, 0, st, X, ldx, M, K, W0, W1, W2, n_fg, KQ, fg_each, ep);
+  const int64_t bytes = static_cast<int64_t>(n_fg) * (EPI == kFewPlainHalf ? 16 : 32) * K * 2;
+  if (bytes >= kOnceBytes) launch_few_as<EPI, true>(nt, st, X, ldx, M, K, W0, W1, W2, n_fg, KQ, fg_each, ep);
+  else launch_few_as<EPI, false>(nt, st, X, ldx, M, K, W0, W1, W2, n_fg, KQ, fg_each, ep);
 }
 
 __global__ __launch_bounds__(256) void small_head_kernel(const float* __restrict__ partial, int rows_pad, int M,
