@@ -322,6 +322,26 @@ struct GatherArgs {
   double keep_ratio;
 };
 
+// Inputs of 256 MiB and more -- the size of the memory-side cache -- are read past the caches (kernels of their own: a test for it in
+// the copy loop costs the small calls 0.5 us): each row is read once, nothing of
+// them is left there from the launch that wrote them, and lines that are not put there leave room for the outputs, which the next
+// launches read.  Compaction / the same with attention and RMSNorm of its outputs behind it, 16 sequences of 7B (354 MB of inputs):
+// 60.8 -> 58.9 / 116 -> 112 us; 32 sequences 115 -> 88, 8 of five-tile pictures 78 -> 69, threshold mode 96 -> 75.  Smaller
+// inputs are often still cached (8 sequences, 184 MB, again and again: 26.5 plain, 29.4 past the caches).  Stores past the caches were
+// faster here (55.2) and slower together with what reads the outputs (119).
+constexpr int64_t kOnceBytes = 256ll << 20;
+bool read_once(const GatherArgs& a, int64_t sumN) {
+  const int64_t chunks = (a.hidden ? a.hidden_chunks : 0) + (a.Q ? a.q_chunks : 0) + (a.K ? 2 * a.kv_chunks : 0);
+  return sumN * chunks * 16 >= kOnceBytes;
+}
+template <bool ONCE>
+__device__ __forceinline__ uint4 read_piece(const uint4* p) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  if constexpr (!ONCE) return *p;
+  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return uint4{v[0], v[1], v[2], v[3]};
+}
+
 // 16 readable bytes: the source of the (unused) clamped loads of a tensor that is not being moved
 static __device__ __attribute__((aligned(16))) uint32_t kGatherPad[4] = {0u, 0u, 0u, 0u};
 
@@ -329,8 +349,10 @@ static __device__ __attribute__((aligned(16))) uint32_t kGatherPad[4] = {0u, 0u,
 // copies (total, binary search for the sequence, kept position) is paid once per row, and every 16-byte load of
 // a trip -- two per thread and tensor, index clamped so that none sits under a condition -- is in flight
 // before the first store.
+template <bool ONCE>
 __device__ __forceinline__ void copy_row(const GatherArgs& a, int b, int pos, size_t src, int j);
 
+template <bool ONCE>
 __global__ __launch_bounds__(kThreads) void gather_kernel(GatherArgs a) {
   const int j = blockIdx.x, tid = threadIdx.x;
   const int total = a.out_off[a.B];
@@ -353,10 +375,11 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(GatherArgs a) {
   const int rel = a.given ? a.kept_idx[j] : a.ws_kept[static_cast<size_t>(s0) + pos];
   const size_t src = static_cast<size_t>(s0) + rel;
   if (tid == 0 && !a.given) a.kept_idx[j] = rel;
-  copy_row(a, b, pos, src, j);
+  copy_row<ONCE>(a, b, pos, src, j);
 }
 
 // The block moves source row `src` (kept row `pos` of sequence b) to compacted row j and its page slot.
+template <bool ONCE>
 __device__ __forceinline__ void copy_row(const GatherArgs& a, int b, int pos, size_t src, int j) {
   const int tid = threadIdx.x;
   const bool do_h = a.hidden != nullptr, do_q = a.Q != nullptr;
@@ -382,10 +405,10 @@ __device__ __forceinline__ void copy_row(const GatherArgs& a, int b, int pos, si
   for (int64_t c0 = tid; c0 < nmax; c0 += 2 * kThreads) {
     const int64_t c1 = c0 + kThreads;
 #define DLLAVA_CLAMP(c, n) ((n) > 0 ? ((c) < (n) ? (c) : (n)-1) : 0)
-    const uint4 h0 = in_h[DLLAVA_CLAMP(c0, nh)], h1 = in_h[DLLAVA_CLAMP(c1, nh)];
-    const uint4 q0 = in_q[DLLAVA_CLAMP(c0, nq)], q1 = in_q[DLLAVA_CLAMP(c1, nq)];
-    const uint4 k0 = in_k[DLLAVA_CLAMP(c0, nkv)], k1 = in_k[DLLAVA_CLAMP(c1, nkv)];
-    const uint4 v0 = in_v[DLLAVA_CLAMP(c0, nkv)], v1 = in_v[DLLAVA_CLAMP(c1, nkv)];
+    const uint4 h0 = read_piece<ONCE>(in_h + DLLAVA_CLAMP(c0, nh)), h1 = read_piece<ONCE>(in_h + DLLAVA_CLAMP(c1, nh));
+    const uint4 q0 = read_piece<ONCE>(in_q + DLLAVA_CLAMP(c0, nq)), q1 = read_piece<ONCE>(in_q + DLLAVA_CLAMP(c1, nq));
+    const uint4 k0 = read_piece<ONCE>(in_k + DLLAVA_CLAMP(c0, nkv)), k1 = read_piece<ONCE>(in_k + DLLAVA_CLAMP(c1, nkv));
+    const uint4 v0 = read_piece<ONCE>(in_v + DLLAVA_CLAMP(c0, nkv)), v1 = read_piece<ONCE>(in_v + DLLAVA_CLAMP(c1, nkv));
 #undef DLLAVA_CLAMP
     if (c0 < nh) out_h[c0] = h0;
     if (c1 < nh) out_h[c1] = h1;
@@ -642,6 +665,7 @@ constexpr int kSpinLimit = 1 << 18;  // polls before it gives up (over a tenth o
 // and the last of those clears claim[b], ready[b] and done[b].  All of these words sit at fixed offsets at the
 // start of the workspace, whatever the call's shape: a workspace serves calls of different shapes in turn, and a
 // word that one shape expects to be zero must never lie where another shape keeps data.
+template <bool ONCE>
 __global__ __launch_bounds__(kThreads) void select_compact_topk_kernel(SelectArgs a, GatherArgs g, int rest_blocks) {
   union Shared {
     TopkShared sel;
@@ -673,7 +697,7 @@ __global__ __launch_bounds__(kThreads) void select_compact_topk_kernel(SelectArg
       const RowPlace p = place_row<0>(S.lay, a.B, r);
       const int rel = p.pos < S.lay.v0[p.b] ? p.pos : p.pos - S.lay.k[p.b] + S.lay.n[p.b];
       if (tid == 0) g.kept_idx[p.j] = rel;
-      copy_row(g, p.b, p.pos, static_cast<size_t>(p.s0) + rel, p.j);
+      copy_row<ONCE>(g, p.b, p.pos, static_cast<size_t>(p.s0) + rel, p.j);
     }
     return;
   } else {
@@ -718,7 +742,7 @@ __global__ __launch_bounds__(kThreads) void select_compact_topk_kernel(SelectArg
     const int rel = __hip_atomic_load(&a.ws_kept[static_cast<size_t>(place.s0) + place.pos], __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
     if (tid == 0) g.kept_idx[place.j] = rel;
-    copy_row(g, b, place.pos, static_cast<size_t>(place.s0) + rel, place.j);
+    copy_row<ONCE>(g, b, place.pos, static_cast<size_t>(place.s0) + rel, place.j);
   }
   // (only this thread read the hand-off words, before the barrier above; the kept positions themselves stay)
   if (tid == 0) {
@@ -836,18 +860,19 @@ extern "C" int dllava_select_compact(const float* logits, int32_t B, const int32
   }
   ga.Q = static_cast<const uint4*>(Q); ga.Q_out = static_cast<uint4*>(Q_out);
   ga.K = static_cast<const uint4*>(K); ga.V = static_cast<const uint4*>(V);
+  const bool once = read_once(ga, sumN);
   if (analytic) {
     // rows outside the spans number at most sumN (their blocks loop: the grid is not sized for the worst case); the
     // kept vision rows number sum of floor(ratio * n) <= ratio * sumN
     const int64_t rest_blocks = sumN < kRestBlocks ? sumN : kRestBlocks;
     int64_t vis_blocks = static_cast<int64_t>(ceil(keep_ratio * static_cast<double>(sumN))) + 1;
     if (vis_blocks > sumN) vis_blocks = sumN;
-    hipLaunchKernelGGL(select_compact_topk_kernel, dim3(static_cast<unsigned>(B + rest_blocks + vis_blocks)),
-                       dim3(kThreads), 0, st, sa, ga, static_cast<int>(rest_blocks));
+    hipLaunchKernelGGL(once ? select_compact_topk_kernel<true> : select_compact_topk_kernel<false>,
+                       dim3(static_cast<unsigned>(B + rest_blocks + vis_blocks)), dim3(kThreads), 0, st, sa, ga, static_cast<int>(rest_blocks));
     DLLAVA_CHECK_LAUNCH("select_compact_topk_kernel");
     return DLLAVA_OK;
   }
-  hipLaunchKernelGGL(gather_kernel, dim3(static_cast<unsigned>(sumN)), dim3(kThreads), 0, st, ga);
+  hipLaunchKernelGGL(once ? gather_kernel<true> : gather_kernel<false>, dim3(static_cast<unsigned>(sumN)), dim3(kThreads), 0, st, ga);
   DLLAVA_CHECK_LAUNCH("gather_kernel");
   return DLLAVA_OK;
 }
@@ -895,8 +920,9 @@ extern "C" int dllava_compact(int32_t B, const int32_t* seq_off, const int32_t* 
   }
   ga.Q = static_cast<const uint4*>(Q); ga.Q_out = static_cast<uint4*>(Q_out);
   ga.K = static_cast<const uint4*>(K); ga.V = static_cast<const uint4*>(V);
-  hipLaunchKernelGGL(gather_kernel, dim3(static_cast<unsigned>(sumN)), dim3(kThreads), 0, static_cast<hipStream_t>(stream),
-                     ga);
+  const bool once = read_once(ga, sumN);
+  hipLaunchKernelGGL(once ? gather_kernel<true> : gather_kernel<false>, dim3(static_cast<unsigned>(sumN)), dim3(kThreads), 0,
+                     static_cast<hipStream_t>(stream), ga);
   DLLAVA_CHECK_LAUNCH("gather_kernel");
   return DLLAVA_OK;
 }
