@@ -1,4 +1,5 @@
-// Matrix-core causal attention over the reduced prefill set (Eq. 1 of the paper applied to S^{P*}), bfloat16.
+// Matrix-core causal attention over the reduced prefill set (Eq. 1 of the paper applied to S^{P*}), bfloat16: the kernel for short
+// sequences, and the rule that sends long ones to the software-pipelined kernel of prefill_tiles.hip (`pipelined` below).
 //
 // One block serves (sequence, head, tile of NWQ*32 compacted query rows); each of its NWQ waves owns 32
 // queries and walks the key tiles (32 keys) up to its diagonal.  K and V tiles go from global memory straight
