@@ -161,7 +161,7 @@ struct State {
   u32x4 k[DH / 16];         // K fragments of a tile [16-dim step]
   u32x2 v[DH / 32][2][2];   // V fragments of a tile [32-dim block][16-key half]
   float m_ref, l_run;       // reference of the exponentials (in powers of two), sum of this lane's probabilities
-  float thr;                // raw score above which the reference moves; while it moves, what the outputs are multiplied with
+  float thr;                // scaled score above which the reference moves; while it moves, what the outputs are multiplied with
 };
 struct Probs {
   u32x4 hi[2], lo[2];       // [16-key half]: B operands of the second product
@@ -196,23 +196,23 @@ constexpr Places make_places(int first, int all, int half0, int half1) {
 // A query's maximum over its two lanes becomes the reference of the exponentials; T.thr holds the outputs' factor until
 // reference_moved().
 template <int DH>
-__device__ __forceinline__ void move_reference(State<DH>& T, float x, float scale_log2) {
-  const float m_t = max2(x, __shfl_xor(x, 32, kWave)) * scale_log2;
+__device__ __forceinline__ void move_reference(State<DH>& T, float x) {  // x: the lane's largest scaled score
+  const float m_t = max2(x, __shfl_xor(x, 32, kWave));
   const float m_new = max2(T.m_ref, m_t);
   T.thr = __builtin_amdgcn_exp2f(T.m_ref - m_new);
   T.m_ref = m_new;
   T.l_run *= T.thr;
 }
 template <int DH>
-__device__ __forceinline__ void reference_moved(State<DH>& T, float scale_log2) { T.thr = (T.m_ref + kSlack) / scale_log2; }
+__device__ __forceinline__ void reference_moved(State<DH>& T) { T.thr = T.m_ref + kSlack; }
 __device__ __forceinline__ float max16(const f32x16& S) {
   const float x = max3(max3(S[0], S[1], S[2]), max3(S[3], S[4], S[5]), S[6]), y = max3(max3(S[7], S[8], S[9]), max3(S[10], S[11], S[12]), S[13]);
   return max3(max2(x, y), S[14], S[15]);
 }
 template <int DH>
 __device__ __forceinline__ void first_reference(State<DH>& T, const f32x16& S, float scale_log2) {
-  move_reference(T, max16(S), scale_log2);
-  reference_moved(T, scale_log2);
+  move_reference(T, max16(S) * scale_log2);
+  reference_moved(T);
 }
 
 // Tile t of a wave: the softmax of its scores S into P, beside the products P(t-1) V (PV) and K Q of the next tile (QK, into
@@ -307,13 +307,15 @@ __device__ __forceinline__ void step(State<DH>& T, f32x16& S, f32x16& Sn, Probs&
     });
   }
   // The two lanes of a query look at their own scores only; the maximum itself is needed when one of them is past the threshold.
+  // (Scaled before it is compared, as in the kernel for short sequences: the reference then moves at the same scores there and here.)
+  x *= scale_log2;
   bool moved = false;
   if (__any(x > T.thr)) {
-    move_reference(T, x, scale_log2);
+    move_reference(T, x);
     moved = true;
   }
   constexpr Places places = make_places(kHead, kNM, kNP / 2 + 1, kNP + 1);
-  float p0[8], p1[8], a0[8], a1[8];
+  float p0[8], p1[8], a0[8], a1[8], sum;
   auto op = [&](auto Oi) DLLAVA_INLINE {
     constexpr int st = places.stage[decltype(Oi)::value], p = places.pair[decltype(Oi)::value];
     if constexpr (st == 0) {
@@ -333,12 +335,15 @@ __device__ __forceinline__ void step(State<DH>& T, f32x16& S, f32x16& Sn, Probs&
       here(a0[p]), here(a1[p]);
     } else {
       const float r0 = p0[p] - a0[p], r1 = p1[p] - a1[p];
-      T.l_run += p0[p];
+      // the tile's probabilities are added up among themselves, pair by pair, before they join the sum of the tiles: a long row of
+      // single additions to that sum loses more of it, and these are the sums of the kernel for short sequences, bit for bit
+      const float pair = p0[p] + p1[p];
       uint32_t l = __builtin_amdgcn_perm(__float_as_uint(r1), __float_as_uint(r0), 0x07060302u);
       here(l);
       P.lo[p / 4][p % 4] = l;
-      T.l_run += p1[p];
-      here(T.l_run);
+      sum = p == 0 ? pair : sum + pair;
+      if constexpr (p == 7) T.l_run += sum;
+      here(p == 7 ? T.l_run : sum);
     }
   };
   static_for<(kNM - kHead > 0 ? kNM - kHead : 1)>([&](auto Ri) DLLAVA_INLINE {
@@ -363,7 +368,7 @@ __device__ __forceinline__ void step(State<DH>& T, f32x16& S, f32x16& Sn, Probs&
         tie_o(T.o[I.value]);
       });
     }
-    reference_moved(T, scale_log2);
+    reference_moved(T);
   }
   lds_wait();
   static_for<4 * kNB>([&](auto I) DLLAVA_INLINE { tie2(T.v[I.value % kNB][(I.value / (2 * kNB))][(I.value / kNB) % 2]); });
@@ -742,7 +747,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
         __builtin_amdgcn_sched_barrier(0);
       });
       T.m_ref = -1e30f;  // finite floor, not -inf: a query that sees no key of the first tiles keeps its state
-      T.thr = -INFINITY;
+      T.thr = T.m_ref + kSlack;
       T.l_run = 0.f;
     }
     const Item next = locate(item_of(++jC));

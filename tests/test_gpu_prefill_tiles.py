@@ -17,10 +17,10 @@ from synth import rng
 from synth import workloads as W
 from tests.test_gpu_parity import _assert_out_close
 
-TILES = 16      # added to the waves of LAUNCH_PREFILL_WAVES: this kernel whatever the size
+TILES, SHORT = 16, 32      # added to the waves of LAUNCH_PREFILL_WAVES: this kernel, the one for short sequences, whatever the size
 
 
-def _run(q, k, v, lens, H, Dh, form, waves, blocks, scale):
+def _run(q, k, v, lens, H, Dh, form, waves, blocks, scale, kernel=TILES):
     """q, k, v: bfloat16 bit patterns as the oracle takes them.  Page slots past a sequence's end hold NaN."""
     from tests import harness as h
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
@@ -39,7 +39,7 @@ def _run(q, k, v, lens, H, Dh, form, waves, blocks, scale):
                 pages[pg, 1, :, :m] = vd[off[b] + j:off[b] + j + m].transpose(0, 1)
         cache, kd, vd = P.KVCache(pages, table, torch.tensor(lens, dtype=torch.int32, device=h.DEV)), None, None
     out = []
-    P.dllava_set_launch_override(P.LAUNCH_PREFILL_WAVES, TILES + waves)
+    P.dllava_set_launch_override(P.LAUNCH_PREFILL_WAVES, kernel + waves)
     P.dllava_set_launch_override(P.LAUNCH_PREFILL_BLOCKS, blocks)
     try:
         for _ in range(2):
@@ -82,6 +82,23 @@ def test_tile_edges(lens, waves, blocks, Dh, form):
     q, k, v = _qkv(80 + Dh, rows, H, Dh)
     O, off = _run(q, k, v, lens, H, Dh, form, waves, blocks, 1.0 / math.sqrt(Dh))
     _assert_out_close(O, _reference(q, k, v, off, H, Dh, form, 1.0 / math.sqrt(Dh)), "bf16", f"{form} {lens}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", ["paged", "rows", "full"])
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("spread", [1.0, 6.0])
+@pytest.mark.parametrize("lens", [[1, 31, 33, 64, 97], [160, 257, 385], [1500, 700]])
+def test_the_bits_of_the_kernel_for_short_sequences(lens, spread, Dh, form):
+    """The two kernels differ in when they do things, not in what they add up in which order: a sequence's outputs do not depend on the
+    length from which the library takes the other one.  spread 6: scores of +-36 powers of two or so, the reference moves often."""
+    H, rows = 2, int(sum(lens))
+    q, k, v = _qkv(120 + Dh, rows, H, Dh)
+    q = W.store(R.widen(q, "bf16") * spread, "bf16")
+    for waves in (1, 2, 4):
+        here, _ = _run(q, k, v, lens, H, Dh, form, waves, 0, 1.0 / math.sqrt(Dh))
+        there, _ = _run(q, k, v, lens, H, Dh, form, waves, 0, 1.0 / math.sqrt(Dh), SHORT)
+        assert np.array_equal(here, there), (waves, int((here != there).sum()), here.size)
 
 
 @pytest.mark.gpu
