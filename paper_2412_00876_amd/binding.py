@@ -386,7 +386,9 @@ def _bind_native() -> None:
         code = python.__code__
         names = code.co_varnames[:code.co_argcount]
         if names and names[-1] == "stream":
-            globals()[name] = functools.update_wrapper(_calls.bind(name, python, names), python)
+            function = getattr(_lib, name)
+            native = _calls.bind(name, python, names, function, C.cast(function, C.c_void_p).value)
+            globals()[name] = functools.update_wrapper(native, python)
 
 
 _bind_native()

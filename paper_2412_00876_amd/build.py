@@ -61,8 +61,8 @@ def _compile_calls() -> str:
 
 def _link_calls(obj: str) -> None:
     import torch
-    # torch's libraries are in the process when the binding loads this one; the library beside it is found by its place
-    r = subprocess.run([os.environ.get("CXX", "g++"), "-shared", obj, "-o", CALLS, "-L", LIB_DIR, "-ldllava", "-Wl,-rpath,$ORIGIN/lib",
+    # torch's libraries are in the process when the binding loads this one, and the binding hands it the library's functions
+    r = subprocess.run([os.environ.get("CXX", "g++"), "-shared", obj, "-o", CALLS,
                         "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"], capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
@@ -76,7 +76,7 @@ def build(verbose: bool = True, jobs: int = 8) -> str:
         calls = ex.submit(_compile_calls)
         objs = list(ex.map(_compile, srcs))
         calls = calls.result()
-    cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-Wl,-soname,libdllava.so", *objs, "-o", LIB]
+    cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")

@@ -6,7 +6,9 @@
 //
 // Each entry point is a callable that holds the Python function of the same name.  What it does not convert itself -- a number, a
 // torch.Tensor or Parameter, the binding's own descriptors, None -- or an argument that is missing, it leaves to that function,
-// called with the very same arguments: what is accepted, refused and raised is decided there.
+// called with the very same arguments: what is accepted, refused and raised is decided there.  The C functions are those of the
+// library that the Python function calls, by their addresses in it; when that function has been given another library
+// (binding._lib), the call is left to it, and another binding._stream is asked for the stream.
 #include <Python.h>
 #include <pthread.h>
 
@@ -25,7 +27,8 @@ namespace {
 constexpr size_t kMaxArgs = 32;
 
 // Set once by binding.py (init): its classes, its error check, and where torch keeps the current stream.
-PyObject *g_cache_type, *g_predictor_type, *g_check, *g_current_device, *g_get_device, *g_raw_stream, *g_c;
+PyObject *g_cache_type, *g_predictor_type, *g_check, *g_current_device, *g_get_device, *g_raw_stream;
+PyObject *g_c, *g_lib_name, *g_stream_name, *g_check_name;  // "c", "_lib", "_stream", "_check"
 bool g_device_ready = false;  // torch has initialised the device in this process
 
 // The C structure behind a descriptor object (its ctypes field c), held for the length of a call.
@@ -79,8 +82,32 @@ struct Slot<const dllava_kv_cache*> : DescriptorSlot<dllava_kv_cache, &g_cache_t
 template <>
 struct Slot<const dllava_predictor*> : DescriptorSlot<dllava_predictor, &g_predictor_type> {};
 
+// The callable, and what of the binding its C function was found by.
+struct Kind;
+struct Call {
+  PyObject_HEAD
+  vectorcallfunc vectorcall;
+  const Kind* kind;
+  PyObject* python;      // the function of the same name
+  PyObject* names;       // its parameters, in order; the last one is the stream and defaults to None
+  PyObject* name;
+  PyObject* globals;     // the binding
+  PyObject* c_function;  // _lib.<name>
+  void (*address)();     // where it points
+  PyObject* stream;      // the binding's _stream
+  PyObject* dict;
+};
+
 // torch's current stream of the current device, as binding._stream finds it
-bool current_stream(void*& stream) {
+bool current_stream(const Call& c, void*& stream) {
+  PyObject* const f = PyDict_GetItemWithError(c.globals, g_stream_name);
+  if (f != c.stream) {  // replaced
+    PyObject* r = f ? PyObject_CallOneArg(f, Py_None) : nullptr;
+    const bool ok = r && (r == Py_None || PyLong_Check(r));
+    if (ok) stream = r == Py_None ? nullptr : PyLong_AsVoidPtr(r);
+    Py_XDECREF(r);
+    return ok && !PyErr_Occurred();
+  }
   PyObject* dev = g_device_ready ? PyObject_CallNoArgs(g_get_device) : PyObject_CallNoArgs(g_current_device);
   if (!dev) return false;
   g_device_ready = true;
@@ -94,11 +121,11 @@ bool current_stream(void*& stream) {
 
 enum class Outcome { kDone, kFallback };
 
-// The C function F(A...): its last argument is the stream; a size_t is the size of the buffer before it.
-template <auto F>
+// A C function of type int(A...): its last argument is the stream; a size_t is the size of the buffer before it.
+template <typename F>
 struct Entry;
-template <typename... A, int (*F)(A...)>
-struct Entry<F> {
+template <typename... A>
+struct Entry<int (*)(A...)> {
   static constexpr size_t N = sizeof...(A);
   using Slots = std::tuple<Slot<std::remove_cv_t<A>>...>;
 
@@ -119,17 +146,18 @@ struct Entry<F> {
     }
   }
   // no_cache: the function may be called without a cache
-  static Outcome call(PyObject* const* args, bool no_cache, int& rc) {
+  static Outcome call(const Call& c, PyObject* const* args, bool no_cache, int& rc) {
     Slots s;
-    return all(s, args, no_cache, rc, std::make_index_sequence<N - 1>{}, std::make_index_sequence<N>{});
+    return all(c, s, args, no_cache, rc, std::make_index_sequence<N - 1>{}, std::make_index_sequence<N>{});
   }
   template <size_t... I, size_t... J>
-  static Outcome all(Slots& s, PyObject* const* args, bool no_cache, int& rc, std::index_sequence<I...>, std::index_sequence<J...>) {
+  static Outcome all(const Call& c, Slots& s, PyObject* const* args, bool no_cache, int& rc, std::index_sequence<I...>, std::index_sequence<J...>) {
     size_t at = 0;
     if (!(take<I>(s, args, at, no_cache) && ...)) return Outcome::kFallback;
-    if (args[at] != Py_None || !current_stream(std::get<N - 1>(s).value)) return Outcome::kFallback;
+    if (args[at] != Py_None || !current_stream(c, std::get<N - 1>(s).value)) return Outcome::kFallback;
+    const auto f = reinterpret_cast<int (*)(A...)>(c.address);
     Py_BEGIN_ALLOW_THREADS
-    rc = F(std::get<J>(s).value...);
+    [&]() noexcept { rc = f(std::get<J>(s).value...); }();
     Py_END_ALLOW_THREADS
     return Outcome::kDone;
   }
@@ -140,50 +168,50 @@ struct Kind {
   const char* name;
   size_t n_args;
   bool no_cache;
-  Outcome (*call)(PyObject* const*, bool, int&);
+  Outcome (*call)(const Call&, PyObject* const*, bool, int&);
 };
-template <auto F>
+template <typename F>
 constexpr Kind kind(const char* name, bool no_cache = false) {
   static_assert(Entry<F>::python_args() <= kMaxArgs);
   return {name, Entry<F>::python_args(), no_cache, Entry<F>::call};
 }
 const Kind kKinds[] = {
-    kind<dllava_score>("dllava_score"),
-    kind<dllava_select_compact>("dllava_select_compact", true),
-    kind<dllava_compact>("dllava_compact", true),
-    kind<dllava_prefill_attn>("dllava_prefill_attn", true),
-    kind<dllava_decode_attn_append>("dllava_decode_attn_append"),
-    kind<dllava_decode_attn_append_static>("dllava_decode_attn_append_static"),
-    kind<dllava_decode_step>("dllava_decode_step"),
-    kind<dllava_decode_commit>("dllava_decode_commit"),
-    kind<dllava_qkv_project>("dllava_qkv_project"),
-    kind<dllava_predict>("dllava_predict"),
-    kind<dllava_linear>("dllava_linear"),
-    kind<dllava_layer_norm>("dllava_layer_norm"),
-    kind<dllava_rms_norm>("dllava_rms_norm"),
-    kind<dllava_span_attn>("dllava_span_attn"),
-    kind<dllava_masked_attn>("dllava_masked_attn"),
-    kind<dllava_linear_few>("dllava_linear_few"),
-    kind<dllava_rope>("dllava_rope"),
-    kind<dllava_qkv_few>("dllava_qkv_few"),
-    kind<dllava_gated_few>("dllava_gated_few"),
+    kind<decltype(&dllava_score)>("dllava_score"),
+    kind<decltype(&dllava_select_compact)>("dllava_select_compact", true),
+    kind<decltype(&dllava_compact)>("dllava_compact", true),
+    kind<decltype(&dllava_prefill_attn)>("dllava_prefill_attn", true),
+    kind<decltype(&dllava_decode_attn_append)>("dllava_decode_attn_append"),
+    kind<decltype(&dllava_decode_attn_append_static)>("dllava_decode_attn_append_static"),
+    kind<decltype(&dllava_decode_step)>("dllava_decode_step"),
+    kind<decltype(&dllava_decode_commit)>("dllava_decode_commit"),
+    kind<decltype(&dllava_qkv_project)>("dllava_qkv_project"),
+    kind<decltype(&dllava_predict)>("dllava_predict"),
+    kind<decltype(&dllava_linear)>("dllava_linear"),
+    kind<decltype(&dllava_layer_norm)>("dllava_layer_norm"),
+    kind<decltype(&dllava_rms_norm)>("dllava_rms_norm"),
+    kind<decltype(&dllava_span_attn)>("dllava_span_attn"),
+    kind<decltype(&dllava_masked_attn)>("dllava_masked_attn"),
+    kind<decltype(&dllava_linear_few)>("dllava_linear_few"),
+    kind<decltype(&dllava_rope)>("dllava_rope"),
+    kind<decltype(&dllava_qkv_few)>("dllava_qkv_few"),
+    kind<decltype(&dllava_gated_few)>("dllava_gated_few"),
 };
 
 // ---- the callable -----------------------------------------------------------------------------------------------------------
-struct Call {
-  PyObject_HEAD
-  vectorcallfunc vectorcall;
-  const Kind* kind;
-  PyObject* python;  // the function of the same name
-  PyObject* names;   // its parameters, in order; the last one is the stream and defaults to None
-  PyObject* dict;
-};
+// the Python function would call the C function of this callable
+bool same_library(const Call& c) {
+  PyObject* const lib = PyDict_GetItemWithError(c.globals, g_lib_name);
+  PyObject* const f = lib ? PyObject_GetAttr(lib, c.name) : nullptr;
+  Py_XDECREF(f);  // compared only
+  if (!f) PyErr_Clear();
+  return f == c.c_function;
+}
 
 PyObject* call_vector(PyObject* self, PyObject* const* args, size_t nargsf, PyObject* kwnames) {
   Call* c = reinterpret_cast<Call*>(self);
   const size_t n = PyVectorcall_NARGS(nargsf), want = c->kind->n_args, nkw = kwnames ? PyTuple_GET_SIZE(kwnames) : 0;
   PyObject* all[kMaxArgs];
-  bool ok = n <= want && !at::impl::PythonTorchFunctionTLS::stack_len();
+  bool ok = n <= want && !at::impl::PythonTorchFunctionTLS::stack_len() && same_library(*c);
   if (ok) {
     memcpy(all, args, n * sizeof(PyObject*));
     for (size_t i = n; i < want; ++i) all[i] = nullptr;
@@ -201,14 +229,15 @@ PyObject* call_vector(PyObject* self, PyObject* const* args, size_t nargsf, PyOb
     int rc = 0;
     Outcome o = Outcome::kFallback;
     try {
-      o = c->kind->call(all, c->kind->no_cache, rc);
+      o = c->kind->call(*c, all, c->kind->no_cache, rc);
     } catch (const std::exception&) {  // a tensor without memory of its own: torch's own message comes from the Python function
     }
     if (o == Outcome::kDone) {
       if (__builtin_expect(rc != 0, 0)) {
         PyObject* code = PyLong_FromLong(rc);
         if (!code) return nullptr;
-        PyObject* r = PyObject_CallOneArg(g_check, code);  // raises
+        PyObject* const check = PyDict_GetItemWithError(c->globals, g_check_name);
+        PyObject* r = PyObject_CallOneArg(check ? check : g_check, code);  // raises
         Py_DECREF(code);
         return r;
       }
@@ -221,16 +250,12 @@ PyObject* call_vector(PyObject* self, PyObject* const* args, size_t nargsf, PyOb
 
 int call_traverse(PyObject* self, visitproc visit, void* arg) {
   Call* c = reinterpret_cast<Call*>(self);
-  Py_VISIT(c->python);
-  Py_VISIT(c->names);
-  Py_VISIT(c->dict);
+  for (PyObject* o : {c->python, c->names, c->name, c->globals, c->c_function, c->stream, c->dict}) Py_VISIT(o);
   return 0;
 }
 int call_clear(PyObject* self) {
   Call* c = reinterpret_cast<Call*>(self);
-  Py_CLEAR(c->python);
-  Py_CLEAR(c->names);
-  Py_CLEAR(c->dict);
+  for (PyObject** o : {&c->python, &c->names, &c->name, &c->globals, &c->c_function, &c->stream, &c->dict}) Py_CLEAR(*o);
   return 0;
 }
 void call_dealloc(PyObject* self) {
@@ -246,21 +271,31 @@ PyGetSetDef call_getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_Gene
 
 PyTypeObject CallType = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
-PyObject* bind(PyObject*, PyObject* args) {  // bind(name, python function, its parameter names) -> callable
+// bind(name, python function, its parameter names, the ctypes function it calls, that function's address) -> callable
+PyObject* bind(PyObject*, PyObject* args) {
   const char* name;
-  PyObject *python, *names;
-  if (!PyArg_ParseTuple(args, "sOO!", &name, &python, &PyTuple_Type, &names)) return nullptr;
+  PyObject *python, *names, *c_function;
+  unsigned long long address;
+  if (!PyArg_ParseTuple(args, "sO!O!OK", &name, &PyFunction_Type, &python, &PyTuple_Type, &names, &c_function, &address)) return nullptr;
+  PyObject* const globals = PyFunction_GetGlobals(python);
+  PyObject* const stream = PyDict_GetItemWithError(globals, g_stream_name);
+  if (!stream) return PyErr_Format(PyExc_KeyError, "_stream");
   for (const Kind& k : kKinds)
     if (!strcmp(k.name, name)) {
       if (static_cast<size_t>(PyTuple_GET_SIZE(names)) != k.n_args)
         return PyErr_Format(PyExc_TypeError, "%s takes %zu arguments, its Python function %zd", name, k.n_args, PyTuple_GET_SIZE(names));
-      Call* c = PyObject_GC_New(Call, &CallType);
-      if (!c) return nullptr;
+      PyObject* const interned = PyUnicode_InternFromString(name);
+      Call* c = interned ? PyObject_GC_New(Call, &CallType) : nullptr;
+      if (!c) {
+        Py_XDECREF(interned);
+        return nullptr;
+      }
       c->vectorcall = call_vector;
       c->kind = &k;
-      c->python = python, c->names = names, c->dict = nullptr;
-      Py_INCREF(python);
-      Py_INCREF(names);
+      c->python = python, c->names = names, c->name = interned, c->globals = globals, c->c_function = c_function, c->stream = stream;
+      c->address = reinterpret_cast<void (*)()>(address);
+      c->dict = nullptr;
+      for (PyObject* o : {python, names, globals, c_function, stream}) Py_INCREF(o);
       PyObject_GC_Track(c);
       return reinterpret_cast<PyObject*>(c);
     }
@@ -279,7 +314,7 @@ PyObject* init(PyObject*, PyObject* args) {
   Py_RETURN_NONE;
 }
 
-PyMethodDef methods[] = {{"bind", bind, METH_VARARGS, "bind(name, function, parameter names): the native call of that name"},
+PyMethodDef methods[] = {{"bind", bind, METH_VARARGS, "bind(name, function, parameter names, C function, its address): the native call of that name"},
                          {"init", init, METH_VARARGS, "init(classes and functions of the binding and of torch)"},
                          {}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", "Native marshalling of the library's calls.", -1, methods};
@@ -300,7 +335,9 @@ PyMODINIT_FUNC PyInit__calls() {
   CallType.tp_methods = call_methods;
   CallType.tp_getset = call_getset;
   if (PyType_Ready(&CallType) < 0) return nullptr;
-  if (!(g_c = PyUnicode_InternFromString("c"))) return nullptr;
+  if (!(g_c = PyUnicode_InternFromString("c")) || !(g_lib_name = PyUnicode_InternFromString("_lib")) ||
+      !(g_stream_name = PyUnicode_InternFromString("_stream")) || !(g_check_name = PyUnicode_InternFromString("_check")))
+    return nullptr;
   // in a forked child torch refuses the device: ask it again there
   pthread_atfork(nullptr, nullptr, [] { g_device_ready = false; });
   return PyModule_Create(&module);

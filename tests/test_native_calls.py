@@ -2,7 +2,11 @@
 library errors for the same arguments, whatever way they are given.  Every call below fails on the host, before a launch."""
 import ctypes
 import inspect
+import os
 import pickle
+import shutil
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -111,3 +115,65 @@ def test_without_a_device_the_python_function_says_so():
     _calls.init(b.KVCache, b.Predictor, b._check, torch.cuda.current_device, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
     with pytest.raises((RuntimeError, AssertionError)):
         b.dllava_rope(torch.zeros(64), torch.zeros(1, dtype=torch.int32), 1, 1, 64, 1e4, b.BF16)
+
+
+_TWO = """
+import importlib, sys
+sys.path.insert(0, sys.argv[1])
+a, b = importlib.import_module("one.binding"), importlib.import_module("two.binding")
+import torch
+for m in (a, b):
+    for f in (m.dllava_rope, m.dllava_rope.__wrapped__):
+        try:
+            f(torch.zeros(64), torch.zeros(1, dtype=torch.int32), 1, 1, 63, 1e4, m.BF16)
+        except m.DllavaError as e:
+            print(e)
+"""
+
+
+def _copy_package(to, name, calls=True):
+    pkg = os.path.dirname(os.path.abspath(b.__file__))
+    os.makedirs(to / name / "lib")
+    for f in ("__init__.py", "binding.py", "lib/libdllava.so") + (("_calls.so",) if calls else ()):
+        shutil.copy(os.path.join(pkg, f), to / name / f)
+
+
+def _python(program, *args):
+    r = subprocess.run([sys.executable, "-c", program, *map(str, args)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return r.stdout.splitlines(), r.stderr
+
+
+def test_two_copies_of_the_library_in_one_process(tmp_path):
+    """Each copy of the package calls the library beside it: the refusal's text comes from the library that refused.  (The stream is
+    read before the call: without a device the Python form's own refusal would come first, so a stream-less stand-in is used.)"""
+    for name in ("one", "two"):
+        _copy_package(tmp_path, name)
+    program = _TWO.replace("import torch\n", "import torch\nfor m in (a, b):\n    m._calls = importlib.import_module(m.__package__ + '._calls')\n"
+                           "    m._calls.init(m.KVCache, m.Predictor, m._check, lambda: 0, lambda: 0, lambda device: 0)\n"
+                           "    torch.cuda.current_device = lambda: 0\n    torch._C._cuda_getCurrentRawStream = lambda device: 0\n")
+    lines, _ = _python(program, tmp_path)
+    assert len(lines) == 4 and len(set(lines)) == 1 and "63" in lines[0], lines
+
+
+def test_another_library_or_stream_is_used(monkeypatch):
+    """The binding's _lib, one of its functions or its _stream replaced: the native form follows, as the Python form does."""
+    args = _valid("dllava_rope")
+    seen = []
+
+    class Lib:
+        def dllava_rope(self, *a):
+            seen.append(a)
+            return 0
+
+    real = b._lib
+    for replace in (lambda: monkeypatch.setattr(b, "_lib", Lib()), lambda: monkeypatch.setattr(b._lib, "dllava_rope", Lib().dllava_rope)):
+        replace()
+        b.dllava_rope(*args), b.dllava_rope.__wrapped__(*args)
+        assert len(seen) == 2 and seen[0] == seen[1]
+        seen.clear()
+        monkeypatch.setattr(b, "_lib", real)
+    monkeypatch.undo()
+    for stream, outcome in ((lambda s: 1 // 0, ZeroDivisionError), (lambda s: None, b.DllavaError), (lambda s: object(), ctypes.ArgumentError)):
+        monkeypatch.setattr(b, "_stream", stream)
+        assert _both("dllava_rope", *args)[0] is outcome
