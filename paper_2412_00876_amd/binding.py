@@ -1,7 +1,9 @@
 """Thin binding of libdllava.so: argument marshalling only.
 
 The functions below say through ctypes what each call takes; at the end of the module they are bound to their native forms
-(native/calls.cpp), which convert the same arguments without ctypes and leave whatever they do not know to them.
+(native/calls.cpp), which convert the same arguments without ctypes and leave whatever they do not know to them.  Where the native
+forms are not there, or were built for another torch, the functions stay what they are: the same calls, a few microseconds of
+host time longer each.
 
 Every function has the name and argument order of its C entry point (include/dllava.h); tensors are
 torch tensors used purely as device buffers (data_ptr), and the stream defaults to torch's current
@@ -13,6 +15,7 @@ from __future__ import annotations
 import ctypes as C
 import functools
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -374,10 +377,15 @@ def dllava_decode_attn_append_static(q, k_new, v_new, B, logits, threshold, keep
 
 
 def _bind_native() -> None:
-    calls_path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_calls.so")
-    if not os.path.exists(calls_path):
-        raise ImportError(f"{calls_path} is missing: build it with `python -m paper_2412_00876_amd.build`")
-    from . import _calls
+    torch_here = f"{torch.__version__} {torch.version.git_version}"
+    try:
+        from . import _calls
+        if _calls.torch_version != torch_here:  # its layouts are that torch's
+            raise ImportError(f"built for torch {_calls.torch_version}, this is {torch_here}")
+    except ImportError as e:
+        warnings.warn(f"calls take their arguments through ctypes, a few microseconds longer each: {e} "
+                      "(`python -m paper_2412_00876_amd.build` builds the native forms)", RuntimeWarning, stacklevel=2)
+        return
     _calls.init(KVCache, Predictor, _check, torch.cuda.current_device, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
     for name in EXPORTS:
         python = globals().get(name)

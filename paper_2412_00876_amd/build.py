@@ -1,5 +1,6 @@
 """Builds libdllava.so (gfx950) in-tree with hipcc: one object per source, compiled in parallel, then linked; and _calls.so, the
-native half of the Python binding, with the host compiler."""
+native half of the Python binding, with the host compiler and torch's headers.  The library needs neither: where the second
+cannot be built, the build says why and the binding does without it."""
 from __future__ import annotations
 
 import os
@@ -43,29 +44,34 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _compile_calls() -> str:
-    import sysconfig
+def build_calls() -> str:
+    """Builds _calls.so; returns what prevented it, or an empty string.  An older one does not stay beside a newer library."""
+    try:
+        import sysconfig
 
-    import torch
-    from torch.utils.cpp_extension import include_paths
-    obj = os.path.join(OBJ, "calls.o")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
-    for p in include_paths():
-        cmd += ["-isystem", p]
-    r = subprocess.run([*cmd, "-c", CALLS_SRC, "-o", obj], capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"{cmd[0]} failed on {CALLS_SRC}:\n{r.stdout}\n{r.stderr}")
-    return obj
-
-
-def _link_calls(obj: str) -> None:
-    import torch
-    # torch's libraries are in the process when the binding loads this one, and the binding hands it the library's functions
-    r = subprocess.run([os.environ.get("CXX", "g++"), "-shared", obj, "-o", CALLS,
-                        "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"], capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+        import torch
+        from torch.utils.cpp_extension import include_paths
+        os.makedirs(OBJ, exist_ok=True)
+        obj, fresh = os.path.join(OBJ, "calls.o"), os.path.join(OBJ, "calls.so")
+        version = f"{torch.__version__} {torch.version.git_version}"
+        compiler = os.environ.get("CXX", "g++")
+        compile_ = [compiler, "-O2", "-std=c++17", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    f'-DDLLAVA_TORCH_VERSION="{version}"', "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
+        for p in include_paths():
+            compile_ += ["-isystem", p]
+        # torch's libraries are in the process when the binding loads this one, and the binding hands it the library's functions
+        link = [compiler, "-shared", obj, "-o", fresh, "-L", os.path.join(os.path.dirname(torch.__file__), "lib"),
+                "-lc10", "-ltorch_cpu", "-ltorch_python"]
+        for cmd in ([*compile_, "-c", CALLS_SRC, "-o", obj], link):
+            r = subprocess.run(cmd, capture_output=True, text=True)
+            if r.returncode != 0:
+                raise OSError(f"{cmd[0]} failed on {CALLS_SRC}:\n{r.stdout}\n{r.stderr}")
+        os.replace(fresh, CALLS)
+        return ""
+    except (OSError, ImportError) as e:
+        if os.path.exists(CALLS):
+            os.remove(CALLS)
+        return str(e)
 
 
 def build(verbose: bool = True, jobs: int = 8) -> str:
@@ -73,14 +79,15 @@ def build(verbose: bool = True, jobs: int = 8) -> str:
     os.makedirs(LIB_DIR, exist_ok=True)
     srcs = sources()
     with ThreadPoolExecutor(max_workers=min(jobs, len(srcs) + 1)) as ex:
-        calls = ex.submit(_compile_calls)
+        calls = ex.submit(build_calls)
         objs = list(ex.map(_compile, srcs))
         calls = calls.result()
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
-    _link_calls(calls)
+    if calls:
+        print(f"{CALLS} was not built, calls will take their arguments through ctypes: {calls}", file=sys.stderr)
     if verbose:
         print(f"built {LIB} from {len(srcs)} sources")
     return LIB

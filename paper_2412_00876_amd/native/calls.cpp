@@ -340,5 +340,7 @@ PyMODINIT_FUNC PyInit__calls() {
     return nullptr;
   // in a forked child torch refuses the device: ask it again there
   pthread_atfork(nullptr, nullptr, [] { g_device_ready = false; });
-  return PyModule_Create(&module);
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "torch_version", DLLAVA_TORCH_VERSION) < 0) Py_CLEAR(m);
+  return m;
 }

@@ -177,3 +177,28 @@ def test_another_library_or_stream_is_used(monkeypatch):
     for stream, outcome in ((lambda s: 1 // 0, ZeroDivisionError), (lambda s: None, b.DllavaError), (lambda s: object(), ctypes.ArgumentError)):
         monkeypatch.setattr(b, "_stream", stream)
         assert _both("dllava_rope", *args)[0] is outcome
+
+
+@pytest.mark.parametrize("state", ["missing", "broken", "another torch"])
+def test_the_package_does_without_the_native_forms(tmp_path, state):
+    """Only libdllava.so is needed: the calls are then the ctypes forms, and the import says so."""
+    _copy_package(tmp_path, "one", calls=state == "another torch")
+    if state == "broken":
+        (tmp_path / "one" / "_calls.so").write_bytes(b"not a library")
+    other = "torch.version.git_version = 'another'\n" if state == "another torch" else ""
+    lines, err = _python("import sys, torch\n" + other + "sys.path.insert(0, sys.argv[1])\nimport one.binding as m\nimport inspect\n"
+                         "print(inspect.isfunction(m.dllava_rope), m.dllava_version())\n"
+                         "try:\n    m.dllava_rope(torch.zeros(64), torch.zeros(1, dtype=torch.int32), 1, 1, 63, 1e4, m.BF16, 0)\n"
+                         "except m.DllavaError as e:\n    print(e)\n", tmp_path)
+    assert lines[0].startswith("True ") and "63" in lines[1] and "RuntimeWarning" in err, (lines, err)
+
+
+def test_the_library_is_built_without_a_host_compiler(tmp_path, monkeypatch):
+    from paper_2412_00876_amd import build
+    stale = tmp_path / "_calls.so"
+    stale.write_bytes(b"an older one")
+    monkeypatch.setattr(build, "CALLS", str(stale))
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    for compiler in ("false", "no-such-compiler"):
+        monkeypatch.setenv("CXX", compiler)
+        assert compiler in build.build_calls() and not stale.exists()
