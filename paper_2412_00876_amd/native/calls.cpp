@@ -95,7 +95,7 @@ struct Call {
   PyObject* c_function;  // _lib.<name>
   void (*address)();     // where it points
   PyObject* stream;      // the binding's _stream
-  PyObject* dict;
+  PyObject *dict, *weak_references;
 };
 
 // torch's current stream of the current device, as binding._stream finds it
@@ -260,10 +260,17 @@ int call_clear(PyObject* self) {
 }
 void call_dealloc(PyObject* self) {
   PyObject_GC_UnTrack(self);
+  if (reinterpret_cast<Call*>(self)->weak_references) PyObject_ClearWeakRefs(self);
   call_clear(self);
   Py_TYPE(self)->tp_free(self);
 }
 PyObject* call_repr(PyObject* self) { return PyUnicode_FromFormat("<call %s>", reinterpret_cast<Call*>(self)->kind->name); }
+// in a class it is a method, as a function is
+PyObject* call_get(PyObject* self, PyObject* object, PyObject*) {
+  if (object && object != Py_None) return PyMethod_New(self, object);
+  Py_INCREF(self);
+  return self;
+}
 PyObject* call_reduce(PyObject* self, PyObject*) { return PyUnicode_FromString(reinterpret_cast<Call*>(self)->kind->name); }
 
 PyMethodDef call_methods[] = {{"__reduce__", call_reduce, METH_NOARGS, "pickled by name"}, {}};
@@ -294,7 +301,7 @@ PyObject* bind(PyObject*, PyObject* args) {
       c->kind = &k;
       c->python = python, c->names = names, c->name = interned, c->globals = globals, c->c_function = c_function, c->stream = stream;
       c->address = reinterpret_cast<void (*)()>(address);
-      c->dict = nullptr;
+      c->dict = c->weak_references = nullptr;
       for (PyObject* o : {python, names, globals, c_function, stream}) Py_INCREF(o);
       PyObject_GC_Track(c);
       return reinterpret_cast<PyObject*>(c);
@@ -327,6 +334,8 @@ PyMODINIT_FUNC PyInit__calls() {
   CallType.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_GC | Py_TPFLAGS_HAVE_VECTORCALL;
   CallType.tp_vectorcall_offset = offsetof(Call, vectorcall);
   CallType.tp_dictoffset = offsetof(Call, dict);
+  CallType.tp_weaklistoffset = offsetof(Call, weak_references);
+  CallType.tp_descr_get = call_get;
   CallType.tp_call = PyVectorcall_Call;
   CallType.tp_traverse = call_traverse;
   CallType.tp_clear = call_clear;

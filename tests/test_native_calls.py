@@ -7,6 +7,7 @@ import pickle
 import shutil
 import subprocess
 import sys
+import weakref
 
 import numpy as np
 import pytest
@@ -202,3 +203,18 @@ def test_the_library_is_built_without_a_host_compiler(tmp_path, monkeypatch):
     for compiler in ("false", "no-such-compiler"):
         monkeypatch.setenv("CXX", compiler)
         assert compiler in build.build_calls() and not stale.exists()
+
+
+def test_used_as_functions_are():
+    """Weak references and methods."""
+    f = b.dllava_rope
+    assert weakref.ref(f)() is f and weakref.WeakKeyDictionary({f: 1})[f] == 1
+
+    class Layer:
+        run = f
+        plain = f.__wrapped__
+
+    x = Layer()
+    assert Layer.run is f and x.run.__self__ is x and x.run.__func__ is f
+    args = _valid("dllava_rope")[1:]
+    assert _outcome(x.run, *args) == _outcome(x.plain, *args)
