@@ -9,8 +9,10 @@ import torch
 import paper_2412_00876_amd as P
 from oracle import dllava_ref as R
 from synth import rng
+from synth import workloads as W
 from tests.test_gpu_masked_attn import _H, _qkv, _run
 from tests.test_gpu_parity import _assert_out_close
+from tests.test_gpu_prefill_tiles import growing, growing_reference
 
 
 @pytest.mark.gpu
@@ -35,6 +37,32 @@ def test_tile_edges(lens, blocks, Dh):
         P.dllava_set_launch_override(P.LAUNCH_PREFILL_BLOCKS, 0)
     _assert_out_close(h.as_f64(O), R.masked_attn(q, k, v, off, keep, 1.0 / math.sqrt(Dh), "bf16"), "bf16", f"masked {lens}")
     assert torch.equal(O.view(torch.int16), again.view(torch.int16))   # same bits every time
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("slope", ["steep", "some", "falling"])
+def test_growing_maximum(Dh, slope):
+    """The reference of the exponentials moves from tile to tile, with whole hidden tiles and hidden keys between: odd and even numbers
+    of visible tiles, so that the walk ends on a tile of its own or on one without keys."""
+    h = _H()
+    H, lens = 2, [200, 33, 96, 161, 288, 321]
+    q, k, v, _ = growing(190 + Dh, lens, H, Dh, slope)
+    scale = 1.0 / math.sqrt(Dh)                                          # the one that _run passes
+    q = W.store(R.widen(q, "bf16") * (8.0 / Dh / scale), "bf16")
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    pos = np.concatenate([np.arange(n) for n in lens])
+    keep = rng.bernoulli(191, "keep", (len(pos),), 0.7).astype(np.uint8)
+    keep[(pos // 32 % 4 == 1) | (pos // 32 == 6)] = 0
+    O = h.as_f64(_run(h, q, k, v, off, keep, H, Dh))
+
+    def seen(a, b):
+        n = b - a
+        return np.tril(np.broadcast_to(keep[a:b] != 0, (n, n)) | np.eye(n, dtype=bool))
+
+    ref = growing_reference(q, k, v, off, seen, scale, slope, Dh)
+    assert np.allclose(ref, R.masked_attn(q, k, v, off, keep, scale, "bf16"), rtol=1e-9, atol=1e-12)
+    _assert_out_close(O, ref, "bf16", f"growing maximum, masked {Dh} {slope}")
 
 
 @pytest.mark.gpu
