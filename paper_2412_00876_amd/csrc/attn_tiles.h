@@ -54,11 +54,14 @@ __device__ __forceinline__ int lane_here() {
 }
 
 // One wave-wide load straight into LDS: 16 bytes per lane from base + offset to lds_addr + 16*lane (wave-uniform base and
-// lds_addr).  Written as an instruction for its scalar base: the compiler adds the base in every lane.
+// lds_addr).  Written as an instruction for its scalar base: the compiler adds the base in every lane.  The base has passed
+// through base_ready() since it was computed.
 __device__ __forceinline__ uint32_t lds_address(bf16_t* p) { return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((DLLAVA_LDS bf16_t*)p)); }
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_addr) : "memory");
 }
+// A scalar register that a vector instruction has written (a lane's value made uniform) may be a load's base five wait states later.
+__device__ __forceinline__ void base_ready(const char*& lo, const char*& hi) { asm volatile("s_nop 4" : "+s"(lo), "+s"(hi)); }
 // the same from an address per lane (M0, the LDS address of such loads, is set by these two statements only)
 __device__ __forceinline__ void load_to_lds(const char* src, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr) : "memory");
@@ -679,6 +682,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
       }
       if (at.lim < kPage) hi = lo;
     }
+    base_ready(lo, hi);
 #pragma unroll
     for (int i = 0; i < D::kLoads; ++i) {
       const bool first_half = D::kLoads >= 2 ? i < D::kLoads / 2 : D::kRowsPerLoad * wq < kPage;
@@ -795,9 +799,9 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
         step<DH, true, true>(T, SA, SB, P2, kb, vb, aScale, open, any_mask, open_v, open_k);
         t = after;
       } else {  // an odd number: pairs from the first tile on, behind products with probabilities of zero
+        products_done();  // the copy reads the scores
+        tie_s(SA);
         SB = SA;
-        products_done();
-        tie_s(SB);
         if constexpr (kMasks) kmask = mask_word(C, t);
         if (kMasks || t == last) mask_scores(SB, q0, C, t, kmask);
         first_reference(T, SB, aScale);
