@@ -24,6 +24,18 @@ struct PrefillArgs {
   const uint32_t* key_words;
 };
 
+// A value of DLLAVA_LAUNCH_PREFILL_WAVES: 1, 2 or 4 waves, or 0; plus 16 (the kernel for long sequences) or 32 (the one for short
+// ones), or neither.  Any other value counts as 0.
+struct ForcedForm {
+  int waves;        // 0: automatic
+  bool tiles, few;  // long, short; neither: automatic
+};
+constexpr ForcedForm forced_form(int v) {
+  const int waves = v & 15, kernel = v & ~15;
+  if ((waves != 0 && waves != 1 && waves != 2 && waves != 4) || (kernel != 0 && kernel != 16 && kernel != 32)) return {0, false, false};
+  return {waves, kernel == 16, kernel == 32};
+}
+
 // matrix-core path (prefill_mfma.hip); returns 1 if it does not handle the shape
 int prefill_mfma_launch(const PrefillArgs& a, int64_t rows, int Dh, hipStream_t st);
 // its software-pipelined kernel (prefill_tiles.hip), blocks of nwq waves; Dh 64 or 128; 1 if the launch would be too large

@@ -561,9 +561,9 @@ int prefill_mfma_launch(const PrefillArgs& a, int64_t rows, int Dh, hipStream_t 
   // measured: 2 waves win for the 7B batch-1 prefill (214 rows x 32 heads), 4 waves from batch 2 upwards
   const int64_t work = rows * a.H;  // query rows x heads
   int nwq = work >= 8 * 1024 ? 4 : (work >= 1024 ? 2 : 1);
-  const int forced = launch_override(DLLAVA_LAUNCH_PREFILL_WAVES);  // through dllava_set_launch_override
-  if (const int v = forced & 7; v == 1 || v == 2 || v == 4) nwq = v;
-  const bool tiles = forced & 16 ? true : forced & 32 ? false : pipelined(a, rows, Dh);
+  const ForcedForm forced = forced_form(launch_override(DLLAVA_LAUNCH_PREFILL_WAVES));  // through dllava_set_launch_override
+  if (forced.waves) nwq = forced.waves;
+  const bool tiles = forced.tiles || (!forced.few && pipelined(a, rows, Dh));
   if ((Dh == 128 || Dh == 64) && tiles) return prefill_tiles_launch(a, rows, Dh, nwq, st);
   if (Dh == 128) {
     if (nwq == 4) return launch<128, 4>(a, rows, st);

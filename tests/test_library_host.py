@@ -349,3 +349,20 @@ def test_few_rows_workspaces_over_a_sweep_of_shapes(lib):
     assert L.dllava_decode_proj_workspace(3 * 4096, 4096) == 4096   # 384 blocks of 32 features
     assert L.dllava_decode_proj_workspace(2 * 11008, 4096) == 4096
     assert L.dllava_linear_few_workspace(0, 4096) == 4096 and L.dllava_decode_proj_workspace(64, 0) == 4096
+
+
+def test_launch_forms_of_attention(tmp_path):
+    """DLLAVA_LAUNCH_PREFILL_WAVES: the documented values are taken, every other one is as good as none."""
+    import subprocess
+
+    from paper_2412_00876_amd import build
+    checks = []
+    for v in list(range(80)) + [128, 1000, 1 << 20, (1 << 31) - 1]:
+        waves, kernel = v % 16, v - v % 16
+        ok = waves in (0, 1, 2, 4) and kernel in (0, 16, 32)
+        checks.append(f"constexpr ForcedForm f{v} = forced_form({v}); static_assert(f{v}.waves == {waves if ok else 0} && "
+                      f"f{v}.tiles == {int(ok and kernel == 16)} && f{v}.few == {int(ok and kernel == 32)}, \"{v}\");")
+    src = tmp_path / "forms.cpp"
+    src.write_text('#include "prefill_args.h"\nusing namespace dllava;\n' + "\n".join(checks) + "\n")
+    r = subprocess.run([build.HIPCC, *build.COMMON, "--cuda-host-only", "-x", "hip", "-fsyntax-only", str(src)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
