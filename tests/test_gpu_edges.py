@@ -300,8 +300,9 @@ def test_prefill_persistent_blocks_walk_many_items(blocks, waves, from_cache):
     assert torch.equal(O.view(torch.int16), again.view(torch.int16))
 
 
-def test_prefill_long_sequences_from_pages():
-    """Sequences of more than 1024 keys (more than 64 pages each) read from the paged cache: the result must equal, bit
+@pytest.mark.parametrize("kernel", [0, 16, 32])
+def test_prefill_long_sequences_from_pages(kernel):
+    """Both kernels, whichever the lengths pick (0), on sequences of more than 1024 keys (more than 64 pages each) read from the paged cache: the result must equal, bit
     for bit, the one computed from plain K/V rows, and match the oracle (the context a decoding step without KV cache
     reaches: reduced prompt plus a thousand generated tokens)."""
     h = _H()
@@ -313,8 +314,12 @@ def test_prefill_long_sequences_from_pages():
     out = g.select_compact(torch.from_numpy(D).to(h.DEV), with_hidden=False)
     off = np.asarray(w.seq_off, np.int32)
     Qc = out["Q_out"].contiguous()
-    O_pages = g.prefill(Qc, out["out_off"])
-    O_rows = g.prefill(Qc, out["out_off"], g.pre["K"], g.pre["V"])
+    P.dllava_set_launch_override(P.LAUNCH_PREFILL_WAVES, kernel)
+    try:
+        O_pages = g.prefill(Qc, out["out_off"])
+        O_rows = g.prefill(Qc, out["out_off"], g.pre["K"], g.pre["V"])
+    finally:
+        P.dllava_set_launch_override(P.LAUNCH_PREFILL_WAVES, 0)
     assert torch.equal(O_pages.view(torch.int16), O_rows.view(torch.int16))
     ref = R.prefill_attn(pre["Q"], pre["K"], pre["V"], off, g.scale, w.dtype)
     _assert_out_close(h.as_f64(O_pages), ref, w.dtype, "long sequences from pages")
