@@ -353,8 +353,9 @@ __device__ __forceinline__ void want_now(const uint4& v) { asm volatile("" ::"v"
 // LB lines are always in flight: a line's registers are asked for the line LB further on as soon as it has been staged, before its
 // products.  (Whole batches of LB lines, waited for together, leave the memory idle while a batch is staged and multiplied: q|k|v of 8
 // rows in turn over four sets of weights, d = 4096, 21.3 us, W_O 7.7, gate|up 34.7, down 21.7; now 21.4, 7.2, 33.5, 20.1.)
-// JX: row groups of 8 of the LAST row tile that hold input rows; the others are neither loaded nor staged: they are
-// zeroed once, like the absent weight rows of HALF, and feed result entries nobody reads.
+// JX: row groups of 8 of the LAST row tile that are loaded and staged, at least those with input rows; the others are zeroed once,
+// like the absent weight rows of HALF, and feed result entries nobody reads.  The launch rounds up (see launch_few_as): a group
+// without rows of its own then holds repeats of the last row.
 // HALF: only weight rows 0..15 exist (features 16..31 of the result are zero).  ONCE: the weights are not looked for in, nor left
 // in, the caches (see few_once).
 template <int NT, int LB, int JX, bool HALF = false, bool ONCE = false>
@@ -741,16 +742,25 @@ __global__ __launch_bounds__(64 * few_waves<EPI>()) void few_fused_kernel(const 
 }
 
 // Weights of 64 MiB and more are read past the caches: the memory-side cache holds 256 MiB, a decode step streams all matrices of its
-// layers between two uses of one, and lines that are not put there cost less to read.  q|k|v, gate|up, down of 8 rows in turn
-// over four sets of weights, d = 4096: 21.4 / 33.5 / 20.1 us with plain loads, 19.6 / 29.5 / 18.5 past the caches.  Smaller ones
-// (W_O: 32 MiB, four of them fit that cache) are found there by programs of few layers: 7.2 plain, 7.8 past; d = 5120 10.7, 15.1.
+// layers between two uses of one (386 MiB for one layer of d = 4096), and lines that are not put there cost less to read.  The four
+// linear calls of a layer in turn over four layers, plain loads / past the caches: d = 4096, 1 row 79 / 74 us, 8 rows 82 / 75, 32
+// rows 101 / 92, 64 rows 133 / 126; over ONE layer, 8 rows 83 / 75; d = 5120, 8 rows 132 / 120, 64 rows 222 / 209.  (Every other line
+// past the caches: 77 at 8 rows, 99 at 32.)  Smaller ones (W_O: 32 MiB, four of them fit that cache) are found there by
+// programs of few layers: 7.2 plain, 7.8 past; d = 5120 10.7, 15.1.
+// The other side, which a call cannot know of: a program whose weights fit that cache all together and are used again and again
+// found them there.  ONE matrix alone, plain / past: q|k|v of d = 4096, 8 rows 18.5 / 19.0, 32 rows 19.7 / 24.0, 64 rows 24.1 / 32.0;
+// 8 rows over 128 MiB 23.5 / 22.8 (rows of 4096), 224 MiB 36.9 / 39.5 and 34.5 / 48.9 (rows of 8192); 64 rows over 224 MiB 44 / 63.
+// From 344 MiB on it is slower with plain loads (8 rows 67 / 59).  The line is drawn for decoders, none of which is that small.
 constexpr int64_t kOnceBytes = 64ll << 20;
 
 template <int EPI, bool ONCE>
 void launch_few_as(int nt, hipStream_t st, const bf16_t* X, int64_t ldx, int M, int K, const bf16_t* W0, const bf16_t* W1,
                    const bf16_t* W2, int n_fg, int KQ, int fg_each, const FewEpi& ep) {
   const dim3 grid(static_cast<unsigned>(n_fg) * static_cast<unsigned>(KQ)), block(64 * few_waves<EPI>());
-  const int jx = (M - 32 * (nt - 1) + 7) / 8;  // row groups of 8 of the last row tile
+  // Row groups of 8 of the last row tile, in the forms 1, 2 and 4; two row tiles always whole.  Against the form before, which skipped
+  // every empty group at run time, 17..24 rows take 0.86..0.97 of the time and 33..56 rows 0.82..1.01 (over the four layers of d = 4096
+  // and 5120): the loads of the repeated rows find their lines in the first-level cache.
+  const int jx = (M - 32 * (nt - 1) + 7) / 8;
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, X, ldx, M, K, W0, W1, W2, n_fg, KQ, fg_each, ep); };
   if (nt == 2) go(few_fused_kernel<2, 4, EPI, ONCE>);
   else if (jx == 1) go(few_fused_kernel<1, 1, EPI, ONCE>);

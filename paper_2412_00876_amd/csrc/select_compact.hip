@@ -323,12 +323,18 @@ struct GatherArgs {
 };
 
 // Inputs of 256 MiB and more -- the size of the memory-side cache -- are read past the caches (kernels of their own: a test for it in
-// the copy loop costs the small calls 0.5 us): each row is read once, nothing of
-// them is left there from the launch that wrote them, and lines that are not put there leave room for the outputs, which the next
-// launches read.  Compaction / the same with attention and RMSNorm of its outputs behind it, 16 sequences of 7B (354 MB of inputs):
-// 60.8 -> 58.9 / 116 -> 112 us; 32 sequences 115 -> 88, 8 of five-tile pictures 78 -> 69, threshold mode 96 -> 75.  Smaller
-// inputs are often still cached (8 sequences, 184 MB, again and again: 26.5 plain, 29.4 past the caches).  Stores past the caches were
-// faster here (55.2) and slower together with what reads the outputs (119).
+// the copy loop costs the small calls 0.5 us): each row is read once, and lines that are not put there leave room for the outputs,
+// which the next launches read.  Measured over inputs of 269..1120 MiB, one- and five-tile pictures, keep ratios 0.1..1, both modes, as a
+// share of the time with plain loads:
+//   behind the launches that wrote the inputs in place (the last written ones are still cached, at 358 MiB up to two thirds): 0.87..1.04,
+//   16 sequences of 576 vision tokens at 0.2 (358 MiB in, 128 MiB kept) 54 -> 53 us, 32 sequences 115 -> 103; writer and
+//   compaction together 0.94..1.01;
+//   on inputs not touched for long: 0.83..1.02;
+//   the same call on the same buffers again and again: 0.77..1.02 where 130 MiB and more are kept, 1.0..1.13 where less is: what
+//   is read and written then fits the cache with plain loads (12 sequences at 0.1, 74 MiB kept, 31 -> 35).  No program has that twice.
+// Compaction of 16 sequences with attention and RMSNorm of its outputs behind it 116 -> 112.  Smaller inputs are often still
+// cached whole (8 sequences, 184 MB, again and again: 26.5 plain, 29.4 past the caches).  Stores past the caches were faster
+// alone (55.2 of 60.8) and slower together with what reads the outputs (119).
 constexpr int64_t kOnceBytes = 256ll << 20;
 bool read_once(const GatherArgs& a, int64_t sumN) {
   const int64_t chunks = (a.hidden ? a.hidden_chunks : 0) + (a.Q ? a.q_chunks : 0) + (a.K ? 2 * a.kv_chunks : 0);
