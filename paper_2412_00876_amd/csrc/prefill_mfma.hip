@@ -545,6 +545,13 @@ int launch(const PrefillArgs& a, int64_t rows, hipStream_t st) {
 // 224 rows 12.9 / 12.6 (paged), 11.7 / 11.9 (rows), 768 rows 29.9 / 25.0; 64x40: 64 rows 42.7 / 43.9, 96 rows 59.7 / 53.7.  Head size 64,
 // 16x32: 256 rows 25.9 / 26.3, 320 rows 33.3 / 32.0; 1x32: 320 rows 10.6 / 10.9, 384 rows 13.9 / 13.6; 64x40: 128 rows 43.7 / 41.2.
 // Unmasked, head size 64: 4x32: 96 rows 7.4 / 7.3, 320 rows 18.3 / 16.1; 1x32: 128 rows 6.6 / 6.8, 160 rows 8.2 / 7.9.
+// The host knows the mean of what it was told, no more.  One long sequence among short ones goes by that mean, here although its
+// own tiles would be faster there (32 heads of 128, pages): 40 x 60 rows and one of 3000 133 / 120, 8 x 30 and one of 1000 40 / 32.  And
+// `rows` may be more than there are: where the rows there are would have stayed here, the call takes up to 1.5 us per item of a
+// block longer (1x32: 48 rows told 288, 5.7 / 7.5; 96 rows told 307, 7.5 / 8.6; 160 rows and more are level or faster there whatever
+// they are told).  Over random calls told three times their rows the choice is worth 7 % on average.  (A kernel that holds both bodies
+// and looks at off[B] was measured: its short form took as long as the long one -- one more trip to memory, queries through LDS
+// to fit the registers -- and the long form 1 % more.)
 bool pipelined(const PrefillArgs& a, int64_t rows, int Dh) {
   const int64_t mean = rows / a.B, work = rows * a.H;
   if (a.full) return mean >= 160 || (mean >= 96 && work >= 16384);
