@@ -1,8 +1,9 @@
 // Marshalling of the library's calls from Python in native code: binding.py's functions, argument by argument, without ctypes.
 //
 // A decode step is one launch of 8 us and its caller's program is a loop of such calls, so the time that a call takes the host
-// is a large part of it: through ctypes it took 6.6 us (14 tensor addresses, 26 conversions, a structure reference, the current
-// stream), here 3.7, of which 2.8 are the launch.  16 steps of one 7B sequence 246 -> 200 us, the float32 path 161 -> 122.
+// is a large part of it: through ctypes it took 6.2 us (14 tensor addresses, 26 conversions, a structure reference, the current
+// stream), here 4.4, of which about 3 are the launch; a call that launches nothing 1.31 and 0.34.  16 steps of one 7B sequence, both
+// forms timed in turn, 230..238 -> 190..201 us (1.15..1.19), the float32 path 153 -> 115..124 (1.22..1.26).
 //
 // Each entry point is a callable that holds the Python function of the same name.  What it does not convert itself -- a number, a
 // torch.Tensor or Parameter, the binding's own descriptors, None -- or an argument that is missing, it leaves to that function,
