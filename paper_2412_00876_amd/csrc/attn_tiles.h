@@ -32,6 +32,7 @@
 // masked, 8 of 619..816 rows 111 -> 84; unmasked, 4 spans of 2880, 8 heads of 64 138 -> 120.
 #pragma once
 
+#include <atomic>
 #include <type_traits>
 
 #include "gemm_ring.h"
@@ -859,20 +860,22 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
 
 // The blocks of a persistent launch: as many as fit the chip at once, found once per kernel.
 template <typename Kernel>
-int64_t resident_blocks(Kernel kernel, int threads, int64_t& cached) {
-  if (cached) return cached;  // the same value whichever thread gets here first
+int64_t resident_blocks(Kernel kernel, int threads, std::atomic<int64_t>& cached) {
+  if (const int64_t known = cached.load(std::memory_order_relaxed)) return known;  // the same value whichever thread gets here first
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu <= 0)
     per_cu = 2;
-  return cached = static_cast<int64_t>(cus) * per_cu;
+  const int64_t blocks = static_cast<int64_t>(cus) * per_cu;
+  cached.store(blocks, std::memory_order_relaxed);
+  return blocks;
 }
 
 // Launches `kernel` (blocks of nwq waves) over all items; 1 if there are too many of them.
 template <typename Kernel>
-int launch_items(Kernel kernel, int nwq, int64_t& cached_blocks, const char* name, const PrefillArgs& a, int64_t rows, hipStream_t st) {
+int launch_items(Kernel kernel, int nwq, std::atomic<int64_t>& cached_blocks, const char* name, const PrefillArgs& a, int64_t rows, hipStream_t st) {
   const int64_t tiles = ceil_div(rows, nwq * 32) + a.B;  // upper bound on sum_b ceil(n_b / (nwq * 32))
   const int64_t items = tiles * a.H;
   if (items > 0x7fffffffLL) return 1;

@@ -21,7 +21,7 @@ __global__ __launch_bounds__(4 * kWave, 2) __attribute__((amdgpu_num_vgpr(104)))
 // 0.64..0.89 of what it took on the kernel before (which was level with smaller items at every size).
 template <int DH>
 int launch(const PrefillArgs& a, int64_t rows, hipStream_t st) {
-  static int64_t blocks = 0;
+  static std::atomic<int64_t> blocks{0};
   return launch_items(masked_mfma_kernel<DH>, 4, blocks, "masked_mfma_kernel", a, rows, st);
 }
 

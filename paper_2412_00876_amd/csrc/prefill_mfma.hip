@@ -14,6 +14,7 @@
 // registers.  The contraction order of that second product is chosen to match the order in which S^T leaves
 // the keys in a lane; V stays row-major ([key][dim]) in LDS and the matching A fragments (four consecutive keys
 // of one dim per lane) come from the transposing LDS read of this target.
+#include <atomic>
 #include <type_traits>
 
 #include "attend.h"
@@ -509,8 +510,8 @@ __global__ __launch_bounds__(NWQ * kWave, NWQ >= 2 ? 2 : 1) void prefill_mfma_ke
 // blocks that fit the chip at once (persistent launch): compute units x blocks per compute unit, found once per kernel
 template <int DH, int NWQ>
 int64_t resident_blocks() {
-  static int64_t cached = 0;  // the same value whichever thread gets here first
-  if (cached) return cached;
+  static std::atomic<int64_t> cached{0};
+  if (const int64_t known = cached.load(std::memory_order_relaxed)) return known;  // the same value whichever thread gets here first
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
@@ -518,8 +519,9 @@ int64_t resident_blocks() {
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, prefill_mfma_kernel<DH, NWQ>, NWQ * kWave, 0) != hipSuccess ||
       per_cu <= 0)
     per_cu = 2;
-  cached = static_cast<int64_t>(cus) * per_cu;
-  return cached;
+  const int64_t blocks = static_cast<int64_t>(cus) * per_cu;
+  cached.store(blocks, std::memory_order_relaxed);
+  return blocks;
 }
 
 template <int DH, int NWQ>

@@ -14,7 +14,7 @@ __global__ __launch_bounds__(NWQ * kWave, NWQ < 4 ? 1 : 2) void prefill_tiles_ke
 
 template <int DH, int NWQ, Mode MODE>
 int launch(const PrefillArgs& a, int64_t rows, hipStream_t st) {
-  static int64_t blocks = 0;
+  static std::atomic<int64_t> blocks{0};
   return launch_items(prefill_tiles_kernel<DH, NWQ, MODE>, NWQ, blocks, "prefill_tiles_kernel", a, rows, st);
 }
 
