@@ -380,8 +380,8 @@ def _bind_native() -> None:
     torch_here = f"{torch.__version__} {torch.version.git_version}"
     try:
         from . import _calls
-        if _calls.torch_version != torch_here:  # its layouts are that torch's
-            raise ImportError(f"built for torch {_calls.torch_version}, this is {torch_here}")
+        if getattr(_calls, "torch_version", None) != torch_here:  # its layouts are that torch's
+            raise ImportError(f"_calls was built for torch {getattr(_calls, 'torch_version', '(not named)')}, this is {torch_here}")
     except ImportError as e:
         warnings.warn(f"calls take their arguments through ctypes, a few microseconds longer each: {e} "
                       "(`python -m paper_2412_00876_amd.build` builds the native forms)", RuntimeWarning, stacklevel=2)

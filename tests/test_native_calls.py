@@ -112,10 +112,12 @@ def test_what_is_refused_is_refused_alike(name):
             assert _both(name, *args[:i], 1.0, *args[i + 1:])[0] is ctypes.ArgumentError
 
 
-def test_without_a_device_the_python_function_says_so():
+def test_without_a_device_the_python_function_says_so(monkeypatch):
+    monkeypatch.undo()  # the binding's own _stream
     _calls.init(b.KVCache, b.Predictor, b._check, torch.cuda.current_device, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
-    with pytest.raises((RuntimeError, AssertionError)):
+    with pytest.raises((RuntimeError, AssertionError)) as e:
         b.dllava_rope(torch.zeros(64), torch.zeros(1, dtype=torch.int32), 1, 1, 64, 1e4, b.BF16)
+    assert not isinstance(e.value, b.DllavaError) and any(f.name == "_stream" for f in e.traceback)
 
 
 _TWO = """
@@ -180,12 +182,14 @@ def test_another_library_or_stream_is_used(monkeypatch):
         assert _both("dllava_rope", *args)[0] is outcome
 
 
-@pytest.mark.parametrize("state", ["missing", "broken", "another torch"])
+@pytest.mark.parametrize("state", ["missing", "broken", "another torch", "an older one"])
 def test_the_package_does_without_the_native_forms(tmp_path, state):
     """Only libdllava.so is needed: the calls are then the ctypes forms, and the import says so."""
     _copy_package(tmp_path, "one", calls=state == "another torch")
     if state == "broken":
         (tmp_path / "one" / "_calls.so").write_bytes(b"not a library")
+    if state == "an older one":             # without the name of its torch, and with other functions
+        (tmp_path / "one" / "_calls.py").write_text("def init(): pass\n")
     other = "torch.version.git_version = 'another'\n" if state == "another torch" else ""
     lines, err = _python("import sys, torch\n" + other + "sys.path.insert(0, sys.argv[1])\nimport one.binding as m\nimport inspect\n"
                          "print(inspect.isfunction(m.dllava_rope), m.dllava_version())\n"
