@@ -469,7 +469,9 @@ int dllava_span_attn(const void* Q, const void* K, const void* V, int32_t B, con
  *   Q, K, V, O  [rows, H, Dh] dtype (DLLAVA_BF16 only), all tokens of the batch, sequences back to back
  *   off       [B+1] row offsets of the sequences;  rows = host upper bound on off[B]
  *   keep_mask [rows] uint8, 0 = dropped, anything else = kept (keep_mask of dllava_select_compact)
- *   workspace device, 256-byte aligned, dllava_masked_attn_workspace(rows, B) bytes, scratch (need not be initialised)
+ *   workspace device, 256-byte aligned, dllava_masked_attn_workspace(rows, B) bytes, scratch (need not be initialised): the mask
+ *             as words and the list of the visible keys.  Without room for the list the call works on all keys instead:
+ *             (rows/32 + B + 2) * 4 bytes, rounded up to 256, are the least it takes
  * Sizes: Dh in {64, 128}, scale > 0.
  */
 int dllava_masked_attn(const void* Q, const void* K, const void* V, int32_t B, const int32_t* off, int64_t rows,

@@ -30,6 +30,13 @@
 // Measured against the forms before it (products, softmax and products one after the other; for masks two groups of 16 queries with
 // 16x16x32 products): 4 sequences of 2888..3085 rows, 32 heads of 128, pages 500 -> 428 us; 16 of 158..355 rows 43.3 -> 38.2;
 // masked, 8 of 619..816 rows 111 -> 84; unmasked, 4 spans of 2880, 8 heads of 64 138 -> 120.
+//
+// With masks the work is the visible keys, not all keys: in front of an item's own 128 rows a key is either visible to all of its
+// queries or to none, so those keys come from a list of the visible ones (prefill_args.h), 32 at a time, and such a tile needs no
+// mask; only the item's own rows are walked as they stand, under the mask words.  A row's place is a scalar load, dealt to the lanes
+// that fetch the row.  8 sequences of 619..816 rows, 32 heads of 128, a fifth of the picture kept: 84 -> 58 us; 4 of 2900..3050
+// 478 -> 173; heads of 64 60 -> 37; nothing hidden 93 -> 91 and 477 -> 460 (rows: the number of tiles is now known, so they go in
+// pairs without a spare one).
 #pragma once
 
 #include <atomic>
@@ -92,6 +99,7 @@ struct Dma {
 // more than this many powers of two (probabilities then stay below 2^kSlack; their bfloat16 split is relative, so
 // nothing is lost), which after the first tile of a sequence is rare.
 constexpr float kSlack = 8.f;
+constexpr float kNoReference = -1e30f;  // finite floor, not -inf: a query that sees no key of the first tiles keeps its state
 
 // LDS reads of the tiles are written as instructions: the compiler would otherwise order every LDS read after ALL
 // outstanding asynchronous fills (it cannot tell the buffers apart) and so wait for the tiles just requested.
@@ -134,6 +142,34 @@ __device__ __forceinline__ void zero_o(f32x16& o) {
     o[I.value] = z;
   });
   tie_o(o);
+}
+
+// Scalars dealt to the lanes, v[i] to the i-th fourth or eighth of the wave: a plain move each, under a mask of lanes that walks
+// through the wave.  (As selections between the scalars, each of which takes a vector register first, it is twice the
+// instructions.)  All lanes are active.
+__device__ __forceinline__ uint32_t by_lanes(const uint32_t (&v)[4]) {
+  uint32_t r;
+  uint64_t all;
+  asm volatile(
+      "s_mov_b64 %1, exec\n\ts_mov_b64 exec, 0xffff\n\tv_mov_b32 %0, %2\n\ts_lshl_b64 exec, exec, 16\n\tv_mov_b32 %0, %3\n\t"
+      "s_lshl_b64 exec, exec, 16\n\tv_mov_b32 %0, %4\n\ts_lshl_b64 exec, exec, 16\n\tv_mov_b32 %0, %5\n\ts_mov_b64 exec, %1"
+      : "=&v"(r), "=&s"(all)
+      : "s"(v[0]), "s"(v[1]), "s"(v[2]), "s"(v[3])
+      : "scc");
+  return r;
+}
+__device__ __forceinline__ uint32_t by_lanes(const uint32_t (&v)[8]) {
+  uint32_t r;
+  uint64_t all;
+  asm volatile(
+      "s_mov_b64 %1, exec\n\ts_mov_b64 exec, 0xff\n\tv_mov_b32 %0, %2\n\ts_lshl_b64 exec, exec, 8\n\tv_mov_b32 %0, %3\n\t"
+      "s_lshl_b64 exec, exec, 8\n\tv_mov_b32 %0, %4\n\ts_lshl_b64 exec, exec, 8\n\tv_mov_b32 %0, %5\n\t"
+      "s_lshl_b64 exec, exec, 8\n\tv_mov_b32 %0, %6\n\ts_lshl_b64 exec, exec, 8\n\tv_mov_b32 %0, %7\n\t"
+      "s_lshl_b64 exec, exec, 8\n\tv_mov_b32 %0, %8\n\ts_lshl_b64 exec, exec, 8\n\tv_mov_b32 %0, %9\n\ts_mov_b64 exec, %1"
+      : "=&v"(r), "=&s"(all)
+      : "s"(v[0]), "s"(v[1]), "s"(v[2]), "s"(v[3]), "s"(v[4]), "s"(v[5]), "s"(v[6]), "s"(v[7])
+      : "scc");
+  return r;
 }
 
 __device__ __forceinline__ float select_bits(uint32_t m, float a, float b) {  // a where m has ones, else b
@@ -314,7 +350,9 @@ __device__ __forceinline__ void step(State<DH>& T, f32x16& S, f32x16& Sn, Probs&
   // (Scaled before it is compared, as in the kernel for short sequences: the reference then moves at the same scores there and here.)
   x *= scale_log2;
   bool moved = false;
-  if (__any(x > T.thr)) {
+  if constexpr (FIRST) {  // neither the threshold nor a factor takes a register before the end of the tile
+    if (__any(x > kNoReference + kSlack)) T.m_ref = max2(T.m_ref, max2(x, __shfl_xor(x, 32, kWave)));
+  } else if (__any(x > T.thr)) {
     move_reference(T, x);
     moved = true;
   }
@@ -363,15 +401,15 @@ __device__ __forceinline__ void step(State<DH>& T, f32x16& S, f32x16& Sn, Probs&
     if constexpr (!FIRST) asm volatile("s_nop 7" ::: "memory");
     static_for<4 * kNB - from>([&](auto I) DLLAVA_INLINE { read_v(std::integral_constant<int, from + decltype(I)::value>{}); });
   }
-  if (moved) {
-    if constexpr (!FIRST) {  // P(t-1) V went in under the old reference
-      products_done();
-      static_for<kNB>([&](auto I) DLLAVA_INLINE {
-        tie_o(T.o[I.value]);
-        T.o[I.value] *= T.thr;
-        tie_o(T.o[I.value]);
-      });
-    }
+  if constexpr (FIRST) {
+    reference_moved(T);
+  } else if (moved) {  // P(t-1) V went in under the old reference
+    products_done();
+    static_for<kNB>([&](auto I) DLLAVA_INLINE {
+      tie_o(T.o[I.value]);
+      T.o[I.value] *= T.thr;
+      tie_o(T.o[I.value]);
+    });
     reference_moved(T);
   }
   lds_wait();
@@ -438,6 +476,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   const ConstI32 off_c = (ConstI32)args.off;
   const ConstI32 bt_c = (ConstI32)args.block_table;
   const ConstU32 kw_c = (ConstU32)args.key_words;
+  const int mask_slots = args.mask_slots;
   constexpr bool paged = MODE == Mode::Paged;
   const int step_blocks = static_cast<int>(gridDim.x);
 
@@ -458,10 +497,18 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   }
   struct Item {
     int valid, b, h, tile, r0, n;
+    int seen;  // with masks: visible keys in front of the item's own queries, which it takes from the list; -1: it walks all keys
+  };
+  auto seen_before = [&](const Item& it) DLLAVA_INLINE {
+    if (!kMasks || mask_slots == 0 || static_cast<uint64_t>(static_cast<uint32_t>(it.n)) * static_cast<uint32_t>(H) * kRowBytes >> 32) return -1;
+    // A listed tile takes up to 1.3 times as long as one in rows (its rows' places are loads in front of it): with a list for every
+    // item that it spares a tile, 800 rows of 32 heads took 37 us at 84 % visible keys and 29 at 60 %, in rows 33 at either.
+    const int seen = static_cast<int>((kw_c + mask_slots)[(it.r0 >> 5) + it.b + it.tile * (kBM / kBN)]);
+    return seen <= it.tile * (kBM * 3 / 4) ? seen : -1;
   };
   // Item k of a launch over at most 64 sequences.
   auto locate = [&](int k) __attribute__((always_inline)) {
-    Item it{0, 0, 0, 0, 0, 0};
+    Item it{0, 0, 0, 0, 0, 0, -1};
     const int yd = k / H;  // position in DESCENDING tile-index order
     it.h = k - yd * H;
     const int y = total - 1 - yd;  // position in ascending order
@@ -482,6 +529,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
     it.r0 = off_c[it.b];
     it.n = off_c[it.b + 1] - it.r0;
     it.valid = 1;
+    it.seen = seen_before(it);
     return it;
   };
   // keys 0..last_key of its sequence are needed by an item
@@ -495,7 +543,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   const int pblk = static_cast<int>(blockIdx.x);
   auto item_of = [&](int j) __attribute__((always_inline)) { return ((j & 1) ? step_blocks - 1 - pblk : pblk) + j * step_blocks; };
   int jC = 0;
-  Item C{0, 0, 0, 0, 0, 0};
+  Item C{0, 0, 0, 0, 0, 0, -1};
   if (by_lane) {
     C = locate(item_of(0));
   } else {
@@ -510,7 +558,8 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
       if (past) {
         const int l = __builtin_ctzll(past);
         // the sequence's first tile is number upto - nt, its last upto - 1: counted from the last
-        C = {1, b0 + l, pblk % H, __builtin_amdgcn_readlane(upto, l) - 1 - tile, __builtin_amdgcn_readlane(r0, l), __builtin_amdgcn_readlane(n, l)};
+        C = {1, b0 + l, pblk % H, __builtin_amdgcn_readlane(upto, l) - 1 - tile, __builtin_amdgcn_readlane(r0, l), __builtin_amdgcn_readlane(n, l), -1};
+        C.seen = seen_before(C);
         break;
       }
       tile -= __builtin_amdgcn_readlane(upto, kWave - 1);
@@ -537,14 +586,10 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
       load_to_lds(reinterpret_cast<const char*>(src), lds_address(myQ) + i * (kWave * 16));
     }
   };
-  auto mask_word = [&](const Item& it, int t) DLLAVA_INLINE { return kw_c[(it.r0 >> 5) + it.b + t]; };
-  // The key tiles of an item, in order.  With masks, tiles whose keys are all hidden and hold none of the item's own
-  // queries are left out of the stream.
-  auto shown = [&](const Item& it, int t) DLLAVA_INLINE {
-    if constexpr (kMasks)
-      while (t * kBN + kBN - 1 < it.tile * kBM && mask_word(it, t) == 0u) ++t;
-    return t;
-  };
+  // The key tiles of an item: with masks the visible keys in front of its own queries first, as they are listed (listed() tiles), then
+  // keys in rows, from tile first_plain() of the sequence on.
+  auto listed = [&](const Item& it) DLLAVA_INLINE { return kMasks ? (it.seen + kBN - 1) / kBN : 0; };
+  auto first_plain = [&](const Item& it) DLLAVA_INLINE { return kMasks && it.seen >= 0 ? it.tile * (kBM / kBN) : 0; };
 
   // Fragment addresses (LDS bytes, stage 0).  K: row lq, logical chunk 2*ks + g, stored at chunk ^ swizzle(lq): the
   // step ks enters as an exclusive-or with 32*ks.  Queries alike.  V: the transposing read of 16 lanes (j = lane mod 16)
@@ -556,16 +601,17 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   const uint32_t vb0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((DLLAVA_LDS bf16_t*)sV)) +
                        (4 * g + (j16 >> 2)) * kRowBytes + ((j16 >> 2) % (kChunks / 4)) * 64 + ((lane >> 4) & 1) * 32 + (j16 & 3) * 8;
 
-  // scores above the diagonal of some query (keys > qi), past the end of the sequence, or hidden by a zero bit of kmask
-  // (except the query's own key)
-  auto mask_scores = [&](f32x16& S, int q0, const Item& it, int t, uint32_t kmask) DLLAVA_INLINE {
+  // scores above the diagonal of some query (keys > qi), past the end of the sequence, or hidden by a zero bit of kmask (except the
+  // query's own key); queries, keys and the sequence's length n as numbered by the tiles of the stream: the wave's queries are
+  // those of its last tile
+  auto mask_scores = [&](f32x16& S, int t, int last, int n, uint32_t kmask) DLLAVA_INLINE {
     const int j0 = t * kBN;
-    if (j0 + kBN - 1 > (kFull ? it.n - 1 : q0) || (kMasks && kmask != ~0u)) {
+    if ((kFull ? j0 + kBN > n : t >= last) || (kMasks && kmask != ~0u)) {
       products_done();
       tie_s(S);
       const int l = lane_here(), g4 = 4 * (l >> 5);
-      int qi = q0 + (l & 31);
-      if (kFull || qi >= it.n) qi = it.n - 1;
+      int qi = last * kBN + (l & 31);
+      if (kFull || qi >= n) qi = n - 1;
       const int self = qi - j0 - g4;  // the query's own key, counted from j0 + g4
       const uint32_t upto = self < 0 ? 0u : (2u << (self < 31 ? self : 31)) - 1u;  // the keys up to it
       uint32_t seen = kMasks ? ((kmask >> g4) & upto) | (static_cast<uint32_t>(self) < 32u ? 1u << self : 0u) : upto;
@@ -612,11 +658,19 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
     k_lane[i] = (rr % kPage) * row_bytes + 16 * (pc ^ D::k_swizzle(rr));
     v_lane[i] = (rr % kPage) * row_bytes + 16 * (pc ^ (4 * (rr % (kChunks / 4))));
   }
+  // With masks: the 16 bytes of a row that a lane fetches, the same in all its loads (their rows are a multiple of 16 apart); those of V
+  // from those of K by an exclusive-or (a row's first byte is a multiple of its length).
+  static_assert(!kMasks || D::kRowsPerLoad * NWQ % 16 == 0, "rows of a lane");
+  auto k_chunk = [&](int l) DLLAVA_INLINE { return 16u * ((l % kChunks) ^ D::k_swizzle(D::kRowsPerLoad * wq + l / kChunks)); };
+  const uint32_t v_flip = k_chunk(lane) ^ (16u * ((lane % kChunks) ^ (4 * ((D::kRowsPerLoad * wq + lane / kChunks) % (kChunks / 4)))));
+  auto first_rows = [&](int i) DLLAVA_INLINE { return D::kLoads >= 2 ? i < D::kLoads / 2 : D::kRowsPerLoad * wq < kPage; };  // load i: of the first half?
   struct TileAt {
     const char *lo, *hi;  // K of the first rows of the tile's halves, this head
     int lim;              // last row of the tile that exists (>= kBN - 1: all of them)
+    uint32_t k[D::kLoads];  // with masks: this lane's bytes of K, from lo (hi and lim are not used)
   };
-  int jP = 0, tP, lastP;
+  int jP = 0, tP, lastP;  // lastP: its last key, as the stream numbers them
+  int listP = 0;
   bool ended = false;  // every K tile of the block has been requested
   const char* baseP;  // K of the first row of P's sequence, its head (paged: the head's K in page 0)
   Item P = C;
@@ -637,19 +691,55 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
     lastP = last_key_of(P);
     baseP = paged ? static_cast<const char*>(args.pages) + static_cast<int64_t>(P.h) * (kPage * kRowBytes)
                   : static_cast<const char*>(aK) + static_cast<int64_t>(P.r0) * row_bytes + P.h * kRowBytes;
-    tP = uniform(shown(P, 0));
+    P.seen = uniform(P.seen);
+    listP = listed(P);
+    lastP -= (first_plain(P) - listP) * kBN;
+    tP = 0;
   };
   auto next_tile_at = [&]() DLLAVA_INLINE {  // tile tP of item P; then on to the next tile of the stream
     TileAt at;
-    at.lim = lastP - tP * kBN;
-    if (paged) {
+    const int lim = lastP - tP * kBN;
+    if constexpr (kMasks) {
+      if (tP < listP) {
+        at.lo = baseP;
+        const ConstU32 list = kw_c + 2 * static_cast<int64_t>(mask_slots) + P.r0 + kBN * static_cast<int64_t>(P.b);
+#pragma unroll
+        for (int i = 0; i < D::kLoads; ++i) {
+          const int first = tP * kBN + D::kRowsPerLoad * (wq + NWQ * i);
+          uint32_t v[D::kRowsPerLoad];
+          if (tP * kBN + kBN <= P.seen) {
+#pragma unroll
+            for (int e = 0; e < D::kRowsPerLoad; ++e) v[e] = list[first + e];
+          } else {  // past its end the list's last row is repeated
+#pragma unroll
+            for (int e = 0; e < D::kRowsPerLoad; ++e) v[e] = list[first + e < P.seen ? first + e : P.seen - 1];
+          }
+          at.k[i] = by_lanes(v) + k_chunk(lane_here());
+        }
+      } else {
+        if (tP == listP) baseP += static_cast<uint64_t>(static_cast<uint32_t>((first_plain(P) - listP) * kBN)) * row_bytes;
+        at.lo = baseP + static_cast<uint64_t>(static_cast<uint32_t>(tP * kBN)) * row_bytes;
+#pragma unroll
+        for (int i = 0; i < D::kLoads; ++i) at.k[i] = k_lane[i % kHalfLoads] + (first_rows(i) ? 0 : kPage * row_bytes);
+        if (__builtin_expect(lim < kBN - 1, 0)) {  // rows past the last key repeat it
+          const int l = lane_here();
+#pragma unroll
+          for (int i = 0; i < D::kLoads; ++i) {
+            const int rr = D::kRowsPerLoad * (wq + NWQ * i) + l / kChunks;
+            at.k[i] = static_cast<uint32_t>(rr < lim ? rr : lim) * row_bytes + k_chunk(l);
+          }
+        }
+      }
+    } else if (paged) {
+      at.lim = lim;
       at.lo = baseP + static_cast<int64_t>(pg_lo) * (2 * page_half);
       at.hi = baseP + static_cast<int64_t>(pg_hi) * (2 * page_half);
     } else {
+      at.lim = lim;
       at.lo = baseP + static_cast<uint64_t>(static_cast<uint32_t>(tP * kBN)) * row_bytes;
       at.hi = at.lo + kPage * row_bytes;
     }
-    tP = shown(P, tP + 1);
+    ++tP;
     if (__builtin_expect(tP > lastP / kBN, 0)) {  // the item's last tile: the stream goes on with the block's next item
       const Item it = locate(item_of(jP + 1));
       if (uniform(it.valid)) {
@@ -670,6 +760,13 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   };
   // loads of one half-stage (K or V) of a tile to the LDS address dst
   auto request = [&](const TileAt& at, int64_t step, const uint32_t (&lane_off)[kHalfLoads], bool is_v, uint32_t dst) DLLAVA_INLINE {
+    if constexpr (kMasks) {
+      const char *lo = at.lo + step, *hi = lo;
+      base_ready(lo, hi);
+#pragma unroll
+      for (int i = 0; i < D::kLoads; ++i) load_to_lds(lo, is_v ? at.k[i] ^ v_flip : at.k[i], dst + (wq + NWQ * i) * (kWave * 16));
+      return;
+    }
     const char *lo = uniform_ptr(at.lo) + step, *hi = paged ? uniform_ptr(at.hi) + step : lo + kPage * row_bytes;
     uint32_t o[D::kLoads];
 #pragma unroll
@@ -686,8 +783,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
     base_ready(lo, hi);
 #pragma unroll
     for (int i = 0; i < D::kLoads; ++i) {
-      const bool first_half = D::kLoads >= 2 ? i < D::kLoads / 2 : D::kRowsPerLoad * wq < kPage;
-      load_to_lds(first_half ? lo : hi, o[i], dst + (wq + NWQ * i) * (kWave * 16));
+      load_to_lds(first_rows(i) ? lo : hi, o[i], dst + (wq + NWQ * i) * (kWave * 16));
     }
   };
   const uint32_t sK0 = lds_address(sK), sV0 = lds_address(sV);
@@ -726,10 +822,16 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   uint32_t s0 = 0, s1 = kSlot, s2 = 2 * kSlot;  // ring slots of K and V of the tile at hand, the next, the one after
   int tile = tile_first;
   for (;;) {  // items
-    const int lastC = last_key_of(C) / kBN;
-    const int last = kFull ? (tile < 0 ? -1 : lastC) : tile;  // this wave's last key tile; -1: it has no queries
+    // Keys are numbered as they come in the stream: the listed ones, then the rows from first_plain on, `skipped` fewer than in the
+    // sequence.
+    const int listC = listed(C), skipped = (first_plain(C) - listC) * kBN, nC = C.n - skipped;
+    const int lastC = (last_key_of(C) - skipped) / kBN;
+    const int last = kFull || tile < 0 ? (tile < 0 ? -1 : lastC) : tile - skipped / kBN;  // this wave's last key tile; -1: it has no queries
+    const uint32_t list_tail = C.seen > 0 && C.seen % kBN ? (1u << C.seen % kBN) - 1u : ~0u;  // the keys of the last listed tile
+    const int wordC = (C.r0 >> 5) + C.b + skipped / kBN;
+    auto mask_word = [&](int t) DLLAVA_INLINE { return t >= listC ? kw_c[wordC + t] : t == listC - 1 ? list_tail : ~0u; };
     const int q0 = tile * 32;
-    int t = shown(C, 0);
+    int t = 0;
     f32x16 SA, SB;
     Probs P2;
     if (t <= last) {
@@ -751,7 +853,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
         }
         __builtin_amdgcn_sched_barrier(0);
       });
-      T.m_ref = -1e30f;  // finite floor, not -inf: a query that sees no key of the first tiles keeps its state
+      T.m_ref = kNoReference;
       T.thr = T.m_ref + kSlack;
       T.l_run = 0.f;
     }
@@ -773,7 +875,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
       __builtin_amdgcn_s_barrier();
       vb = vb0 + s0;
       kb = kb0 + s1;
-      if constexpr (kMasks) kmask = mask_word(C, t);
+      if constexpr (kMasks) kmask = mask_word(t);
     };
     auto open_v = [&]() DLLAVA_INLINE {
       q_late = false;
@@ -790,21 +892,20 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
       s0 = s1, s1 = s2, s2 = s3;
     };
     auto any_mask = [&](f32x16& S) DLLAVA_INLINE {
-      if constexpr (kMasks) mask_scores(S, q0, C, t, kmask);
+      if constexpr (kMasks) mask_scores(S, t, last, nC, kmask);
     };
     // On entry of the loop: scores of tile t in SB, V and the probabilities of the tile before pending.  (The two score buffers
     // take turns; a loop that can be left in its middle, or entered there, makes the compiler move accumulators.)
     if (t <= last) {
-      const int after = shown(C, t + 1);
-      if (kMasks ? after <= last : (last - t) & 1) {  // an even number of tiles (with masks their number is not known)
+      if ((last - t) & 1) {  // an even number of tiles
         step<DH, true, true>(T, SA, SB, P2, kb, vb, aScale, open, any_mask, open_v, open_k);
-        t = after;
+        ++t;
       } else {  // an odd number: pairs from the first tile on, behind products with probabilities of zero
         products_done();  // the copy reads the scores
         tie_s(SA);
         SB = SA;
-        if constexpr (kMasks) kmask = mask_word(C, t);
-        if (kMasks || t == last) mask_scores(SB, q0, C, t, kmask);
+        if constexpr (kMasks) kmask = mask_word(t);
+        if (kMasks || t == last) mask_scores(SB, t, last, nC, kmask);
         first_reference(T, SB, aScale);
         P2.hi[0] = P2.hi[1] = P2.lo[0] = P2.lo[1] = u32x4{0u, 0u, 0u, 0u};
         static_for<4 * kNB>([&](auto I) DLLAVA_INLINE { T.v[I.value % kNB][I.value / (2 * kNB)][(I.value / kNB) % 2] = u32x2{0u, 0u}; });
@@ -812,38 +913,21 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
       }
       while (t < last) {
         step<DH, false, true>(T, SB, SA, P2, kb, vb, aScale, open, any_mask, open_v, open_k);
-        t = shown(C, t + 1);
+        ++t;
         step<DH, false, true>(T, SA, SB, P2, kb, vb, aScale, open, any_mask, open_v, open_k);
-        t = shown(C, t + 1);
-        if (kMasks && t > last) break;
+        ++t;
       }
-      // With masks the tiles may have run out in the middle of a pair: one more without visible keys, of the same V.
-      const bool spent = kMasks && t > last;
-      step<DH, false, false>(
-          T, SB, SA, P2, kb, vb, aScale,
-          [&]() DLLAVA_INLINE {
-            if (!spent) open();
-          },
-          [&](f32x16& S) DLLAVA_INLINE {
-            if (!spent) mask_scores(S, q0, C, t, kmask);  // the diagonal, or the end of the sequence
-            else
-#pragma unroll
-              for (int r = 0; r < 16; ++r) S[r] = -INFINITY;
-          },
-          [&]() DLLAVA_INLINE {
-            if (!spent) open_v();
-          },
-          [&]() DLLAVA_INLINE {
-            if (!spent) open_k();
-          });
-      if (!spent) t = shown(C, t + 1);
+      step<DH, false, false>(T, SB, SA, P2, kb, vb, aScale, open,
+                             [&](f32x16& S) DLLAVA_INLINE { mask_scores(S, t, last, nC, kmask); },  // the diagonal, or the end of the sequence
+                             open_v, open_k);
+      ++t;
       finish<DH>(T, P2);
     }
     while (t <= lastC) {  // later waves of the block have more tiles
       open();
       open_v();
       open_k();
-      t = shown(C, t + 1);
+      ++t;
     }
     if (q_next < kQLoads) {
       request_queries(next, next_wave_tile, q_next, kQLoads);

@@ -18,7 +18,8 @@ __global__ __launch_bounds__(4 * kWave, 2) __attribute__((amdgpu_num_vgpr(104)))
 }
 
 // Items of 128 rows whatever the size of the launch: over means of 32..768 rows and 1x8..64x40 sequences x heads the call takes
-// 0.64..0.89 of what it took on the kernel before (which was level with smaller items at every size).
+// 0.64..0.89 of what it took on the kernel before (which was level with smaller items at every size).  (Measured before the visible
+// keys came from a list.)
 template <int DH>
 int launch(const PrefillArgs& a, int64_t rows, hipStream_t st) {
   static std::atomic<int64_t> blocks{0};
