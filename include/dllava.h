@@ -108,7 +108,8 @@ const char* dllava_last_error(void);
  *                                10 = 128 x 64, 4 .. 8 = 256 units x 32*value tokens
  *   DLLAVA_LAUNCH_QKV_TILE       the same for the projection kernel of dllava_qkv_project
  *   DLLAVA_LAUNCH_LINEAR_TILE    tile of the many-rows linear layers (dllava_linear, dllava_predict): 1 = 64 features x
- *                                64 rows, 2 = 64 x 128, 3 = 128 x 128, 9 = 128 x 192, 4 .. 8 = 256 x 32*value
+ *                                64 rows, 2 = 64 x 128, 3 = 128 x 128, 9 = 128 x 192, 4 .. 8 = 256 x 32*value; three
+ *                                blocks per compute unit: 11 = 64 x 64; two: 12 = 128 x 128
  *   DLLAVA_LAUNCH_SELECT_LAUNCHES 1 = dllava_select_compact in top-k mode as one launch (selection and copies side by
  *                                side; what it picks for up to 256 sequences), 2 = selection, then the copies,
  *                                3 = one launch in which the selection blocks stand back, so that a copying block

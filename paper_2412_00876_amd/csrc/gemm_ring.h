@@ -55,7 +55,6 @@ constexpr int kRingRowBytes = 128;                // bytes per row per stage
 constexpr int kRingSlotBytes = 256 * kRingRowBytes;
 constexpr int kRingSlots = 5;
 constexpr int kRingLdsBytes = kRingSlots * kRingSlotBytes;  // 160 KiB: all of a compute unit's LDS
-constexpr int kRingALoads = 8;                    // tile loads per wave per stage for A (256 rows); JT for B
 
 template <int... I, typename F>
 __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
@@ -110,25 +109,33 @@ __device__ __forceinline__ bool ring_tile(int n_at, int n_bt, int per_xcd, int& 
   return true;
 }
 
-// The tiles of the products below: 32*fi rows of A x 32*jt rows of B, one block per compute unit.  Nanoseconds per stage when
-// every compute unit works and when few do -- the clock gives way to the power --, beside the stages (prologue and
-// epilogue), and what the tile loads of a stage alone take (measured on linear layers of d = 512 .. 11008).
+// The tiles of the products below: 32*fi rows of A x 32*jt rows of B.  Nanoseconds per stage when every compute unit works and
+// when few do -- the clock gives way to the power --, beside the stages (prologue and epilogue), and what the tile loads of a
+// stage alone take (measured on linear layers of d = 512 .. 11008).  Blocks that share a compute unit: one; three of the shallow
+// small tiles (times: of a whole round of them); two of the tiles that stand with GELU (see ring_pick).  The small tile with the
+// deep ring has half of the LDS, but is only taken for one block per compute unit.
 struct RingTile {
   int id;  // what the launch overrides take
   int fi, jt;
   int64_t busy, alone, ends, load;
+  int per_cu;
 };
-constexpr RingTile kRingTiles[] = {{8, 8, 8, 1310, 990, 10200, 800}, {7, 8, 7, 1120, 855, 9300, 750}, {6, 8, 6, 1030, 760, 8400, 700},
-                                   {5, 8, 5, 870, 660, 7300, 650},   {4, 8, 4, 750, 600, 6300, 600},  {9, 4, 6, 540, 430, 7500, 430},
-                                   {3, 4, 4, 460, 370, 6200, 370},   {10, 4, 2, 300, 270, 4700, 270}, {2, 2, 4, 300, 260, 4500, 260},
-                                   {1, 2, 2, 210, 200, 4200, 200}};
+constexpr int kRingGeluPair = 12;
+constexpr RingTile kRingTiles[] = {{8, 8, 8, 1310, 990, 10200, 800, 1}, {7, 8, 7, 1120, 855, 9300, 750, 1},  {6, 8, 6, 1030, 760, 8400, 700, 1},
+                                   {5, 8, 5, 870, 660, 7300, 650, 1},   {4, 8, 4, 750, 600, 6300, 600, 1},   {9, 4, 6, 540, 430, 7500, 430, 1},
+                                   {3, 4, 4, 460, 370, 6200, 370, 1},   {10, 4, 2, 300, 270, 4700, 270, 1},  {2, 2, 4, 300, 260, 4500, 260, 1},
+                                   {1, 2, 2, 210, 190, 3800, 200, 1},   {11, 2, 2, 700, 210, 3400, 200, 3},  {kRingGeluPair, 4, 4, 930, 930, 6100, 740, 2}};
 
 // The tile that takes least; tiles_of(t): how many of it the launch has, 0 if it cannot use it.  Null if none can be used.
 // A stage touches one 128-byte line of every row of its tile: once those rows span more than about 2.5 MiB (11008
 // columns: 22 KiB apart) its loads slow down, by about 65 ns for every further MiB -- 4096 x 500 results: 0.98 us a stage
 // of 256 x 128 at 11008 columns against 0.60 at 4096, 0.25 against 0.20 of 64 x 64.
+// gelu: the epilogue takes the GELU of 4 fi jt results per lane, 32 ns each (vector arithmetic, nothing beside it).  Only then do
+// two blocks per compute unit pay, one's products beside the other's GELU: they are paced by the LDS, which two tiles of 128 x 128
+// read and write 1.4 times as much per product as one of 256 x 256 (11520 rows, 512 wide: 2048 features with GELU 43.3 us against
+// 48.3, 1536 without 31.5 against 29.7).  Their time is proportional to their number, rounds cannot be told.
 template <typename F>
-inline const RingTile* ring_pick(int64_t d, int forced, F&& tiles_of) {
+inline const RingTile* ring_pick(int64_t d, int forced, F&& tiles_of, bool gelu = false) {
   const int64_t nk = d / kRingBK;
   const RingTile* best = nullptr;
   int64_t best_cost = 0;
@@ -138,36 +145,44 @@ inline const RingTile* ring_pick(int64_t d, int forced, F&& tiles_of) {
     if (t.id == forced) return &t;
     const int64_t span = 32 * (t.fi + t.jt) * d * 2 - (5 << 19), slow = t.load + (span > 0 ? span / (1 << 10) * 65 / (1 << 10) : 0);
     const int64_t busy = t.busy > slow ? t.busy : slow, alone = t.alone > slow ? t.alone : slow;
-    const int64_t per_xcd = ceil_div(tiles, kRingXcds), full = per_xcd / 32, rest = per_xcd % 32;
-    int64_t cost = full * (nk * busy + t.ends);
-    if (rest) cost += nk * (alone + (busy - alone) * rest / 32) + t.ends;
+    int64_t cost;
+    if (t.id == kRingGeluPair) {
+      if (!gelu || tiles <= 512) continue;  // within one round the blocks of a compute unit stay in step: nothing of one stands beside the other
+      cost = tiles * (nk * busy + t.ends) / 512 + 5000;
+    } else {
+      const int64_t ends = t.ends + (gelu ? 4 * 32 * t.fi * t.jt : 0), at_once = 32 * t.per_cu;
+      const int64_t per_xcd = ceil_div(tiles, kRingXcds), full = per_xcd / at_once, rest = per_xcd % at_once;
+      cost = full * (nk * busy + ends);
+      if (rest) cost += nk * (alone + (busy - alone) * rest / at_once) + ends;
+    }
     if (!best || cost < best_cost) best = &t, best_cost = cost;
   }
   return best;
 }
 
-// Main loop.  Abase / Bbase: wave-uniform byte pointers to element 0 of the tiles' first rows; ga[j] / gb[j]: this
+// Main loop, A tile of 32*FI rows, a ring of five half-stage slots of 32*FI rows (FI = 8: all of the LDS, FI = 4: half of it, for two
+// blocks per compute unit).  Abase / Bbase: wave-uniform byte pointers to element 0 of the tiles' first rows; ga[j] / gb[j]: this
 // lane's byte offsets (ring_load_row / ring_load_chunk_bytes) for its tile loads; nk = d / 64 >= 1;
 // w = wave index 0..3 (wave-uniform).  acc: register r of acc[i][j] in a lane is
-//   A row 128*(w/2) + 16*i + 4*(lane/16) + r  .  B row 16*JT*(w%2) + 16*j + lane%16.
+//   A row 16*FI*(w/2) + 16*i + 4*(lane/16) + r  .  B row 16*JT*(w%2) + 16*j + lane%16.
 // Every row touched must be readable for all d (clamp rows past the end of a matrix to its last row).
 // On return all LDS traffic of the loop has completed; the caller must still place a block barrier before it
 // reuses the ring memory for something else.
 // BOff: uint32_t, or int64_t when the rows of B may lie more than 4 GiB apart (gathered rows).
-template <int JT, typename BOff>
-__device__ __forceinline__ void gemm_ring_256(const char* Abase, const uint32_t (&ga)[kRingALoads], const char* Bbase,
-                                              const BOff (&gb)[JT], int nk, DLLAVA_LDS char* smem, int w,
-                                              ring_f32x4 (&acc)[8][JT]) {
-  static_assert(JT >= 4 && JT <= 8, "B tile of 128 .. 256 rows");
-  constexpr int kMF = 8 * JT;  // products per k-step of 32
-  constexpr int kNR = 8 + JT;  // fragment reads per k-step
+template <int FI, int JT, typename AOff, typename BOff>
+__device__ __forceinline__ void gemm_ring_halves(const char* Abase, const AOff (&ga)[FI], const char* Bbase,
+                                                 const BOff (&gb)[JT], int nk, DLLAVA_LDS char* smem, int w,
+                                                 ring_f32x4 (&acc)[FI][JT]) {
+  static_assert(JT >= 4 && JT <= FI, "a slot holds the rows of either tile");
+  constexpr int kMF = FI * JT;  // products per k-step of 32
+  constexpr int kNR = FI + JT;  // fragment reads per k-step
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t s0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
   // fragment of k-step ks: chunk 4*ks + lane/16 of row lane%16 (+ multiples of 16): ks enters as an exclusive-or with 64*ks
   const uint32_t fo = (lane & 15) * kRingRowBytes + (((lane >> 4) ^ ((lane & 15) >> 1)) * 16);
-  const uint32_t a_at = s0 + (w >> 1) * 128 * kRingRowBytes + fo, b_at = s0 + (w & 1) * (16 * JT) * kRingRowBytes + fo;
+  const uint32_t a_at = s0 + (w >> 1) * (16 * FI) * kRingRowBytes + fo, b_at = s0 + (w & 1) * (16 * JT) * kRingRowBytes + fo;
 
-  ring_u32x4 ua[8], ub[JT], va[8], vb[JT];  // two fragment sets: one is multiplied while the other is read
+  ring_u32x4 ua[FI], ub[JT], va[FI], vb[JT];  // two fragment sets: one is multiplied while the other is read
 
   // stages past the end re-read the last one (in bounds, unused)
   auto koff = [&](int kt) DLLAVA_INLINE { return static_cast<int64_t>(kt < nk ? kt : nk - 1) * (kRingBK * 2); };
@@ -175,23 +190,23 @@ __device__ __forceinline__ void gemm_ring_256(const char* Abase, const uint32_t 
     __builtin_amdgcn_global_load_lds((const DLLAVA_GLB void*)src,
                                      (DLLAVA_LDS void*)(smem + slot + (w + 4 * j) * 1024), 16, 0, 0);
   };
-  auto read1 = [&](ring_u32x4 (&fa)[8], ring_u32x4 (&fb)[JT], uint32_t ab, uint32_t bb, auto I) DLLAVA_INLINE {
+  auto read1 = [&](ring_u32x4 (&fa)[FI], ring_u32x4 (&fb)[JT], uint32_t ab, uint32_t bb, auto I) DLLAVA_INLINE {
     constexpr int i = decltype(I)::value;
-    if constexpr (i < 8)
+    if constexpr (i < FI)
       fa[i] = ring_lds_read16<i * 16 * kRingRowBytes>(ab);
     else
-      fb[i - 8] = ring_lds_read16<(i - 8) * 16 * kRingRowBytes>(bb);
+      fb[i - FI] = ring_lds_read16<(i - FI) * 16 * kRingRowBytes>(bb);
   };
-  auto wait = [&](ring_u32x4 (&fa)[8], ring_u32x4 (&fb)[JT]) DLLAVA_INLINE {
+  auto wait = [&](ring_u32x4 (&fa)[FI], ring_u32x4 (&fb)[JT]) DLLAVA_INLINE {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     ring_tie(fa);
     ring_tie(fb);
   };
   // One k-step: the products of (fa, fb); behind every other one a fragment read of the NEXT k-step into (na, nb),
   // and NL tile loads, evenly spaced, into the slot at byte offset `slot`.  hook(m): what else is to stand behind product m.
-  auto kstep = [&](ring_u32x4 (&fa)[8], ring_u32x4 (&fb)[JT], ring_u32x4 (&na)[8], ring_u32x4 (&nb)[JT], uint32_t ab, uint32_t bb,
+  auto kstep = [&](ring_u32x4 (&fa)[FI], ring_u32x4 (&fb)[JT], ring_u32x4 (&na)[FI], ring_u32x4 (&nb)[JT], uint32_t ab, uint32_t bb,
                    auto IS_A, const char* base, uint32_t slot, auto&& hook) DLLAVA_INLINE {
-    constexpr int NL = decltype(IS_A)::value ? kRingALoads : JT;
+    constexpr int NL = decltype(IS_A)::value ? FI : JT;
     constexpr int kGap = kMF / NL;
     static_for<kMF>([&](auto Mi) DLLAVA_INLINE {
       constexpr int m = decltype(Mi)::value;
@@ -213,12 +228,12 @@ __device__ __forceinline__ void gemm_ring_256(const char* Abase, const uint32_t 
   // Iteration k multiplies stage k.  Behind its first k-step it requests B(k+2) into the slot of A(k-1), behind its
   // second -- after its barrier -- A(k+2) into stage k's own B slot.  The barrier needs A(k+1) and B(k+1): everything
   // but the JT loads of B(k+2).
-  constexpr uint32_t kS = kRingSlotBytes;
+  constexpr uint32_t kS = 32 * FI * kRingRowBytes;
   static_for<JT>([&](auto J) DLLAVA_INLINE { dma(Bbase + koff(0) + gb[J.value], 0 * kS, J.value); });
-  static_for<8>([&](auto J) DLLAVA_INLINE { dma(Abase + koff(0) + ga[J.value], 1 * kS, J.value); });
+  static_for<FI>([&](auto J) DLLAVA_INLINE { dma(Abase + koff(0) + ga[J.value], 1 * kS, J.value); });
   static_for<JT>([&](auto J) DLLAVA_INLINE { dma(Bbase + koff(1) + gb[J.value], 2 * kS, J.value); });
-  static_for<8>([&](auto J) DLLAVA_INLINE { dma(Abase + koff(1) + ga[J.value], 3 * kS, J.value); });
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(JT + 8) : "memory");
+  static_for<FI>([&](auto J) DLLAVA_INLINE { dma(Abase + koff(1) + ga[J.value], 3 * kS, J.value); });
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(JT + FI) : "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("s_nop 15" ::: "memory");  // the accumulators' first values, written by plain instructions, before the first product
   static_for<kNR>([&](auto I) DLLAVA_INLINE { read1(ua, ub, a_at + kS, b_at, I); });
@@ -261,7 +276,7 @@ __device__ __forceinline__ void gemm_ring_256(const char* Abase, const uint32_t 
   // compiler does not know) have been written
   wait(ua, ub);
   asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-  static_for<8>([&](auto I) DLLAVA_INLINE { static_for<JT>([&](auto J) DLLAVA_INLINE { ring_tie_acc(acc[I.value][J.value]); }); });
+  static_for<FI>([&](auto I) DLLAVA_INLINE { static_for<JT>([&](auto J) DLLAVA_INLINE { ring_tie_acc(acc[I.value][J.value]); }); });
 }
 
 // 32*FI x 32*TJ x d tile product for launches whose tiles of 256 rows would leave most of the chip idle: the same wave

@@ -68,12 +68,14 @@ struct LinArgs {
   const int32_t* vis_len;
 };
 
-// A linear layer on the products of gemm_ring.h, one block per compute unit: 32*FI features x 32*JT rows.
-template <int FI, int JT>
-__global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, int n_ft, int n_rt, int per_xcd) {
+// A linear layer on the products of gemm_ring.h, PER_CU blocks per compute unit: 32*FI features x 32*JT rows.
+template <int FI, int JT, int PER_CU>
+__device__ __forceinline__ void lin_ring(const LinArgs& a, int n_ft, int n_rt, int per_xcd) {
   constexpr int kTok = 32 * JT, kFeat = 32 * FI, kChunks = kFeat / 8;
-  constexpr int kDepth = kRingLdsBytes / ((FI + JT) * 32 * kRingRowBytes);  // FI < 8: stages that LDS holds
-  __shared__ __align__(1024) char smem_raw[kRingLdsBytes];
+  constexpr bool kHalves = FI == 8 || (FI == 4 && PER_CU == 2);
+  constexpr int kStage = (FI + JT) * 32 * kRingRowBytes, kDepth = kRingLdsBytes / PER_CU / kStage;  // FI < 8: stages that LDS holds
+  constexpr int kLds = PER_CU == 1 || kHalves ? kRingLdsBytes / PER_CU : kDepth * kStage;
+  __shared__ __align__(1024) char smem_raw[kLds];
   DLLAVA_LDS char* smem = (DLLAVA_LDS char*)smem_raw;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -116,8 +118,8 @@ __global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, in
   for (int i = 0; i < FI; ++i)
 #pragma unroll
     for (int j = 0; j < JT; ++j) acc[i][j] = ring_f32x4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (FI == 8)
-    gemm_ring_256<JT, int64_t>(Wt, ga, reinterpret_cast<const char*>(a.X), gb, K / kRingBK, smem, w, acc);
+  if constexpr (kHalves)
+    gemm_ring_halves<FI, JT>(Wt, ga, reinterpret_cast<const char*>(a.X), gb, K / kRingBK, smem, w, acc);
   else
     gemm_ring_small<FI, JT, kDepth>(Wt, ga, reinterpret_cast<const char*>(a.X), gb, K / kRingBK, smem, w, acc);
   __syncthreads();  // the ring memory becomes the transposed output tile
@@ -191,31 +193,50 @@ __global__ __launch_bounds__(kRingThreads, 1) void lin_ring_kernel(LinArgs a, in
   }
 }
 
-template <int FI, int JT>
+template <int FI, int JT>  // one block per compute unit; the small tile's ring leaves room for a second
+__global__ __launch_bounds__(kRingThreads, FI + JT == 4 ? 2 : 1) void lin_ring_kernel(LinArgs a, int n_ft, int n_rt, int per_xcd) {
+  lin_ring<FI, JT, FI + JT == 4 ? 2 : 1>(a, n_ft, n_rt, per_xcd);
+}
+template <int FI, int JT, int PER_CU>  // tiles that share a compute unit, see ring_pick
+__global__ __launch_bounds__(kRingThreads, PER_CU) void lin_shared_kernel(LinArgs a, int n_ft, int n_rt, int per_xcd) {
+  lin_ring<FI, JT, PER_CU>(a, n_ft, n_rt, per_xcd);
+}
+
+template <int FI, int JT, int SHARED = 0>
 int launch_lin_ring(const LinArgs& a, hipStream_t st) {
   const int64_t n_ft = ceil_div(a.N, 32 * FI), n_rt = ceil_div(a.M, 32 * JT);
   const int64_t per_xcd = ceil_div(n_ft * n_rt, kRingXcds);
   if (per_xcd * kRingXcds > 0x7fffffffLL) DLLAVA_FAIL(DLLAVA_ESHAPE, "linear: too many rows");
-  hipLaunchKernelGGL((lin_ring_kernel<FI, JT>), dim3(static_cast<unsigned>(per_xcd * kRingXcds)), dim3(kRingThreads), 0, st, a,
-                     static_cast<int>(n_ft), static_cast<int>(n_rt), static_cast<int>(per_xcd));
+  void (*kernel)(LinArgs, int, int, int);
+  if constexpr (SHARED > 0)
+    kernel = lin_shared_kernel<FI, JT, SHARED>;
+  else
+    kernel = lin_ring_kernel<FI, JT>;
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(per_xcd * kRingXcds)), dim3(kRingThreads), 0, st, a, static_cast<int>(n_ft),
+                     static_cast<int>(n_rt), static_cast<int>(per_xcd));
   DLLAVA_CHECK_LAUNCH("lin_ring_kernel");
   return DLLAVA_OK;
 }
 
 // The tile that takes least: few rows or features want the small tiles, which leave less of the chip idle (this pick / the
 // best tile of 256 features: 214 rows x 4096 features x 4096 wide 17 / 44 us, 214 x 4096 x 11008 38 / 113, 1000 x 4096 x
-// 11008 80 / 118, 2000 x 512 x 4096 17 / 45; 3982 x 4096 x 4096 takes the latter, 96).
+// 11008 80 / 118, 2000 x 512 x 4096 17 / 45; 3982 x 4096 x 4096 takes the latter, 96).  Of the 64 x 64 tiles the ring of five
+// stages (two blocks' worth of LDS in a compute unit) is never behind the one of ten that it replaced (66 rows x 11008 x 4096 27.6 /
+// 29.9, 214 x 512 x 2048 9.4 / 9.8); rings of three, three blocks to a compute unit, win while one round of them does and the rows are
+// short (512 wide: 576 rows x 2048 features 6.7 / 7.7, 1152 x 2048 9.1 / 11.1, 11520 x 256 9.6 / 11.4; 2048 wide, 2304 x 512 15.3 / 13.8).
 int launch_lin(const LinArgs& a, hipStream_t st) {
   const RingTile* t = ring_pick(a.K, launch_override(DLLAVA_LAUNCH_LINEAR_TILE), [&](const RingTile& c) -> int64_t {
     if (c.id == 10) return 0;  // 64 x 128 does the same with its roles exchanged, and reads fewer of the weights per block
     if (c.fi == 8 && static_cast<int64_t>(a.K) * 512 >= (int64_t{1} << 32)) return 0;  // 32-bit lane offsets into the rows of a W tile
     return ceil_div(a.M, 32 * c.jt) * ceil_div(a.N, 32 * c.fi);
-  });
+  }, a.act == 1);
   switch (t->id) {
     case 1: return launch_lin_ring<2, 2>(a, st);
     case 2: return launch_lin_ring<2, 4>(a, st);
     case 3: return launch_lin_ring<4, 4>(a, st);
     case 9: return launch_lin_ring<4, 6>(a, st);
+    case 11: return launch_lin_ring<2, 2, 3>(a, st);
+    case kRingGeluPair: return launch_lin_ring<4, 4, 2>(a, st);
     case 4: return launch_lin_ring<8, 4>(a, st);
     case 5: return launch_lin_ring<8, 5>(a, st);
     case 6: return launch_lin_ring<8, 6>(a, st);

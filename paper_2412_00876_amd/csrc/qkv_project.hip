@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void qkv_ring_kernel(QkvArgs a, Ro
     for (int j = 0; j < JB; ++j) acc[i][j] = ring_f32x4{0.f, 0.f, 0.f, 0.f};
   const char *Ab = static_cast<const char*>(a.W[which]), *Bb = static_cast<const char*>(a.x);
   if constexpr (FI == 8)
-    gemm_ring_256<JB, uint32_t>(Ab, ga, Bb, gb, static_cast<int>(d / kRingBK), smem, w, acc);
+    gemm_ring_halves<FI, JB>(Ab, ga, Bb, gb, static_cast<int>(d / kRingBK), smem, w, acc);
   else
     gemm_ring_small<FI, JB, kDepth>(Ab, ga, Bb, gb, static_cast<int>(d / kRingBK), smem, w, acc);
   __syncthreads();  // the ring memory becomes the transposed output tile
@@ -287,7 +287,7 @@ int launch_mfma(const QkvArgs& a, int64_t rows, double base, hipStream_t st) {
   const int forced = launch_override(DLLAVA_LAUNCH_QKV_TILE);
   auto heads_tiles = [&](const RingTile& c) -> int64_t { return 3 * ceil_div(a.H, c.fi / 4); };
   const RingTile* t = ring_pick(a.d, forced == 1 ? 3 : forced, [&](const RingTile& c) -> int64_t {
-    if (c.fi < 4) return 0;
+    if (c.per_cu > 1 || c.fi < 4) return 0;
     const bool fits = static_cast<int64_t>(a.H) * 128 * a.d * 2 < (int64_t{1} << 32) && rows * a.ldx * 2 < (int64_t{1} << 32);
     const int64_t n = ceil_div(rows, 32 * c.jt) * heads_tiles(c);
     return (c.fi == 8 && !fits) || n > 0x7fffffffLL - 8 ? 0 : n;

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void score_ring_kernel(ScoreArgs a
     for (int j = 0; j < JB; ++j) acc[i][j] = ring_f32x4{0.f, 0.f, 0.f, 0.f};
   const char *Ab = static_cast<const char*>(a.W1), *Bb = static_cast<const char*>(a.x);
   if constexpr (FI == 8)
-    gemm_ring_256<JB, int64_t>(Ab, ga, Bb, gb, static_cast<int>(d / kRingBK), smem, w, acc);
+    gemm_ring_halves<FI, JB>(Ab, ga, Bb, gb, static_cast<int>(d / kRingBK), smem, w, acc);
   else
     gemm_ring_small<FI, JB, kDepth>(Ab, ga, Bb, gb, static_cast<int>(d / kRingBK), smem, w, acc);
 
@@ -250,7 +250,7 @@ int score_mfma_launch(const ScoreArgs& a, hipStream_t st) {
   const int forced = launch_override(DLLAVA_LAUNCH_SCORE_TILE);
   const RingTile* t = ring_pick(a.d, forced == 1 ? 3 : forced, [&](const RingTile& c) -> int64_t {
     const int64_t n_mt = ceil_div(a.M, 32 * c.jt), n = n_mt * ceil_div(a.dh, 32 * c.fi);
-    if (c.fi < 4 || n_mt > kMaxCounters || n > 0x7fffffffLL - 8) return 0;
+    if (c.per_cu > 1 || c.fi < 4 || n_mt > kMaxCounters || n > 0x7fffffffLL - 8) return 0;
     return c.fi == 8 && a.dh * a.d * 2 >= (int64_t{1} << 32) ? 0 : n;
   });
   if (!t) return 1;
