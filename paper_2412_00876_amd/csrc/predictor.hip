@@ -8,7 +8,7 @@
 //                      pieces.  The first layer gathers its rows from the vision spans.
 //  * ln_kernel         LayerNorm of 512-wide rows, one wave per row, the row held in registers.
 //  * attention         prefill_mfma_kernel without the causal mask, 8 heads of 64, one "sequence" per span.
-//  * head_out_kernel   the last layer 128 -> 2, one wave per row.
+//  * head_kernel       the head 512 -> 256 -> 128 -> 2 in one launch.
 //  * small_in_kernel, small_head_kernel   the whole text form on at most 64 rows (a decode step), see below.
 // The same file holds the remaining layers of a LLaMA-family decoder layer (Eq. 2-3 of the paper name only W^Q, W^K,
 // W^V, W^O and an FFN; RMSNorm, rotary positions and the gated FFN are the family's):
@@ -245,12 +245,40 @@ int launch_lin(const LinArgs& a, hipStream_t st) {
   }
 }
 
+// span_off[b] = sum of the span lengths before b (one wave; B+1 entries); without spans: {0, M}
+__device__ __forceinline__ void span_offsets(const int32_t* __restrict__ vis_len, int32_t B, int64_t M, int32_t* __restrict__ span_off) {
+  const int lane = threadIdx.x & (kWave - 1);
+  if (!vis_len) {
+    if (lane == 0) {
+      span_off[0] = 0;
+      span_off[1] = static_cast<int32_t>(M);
+    }
+    return;
+  }
+  int carry = 0;
+  if (lane == 0) span_off[0] = 0;
+  for (int base = 0; base < B; base += kWave) {
+    const int i = base + lane;
+    int n = i < B ? vis_len[i] : 0;
+    if (n < 0) n = 0;
+    const int incl = wave_incl_scan(n);
+    if (i < B) span_off[i + 1] = carry + incl;
+    carry += __shfl(incl, kWave - 1, kWave);
+  }
+}
+__global__ __launch_bounds__(kWave) void span_offsets_kernel(const int32_t* __restrict__ vis_len, int32_t B, int64_t M,
+                                                             int32_t* __restrict__ span_off) {
+  span_offsets(vis_len, B, M, span_off);
+}
+
 // LayerNorm over rows of 512: lane holds 8 consecutive elements; mean and biased variance in two passes over the
-// registers.
+// registers.  With span_off: the span offsets are written on the way, for the attention two launches on (a launch of their own takes
+// 2 us, more between two others).
 __global__ __launch_bounds__(256) void ln_kernel(const bf16_t* __restrict__ Z, bf16_t* __restrict__ Y,
                                                  const float* __restrict__ gam, const float* __restrict__ bet,
-                                                 int64_t M) {
+                                                 int64_t M, const int32_t* __restrict__ vis_len, int32_t B, int32_t* __restrict__ span_off) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  if (span_off && blockIdx.x == 0 && w == 0) span_offsets(vis_len, B, M, span_off);
   const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + w;
   if (row >= M) return;
   const uint4 raw = *reinterpret_cast<const uint4*>(Z + row * kPW + lane * 8);
@@ -294,52 +322,6 @@ __global__ __launch_bounds__(256) void ln_kernel(const bf16_t* __restrict__ Z, b
   o.w = pack_bf16x2(y[6], y[7]);
   *reinterpret_cast<uint4*>(Y + row * kPW + lane * 8) = o;
 }
-
-// last layer of the head: D[m] = h[m] W^T + b, h [M, 128], W [2, 128]; one wave per row, lane holds two inputs
-__global__ __launch_bounds__(256) void head_out_kernel(const bf16_t* __restrict__ Hd, const bf16_t* __restrict__ W,
-                                                       const float* __restrict__ b, float* __restrict__ logits,
-                                                       int64_t M, const int32_t* __restrict__ span_off, int32_t B) {
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + w;
-  const int64_t total = span_off ? span_off[B] : M;  // rows beyond the spans are left untouched
-  if (row >= M || row >= total) return;
-  const uint32_t x = *reinterpret_cast<const uint32_t*>(Hd + row * kPH2 + lane * 2);
-  const uint32_t w0 = *reinterpret_cast<const uint32_t*>(W + lane * 2);
-  const uint32_t w1 = *reinterpret_cast<const uint32_t*>(W + kPH2 + lane * 2);
-  const float x0 = bf16lo_to_f32(x), x1 = bf16hi_to_f32(x);
-  float p0 = fmaf(x1, bf16hi_to_f32(w0), x0 * bf16lo_to_f32(w0));
-  float p1 = fmaf(x1, bf16hi_to_f32(w1), x0 * bf16lo_to_f32(w1));
-  p0 = wave_sum(p0);
-  p1 = wave_sum(p1);
-  if (lane == 0) {
-    logits[2 * row] = p0 + (b ? b[0] : 0.f);
-    logits[2 * row + 1] = p1 + (b ? b[1] : 0.f);
-  }
-}
-
-// span_off[b] = sum of the span lengths before b (one wave; B+1 entries); without spans: {0, M}
-__global__ __launch_bounds__(kWave) void span_offsets_kernel(const int32_t* __restrict__ vis_len, int32_t B, int64_t M,
-                                                             int32_t* __restrict__ span_off) {
-  const int lane = threadIdx.x;
-  if (!vis_len) {
-    if (lane == 0) {
-      span_off[0] = 0;
-      span_off[1] = static_cast<int32_t>(M);
-    }
-    return;
-  }
-  int carry = 0;
-  if (lane == 0) span_off[0] = 0;
-  for (int base = 0; base < B; base += kWave) {
-    const int i = base + lane;
-    int n = i < B ? vis_len[i] : 0;
-    if (n < 0) n = 0;
-    const int incl = wave_incl_scan(n);
-    if (i < B) span_off[i + 1] = carry + incl;
-    carry += __shfl(incl, kWave - 1, kWave);
-  }
-}
-
 
 // ---- the output-text predictor on a handful of rows (one per sequence and decode step) ---------------------------
 // With at most 64 rows the tile kernel above would pull the 2*512*d bytes of W_in through four compute units.
@@ -962,6 +944,161 @@ __global__ __launch_bounds__(256) void small_head_kernel(const float* __restrict
   }
 }
 
+// The head 512 -> 256 -> 128 -> 2 on the rows of Z, one launch: a persistent block holds the weights of both layers in registers as
+// matrix-core fragments (turned once, through LDS) and takes tiles of 32 rows; only the rows' own values pass through LDS.  The same
+// products, epilogues and orders of sums as linear layers of those shapes and a wave per row for the last layer, so the same bits.
+// As three launches (two linear layers, a wave per row) the head was latency three times over: 9.6 + 6.1 + 4.8 us and the gaps between
+// them at 11520 rows, now 18.5; with the span offsets' launch gone as well the image predictor takes 123.9 instead of 128.6 us on one
+// picture of 576 tokens, 270 instead of 281 on one of 2880, 645 instead of 660 on four of those.
+constexpr int kHeadRows = 32, kHeadBlocks = 256, kHeadThreads = 512;  // one block per compute unit: 91 KiB of LDS, 242 registers
+__global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(const bf16_t* __restrict__ Z, int64_t M, const bf16_t* __restrict__ W1,
+                                                      const float* __restrict__ b1, const bf16_t* __restrict__ W2,
+                                                      const float* __restrict__ b2, const bf16_t* __restrict__ W3,
+                                                      const float* __restrict__ b3, float* __restrict__ logits,
+                                                      const int32_t* __restrict__ vis_len, int32_t B, int64_t n_tiles) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  __shared__ __align__(16) bf16_t zT[kHeadRows * kZs];
+  __shared__ __align__(16) bf16_t h1T[kHeadRows * kH1s];
+  __shared__ __align__(16) bf16_t h2T[kHeadRows * kH2s];
+  __shared__ __align__(16) bf16_t stage[8][32 * 64];  // per wave: 32 weight rows x 64 elements
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+  const int r16 = lane & 15, g = lane >> 4, lr8 = lane >> 3, lc = lane & 7;
+  constexpr int kPieces = kHeadRows * kPW / 8 / kHeadThreads;  // 16-byte pieces of a tile per thread
+  ring_u32x4 zr[kPieces];
+  auto want_rows = [&](int64_t tile) DLLAVA_INLINE {
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+      const int at = kHeadThreads * u + tid;
+      int64_t m = tile * kHeadRows + at / (kPW / 8);
+      if (m >= M) m = M - 1;  // rows past M are computed and dropped
+      zr[u] = *reinterpret_cast<const ring_u32x4*>(Z + m * kPW + at % (kPW / 8) * 8);
+    }
+  };
+  want_rows(blockIdx.x);
+  const uint32_t w30 = *reinterpret_cast<const uint32_t*>(W3 + lane * 2), w31 = *reinterpret_cast<const uint32_t*>(W3 + kPH2 + lane * 2);
+  int64_t total = M;
+  if (vis_len) {  // rows beyond the spans are left untouched
+    int n = 0;
+    for (int b = lane; b < B; b += kWave) n += vis_len[b] > 0 ? vis_len[b] : 0;
+    total = wave_sum_i(n);
+  }
+  bf16_t* st = stage[w];
+  const int st_off = lr8 * 64 + ((lc ^ ((lr8 >> 1) & 3)) * 8);   // row 8j + lane/8: ((8j + lr8) / 2) % 8 = 4*(j%2) + lr8/2
+  const int fr_off = r16 * 64 + ((g ^ ((r16 >> 1) & 7)) * 8);    // row lane%16 (+ 16i), chunk 4*ks + lane/16
+  // Weights: wave w has features 32w .. 32w+31 of the first layer and 16w .. 16w+15 of the second.  Half of the first layer's are on
+  // their way while the other half is turned.
+  ring_u32x4 f1[16][2], f2[8];  // [k-step of 32][16 features]
+  ring_u32x4 wa[4][4], wb[4][4];  // [rows 8j + lane/8][elements 64c + 8 (lane%8) ..]
+  const bf16_t *w1 = W1 + static_cast<int64_t>(32 * w + lr8) * kPW + 8 * lc, *w2 = W2 + static_cast<int64_t>(16 * w + lr8) * kPH1 + 8 * lc;
+  auto turn = [&](const ring_u32x4 (&v)[4][4], auto C0, auto NJ, auto&& to) DLLAVA_INLINE {
+    static_for<4>([&](auto C) DLLAVA_INLINE {
+      wave_lds_order();
+      static_for<NJ.value>([&](auto J) DLLAVA_INLINE {
+        *reinterpret_cast<ring_u32x4*>(st + 8 * J.value * 64 + (st_off ^ ((J.value & 1) * 32))) = v[J.value][C.value];
+      });
+      wave_lds_order();
+      static_for<2>([&](auto S) DLLAVA_INLINE {
+        static_for<NJ.value / 2>([&](auto I) DLLAVA_INLINE {
+          to(std::integral_constant<int, 2 * (C0.value + C.value) + S.value>{}, I,
+             *reinterpret_cast<const ring_u32x4*>(st + 16 * I.value * 64 + (fr_off ^ (S.value * 32))));
+        });
+      });
+    });
+  };
+  auto load1 = [&](ring_u32x4 (&v)[4][4], int c0) DLLAVA_INLINE {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j][c] = *reinterpret_cast<const ring_u32x4*>(w1 + 8 * j * kPW + 64 * (c0 + c));
+  };
+  auto to1 = [&](auto S, auto I, const ring_u32x4& v) DLLAVA_INLINE { f1[S.value][I.value] = v; };
+  using I0 = std::integral_constant<int, 0>;
+  using I4 = std::integral_constant<int, 4>;
+  load1(wa, 0);
+  load1(wb, 4);
+  __builtin_amdgcn_sched_barrier(0);
+  turn(wa, I0{}, I4{}, to1);
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) wa[j][c] = *reinterpret_cast<const ring_u32x4*>(w2 + 8 * j * kPH1 + 64 * c);
+  __builtin_amdgcn_sched_barrier(0);
+  turn(wb, I4{}, I4{}, to1);
+  turn(wa, I0{}, std::integral_constant<int, 2>{}, [&](auto S, auto, const ring_u32x4& v) DLLAVA_INLINE { f2[S.value] = v; });
+  for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+      const int at = kHeadThreads * u + tid;
+      *reinterpret_cast<ring_u32x4*>(zT + at / (kPW / 8) * kZs + at % (kPW / 8) * 8) = zr[u];
+    }
+    __syncthreads();
+    if (tile + gridDim.x < n_tiles) want_rows(tile + gridDim.x);
+    {  // h1 = GELU(W1 z + b1)
+      f32x4 acc[2][2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      static_for<16>([&](auto S) DLLAVA_INLINE {
+        static_for<2>([&](auto J) DLLAVA_INLINE {
+          const bf16x8 bz = as_frag(*reinterpret_cast<const uint4*>(zT + (16 * J.value + r16) * kZs + 32 * S.value + 8 * g));
+          static_for<2>([&](auto I) DLLAVA_INLINE {
+            acc[I.value][J.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f1[S.value][I.value]), bz, acc[I.value][J.value], 0, 0, 0);
+          });
+        });
+      });
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int f = 32 * w + 16 * i + 4 * g;
+        const float4 bs = *reinterpret_cast<const float4*>(b1 ? b1 + f : kZeroWords);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          uint2 v;
+          v.x = pack_bf16x2(gelu_erf_fast(acc[i][j][0] + bs.x), gelu_erf_fast(acc[i][j][1] + bs.y));
+          v.y = pack_bf16x2(gelu_erf_fast(acc[i][j][2] + bs.z), gelu_erf_fast(acc[i][j][3] + bs.w));
+          *reinterpret_cast<uint2*>(h1T + (16 * j + r16) * kH1s + f) = v;
+        }
+      }
+    }
+    __syncthreads();
+    {  // h2 = GELU(W2 h1 + b2)
+      f32x4 acc[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      static_for<8>([&](auto S) DLLAVA_INLINE {
+        static_for<2>([&](auto J) DLLAVA_INLINE {
+          const bf16x8 bh = as_frag(*reinterpret_cast<const uint4*>(h1T + (16 * J.value + r16) * kH1s + 32 * S.value + 8 * g));
+          acc[J.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f2[S.value]), bh, acc[J.value], 0, 0, 0);
+        });
+      });
+      const int f = 16 * w + 4 * g;
+      const float4 bs = *reinterpret_cast<const float4*>(b2 ? b2 + f : kZeroWords);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        uint2 v;
+        v.x = pack_bf16x2(gelu_erf_fast(acc[j][0] + bs.x), gelu_erf_fast(acc[j][1] + bs.y));
+        v.y = pack_bf16x2(gelu_erf_fast(acc[j][2] + bs.z), gelu_erf_fast(acc[j][3] + bs.w));
+        *reinterpret_cast<uint2*>(h2T + (16 * j + r16) * kH2s + f) = v;
+      }
+    }
+    __syncthreads();
+    // the last layer: a wave per row, a lane two inputs
+#pragma unroll
+    for (int u = 0; u < kHeadRows / 8; ++u) {
+      const int row = kHeadRows / 8 * w + u;
+      const int64_t m = tile * kHeadRows + row;
+      const uint32_t x = *reinterpret_cast<const uint32_t*>(h2T + row * kH2s + lane * 2);
+      const float x0 = bf16lo_to_f32(x), x1 = bf16hi_to_f32(x);
+      const float p0 = wave_sum(fmaf(x1, bf16hi_to_f32(w30), x0 * bf16lo_to_f32(w30)));
+      const float p1 = wave_sum(fmaf(x1, bf16hi_to_f32(w31), x0 * bf16lo_to_f32(w31)));
+      if (lane == 0 && m < M && m < total) {
+        logits[2 * m] = p0 + (b3 ? b3[0] : 0.f);
+        logits[2 * m + 1] = p1 + (b3 ? b3[1] : 0.f);
+      }
+    }
+  }
+}
+
 // RMSNorm of d-wide rows: y = x / sqrt(mean(x^2) + eps) * w.  One wave per row, the row held in registers
 // (16-byte pieces, lane-strided: up to 16 pieces = 8192 elements), sum of squares in float32.
 constexpr int kRmsMaxPieces = 16;
@@ -1161,8 +1298,8 @@ extern "C" int dllava_predict(const void* x, int64_t ldx, int64_t M, int32_t B, 
     return a;
   };
 
-  if (nb > 0 || seq_off) {
-    hipLaunchKernelGGL(span_offsets_kernel, dim3(1), dim3(kWave), 0, st, seq_off ? vis_len : nullptr, B, M, r.span_off);
+  if (nb == 0 && M <= kSmallRows && seq_off) {
+    hipLaunchKernelGGL(span_offsets_kernel, dim3(1), dim3(kWave), 0, st, vis_len, B, M, r.span_off);
     DLLAVA_CHECK_LAUNCH("span_offsets_kernel");
   }
   if (nb == 0 && M <= kSmallRows) {  // a handful of rows: the output-text predictor of a decode step
@@ -1192,7 +1329,8 @@ extern "C" int dllava_predict(const void* x, int64_t ldx, int64_t M, int32_t B, 
   const unsigned row_blocks = static_cast<unsigned>(ceil_div(M, 4));
   for (int i = 0; i < nb; ++i) {
     const dllava_vit_block& k = p->blocks[i];
-    hipLaunchKernelGGL(ln_kernel, dim3(row_blocks), dim3(256), 0, st, r.Z, r.Y, k.ln1_g, k.ln1_b, M);
+    hipLaunchKernelGGL(ln_kernel, dim3(row_blocks), dim3(256), 0, st, r.Z, r.Y, k.ln1_g, k.ln1_b, M,
+                       seq_off ? vis_len : nullptr, B, i == 0 ? r.span_off : nullptr);
     DLLAVA_CHECK_LAUNCH("ln_kernel");
     {  // q | k | v into three [M, 512] matrices
       LinArgs a = lin(r.Y, kPW, kPW, k.Wqkv, k.bqkv, 3 * kPW, r.QKV, kPW, 0, nullptr);
@@ -1211,16 +1349,17 @@ extern "C" int dllava_predict(const void* x, int64_t ldx, int64_t M, int32_t B, 
       if (rc > 0) DLLAVA_FAIL(DLLAVA_ESHAPE, "predict: too many rows or spans for the attention step");
     }
     if (int rc = launch_lin(lin(r.Y, kPW, kPW, k.Wo, k.bo, kPW, r.Z, kPW, 0, r.Z), st)) return rc;
-    hipLaunchKernelGGL(ln_kernel, dim3(row_blocks), dim3(256), 0, st, r.Z, r.Y, k.ln2_g, k.ln2_b, M);
+    hipLaunchKernelGGL(ln_kernel, dim3(row_blocks), dim3(256), 0, st, r.Z, r.Y, k.ln2_g, k.ln2_b, M, nullptr, 0,
+                       nullptr);
     DLLAVA_CHECK_LAUNCH("ln_kernel");
     if (int rc = launch_lin(lin(r.Y, kPW, kPW, k.Wfc1, k.bfc1, kPMlp, r.Hb, kPMlp, 1, nullptr), st)) return rc;
     if (int rc = launch_lin(lin(r.Hb, kPMlp, kPMlp, k.Wfc2, k.bfc2, kPW, r.Z, kPW, 0, r.Z), st)) return rc;
   }
-  if (int rc = launch_lin(lin(r.Z, kPW, kPW, p->W_h1, p->b_h1, kPH1, r.Hb, kPH1, 1, nullptr), st)) return rc;
-  if (int rc = launch_lin(lin(r.Hb, kPH1, kPH1, p->W_h2, p->b_h2, kPH2, r.Y, kPH2, 1, nullptr), st)) return rc;
-  hipLaunchKernelGGL(head_out_kernel, dim3(row_blocks), dim3(256), 0, st, r.Y, static_cast<const bf16_t*>(p->W_h3),
-                     p->b_h3, logits, M, seq_off ? r.span_off : nullptr, B);
-  DLLAVA_CHECK_LAUNCH("head_out_kernel");
+  const int64_t n_tiles = ceil_div(M, kHeadRows);
+  hipLaunchKernelGGL(head_kernel, dim3(static_cast<unsigned>(n_tiles < kHeadBlocks ? n_tiles : kHeadBlocks)), dim3(kHeadThreads), 0, st, r.Z, M,
+                     static_cast<const bf16_t*>(p->W_h1), p->b_h1, static_cast<const bf16_t*>(p->W_h2), p->b_h2,
+                     static_cast<const bf16_t*>(p->W_h3), p->b_h3, logits, seq_off ? vis_len : nullptr, B, n_tiles);
+  DLLAVA_CHECK_LAUNCH("head_kernel");
   return DLLAVA_OK;
 }
 
@@ -1260,7 +1399,7 @@ extern "C" int dllava_layer_norm(const void* z, int64_t M, const float* gamma, c
                  "layer_norm: z, y, gamma, beta must be 16-byte aligned");
   hipLaunchKernelGGL(ln_kernel, dim3(static_cast<unsigned>(ceil_div(M, 4))), dim3(256), 0,
                      static_cast<hipStream_t>(stream), static_cast<const bf16_t*>(z), static_cast<bf16_t*>(y), gamma,
-                     beta, M);
+                     beta, M, nullptr, 0, nullptr);
   DLLAVA_CHECK_LAUNCH("ln_kernel");
   return DLLAVA_OK;
 }
