@@ -463,7 +463,7 @@ __global__ __launch_bounds__(256) void small_in_kernel(const bf16_t* __restrict_
   // The blocks past the product's bring the head's weights into the second-level cache of the dies that small_head_kernel
   // runs on next, where one compute unit pulls all 320 KiB of them: block 8p + x, on die x like block x of that launch,
   // reads part p while the others stream W_in.  At the end of a decode step over whole layers, whose weights leave nothing
-  // cached, that took small_head_kernel from 19.8 to 12.0 us (8 rows), with this launch at 6.1 us as before.
+  // cached, that took small_head_kernel (then of 4 waves) from 19.8 to 12.0 us (8 rows), with this launch at 6.1 us as before.
   if (static_cast<int>(blockIdx.x) >= n_fg * KQ) {
     const int p = (static_cast<int>(blockIdx.x) - n_fg * KQ) / kSmallXcds;
     if (static_cast<int>(blockIdx.x) % kSmallXcds >= NT) return;
@@ -778,151 +778,164 @@ void launch_few_fused(int nt, hipStream_t st, const bf16_t* X, int64_t ldx, int 
   else launch_few_as<EPI, false>(nt, st, X, ldx, M, K, W0, W1, W2, n_fg, KQ, fg_each, ep);
 }
 
-__global__ __launch_bounds__(256) void small_head_kernel(const float* __restrict__ partial, int rows_pad, int M,
-                                                         const float* __restrict__ b_in,
-                                                         const bf16_t* __restrict__ W1, const float* __restrict__ b1,
-                                                         const bf16_t* __restrict__ W2, const float* __restrict__ b2,
-                                                         const bf16_t* __restrict__ W3, const float* __restrict__ b3,
-                                                         float* __restrict__ logits,
-                                                         const int32_t* __restrict__ span_off, int32_t B) {
+// One block's chain of trips to memory and LDS is all there is to this launch, so everything it reads is asked for at its start, the
+// partial sums first: they arrive and are rounded into LDS while the weights of the first layer still come in, and the product takes
+// those 64 elements at a time in the order they arrive.  Biases wait in LDS.  8 waves, 32 features of the first layer and 16 rows of
+// the second's weights each.  With 4 waves, the weights waited for together and the biases and the row count fetched where they are
+// used, the whole predictor took 15.8 us on 8 rows, 17.2 on 16 and 19.8 on 32 (d = 4096); now 14.2, 14.9 and 16.4.  NZ: groups of 8
+// rows that may exist, so that fewer rows hold fewer registers and all their loads fit in flight together; the rows past them are
+// undefined in LDS, and a row only ever influences its own outputs.
+template <int NZ>
+__global__ __launch_bounds__(512, 2) void small_head_kernel(const float* __restrict__ partial, int rows_pad, int M,
+                                                            const float* __restrict__ b_in,
+                                                            const bf16_t* __restrict__ W1, const float* __restrict__ b1,
+                                                            const bf16_t* __restrict__ W2, const float* __restrict__ b2,
+                                                            const bf16_t* __restrict__ W3, const float* __restrict__ b3,
+                                                            float* __restrict__ logits,
+                                                            const int32_t* __restrict__ span_off, int32_t B) {
   __shared__ __align__(16) bf16_t zT[32 * kZs];
   __shared__ __align__(16) bf16_t h1T[32 * kH1s];
-  __shared__ __align__(16) bf16_t h2T[32 * kH2s];
-  __shared__ __align__(16) bf16_t stage[4][64 * 64];  // per wave: 64 weight rows x 64 elements
-  __shared__ float w3s[2 * kPH2];
+  __shared__ __align__(16) bf16_t stage[8][32 * 64];  // per wave: 32 weight rows x 64 elements
+  __shared__ __align__(16) bf16_t w2T[4][4][32 * 64];  // second layer: [32 features][64 elements]
+  __shared__ __align__(16) float w3s[2 * kPH2], b1s[kPH1], b2s[kPH2];
+  bf16_t* h2T = zT;  // z is read before the barrier that h2 is written behind
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   const int r = lane & 31, g = lane >> 5;
   const int lr8 = lane >> 3, lc = lane & 7;
   const int t0 = blockIdx.x * 32;
-  const bf16_t w3v = W3[tid];  // last layer's 2 x 128 weights: one per thread, into LDS before the first barrier
-  // The weights of both layers, requested before anything else: wave w owns features 64w..64w+63 of the first layer
-  // and 32w..32w+31 of the second.  Register [j][c] of a lane: row 8j + lane/8 of the wave's rows, elements
-  // 64c + 8*(lane%8) .. +7.
-  uint4 w1r[8][8], w2r[4][4];
-#pragma unroll
-  for (int j = 0; j < 8; ++j)
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-      w1r[j][c] = *reinterpret_cast<const uint4*>(W1 + static_cast<int64_t>(64 * w + 8 * j + lr8) * kPW + 64 * c + 8 * lc);
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      w2r[j][c] = *reinterpret_cast<const uint4*>(W2 + static_cast<int64_t>(32 * w + 8 * j + lr8) * kPH1 + 64 * c + 8 * lc);
-  // z = bias + the partial sums, in a fixed order, rounded to the storage type: rows of this tile that exist only
-  // (the others stay undefined in LDS: a row only ever influences its own outputs, which are dropped), four
-  // items per thread at a time; the loads of the first four are issued together with the weights.
   const int n_valid = M - t0 < 32 ? M - t0 : 32;
-  const int items = n_valid * (kPW / 4);
-  float4 sum[4], pq[4][kSmallSplit];
-  auto z_load = [&](int base) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  // z = bias + the partial sums, in a fixed order, rounded to the storage type; a group of 8 rows is two items of four features per
+  // thread.  Rows past the last repeat it.
+  constexpr int kGroups = NZ == 1 ? 1 : 2;  // groups in flight
+  f32x4 sum[kGroups][2], pq[kGroups][2][kSmallSplit];
+  auto z_load = [&](auto G, int group) DLLAVA_INLINE {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      int it = base + 256 * u + tid;
-      if (it >= items) it = items - 1;
-      const int tok = it / (kPW / 4), f = (it % (kPW / 4)) * 4;
-      sum[u] = *reinterpret_cast<const float4*>(b_in ? b_in + f : kZeroWords);
+    for (int u = 0; u < 2; ++u) {
+      int tok = 8 * group + 4 * u + tid / (kPW / 4);
+      if (tok >= n_valid) tok = n_valid - 1;
+      const int f = tid % (kPW / 4) * 4;
+      sum[G.value][u] = *reinterpret_cast<const f32x4*>(b_in ? b_in + f : kZeroWords);
 #pragma unroll
       for (int q = 0; q < kSmallSplit; ++q)
-        pq[u][q] = *reinterpret_cast<const float4*>(partial + static_cast<int64_t>(q * rows_pad + t0 + tok) * kPW + f);
+        pq[G.value][u][q] = *reinterpret_cast<const f32x4*>(partial + static_cast<int64_t>(q * rows_pad + t0 + tok) * kPW + f);
     }
   };
-  auto z_finish = [&](int base) {
+  auto z_finish = [&](auto G, int group) DLLAVA_INLINE {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int it = base + 256 * u + tid;
-      if (it < items) {
-        const int tok = it / (kPW / 4), f = (it % (kPW / 4)) * 4;
+    for (int u = 0; u < 2; ++u) {
+      f32x4 z = sum[G.value][u];
 #pragma unroll
-        for (int q = 0; q < kSmallSplit; ++q) {
-          sum[u].x += pq[u][q].x; sum[u].y += pq[u][q].y; sum[u].z += pq[u][q].z; sum[u].w += pq[u][q].w;
-        }
-        uint2 v;
-        v.x = pack_bf16x2(sum[u].x, sum[u].y);
-        v.y = pack_bf16x2(sum[u].z, sum[u].w);
-        *reinterpret_cast<uint2*>(zT + tok * kZs + f) = v;
-      }
+      for (int q = 0; q < kSmallSplit; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] += pq[G.value][u][q][e];
+      uint2 v;
+      v.x = pack_bf16x2(z[0], z[1]);
+      v.y = pack_bf16x2(z[2], z[3]);
+      *reinterpret_cast<uint2*>(zT + (8 * group + 4 * u + tid / (kPW / 4)) * kZs + tid % (kPW / 4) * 4) = v;
     }
   };
-  z_load(0);
-  // The weights are wanted in registers HERE, all loads of a lane in flight together: without a use at this point
-  // the compiler moves each load down to its slice of the product, one memory round trip per slice.
+  // Wave w owns features 32w .. 32w+31 of the first layer and rows 16w .. 16w+15 of the second's weights.  Register [j][c] of a lane:
+  // row 8j + lane/8 of the wave's rows, elements 64c + 8*(lane%8) .. +7.
+  ring_u32x4 w1r[4][8], w2r[2][4];
+  auto w1_load = [&](int c0) DLLAVA_INLINE {
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
+    for (int c = c0; c < c0 + 4; ++c)
 #pragma unroll
-    for (int c = 0; c < 8; ++c) want_now(w1r[j][c]);
+      for (int j = 0; j < 4; ++j)
+        w1r[j][c] = *reinterpret_cast<const ring_u32x4*>(W1 + static_cast<int64_t>(32 * w + 8 * j + lr8) * kPW + 64 * c + 8 * lc);
+  };
+  auto rest_load = [&]() DLLAVA_INLINE {
+    w1_load(4);
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) want_now(w2r[j][c]);
-  w3s[tid] = bf16_to_f32(w3v);
-  z_finish(0);
-  for (int base = 4 * 256; base < items; base += 4 * 256) {
-    z_load(base);
-    z_finish(base);
+      for (int j = 0; j < 2; ++j)
+        w2r[j][c] = *reinterpret_cast<const ring_u32x4*>(W2 + static_cast<int64_t>(16 * w + 8 * j + lr8) * kPH1 + 64 * c + 8 * lc);
+  };
+  using G0 = std::integral_constant<int, 0>;
+  using G1 = std::integral_constant<int, kGroups - 1>;
+  const int64_t lim = span_off ? span_off[B] : M;
+  const float b3v = b3 ? b3[(tid >> 2) & 1] : 0.f;
+  const bf16_t w3v = W3[tid & (2 * kPH2 - 1)];
+  const float b1v = b1 ? b1[tid & (kPH1 - 1)] : 0.f, b2v = b2 ? b2[tid & (kPH2 - 1)] : 0.f;
+#pragma unroll
+  for (int group = 0; group + kGroups < NZ; group += kGroups) {  // only with more than 16 rows
+    z_load(G0{}, group);
+    z_load(G1{}, group + 1);
+    z_finish(G0{}, group);
+    z_finish(G1{}, group + 1);
+  }
+  z_load(G0{}, NZ - kGroups);
+  if constexpr (kGroups == 2) z_load(G1{}, NZ - 1);
+  w1_load(0);
+  if constexpr (kGroups == 1) rest_load();
+  __builtin_amdgcn_sched_barrier(0);  // every load above is on its way before the first is waited for
+  if (tid < 2 * kPH2) w3s[tid] = bf16_to_f32(w3v);
+  if (tid < kPH1) b1s[tid] = b1v;
+  if (tid < kPH2) b2s[tid] = b2v;
+  z_finish(G0{}, NZ - kGroups);
+  if constexpr (kGroups == 2) {
+    z_finish(G1{}, NZ - 1);
+    rest_load();
+    __builtin_amdgcn_sched_barrier(0);
   }
   __syncthreads();
   bf16_t* st = stage[w];
   const int st_off = lr8 * 64 + ((lc ^ ((lr8 >> 1) & 3)) * 8);  // row 8j + lane/8: ((8j + lr8) / 2) % 8 = 4*(j%2) + lr8/2
-  const int fr_off = r * 64 + ((g ^ ((r >> 1) & 7)) * 8);       // row r (+32), chunk 2s + g
-  {  // h1 = GELU(W1 z + b1): two 32-feature tiles per wave
-    f32x16 a0, a1;
+  const int fr_off = r * 64 + ((g ^ ((r >> 1) & 7)) * 8);       // row r, chunk 2s + g
+  {  // h1 = GELU(W1 z + b1): 32 features per wave
+    f32x16 a;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) a0[i] = a1[i] = 0.f;
+    for (int i = 0; i < 16; ++i) a[i] = 0.f;
     const bf16_t* zb = zT + r * kZs + 8 * g;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       wave_lds_order();
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        *reinterpret_cast<uint4*>(st + 8 * j * 64 + (st_off ^ ((j & 1) * 32))) = w1r[j][c];
+      for (int j = 0; j < 4; ++j) *reinterpret_cast<ring_u32x4*>(st + 8 * j * 64 + (st_off ^ ((j & 1) * 32))) = w1r[j][c];
       wave_lds_order();
 #pragma unroll
       for (int sk = 0; sk < 4; ++sk) {
         const bf16x8 bz = as_frag(*reinterpret_cast<const uint4*>(zb + 64 * c + 16 * sk));
         const bf16x8 fa = as_frag(*reinterpret_cast<const uint4*>(st + (fr_off ^ (sk * 16))));
-        const bf16x8 fb = as_frag(*reinterpret_cast<const uint4*>(st + 32 * 64 + (fr_off ^ (sk * 16))));
-        a0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, bz, a0, 0, 0, 0);
-        a1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb, bz, a1, 0, 0, 0);
+        a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, bz, a, 0, 0, 0);
       }
     }
+    // the wave's 16 rows of the second layer's weights: rows 16 (w%2) + 8j + lane/8 of tile w/2
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int f = 64 * w + 32 * i + 8 * q4 + 4 * g;
-        const float4 bs = *reinterpret_cast<const float4*>(b1 ? b1 + f : kZeroWords);
-        const f32x16& a = i ? a1 : a0;
-        uint2 v;
-        v.x = pack_bf16x2(gelu_erf_fast(a[4 * q4] + bs.x), gelu_erf_fast(a[4 * q4 + 1] + bs.y));
-        v.y = pack_bf16x2(gelu_erf_fast(a[4 * q4 + 2] + bs.z), gelu_erf_fast(a[4 * q4 + 3] + bs.w));
-        *reinterpret_cast<uint2*>(h1T + r * kH1s + f) = v;
-      }
+      for (int j = 0; j < 2; ++j)
+        *reinterpret_cast<ring_u32x4*>(&w2T[w >> 1][c][0] + (16 * (w & 1) + 8 * j) * 64 + (st_off ^ ((j & 1) * 32))) = w2r[j][c];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const int f = 32 * w + 8 * q4 + 4 * g;
+      const float4 bs = *reinterpret_cast<const float4*>(b1s + f);
+      uint2 v;
+      v.x = pack_bf16x2(gelu_erf_fast(a[4 * q4] + bs.x), gelu_erf_fast(a[4 * q4 + 1] + bs.y));
+      v.y = pack_bf16x2(gelu_erf_fast(a[4 * q4 + 2] + bs.z), gelu_erf_fast(a[4 * q4 + 3] + bs.w));
+      *reinterpret_cast<uint2*>(h1T + r * kH1s + f) = v;
+    }
   }
   __syncthreads();
-  {  // h2 = GELU(W2 h1 + b2): one 32-feature tile per wave
+  if (w < kPH2 / 32) {  // h2 = GELU(W2 h1 + b2): 32 features in each of four waves
     f32x16 a;
 #pragma unroll
     for (int i = 0; i < 16; ++i) a[i] = 0.f;
     const bf16_t* hb = h1T + r * kH1s + 8 * g;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      wave_lds_order();
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<uint4*>(st + 8 * j * 64 + (st_off ^ ((j & 1) * 32))) = w2r[j][c];
-      wave_lds_order();
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
       for (int sk = 0; sk < 4; ++sk) {
         const bf16x8 bh = as_frag(*reinterpret_cast<const uint4*>(hb + 64 * c + 16 * sk));
-        const bf16x8 fa = as_frag(*reinterpret_cast<const uint4*>(st + (fr_off ^ (sk * 16))));
+        const bf16x8 fa = as_frag(*reinterpret_cast<const uint4*>(&w2T[w][c][0] + (fr_off ^ (sk * 16))));
         a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, bh, a, 0, 0, 0);
       }
-    }
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
       const int f = 32 * w + 8 * q4 + 4 * g;
-      const float4 bs = *reinterpret_cast<const float4*>(b2 ? b2 + f : kZeroWords);
+      const float4 bs = *reinterpret_cast<const float4*>(b2s + f);
       uint2 v;
       v.x = pack_bf16x2(gelu_erf_fast(a[4 * q4] + bs.x), gelu_erf_fast(a[4 * q4 + 1] + bs.y));
       v.y = pack_bf16x2(gelu_erf_fast(a[4 * q4 + 2] + bs.z), gelu_erf_fast(a[4 * q4 + 3] + bs.w));
@@ -930,17 +943,16 @@ __global__ __launch_bounds__(256) void small_head_kernel(const float* __restrict
     }
   }
   __syncthreads();
-  {  // the two logits of a row: four threads sum a quarter of the 128 inputs each, combined in a fixed order
+  if (tid < 256) {  // the two logits of a row: four threads sum a quarter of the 128 inputs each, combined in a fixed order
     const int out = tid >> 2, part = tid & 3, tok = out >> 1, c = out & 1;
     const int64_t m = t0 + tok;
-    const int64_t lim = span_off ? span_off[B] : M;
     float ps = 0.f;
 #pragma unroll
     for (int k = 32 * part; k < 32 * part + 32; ++k) ps = fmaf(bf16_to_f32(h2T[tok * kH2s + k]), w3s[c * kPH2 + k], ps);
     const int l0 = lane & ~3;
     const float p0 = __shfl(ps, l0, kWave), p1 = __shfl(ps, l0 + 1, kWave), p2 = __shfl(ps, l0 + 2, kWave),
                 p3 = __shfl(ps, l0 + 3, kWave);
-    if (part == 0 && m < M && m < lim) logits[2 * m + c] = ((((b3 ? b3[c] : 0.f) + p0) + p1) + p2) + p3;
+    if (part == 0 && m < M && m < lim) logits[2 * m + c] = (((b3v + p0) + p1) + p2) + p3;
   }
 }
 
@@ -1315,9 +1327,14 @@ extern "C" int dllava_predict(const void* x, int64_t ldx, int64_t M, int32_t B, 
                          r.small, B, seq_off, vis_start, vis_len, 16, kSmallSplit, kPW, static_cast<const bf16_t*>(p->W_h1),
                          static_cast<const bf16_t*>(p->W_h2));
     DLLAVA_CHECK_LAUNCH("small_in_kernel");
-    hipLaunchKernelGGL(small_head_kernel, dim3(nt), dim3(256), 0, st, r.small, 32 * nt, Mi, p->b_in,
-                       static_cast<const bf16_t*>(p->W_h1), p->b_h1, static_cast<const bf16_t*>(p->W_h2), p->b_h2,
-                       static_cast<const bf16_t*>(p->W_h3), p->b_h3, logits, seq_off ? r.span_off : nullptr, B);
+    auto head = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(nt), dim3(512), 0, st, r.small, 32 * nt, Mi, p->b_in, static_cast<const bf16_t*>(p->W_h1),
+                         p->b_h1, static_cast<const bf16_t*>(p->W_h2), p->b_h2, static_cast<const bf16_t*>(p->W_h3), p->b_h3, logits,
+                         seq_off ? r.span_off : nullptr, B);
+    };
+    if (Mi <= 8) head(small_head_kernel<1>);
+    else if (Mi <= 16) head(small_head_kernel<2>);
+    else head(small_head_kernel<4>);
     DLLAVA_CHECK_LAUNCH("small_head_kernel");
     return DLLAVA_OK;
   }
