@@ -471,8 +471,11 @@ int dllava_span_attn(const void* Q, const void* K, const void* V, int32_t B, con
  *   off       [B+1] row offsets of the sequences;  rows = host upper bound on off[B]
  *   keep_mask [rows] uint8, 0 = dropped, anything else = kept (keep_mask of dllava_select_compact)
  *   workspace device, 256-byte aligned, dllava_masked_attn_workspace(rows, B) bytes, scratch (need not be initialised): the mask
- *             as words and the list of the visible keys.  Without room for the list the call works on all keys instead:
- *             (rows/32 + B + 2) * 4 bytes, rounded up to 256, are the least it takes
+ *             as words, their counts and the list of the visible keys.  Without room for counts and list the call takes whole
+ *             tiles of 32 keys, those with a visible one: (rows/32 + B + 2) * 4 bytes, rounded up to 256, are the least it takes
+ * Rows of K and V must be readable and finite, hidden ones too: which hidden rows are read beside the visible ones, and in which order a
+ * query's sums run (its last bits), follows from the mask in front of it and from the size of the workspace.  Calls with the same
+ * arguments and workspace size give the same bits.
  * Sizes: Dh in {64, 128}, scale > 0.
  */
 int dllava_masked_attn(const void* Q, const void* K, const void* V, int32_t B, const int32_t* off, int64_t rows,

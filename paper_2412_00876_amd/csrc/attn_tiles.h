@@ -34,9 +34,13 @@
 // With masks the work is the visible keys, not all keys: in front of an item's own 128 rows a key is either visible to all of its
 // queries or to none, so those keys come from a list of the visible ones (prefill_args.h), 32 at a time, and such a tile needs no
 // mask; only the item's own rows are walked as they stand, under the mask words.  A row's place is a scalar load, dealt to the lanes
-// that fetch the row.  8 sequences of 619..816 rows, 32 heads of 128, a fifth of the picture kept: 84 -> 58 us; 4 of 2900..3050
-// 478 -> 173; heads of 64 60 -> 37; nothing hidden 93 -> 91 and 477 -> 460 (rows: the number of tiles is now known, so they go in
-// pairs without a spare one).
+// that fetch the row.  Where the visible keys fill the tiles that have any (hidden tokens in long runs), those tiles are walked as they
+// stand, and the tiles without a visible key are left out; their number, which the mask kernel counts, says how the item's tiles pair.
+// 8 sequences of 619..816 rows, 32 heads of 128, walking all tiles / now: a fifth of the picture kept 92 / 56 us, half 92 / 69, nothing
+// hidden 87 / 86; 4 of 2900..3050 461 / 156, 481 / 275, 468 / 447, of five pictures of 576 rows three visible 312 / 301 (walking the tiles with a
+// visible key / now); heads of 64 303 / 92, 306 / 166, 282 / 271, 196 / 185.
+// The stream of tile loads meets every tile first, so it hands the tiles' masks on (mask0..2); what an item needs once is read
+// from the kernel's arguments each time.  With those kept and the masks found twice 29 to 47 scalar registers were spilled, now none.
 #pragma once
 
 #include <atomic>
@@ -430,8 +434,8 @@ __device__ __forceinline__ void finish(State<DH>& T, const Probs& P) {
 }
 
 // Paged: causal, keys and values in the cache's pages.  Rows: causal, in rows.  Full: every query sees all keys of its sequence.
-// Masked: causal, keys hidden by key words but from their own query.
-enum class Mode { Paged, Rows, Full, Masked };
+// Masked: causal, keys hidden by key words but from their own query.  Words: the same without counts and list of the visible keys.
+enum class Mode { Paged, Rows, Full, Masked, Words };
 
 // One work item = (sequence, head, tile of NWQ*32 query rows).  Blocks are PERSISTENT: the launch holds as many blocks as
 // fit the chip at once (slots), block p takes every slots-th item and walks their key tiles as ONE stream: the tile
@@ -442,13 +446,24 @@ enum class Mode { Paged, Rows, Full, Masked };
 // with its tile index, so every block takes its longest items first and the launch ends with the shortest ones.
 template <int DH, int NWQ, Mode MODE>
 __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
-  constexpr bool kFull = MODE == Mode::Full, kMasks = MODE == Mode::Masked;
+  constexpr bool kFull = MODE == Mode::Full, kList = MODE == Mode::Masked, kMasks = kList || MODE == Mode::Words;
   // the arguments as locals (the closures below then capture plain values, which the compiler keeps in registers)
   const int aB = args.B;
   const float aScale = args.scale_log2;
   const void* const aK = args.K;
   const void* const aV = args.V;
-  void* const aO = args.O;
+  // What is needed once an item is, with masks, read from the arguments each time (`args` is the kernel's one parameter): kept, it would
+  // cost spills of scalar registers.
+  typedef const PrefillArgs __attribute__((address_space(4)))* ConstArgs;
+  auto arg = [&](auto field) DLLAVA_INLINE {
+    if constexpr (kMasks) {
+      ConstArgs p = (ConstArgs)__builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+s"(p));
+      return p->*field;
+    } else {
+      return args.*field;
+    }
+  };
   constexpr int kBM = NWQ * 32;
   constexpr int kChunks = DH / 8;  // 16-byte chunks per row
   constexpr int kNB = DH / 32;     // 32-dim blocks of the output
@@ -476,9 +491,9 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   const ConstI32 off_c = (ConstI32)args.off;
   const ConstI32 bt_c = (ConstI32)args.block_table;
   const ConstU32 kw_c = (ConstU32)args.key_words;
-  const int mask_slots = args.mask_slots;
   constexpr bool paged = MODE == Mode::Paged;
   const int step_blocks = static_cast<int>(gridDim.x);
+  const uint32_t row_bytes = paged ? kRowBytes : static_cast<uint32_t>(H) * kRowBytes;
 
   auto uniform = [](int v) DLLAVA_INLINE { return __builtin_amdgcn_readfirstlane(v); };  // said to the compiler where it cannot see it
   // Which (sequence, query tile) is item k?  With at most 64 sequences every wave keeps the sequences' offsets in
@@ -497,20 +512,35 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   }
   struct Item {
     int valid, b, h, tile, r0, n;
-    int seen;  // with masks: visible keys in front of the item's own queries, which it takes from the list; -1: it walks all keys
+    int seen;  // with masks, in front of the item's own queries: the visible keys, which it takes from the list; or ~(tiles with a
+               // visible key), which it walks
   };
+  constexpr int kListPays = DH == 128 ? 11 : 16;
+  auto tiles_listed = [](int seen) DLLAVA_INLINE { return static_cast<int>((static_cast<uint32_t>(seen) + kBN - 1) / kBN); };
+  auto words_of = [&](const Item& it) DLLAVA_INLINE { return kw_c + ((it.r0 >> 5) + it.b); };
   auto seen_before = [&](const Item& it) DLLAVA_INLINE {
-    if (!kMasks || mask_slots == 0 || static_cast<uint64_t>(static_cast<uint32_t>(it.n)) * static_cast<uint32_t>(H) * kRowBytes >> 32) return -1;
-    // A listed tile takes up to 1.3 times as long as one in rows (its rows' places are loads in front of it): with a list for every
-    // item that it spares a tile, 800 rows of 32 heads took 37 us at 84 % visible keys and 29 at 60 %, in rows 33 at either.
-    const int seen = static_cast<int>((kw_c + mask_slots)[(it.r0 >> 5) + it.b + it.tile * (kBM / kBN)]);
-    return seen <= it.tile * (kBM * 3 / 4) ? seen : -1;
+    int shown = 0;
+    const int own = it.tile * (kBM / kBN);
+    if constexpr (kList) {
+      if (own == 0) return 0;
+      const ConstU32 counts = words_of(it) + arg(&PrefillArgs::mask_slots) + own;
+      const int seen = static_cast<int>(counts[0]);
+      shown = static_cast<int>(counts[-1]);
+      // A tile from the list takes about 1.1 times as long as one in rows whose keys are all visible (its rows' places are loads in
+      // front of it; heads of 64: 1.05) and no longer than one in rows with hidden keys, whose scores pass a mask.  4 x 3000 rows, 32
+      // heads, from the list / in rows: 85 % visible, scattered, 411 / 485 us (heads of 64: 251 / 308), half visible in runs of 192 on
+      // average 282 / 300 (167 / 180), three of five pictures of 576 rows 316 / 301.  Short sequences: the list has to spare a tile.
+      if (kListPays * tiles_listed(seen) <= (kListPays - 1) * shown && !(static_cast<uint64_t>(static_cast<uint32_t>(it.n)) * row_bytes >> 32)) return seen;
+    } else if constexpr (kMasks) {
+      for (int t = 0; t < own; ++t) shown += words_of(it)[t] != 0u;
+    }
+    return ~shown;
   };
   // Item k of a launch over at most 64 sequences.
   auto locate = [&](int k) __attribute__((always_inline)) {
     Item it{0, 0, 0, 0, 0, 0, -1};
-    const int yd = k / H;  // position in DESCENDING tile-index order
-    it.h = k - yd * H;
+    const int heads = arg(&PrefillArgs::H), yd = k / heads;  // position in DESCENDING tile-index order
+    it.h = k - yd * heads;
     const int y = total - 1 - yd;  // position in ascending order
     if (y < 0) return it;          // (total is 0 for more sequences: those have one item per block)
     int below = 0, tile = 0;       // tiles with a smaller index
@@ -526,8 +556,9 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
     const unsigned long long me = __ballot(nb_l > tile && before == y - below);
     it.b = uniform(__builtin_ctzll(me));
     it.tile = tile;
-    it.r0 = off_c[it.b];
-    it.n = off_c[it.b + 1] - it.r0;
+    const ConstI32 off = (ConstI32)arg(&PrefillArgs::off) + it.b;
+    it.r0 = off[0];
+    it.n = off[1] - it.r0;
     it.valid = 1;
     it.seen = seen_before(it);
     return it;
@@ -573,23 +604,25 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
     const int t = it.tile * NWQ + ((j ^ (pblk >> 8)) & 1 ? NWQ - 1 - wq : wq);
     return it.valid && t * 32 < it.n ? t : -1;
   };
-  const bf16_t* Qp = static_cast<const bf16_t*>(args.Q);
   constexpr int kQLoads = 32 / D::kRowsPerLoad;  // wave-wide loads of a wave's 32 query rows
   bf16_t* myQ = sQ + wq * 32 * DH;
   auto request_queries = [&](const Item& it, int tile, int from, int to) DLLAVA_INLINE {  // loads from .. to-1 of a wave's queries
     const int l = lane_here();
+    const bf16_t* Qp = static_cast<const bf16_t*>(arg(&PrefillArgs::Q));
+    const int heads = arg(&PrefillArgs::H);
     for (int i = from; i < to; ++i) {
       const int rr = D::kRowsPerLoad * i + l / kChunks, pc = l % kChunks;
       int q = (tile < 0 ? 0 : tile * 32) + rr;
       if (q >= it.n) q = it.n - 1;
-      const bf16_t* src = Qp + (static_cast<size_t>(it.r0 + q) * H + it.h) * DH + 8 * (pc ^ D::k_swizzle(rr));
+      const bf16_t* src = Qp + (static_cast<size_t>(it.r0 + q) * heads + it.h) * DH + 8 * (pc ^ D::k_swizzle(rr));
       load_to_lds(reinterpret_cast<const char*>(src), lds_address(myQ) + i * (kWave * 16));
     }
   };
-  // The key tiles of an item: with masks the visible keys in front of its own queries first, as they are listed (listed() tiles), then
-  // keys in rows, from tile first_plain() of the sequence on.
-  auto listed = [&](const Item& it) DLLAVA_INLINE { return kMasks ? (it.seen + kBN - 1) / kBN : 0; };
-  auto first_plain = [&](const Item& it) DLLAVA_INLINE { return kMasks && it.seen >= 0 ? it.tile * (kBM / kBN) : 0; };
+  // The key tiles of an item with masks: in front of its own queries the visible keys as they are listed, 32 a tile, or the tiles of the
+  // sequence that have a visible key; then its own rows.  hidden(): by how many tiles these are fewer than the sequence's.
+  auto hidden = [&](const Item& it) DLLAVA_INLINE {
+    return kMasks ? it.tile * (kBM / kBN) - (kList && it.seen >= 0 ? tiles_listed(it.seen) : ~it.seen) : 0;
+  };
 
   // Fragment addresses (LDS bytes, stage 0).  K: row lq, logical chunk 2*ks + g, stored at chunk ^ swizzle(lq): the
   // step ks enters as an exclusive-or with 32*ks.  Queries alike.  V: the transposing read of 16 lanes (j = lane mod 16)
@@ -629,7 +662,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   auto store_item = [&](int q0, const Item& it) DLLAVA_INLINE {
     const float inv = 1.f / (T.l_run + __shfl_xor(T.l_run, 32, kWave));
     const int l = lane_here(), g = l >> 5, qi = q0 + (l & 31);
-    bf16_t* orow = static_cast<bf16_t*>(aO) + (static_cast<size_t>(it.r0 + qi) * H + it.h) * DH + 8 * g;
+    bf16_t* orow = static_cast<bf16_t*>(arg(&PrefillArgs::O)) + (static_cast<size_t>(it.r0 + qi) * arg(&PrefillArgs::H) + it.h) * DH + 8 * g;
 #pragma unroll
     for (int nb = 0; nb < kNB; ++nb)
 #pragma unroll
@@ -647,7 +680,6 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   // ---- the stream of tile loads: item P, its tile tP is the next one whose K is requested; V follows one tile behind --------
   // A tile is two halves of 16 rows (two pages, where paged); all of a half's rows lie at fixed offsets from its first, so a
   // tile's loads are a scalar base plus a lane constant each.
-  const uint32_t row_bytes = paged ? kRowBytes : static_cast<uint32_t>(H) * kRowBytes;
   const int64_t page_half = static_cast<int64_t>(H) * kPage * kRowBytes;  // K, or V, of a page
   const int64_t v_step = paged ? page_half : static_cast<const char*>(aV) - static_cast<const char*>(aK);
   constexpr int kHalfLoads = D::kLoads >= 2 ? D::kLoads / 2 : 1;  // distinct row sets of a wave within a half
@@ -661,16 +693,19 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   // With masks: the 16 bytes of a row that a lane fetches, the same in all its loads (their rows are a multiple of 16 apart); those of V
   // from those of K by an exclusive-or (a row's first byte is a multiple of its length).
   static_assert(!kMasks || D::kRowsPerLoad * NWQ % 16 == 0, "rows of a lane");
-  auto k_chunk = [&](int l) DLLAVA_INLINE { return 16u * ((l % kChunks) ^ D::k_swizzle(D::kRowsPerLoad * wq + l / kChunks)); };
+  auto k_chunk = [&](uint32_t l) DLLAVA_INLINE { return 16u * ((l % kChunks) ^ D::k_swizzle(D::kRowsPerLoad * wq + l / kChunks)); };
   const uint32_t v_flip = k_chunk(lane) ^ (16u * ((lane % kChunks) ^ (4 * ((D::kRowsPerLoad * wq + lane / kChunks) % (kChunks / 4)))));
   auto first_rows = [&](int i) DLLAVA_INLINE { return D::kLoads >= 2 ? i < D::kLoads / 2 : D::kRowsPerLoad * wq < kPage; };  // load i: of the first half?
   struct TileAt {
     const char *lo, *hi;  // K of the first rows of the tile's halves, this head
     int lim;              // last row of the tile that exists (>= kBN - 1: all of them)
     uint32_t k[D::kLoads];  // with masks: this lane's bytes of K, from lo (hi and lim are not used)
+    uint32_t mask;          // with masks: the visible keys
   };
-  int jP = 0, tP, lastP;  // lastP: its last key, as the stream numbers them
-  int listP = 0;
+  int jP = 0, tP, lastP;  // lastP: its last key
+  // With masks tP is the next tile in rows, or a hidden one in front of it, and wordP its mask; leftP listed keys from listP on come first.
+  int leftP = 0;
+  uint32_t listP = 0, wordP = 0;
   bool ended = false;  // every K tile of the block has been requested
   const char* baseP;  // K of the first row of P's sequence, its head (paged: the head's K in page 0)
   Item P = C;
@@ -690,52 +725,65 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
     P.b = uniform(P.b), P.h = uniform(P.h), P.tile = uniform(P.tile), P.r0 = uniform(P.r0), P.n = uniform(P.n);
     lastP = last_key_of(P);
     baseP = paged ? static_cast<const char*>(args.pages) + static_cast<int64_t>(P.h) * (kPage * kRowBytes)
-                  : static_cast<const char*>(aK) + static_cast<int64_t>(P.r0) * row_bytes + P.h * kRowBytes;
-    P.seen = uniform(P.seen);
-    listP = listed(P);
-    lastP -= (first_plain(P) - listP) * kBN;
+                  : static_cast<const char*>(arg(&PrefillArgs::K)) + static_cast<int64_t>(P.r0) * row_bytes + P.h * kRowBytes;
     tP = 0;
+    if constexpr (kMasks) {
+      leftP = kList ? uniform(P.seen) : -1;
+      if (leftP >= 0) tP = P.tile * (kBM / kBN);
+      listP = 2u * static_cast<uint32_t>(arg(&PrefillArgs::mask_slots)) + static_cast<uint32_t>(P.r0) + kBN * static_cast<uint32_t>(P.b);
+      wordP = words_of(P)[tP];
+    }
   };
   auto next_tile_at = [&]() DLLAVA_INLINE {  // tile tP of item P; then on to the next tile of the stream
     TileAt at;
-    const int lim = lastP - tP * kBN;
     if constexpr (kMasks) {
-      if (tP < listP) {
+      if (kList && leftP > 0) {
         at.lo = baseP;
-        const ConstU32 list = kw_c + 2 * static_cast<int64_t>(mask_slots) + P.r0 + kBN * static_cast<int64_t>(P.b);
+        const ConstU32 list = kw_c + listP;
 #pragma unroll
-        for (int i = 0; i < D::kLoads; ++i) {
-          const int first = tP * kBN + D::kRowsPerLoad * (wq + NWQ * i);
+        for (int i = 0; i < D::kLoads; ++i) {  // (entries past the list's end are in the workspace, too)
           uint32_t v[D::kRowsPerLoad];
-          if (tP * kBN + kBN <= P.seen) {
 #pragma unroll
-            for (int e = 0; e < D::kRowsPerLoad; ++e) v[e] = list[first + e];
-          } else {  // past its end the list's last row is repeated
-#pragma unroll
-            for (int e = 0; e < D::kRowsPerLoad; ++e) v[e] = list[first + e < P.seen ? first + e : P.seen - 1];
-          }
-          at.k[i] = by_lanes(v) + k_chunk(lane_here());
+          for (int e = 0; e < D::kRowsPerLoad; ++e) v[e] = list[D::kRowsPerLoad * (wq + NWQ * i) + e];
+          at.k[i] = by_lanes(v);
         }
+        const uint32_t l = lane_here();
+        at.mask = ~0u;
+        if (leftP < kBN) {  // past its end the list's last row is repeated
+          at.mask = (1u << leftP) - 1u;
+          const uint32_t end = list[leftP - 1];
+#pragma unroll
+          for (int i = 0; i < D::kLoads; ++i)
+            if (static_cast<int>(D::kRowsPerLoad * (wq + NWQ * i) + l / kChunks) >= leftP) at.k[i] = end;
+        }
+#pragma unroll
+        for (int i = 0; i < D::kLoads; ++i) at.k[i] += k_chunk(l);
+        listP += kBN, leftP -= kBN;
+        --tP;  // no tile in rows
       } else {
-        if (tP == listP) baseP += static_cast<uint64_t>(static_cast<uint32_t>((first_plain(P) - listP) * kBN)) * row_bytes;
+        const ConstU32 words = words_of(P);
+        while (tP < P.tile * (kBM / kBN) && wordP == 0u) wordP = words[++tP];
+        at.mask = wordP;
+        wordP = words[tP + 1];  // on its way until the next tile (behind the item's last tile a word that no one looks at)
+        const int lim = lastP - tP * kBN;
         at.lo = baseP + static_cast<uint64_t>(static_cast<uint32_t>(tP * kBN)) * row_bytes;
 #pragma unroll
         for (int i = 0; i < D::kLoads; ++i) at.k[i] = k_lane[i % kHalfLoads] + (first_rows(i) ? 0 : kPage * row_bytes);
         if (__builtin_expect(lim < kBN - 1, 0)) {  // rows past the last key repeat it
-          const int l = lane_here();
+          const uint32_t l = lane_here();
 #pragma unroll
           for (int i = 0; i < D::kLoads; ++i) {
-            const int rr = D::kRowsPerLoad * (wq + NWQ * i) + l / kChunks;
+            const int rr = D::kRowsPerLoad * (wq + NWQ * i) + static_cast<int>(l / kChunks);
             at.k[i] = static_cast<uint32_t>(rr < lim ? rr : lim) * row_bytes + k_chunk(l);
           }
         }
       }
     } else if (paged) {
-      at.lim = lim;
+      at.lim = lastP - tP * kBN;
       at.lo = baseP + static_cast<int64_t>(pg_lo) * (2 * page_half);
       at.hi = baseP + static_cast<int64_t>(pg_hi) * (2 * page_half);
     } else {
-      at.lim = lim;
+      at.lim = lastP - tP * kBN;
       at.lo = baseP + static_cast<uint64_t>(static_cast<uint32_t>(tP * kBN)) * row_bytes;
       at.hi = at.lo + kPage * row_bytes;
     }
@@ -789,14 +837,17 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   const uint32_t sK0 = lds_address(sK), sV0 = lds_address(sV);
   constexpr uint32_t kSlot = kTileElems * 2;
   TileAt behind;       // the tile whose K was requested last: its V is next
+  uint32_t mask0 = 0, mask1 = 0, mask2 = 0;  // with masks: of the stream's next three tiles
   bool asked = false;  // the latest round requested both (else the stream has ended: there was no K, or neither)
   auto request_v = [&](uint32_t slot) DLLAVA_INLINE {
     if (__builtin_expect(asked, 1)) request(behind, v_step, v_lane, true, sV0 + slot);
   };
   auto request_k = [&](uint32_t slot) DLLAVA_INLINE {
     asked = !ended;
+    if constexpr (kMasks) mask0 = mask1, mask1 = mask2;
     if (__builtin_expect(asked, 1)) {
       behind = next_tile_at();
+      if constexpr (kMasks) mask2 = behind.mask;
       request(behind, 0, k_lane, false, sK0 + slot);
     }
   };
@@ -822,14 +873,10 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
   uint32_t s0 = 0, s1 = kSlot, s2 = 2 * kSlot;  // ring slots of K and V of the tile at hand, the next, the one after
   int tile = tile_first;
   for (;;) {  // items
-    // Keys are numbered as they come in the stream: the listed ones, then the rows from first_plain on, `skipped` fewer than in the
-    // sequence.
-    const int listC = listed(C), skipped = (first_plain(C) - listC) * kBN, nC = C.n - skipped;
+    // Keys are numbered as they come in the stream: at the item's own rows `skipped` fewer than in the sequence.
+    const int skipped = hidden(C) * kBN, nC = C.n - skipped;
     const int lastC = (last_key_of(C) - skipped) / kBN;
     const int last = kFull || tile < 0 ? (tile < 0 ? -1 : lastC) : tile - skipped / kBN;  // this wave's last key tile; -1: it has no queries
-    const uint32_t list_tail = C.seen > 0 && C.seen % kBN ? (1u << C.seen % kBN) - 1u : ~0u;  // the keys of the last listed tile
-    const int wordC = (C.r0 >> 5) + C.b + skipped / kBN;
-    auto mask_word = [&](int t) DLLAVA_INLINE { return t >= listC ? kw_c[wordC + t] : t == listC - 1 ? list_tail : ~0u; };
     const int q0 = tile * 32;
     int t = 0;
     f32x16 SA, SB;
@@ -875,7 +922,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
       __builtin_amdgcn_s_barrier();
       vb = vb0 + s0;
       kb = kb0 + s1;
-      if constexpr (kMasks) kmask = mask_word(t);
+      if constexpr (kMasks) kmask = mask0;
     };
     auto open_v = [&]() DLLAVA_INLINE {
       q_late = false;
@@ -904,7 +951,7 @@ __device__ __forceinline__ void attend_items(const PrefillArgs& args) {
         products_done();  // the copy reads the scores
         tie_s(SA);
         SB = SA;
-        if constexpr (kMasks) kmask = mask_word(t);
+        if constexpr (kMasks) kmask = mask0;
         if (kMasks || t == last) mask_scores(SB, t, last, nC, kmask);
         first_reference(T, SB, aScale);
         P2.hi[0] = P2.hi[1] = P2.lo[0] = P2.lo[1] = u32x4{0u, 0u, 0u, 0u};

@@ -22,8 +22,9 @@ struct PrefillArgs {
   // Key masks (Eq. 7), or null: bit i of word t of sequence b says whether key 32t + i may be seen by LATER queries
   // (a query always sees itself); the words of sequence b start at key_words[off[b] / 32 + b].  masked_mfma_launch only.
   const uint32_t* key_words;
-  // mask_slots > 0: behind the words, mask_slots words on, as many counts, one for each word -- the visible keys of its sequence in
-  // front of the word's --, and behind those the visible keys as a list: entry off[b] + 32 b + r is where the row of sequence b's
+  // mask_slots > 0: behind the words, mask_slots words on, as many counts, one for each word: for word 4i of a sequence (where the
+  // queries of an item of 128 begin) the visible keys of the sequence in front of it, for the word before that, 4i - 1, the words that
+  // are not zero in front of 4i.  Behind those the visible keys as a list: entry off[b] + 32 b + r is where the row of sequence b's
   // visible key r starts, in bytes (mod 2^32) from the row of its key 0.
   int32_t mask_slots;
 };

@@ -78,13 +78,14 @@ int launch_generic(const PrefillArgs& a, int64_t rows, hipStream_t st) {
 // The per-token mask of Eq. 7 in the forms that the attention reads (prefill_args.h): a 32-bit word per key tile -- the words of
 // sequence b start at slot off[b] / 32 + b (disjoint for any offsets, since ceil(n / 32) <= (off + n) / 32 - off / 32 + 1) -- and the
 // list of the visible keys.  A block takes 256 tokens of one sequence, a thread each; what stands in front of them it counts from
-// the mask itself, 16 bytes per thread at a time, so the blocks do not wait for each other.  The launch is latency, 4.7 us
-// under the profiler for 5736 rows of 8 sequences (the words alone 4.6; with the sequence found in one trip to memory the same).
+// the mask itself, 16 bytes per thread at a time (two threads a tile), so the blocks do not wait for each other.  The launch is latency,
+// 4.7 us under the profiler for 5736 rows of 8 sequences (the words alone 4.6; with the sequence found in one trip to memory the same).
 constexpr int kMaskThreads = 256;
 __device__ __forceinline__ int nonzero_bytes(uint32_t x) { return __popc((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u); }
 __global__ __launch_bounds__(kMaskThreads) void key_lists_kernel(const uint8_t* __restrict__ keep, const int32_t* __restrict__ off, int32_t B,
                                                                  int32_t rows, uint32_t row_bytes, uint32_t* __restrict__ words, int32_t slots) {
-  __shared__ int sm_front[kMaskThreads / kWave], sm_mine[kMaskThreads / kWave];
+  __shared__ int sm_front[kMaskThreads / kWave], sm_mine[kMaskThreads / kWave];    // visible keys
+  __shared__ int sm_shown[kMaskThreads / kWave], sm_tiles[kMaskThreads / kWave];   // tiles with one
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   const int64_t chunk = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
   int lo = 0, hi = B;  // the last sequence whose first chunk is <= chunk
@@ -100,22 +101,31 @@ __global__ __launch_bounds__(kMaskThreads) void key_lists_kernel(const uint8_t* 
   const int64_t slot = (r0 >> 5) + b + j / 32;
   if (lane % 32 == 0 && j < n) words[slot] = static_cast<uint32_t>(mask >> (lane & 32));
   if (slots == 0) return;
-  int front = 0;
+  int front = 0, shown = 0;
   for (int64_t i = 16 * tid; i < j0; i += 16 * kMaskThreads) {  // j0 is a multiple of 16: whole pieces, at any alignment
     uint4 v;
     __builtin_memcpy(&v, keep + r0 + i, sizeof(v));
     front += nonzero_bytes(v.x) + nonzero_bytes(v.y) + nonzero_bytes(v.z) + nonzero_bytes(v.w);
+    const uint64_t any = __ballot((v.x | v.y | v.z | v.w) != 0u);  // of the lanes that are still here: whole tiles, lane 0 to the last
+    shown += __builtin_popcountll((any | any >> 1) & 0x5555555555555555ull);
   }
   front = wave_sum_i(front);
   if (lane == 0) {
     sm_front[w] = front;
     sm_mine[w] = __builtin_popcountll(mask);
+    sm_shown[w] = shown;
+    sm_tiles[w] = (static_cast<uint32_t>(mask) != 0u) + (mask >> 32 != 0u);
   }
   __syncthreads();
   int rank = __builtin_popcountll(mask & ((uint64_t{1} << lane) - 1));
 #pragma unroll
   for (int i = 0; i < kMaskThreads / kWave; ++i) rank += sm_front[i] + (i < w ? sm_mine[i] : 0);
-  if (lane % 32 == 0 && j < n) words[slots + slot] = rank;
+  if (lane % 32 == 0 && j < n) {
+    int tiles = 0;  // up to this word's
+#pragma unroll
+    for (int i = 0; i < kMaskThreads / kWave; ++i) tiles += sm_shown[i] + (i <= w ? sm_tiles[i] : 0);
+    words[slots + slot] = j / 32 % 4 == 3 ? tiles : rank;  // the fourth word's is the last of its wave
+  }
   if (open) words[2 * static_cast<int64_t>(slots) + r0 + 32 * static_cast<int64_t>(b) + rank] = static_cast<uint32_t>(j) * row_bytes;
 }
 
@@ -147,7 +157,8 @@ extern "C" int dllava_masked_attn(const void* Q, const void* K, const void* V, i
   DLLAVA_REQUIRE(Q && K && V && O && off && keep_mask, DLLAVA_ENULL, "masked_attn: Q, K, V, O, off and keep_mask are required");
   DLLAVA_REQUIRE(aligned(Q, 16) && aligned(O, 16) && aligned(K, 16) && aligned(V, 16), DLLAVA_EINVAL,
                  "masked_attn: Q, K, V, O must be 16-byte aligned");
-  // With less than the query asks for, but enough for the words, the kernel walks all keys.
+  // With less than the query asks for, but enough for the words, the kernel does without counts and list (and where a place in them does
+  // not fit 32 bits).
   const size_t slots = mask_slot_bytes(rows, B), need = dllava_masked_attn_workspace(rows, B);
   DLLAVA_REQUIRE(workspace && aligned(workspace, 256) && workspace_bytes >= slots, DLLAVA_EWORKSPACE,
                  "masked_attn: workspace needs %zu bytes, 256-byte aligned (got %zu)", need, workspace_bytes);
@@ -157,7 +168,7 @@ extern "C" int dllava_masked_attn(const void* Q, const void* K, const void* V, i
   a.scale_log2 = scale * 1.44269504088896340736f;
   uint32_t* words = static_cast<uint32_t*>(workspace);
   a.key_words = words;
-  a.mask_slots = workspace_bytes >= need && slots / 4 <= 0x7fffffff ? static_cast<int32_t>(slots / 4) : 0;
+  a.mask_slots = workspace_bytes >= need && need / 4 <= 0xffffffffu && slots / 4 <= 0x7fffffff ? static_cast<int32_t>(slots / 4) : 0;
   const int64_t chunks = rows / kMaskThreads + B, gx = chunks < (1 << 20) ? chunks : 1 << 20;  // a grid dimension holds fewer than 2^32 threads
   hipLaunchKernelGGL(key_lists_kernel, dim3(static_cast<unsigned>(gx), static_cast<unsigned>(ceil_div(chunks, gx))), dim3(kMaskThreads), 0, st, keep_mask,
                      off, B, static_cast<int32_t>(rows), static_cast<uint32_t>(H) * static_cast<uint32_t>(Dh) * 2, words, a.mask_slots);
