@@ -31,7 +31,8 @@ def _masks(lens, seen):
 
 def _call(h, q, k, v, off, keep, H, Dh, words_only):
     rows, B = q.shape[0], len(off) - 1
-    ws = torch.full((P.dllava_masked_attn_workspace(rows, B),), 0xff, dtype=torch.uint8, device=h.DEV)  # as a list: rows far outside
+    # an entry that is read without having been written is key 0: a wrong result, nothing outside K and V
+    ws = torch.zeros(P.dllava_masked_attn_workspace(rows, B), dtype=torch.uint8, device=h.DEV)
     if words_only:
         ws = ws[:((rows // 32 + B + 2) * 4 + 255) // 256 * 256]
     O = torch.full((rows, H, Dh), float("nan"), dtype=torch.bfloat16, device=h.DEV)
@@ -69,6 +70,12 @@ def test_list_lengths(lens, seen, blocks, Dh):
     assert torch.equal(O[first].view(torch.int16), walk[first].view(torch.int16))
 
 
+def _scattered(n, rs):
+    """A third visible; of the hidden keys the first 128 are marked."""
+    keep = (rs.rand(n) < 1 / 3).astype(np.uint8)
+    return keep, (keep == 0) & (np.arange(n) < 128)
+
+
 def _whole_tiles(n, rs):
     """Three of the first eight tiles hidden whole, and marked; everything else visible."""
     hidden = np.isin(np.arange(n) // 32, (1, 6, 7))
@@ -77,10 +84,12 @@ def _whole_tiles(n, rs):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("Dh", [64, 128])
-@pytest.mark.parametrize("mask,first,words_only,clean", [(_whole_tiles, 256, False, True), (_whole_tiles, 256, True, True)])
+@pytest.mark.parametrize("mask,first,words_only,clean", [(_scattered, 128, False, True), (_scattered, 128, True, False),
+                                                         (_whole_tiles, 256, False, True), (_whole_tiles, 256, True, True)])
 def test_hidden_rows_that_are_not_read(mask, first, words_only, clean, Dh):
-    """V of the marked hidden keys is NaN, which reaches every query whose tiles hold one (0 times NaN).  Queries of later items:
-    a tile without a visible key is left out on either route."""
+    """V of the marked hidden keys is NaN, which reaches every query whose tiles hold one (0 times NaN).  Queries of later items: the list
+    holds visible keys only, and a tile without a visible key is left out on either route; the walk over partly visible tiles reads
+    the marked ones, which shows that this test can tell."""
     h = _H()
     lens, H = [first + 140, 700], 2
     rows, off = sum(lens), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
@@ -136,6 +145,28 @@ def test_counts_and_list(lens):
                 assert got[at + word - 1] == k[:32 * word].reshape(-1, 32).any(1).sum(), (b, word)
         listed = got[2 * slots + off[b] + 32 * b:][:k.sum()]
         assert (listed == np.flatnonzero(k) * (H * Dh * 2)).all(), b
+
+
+@pytest.mark.gpu
+def test_rows_that_span_4_gib():
+    """Places in the list are 32 bits: a sequence whose rows span more walks its tiles.  The bits of the same heads in a call of
+    their own."""
+    n, H, Dh = 400, 65535, 128   # 256 rows of 16 MiB - 256 bytes: the last items' keys lie on both sides of 4 GiB
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn((n, 64, Dh), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    keep = (torch.rand(n, generator=g, device="cuda") < 1 / 3).to(torch.uint8)
+    off = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+
+    def run(heads, ws):
+        q_, k_, v_ = (t.repeat(1, 1024, 1)[:, :heads].contiguous() if heads > 64 else t for t in (q, k, v))
+        O = torch.zeros_like(q_)
+        P.dllava_masked_attn(q_, k_, v_, 1, off, n, heads, Dh, Dh ** -0.5, keep, O, P.BF16, ws)
+        torch.cuda.synchronize()
+        return O.view(torch.int16)
+
+    full = torch.zeros(P.dllava_masked_attn_workspace(n, 1), dtype=torch.uint8, device="cuda")
+    big, want = run(H, full), run(64, full[:((n // 32 + 3) * 4 + 255) // 256 * 256])
+    assert want.any() and torch.equal(big[:, :64], want) and torch.equal(big[:, -63:], want[:, :63])
 
 
 def test_no_register_is_kept_in_an_accumulator():
