@@ -124,7 +124,7 @@ constexpr int kRingGeluPair = 12;
 constexpr RingTile kRingTiles[] = {{8, 8, 8, 1310, 990, 10200, 800, 1}, {7, 8, 7, 1120, 855, 9300, 750, 1},  {6, 8, 6, 1030, 760, 8400, 700, 1},
                                    {5, 8, 5, 870, 660, 7300, 650, 1},   {4, 8, 4, 750, 600, 6300, 600, 1},   {9, 4, 6, 540, 430, 7500, 430, 1},
                                    {3, 4, 4, 460, 370, 6200, 370, 1},   {10, 4, 2, 300, 270, 4700, 270, 1},  {2, 2, 4, 300, 260, 4500, 260, 1},
-                                   {1, 2, 2, 210, 190, 3800, 200, 1},   {11, 2, 2, 700, 210, 3400, 200, 3},  {kRingGeluPair, 4, 4, 930, 930, 6100, 740, 2}};
+                                   {1, 2, 2, 210, 190, 3800, 200, 1},   {11, 2, 2, 700, 210, 3400, 200, 3},  {kRingGeluPair, 4, 4, 800, 460, 5500, 740, 2}};
 
 // The tile that takes least; tiles_of(t): how many of it the launch has, 0 if it cannot use it.  Null if none can be used.
 // A stage touches one 128-byte line of every row of its tile: once those rows span more than about 2.5 MiB (11008
@@ -133,7 +133,10 @@ constexpr RingTile kRingTiles[] = {{8, 8, 8, 1310, 990, 10200, 800, 1}, {7, 8, 7
 // gelu: the epilogue takes the GELU of 4 fi jt results per lane, 32 ns each (vector arithmetic, nothing beside it).  Only then do
 // two blocks per compute unit pay, one's products beside the other's GELU: they are paced by the LDS, which two tiles of 128 x 128
 // read and write 1.4 times as much per product as one of 256 x 256 (11520 rows, 512 wide: 2048 features with GELU 43.3 us against
-// 48.3, 1536 without 31.5 against 29.7).  Their time is proportional to their number, rounds cannot be told.
+// 48.3, 1536 without 31.5 against 29.7).  Two blocks of a compute unit that start together stay in step, so the first of their rounds
+// of 512 takes 5 us more (and a launch of one round never pays); what is left for a last round of at most 256 runs alone, which takes
+// half of the ends.  (4096 features, 544 / 1056 / 1568 tiles: 512 wide 22 / 34 / 45 us, priced 23 / 35 / 47; 11008 wide 222 / 360 / 501,
+// priced 253 / 419 / 584, where 256 x 160 takes 149 / 293 and 256 x 224 392, priced 206 / 388 / 446.)
 template <typename F>
 inline const RingTile* ring_pick(int64_t d, int forced, F&& tiles_of, bool gelu = false) {
   const int64_t nk = d / kRingBK;
@@ -145,13 +148,15 @@ inline const RingTile* ring_pick(int64_t d, int forced, F&& tiles_of, bool gelu 
     if (t.id == forced) return &t;
     const int64_t span = 32 * (t.fi + t.jt) * d * 2 - (5 << 19), slow = t.load + (span > 0 ? span / (1 << 10) * 65 / (1 << 10) : 0);
     const int64_t busy = t.busy > slow ? t.busy : slow, alone = t.alone > slow ? t.alone : slow;
+    const int64_t at_once = 32 * t.per_cu, per_xcd = ceil_div(tiles, kRingXcds), full = per_xcd / at_once, rest = per_xcd % at_once;
     int64_t cost;
     if (t.id == kRingGeluPair) {
       if (!gelu || tiles <= 512) continue;  // within one round the blocks of a compute unit stay in step: nothing of one stands beside the other
-      cost = tiles * (nk * busy + t.ends) / 512 + 5000;
+      const int64_t single = t.alone > slow / 2 ? t.alone : slow / 2;
+      cost = 5000 + full * (nk * busy + t.ends);
+      if (rest) cost += rest > 32 ? nk * busy + t.ends : nk * single + t.ends / 2;
     } else {
-      const int64_t ends = t.ends + (gelu ? 4 * 32 * t.fi * t.jt : 0), at_once = 32 * t.per_cu;
-      const int64_t per_xcd = ceil_div(tiles, kRingXcds), full = per_xcd / at_once, rest = per_xcd % at_once;
+      const int64_t ends = t.ends + (gelu ? 4 * 32 * t.fi * t.jt : 0);
       cost = full * (nk * busy + ends);
       if (rest) cost += nk * (alone + (busy - alone) * rest / at_once) + ends;
     }
