@@ -50,7 +50,7 @@ def test_every_tile(tile, M, N, K, act, res):
     _assert_same_rounding(got[:M, :N], ref, f"linear {M}x{K}x{N} tile {tile}")
 
 
-TILES = [1, 2, 3, 9, 4, 5, 6, 7, 8]
+TILES = [1, 2, 3, 9, 4, 5, 6, 7, 8, 11, 12]
 
 
 class _Forced:

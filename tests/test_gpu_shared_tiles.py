@@ -1,15 +1,10 @@
 """The tiles of the linear layers that share a compute unit (11: three 64 x 64, 12: two 128 x 128), on the inputs of the tests that
 force the other tiles, and at the edges of their rings: stage counts around three (11) and two (12), many more tiles than fit the chip."""
-import os
-import re
-import subprocess
-
 import pytest
 import torch
 
 from paper_2412_00876_amd import binding as P
 from tests import test_gpu_linear_tiles as T
-
 
 
 @pytest.mark.gpu
@@ -35,13 +30,3 @@ def test_many_tiles(tile, M, N, K):
             P.dllava_linear(x, K, M, K, w, None, N, 1, None, y, N, P.BF16)
         out.append(y.view(torch.int16))
     assert torch.equal(*out) and out[0].any()
-
-
-def test_shared_kernels_do_not_spill():
-    """Scratch traffic would count among the loads that the loops wait for."""
-    from paper_2412_00876_amd import build
-    r = subprocess.run([build.HIPCC, *build.COMMON, *build.HIP_FLAGS, "-Rpass-analysis=kernel-resource-usage", "--cuda-device-only", "-c",
-                        os.path.join(build.CSRC, "predictor.hip"), "-o", os.devnull], capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-2000:]
-    kernels = [b for b in r.stderr.split("Function Name: ")[1:] if "lin_shared_kernel" in b.split()[0]]
-    assert len(kernels) == 2 and all(re.search(r"ScratchSize \[bytes/lane\]: 0\b", b) for b in kernels)

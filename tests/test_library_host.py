@@ -177,11 +177,11 @@ def test_ring_kernels_do_not_spill():
         r = subprocess.run([build.HIPCC, *build.COMMON, *build.HIP_FLAGS, "-Rpass-analysis=kernel-resource-usage", "--cuda-device-only", "-c",
                             os.path.join(build.CSRC, source), "-o", os.devnull], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-2000:]
-        return [b for b in r.stderr.split("Function Name: ")[1:] if "_ring_kernel" in b.split()[0]]
+        return [b for b in r.stderr.split("Function Name: ")[1:] if re.search("_ring_kernel|lin_shared_kernel", b.split()[0])]
 
     with ThreadPoolExecutor(3) as ex:
         kernels = list(ex.map(report, ("score_mfma.hip", "qkv_project.hip", "predictor.hip")))
-    assert [len(k) for k in kernels] == [8, 8, 9]      # every tile
+    assert [len(k) for k in kernels] == [8, 8, 11]     # every tile
     for b in sum(kernels, []):
         assert re.search(r"ScratchSize \[bytes/lane\]: 0\b", b), b[:400]
 
