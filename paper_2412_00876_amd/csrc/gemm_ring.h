@@ -112,8 +112,8 @@ __device__ __forceinline__ bool ring_tile(int n_at, int n_bt, int per_xcd, int& 
 // The tiles of the products below: 32*fi rows of A x 32*jt rows of B.  Nanoseconds per stage when every compute unit works and
 // when few do -- the clock gives way to the power --, beside the stages (prologue and epilogue), and what the tile loads of a
 // stage alone take (measured on linear layers of d = 512 .. 11008).  Blocks that share a compute unit: one; three of the shallow
-// small tiles (times: of a whole round of them); two of the tiles that stand with GELU (see ring_pick).  The small tile with the
-// deep ring has half of the LDS, but is only taken for one block per compute unit.
+// small tiles (times: of a whole round of them); two of the tiles that stand with GELU (see ring_pick).  Of the small tile with the
+// deep ring, which has half of the LDS, two blocks may stand in a compute unit as well; it is priced as if there were one.
 struct RingTile {
   int id;  // what the launch overrides take
   int fi, jt;
@@ -132,11 +132,12 @@ constexpr RingTile kRingTiles[] = {{8, 8, 8, 1310, 990, 10200, 800, 1}, {7, 8, 7
 // of 256 x 128 at 11008 columns against 0.60 at 4096, 0.25 against 0.20 of 64 x 64.
 // gelu: the epilogue takes the GELU of 4 fi jt results per lane, 32 ns each (vector arithmetic, nothing beside it).  Only then do
 // two blocks per compute unit pay, one's products beside the other's GELU: they are paced by the LDS, which two tiles of 128 x 128
-// read and write 1.4 times as much per product as one of 256 x 256 (11520 rows, 512 wide: 2048 features with GELU 43.3 us against
-// 48.3, 1536 without 31.5 against 29.7).  Two blocks of a compute unit that start together stay in step, so the first of their rounds
-// of 512 takes 5 us more (and a launch of one round never pays); what is left for a last round of at most 256 runs alone, which takes
-// half of the ends.  (4096 features, 544 / 1056 / 1568 tiles: 512 wide 22 / 34 / 45 us, priced 23 / 35 / 47; 11008 wide 222 / 360 / 501,
-// priced 253 / 419 / 584, where 256 x 160 takes 149 / 293 and 256 x 224 392, priced 206 / 388 / 446.)
+// read and write 1.4 times as much per product as one of 256 x 256 (11520 rows, 512 wide: 2048 features with GELU 40.5 us against
+// 45.8, 1536 without, over cards, 27.7 to 31.5 against 28.0 to 29.7).  Two blocks of a compute unit that start together stay in
+// step, so the first of their rounds of 512 takes 5 us more (and a launch of one round never pays); what is left for a last round
+// of at most 256 runs alone, which takes half of the ends.  (4096 features, 544 / 1056 / 1568 tiles: 512 wide 22 / 34 / 45 us, priced
+// 23 / 35 / 47; 11008 wide 222 / 360 / 501, priced 253 / 419 / 584, where 256 x 160 takes 149 / 293 and 256 x 224 392, priced
+// 206 / 388 / 446.)
 template <typename F>
 inline const RingTile* ring_pick(int64_t d, int forced, F&& tiles_of, bool gelu = false) {
   const int64_t nk = d / kRingBK;
@@ -287,11 +288,12 @@ __device__ __forceinline__ void gemm_ring_halves(const char* Abase, const AOff (
 // 32*FI x 32*TJ x d tile product for launches whose tiles of 256 rows would leave most of the chip idle: the same wave
 // layout (2 x 2 waves, wave w: A rows 16*FI*(w/2), B rows 16*TJ*(w%2)), fragments and LDS row layout as above.
 // Such a tile is bound by the bytes its compute unit pulls (32 KiB per stage at 128 x 128 against 0.25 us of products)
-// and by their latency, so all of the LDS is a ring of D whole stages: a stage's slot is requested again, D stages ahead,
-// once its last fragments are in registers.  A wave issues in order and stalls on loads issued together, so the loads are
-// dealt out, unconditionally, behind the products of a whole stage (128 x 128: 0.44 us a stage with all of them at its
-// end, 0.37 us dealt out; 0.62 us in the two-slot form with staging registers that this replaced; under a condition each,
-// the compiler moved the accumulators out of their registers and back).  One barrier per stage, before its last k-step.
+// and by their latency, so the block's share of the LDS (all of it, half or a third) is a ring of D whole stages: a stage's
+// slot is requested again, D stages ahead, once its last fragments are in registers.  A wave issues in order and stalls on
+// loads issued together, so the loads are dealt out, unconditionally, behind the products of a whole stage (128 x 128: 0.44 us
+// a stage with all of them at its end, 0.37 us dealt out; 0.62 us in the two-slot form with staging registers that this
+// replaced; under a condition each, the compiler moved the accumulators out of their registers and back).  One barrier per
+// stage, before its last k-step.
 // Register r of acc[i][j]: A row 16*FI*(w/2) + 16*i + 4*(lane/16) + r  .  B row 16*TJ*(w%2) + 16*j + lane%16.
 // As above: clamped rows, all LDS traffic complete on return, a block barrier before the memory is used for something else.
 template <int FI, int TJ, int D>

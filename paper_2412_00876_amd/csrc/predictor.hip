@@ -272,8 +272,8 @@ __global__ __launch_bounds__(kWave) void span_offsets_kernel(const int32_t* __re
 }
 
 // LayerNorm over rows of 512: lane holds 8 consecutive elements; mean and biased variance in two passes over the
-// registers.  With span_off: the span offsets are written on the way, for the attention two launches on (a launch of their own takes
-// 2 us, more between two others).
+// registers.  With span_off: the span offsets are written on the way, for the attention two launches on (a launch of their own took
+// 2.0 to 5.0 us in a trace of the image predictor).
 __global__ __launch_bounds__(256) void ln_kernel(const bf16_t* __restrict__ Z, bf16_t* __restrict__ Y,
                                                  const float* __restrict__ gam, const float* __restrict__ bet,
                                                  int64_t M, const int32_t* __restrict__ vis_len, int32_t B, int32_t* __restrict__ span_off) {
@@ -962,7 +962,7 @@ __global__ __launch_bounds__(512, 2) void small_head_kernel(const float* __restr
 // As three launches (two linear layers, a wave per row) the head was latency three times over: 9.6 + 6.1 + 4.8 us and the gaps between
 // them at 11520 rows, now 18.5; with the span offsets' launch gone as well the image predictor takes 123.9 instead of 128.6 us on one
 // picture of 576 tokens, 270 instead of 281 on one of 2880, 645 instead of 660 on four of those.
-constexpr int kHeadRows = 32, kHeadBlocks = 256, kHeadThreads = 512;  // one block per compute unit: 91 KiB of LDS, 242 registers
+constexpr int kHeadRows = 32, kHeadBlocks = 256, kHeadThreads = 512;  // one block per compute unit: 89.5 KiB of LDS, 242 registers
 __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(const bf16_t* __restrict__ Z, int64_t M, const bf16_t* __restrict__ W1,
                                                       const float* __restrict__ b1, const bf16_t* __restrict__ W2,
                                                       const float* __restrict__ b2, const bf16_t* __restrict__ W3,
@@ -1244,7 +1244,7 @@ Regions carve(void* ws, int64_t M, int32_t B, int32_t n_blocks) {
   const size_t rows = static_cast<size_t>(M > 0 ? M : 0);
   r.span_off = reinterpret_cast<int32_t*>(take((static_cast<size_t>(B > 0 ? B : 0) + 2) * sizeof(int32_t)));
   r.Z = reinterpret_cast<bf16_t*>(take(rows * kPW * 2));
-  r.Y = reinterpret_cast<bf16_t*>(take(rows * kPW * 2));
+  r.Y = reinterpret_cast<bf16_t*>(take(rows * kPW * 2));  // without blocks Y and Hb are not used, on at most 64 rows Z neither: the size asked for is kept
   r.QKV = reinterpret_cast<bf16_t*>(take(n_blocks > 0 ? rows * 3 * kPW * 2 : 0));
   r.Hb = reinterpret_cast<bf16_t*>(take(rows * (n_blocks > 0 ? kPMlp : kPH1) * 2));
   r.small = reinterpret_cast<float*>(take(n_blocks == 0 && M <= kSmallRows ? size_t(kSmallSplit) * kSmallRows * kPW * 4 : 0));
